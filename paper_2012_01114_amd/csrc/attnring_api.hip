@@ -448,7 +448,7 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
                 e = hipMalloc((void**)&ctx->scores, bytes);
                 CHECK("hipMalloc(score scratch)");
             }
-            if (Wq) e = launch_proj_generic(pb, X, Wq, ctx->qf, s);
+            if (Wq) e = launch_proj_generic(pb, X, &Wq, &ctx->qf, 1, s);
             else e = launch_copy_heads_generic(pb, X, ctx->qf, s);
             CHECK("launch projection (q=k=v)");
             MARK(2);
@@ -456,9 +456,9 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
             CHECK("launch q=k=v attention");
             ctx->last_proj_gemms = Wq ? 1 : 0;
         } else {
-            e = launch_proj_generic(pb, X, Wq, ctx->qf, s);
-            if (e == hipSuccess) e = launch_proj_generic(pb, X, Wk, ctx->kf, s);
-            if (e == hipSuccess) e = launch_proj_generic(pb, X, Wv, ctx->vf, s);
+            const void* const W[3] = {Wq, Wk, Wv};
+            float* const qkv[3] = {ctx->qf, ctx->kf, ctx->vf};
+            e = launch_proj_generic(pb, X, W, qkv, 3, s);
             CHECK("launch projection");
             MARK(2);
             e = launch_attn_generic(pb, ctx->qf, ctx->kf, ctx->vf, out, s);

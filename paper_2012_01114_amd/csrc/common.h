@@ -59,7 +59,9 @@ __device__ __forceinline__ unsigned source_row(const int* __restrict__ row0, int
 
 // ---- generic float-compute path (any shape, f32 or bf16 storage) ----------
 // q/k/v workspace: float [B][H][N][d].
-hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* W, float* out, hipStream_t s);
+// out[m] = X . W[m] for `count` (1..3) weight matrices in one launch.
+hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* const* W, float* const* out, int count,
+                               hipStream_t s);
 hipError_t launch_copy_heads_generic(const Problem& pb, const void* X, float* out, hipStream_t s);
 hipError_t launch_attn_generic(const Problem& pb, const float* q, const float* k, const float* v,
                                void* out, hipStream_t s);

@@ -7,7 +7,7 @@
 // (the order in which PE l holds block (l - j) mod m in Algorithm 1).  Blocks
 // that hold no needed pair are never touched: above the diagonal for masked
 // attention (Sec. 5.1), past the key length for padded batches.
-#include "common.h"
+#include "mfma_common.h"
 
 namespace attnring {
 namespace {
@@ -39,54 +39,178 @@ __device__ __forceinline__ float wave_sum(float x)
 }
 
 // ---------------------------------------------------------------------------
-// Projection (Sec. 3.1): out[b][h][i][l] = sum_c X[b][i][c] * W[c][h*d + l].
-// 64 x 64 output tile per workgroup, 16-deep slices through LDS, 4 x 4 per thread.
+// Projections (Sec. 3.1): out_m[b][h][i][l] = sum_c X[b][i][c] * W_m[c][h*d + l], for up to three
+// weight matrices in one launch, any d_model, any number of columns, any alignment.
+//
+// Bound by the matrix cores: float operands are contracted by v_mfma_f32_32x32x2_f32 (one fp32
+// fma per product, as an fmaf loop; 157 TFLOP/s on the chip, a large torch product reaches 153),
+// bfloat16 operands by v_mfma_f32_32x32x16_bf16 (products exact in float).  An MFMA of 64 (32)
+// cycles leaves room for its operand reads, so a tile is staged by plain loads: the next slice is
+// fetched into registers while the current one is contracted, and a CU holds several workgroups.
+//
+// 2 x 2 wavefronts, each RM x RN blocks of 32 x 32.  X rows lie k-contiguous in LDS and are read
+// 16 bytes at a time; the k a lane half contracts in one float MFMA are chosen to suit that read
+// (half g takes 8t + 4g + j in MFMA j), which only orders the sum.  W stays k-major: float columns
+// are read one by one, bfloat16 ones by the transposing read.  Row pitches put the rows that one
+// read touches on different banks.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ __launch_bounds__(256) void proj_generic_kernel(int M, int N, int D, int H, int d, const T* __restrict__ X,
-                                                           const T* __restrict__ W, float* __restrict__ out)
+struct Slice;
+template <>
+struct Slice<float> {
+    static constexpr int KS = 32;              // k per slice
+    static constexpr int VEC = 4;              // elements of a 16-byte piece
+    static constexpr int APITCH = KS + 4;      // elements of an X row in LDS
+    static constexpr int bpitch(int bn) { return bn + 8; }
+};
+template <>
+struct Slice<bf16_t> {
+    static constexpr int KS = 64;
+    static constexpr int VEC = 8;
+    static constexpr int APITCH = KS + 8;
+    static constexpr int bpitch(int bn) { return bn + 32; }
+};
+
+struct ProjArgs {
+    const void* W[3];
+    float* out[3];
+};
+
+// 16 bytes at element `col` of a row of `count` elements; `whole`: pieces are aligned and whole.
+template <typename T>
+__device__ __forceinline__ u32x4 load_piece(const T* __restrict__ row, int col, int count, bool whole)
 {
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64 + 4];
-    const int HD = H * d;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int row0 = blockIdx.y * 64, col0 = blockIdx.x * 64;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < D; k0 += 16) {
-        for (int e = tid; e < 64 * 16; e += 256) {
-            int r = e >> 4, kk = e & 15;
-            int gr = row0 + r, gk = k0 + kk;
-            As[kk][r] = (gr < M && gk < D) ? load_as_float(X, (size_t)gr * D + gk) : 0.f;
+    constexpr int VEC = Slice<T>::VEC;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (whole) {
+        if (col < count) v = *(const u32x4*)(row + col);
+    } else {
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) {
+            if (col + j >= count) break;
+            if constexpr (sizeof(T) == 4) v[j] = __float_as_uint(row[col + j]);
+            else v[j >> 1] |= (unsigned)row[col + j] << (16 * (j & 1));
         }
-        for (int e = tid; e < 16 * 64; e += 256) {
-            int kk = e >> 6, c = e & 63;
-            int gk = k0 + kk, gc = col0 + c;
-            Bs[kk][c] = (gk < D && gc < HD) ? load_as_float(W, (size_t)gk * HD + gc) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], bv[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { a[u] = As[kk][ty * 4 + u]; bv[u] = Bs[kk][tx * 4 + u]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) acc[u][w] = fmaf(a[u], bv[w], acc[u][w]);
-        }
-        __syncthreads();
     }
+    return v;
+}
+
+template <typename T, int RM, int RN>
+__global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, int H, int d, const T* __restrict__ X,
+                                                         ProjArgs pa, int tiles_n, bool xwhole, bool wwhole)
+{
+    typedef Slice<T> SL;
+    constexpr int BM = 64 * RM, BN = 64 * RN, KS = SL::KS, VEC = SL::VEC;
+    constexpr int AP = SL::APITCH, BP = SL::bpitch(BN);
+    constexpr int ACH = KS / VEC, BCH = BN / VEC;             // 16-byte pieces per row
+    constexpr int NAL = BM * ACH / 256, NBL = KS * BCH / 256;  // pieces per thread
+    __shared__ __attribute__((aligned(16))) T As[BM * AP];
+    __shared__ __attribute__((aligned(16))) T Bs[KS * BP];
+    const int HD = H * d;
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = (wave >> 1) * 32 * RM, wn = (wave & 1) * 32 * RN;
+    const int which = blockIdx.x / tiles_n;
+    const int col0 = (blockIdx.x - which * tiles_n) * BN, row0 = blockIdx.y * BM;
+    const T* __restrict__ W = (const T*)pa.W[which];
+
+    f32x16 acc[RM][RN];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        int gr = row0 + ty * 4 + u;
-        if (gr >= M) continue;
-        int bb = gr / N, i = gr - bb * N;
+    for (int a = 0; a < RM; ++a)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            int gc = col0 + tx * 4 + w;
-            if (gc >= HD) continue;
-            int h = gc / d, l = gc - h * d;
-            out[(((size_t)bb * H + h) * N + i) * d + l] = acc[u][w];
+        for (int b = 0; b < RN; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+
+    u32x4 areg[NAL], breg[NBL];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < NAL; ++u) {
+            const int c = tid + 256 * u, r = c / ACH, kk = k0 + (c % ACH) * VEC;
+            areg[u] = u32x4{0u, 0u, 0u, 0u};
+            if (row0 + r < M) areg[u] = load_piece(X + (size_t)(row0 + r) * D, kk, D, xwhole);
+        }
+#pragma unroll
+        for (int u = 0; u < NBL; ++u) {
+            const int c = tid + 256 * u, kk = k0 + c / BCH, cc = col0 + (c % BCH) * VEC;
+            breg[u] = u32x4{0u, 0u, 0u, 0u};
+            if (kk < D) breg[u] = load_piece(W + (size_t)kk * HD, cc, HD, wwhole);
+        }
+    };
+    fetch(0);
+    for (int k0 = 0; k0 < D; k0 += KS) {
+        __syncthreads();  // everyone is done with the slice before
+#pragma unroll
+        for (int u = 0; u < NAL; ++u) {
+            const int c = tid + 256 * u;
+            *(u32x4*)(As + (c / ACH) * AP + (c % ACH) * VEC) = areg[u];
+        }
+#pragma unroll
+        for (int u = 0; u < NBL; ++u) {
+            const int c = tid + 256 * u;
+            *(u32x4*)(Bs + (c / BCH) * BP + (c % BCH) * VEC) = breg[u];
+        }
+        __syncthreads();
+        if (k0 + KS < D) fetch(k0 + KS);
+        if constexpr (sizeof(T) == 4) {
+#pragma unroll
+            for (int t = 0; t < KS / 8; ++t) {
+                f32x4 af[RM];
+                float bf[RN][4];
+#pragma unroll
+                for (int a = 0; a < RM; ++a) af[a] = *(const f32x4*)(As + (wm + 32 * a + ln) * AP + 8 * t + 4 * g);
+#pragma unroll
+                for (int b = 0; b < RN; ++b)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) bf[b][j] = Bs[(8 * t + 4 * g + j) * BP + wn + 32 * b + ln];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int a = 0; a < RM; ++a)
+#pragma unroll
+                        for (int b = 0; b < RN; ++b)
+                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[a][j], bf[b][j], acc[a][b], 0, 0, 0);
+            }
+        } else {
+            // transposing read: 16 lanes hand in a 4 (k) x 16 (columns) patch, lane i gets column i
+            const int i16 = lane & 15;
+            const int kr = 8 * g + (i16 >> 2), cb = wn + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
+#pragma unroll
+            for (int ks = 0; ks < KS / 16; ++ks) {
+                u32x4 af[RM], bf[RN];
+#pragma unroll
+                for (int a = 0; a < RM; ++a) af[a] = *(const u32x4*)(As + (wm + 32 * a + ln) * AP + 16 * ks + 8 * g);
+#pragma unroll
+                for (int b = 0; b < RN; ++b) {
+                    const u32x2 lo = lds_read_tr16(Bs + (16 * ks + kr) * BP + cb + 32 * b);
+                    const u32x2 hi = lds_read_tr16(Bs + (16 * ks + kr + 4) * BP + cb + 32 * b);
+                    bf[b] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+                }
+#pragma unroll
+                for (int a = 0; a < RM; ++a)
+#pragma unroll
+                    for (int b = 0; b < RN; ++b) acc[a][b] = mfma32(af[a], bf[b], acc[a][b]);
+            }
+        }
+    }
+    // register r of a block: vector acc_row(r, g), column ln; 32 lanes write 128 consecutive bytes
+    float* __restrict__ out = pa.out[which];
+#pragma unroll
+    for (int b = 0; b < RN; ++b) {
+        const int gc = col0 + wn + 32 * b + ln;
+        if (gc >= HD) continue;
+        const int h = gc / d, l = gc - h * d;
+#pragma unroll
+        for (int a = 0; a < RM; ++a) {
+            const int first = row0 + wm + 32 * a;
+            const int b0 = first / N, edge = (b0 + 1) * N;  // most blocks lie in one batch item
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int gr = first + acc_row(e, g);
+                if (gr >= M) continue;
+                const int bb = gr < edge ? b0 : gr / N;
+                out[(((size_t)bb * H + h) * N + (gr - bb * N)) * d + l] = acc[a][b][e];
+            }
         }
     }
 }
@@ -285,16 +409,44 @@ __global__ __launch_bounds__(256) void sym_softmax_pv_kernel(Problem pb, const f
 
 }  // namespace
 
-hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* W, float* out, hipStream_t s)
+namespace {
+
+template <typename T, int RM, int RN>
+void launch_proj_tile(const Problem& pb, const T* X, const ProjArgs& pa, int count, hipStream_t s)
 {
     const int M = pb.B * pb.N, HD = pb.H * pb.d;
-    dim3 grid((HD + 63) / 64, (M + 63) / 64);
-    if (pb.is_bf16)
-        hipLaunchKernelGGL(proj_generic_kernel<bf16_t>, grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d,
-                           (const bf16_t*)X, (const bf16_t*)W, out);
-    else
-        hipLaunchKernelGGL(proj_generic_kernel<float>, grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d,
-                           (const float*)X, (const float*)W, out);
+    const int tiles_n = (HD + 64 * RN - 1) / (64 * RN);
+    uintptr_t wbits = 0;
+    for (int m = 0; m < count; ++m) wbits |= reinterpret_cast<uintptr_t>(pa.W[m]);
+    const bool xwhole = pb.D % Slice<T>::VEC == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+    const bool wwhole = HD % Slice<T>::VEC == 0 && (wbits & 15) == 0;
+    hipLaunchKernelGGL((proj_float_kernel<T, RM, RN>), dim3(tiles_n * count, (M + 64 * RM - 1) / (64 * RM)), dim3(256), 0,
+                       s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, xwhole, wwhole);
+}
+
+// Larger tiles read less of X and W per product; smaller ones leave fewer CUs idle.
+template <typename T>
+void launch_proj_pick(const Problem& pb, const T* X, const ProjArgs& pa, int count, hipStream_t s)
+{
+    const long M = (long)pb.B * pb.N, HD = (long)pb.H * pb.d;
+    auto tiles = [&](int rm, int rn) { return ((M + 64 * rm - 1) / (64 * rm)) * ((HD + 64 * rn - 1) / (64 * rn)) * count; };
+    if (tiles(2, 2) >= 4 * 256) launch_proj_tile<T, 2, 2>(pb, X, pa, count, s);
+    else if (tiles(1, 2) >= 4 * 256) launch_proj_tile<T, 1, 2>(pb, X, pa, count, s);
+    else launch_proj_tile<T, 1, 1>(pb, X, pa, count, s);
+}
+
+}  // namespace
+
+hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* const* W, float* const* out, int count,
+                               hipStream_t s)
+{
+    ProjArgs pa = {};
+    for (int m = 0; m < count; ++m) {
+        pa.W[m] = W[m];
+        pa.out[m] = out[m];
+    }
+    if (pb.is_bf16) launch_proj_pick(pb, (const bf16_t*)X, pa, count, s);
+    else launch_proj_pick(pb, (const float*)X, pa, count, s);
     return hipGetLastError();
 }
 

@@ -31,6 +31,16 @@ __device__ __forceinline__ f32x16 mfma32h(u32x4 a, u32x4 b, f32x16 c)
                                                   0, 0, 0);
 }
 
+// ds_read_b64_tr_b16: 16 lanes hand in the addresses of a 4 x 16 patch of 16-bit values in LDS (four rows, four
+// columns per address) and lane i of them gets column i.  Not for kernels with copies into LDS in flight: the
+// compiler waits for all of those first.
+__device__ __forceinline__ u32x2 lds_read_tr16(const void* p)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)const_cast<void*>(p)));
+}
+
 // Row (within a 32-row block) held by accumulator register r of a lane in half g.
 __device__ __forceinline__ constexpr int acc_row(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
 
