@@ -13,6 +13,14 @@ struct CountCfg {
     int b_shift;  // log2(b), or -1 when b is not a power of two
 };
 
+inline CountCfg count_cfg(int b)
+{
+    CountCfg cc = {b, -1};
+    for (int sft = 0; sft < 31; ++sft)
+        if ((1 << sft) == b) cc.b_shift = sft;
+    return cc;
+}
+
 // ceil(x / b): the number of multiples of b in [0, x)
 __device__ __forceinline__ unsigned cdiv_b(unsigned x, const CountCfg& cc)
 {

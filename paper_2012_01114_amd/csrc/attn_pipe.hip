@@ -828,11 +828,7 @@ hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, c
     const int per_head = (causal && !single) ? (n_qtiles + 1) / 2 : n_qtiles;
     const int n_work = pb.B * pb.H * per_head;
     const int grid = ((n_work + 7) / 8) * 8;
-    CountCfg cc;
-    cc.b = pb.b;
-    cc.b_shift = -1;
-    for (int sft = 0; sft < 31; ++sft)
-        if ((1 << sft) == pb.b) cc.b_shift = sft;
+    const CountCfg cc = count_cfg(pb.b);
 #define ATTN_LAUNCH(DK_, W_, C_, F_)                                                                                    \
     hipLaunchKernelGGL((attn_pipe_kernel<DK_, W_, C_, F_>), dim3(grid), dim3(64 * W_), 0, s, pb, cc, q, k, vt, out, \
                        n_qtiles, per_head, n_work, X, Wq, qscale, single ? 1 : 0)

@@ -461,12 +461,12 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
             e = launch_proj_generic(pb, X, W, qkv, 3, s);
             CHECK("launch projection");
             MARK(2);
-            e = launch_attn_generic(pb, ctx->qf, ctx->kf, ctx->vf, out, s);
+            e = launch_attn_float(pb, ctx->qf, ctx->kf, ctx->vf, out, s);
             CHECK("launch attention");
             ctx->last_proj_gemms = 3;
         }
         MARK(3);
-        ctx->last_phys = ctx->b;
+        ctx->last_phys = scheme == ATTN_SCHEME_SYMMETRIC ? ctx->b : FLOAT_BLOCK;
     }
 #undef MARK
 #undef CHECK

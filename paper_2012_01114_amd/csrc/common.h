@@ -63,8 +63,7 @@ __device__ __forceinline__ unsigned source_row(const int* __restrict__ row0, int
 hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* const* W, float* const* out, int count,
                                hipStream_t s);
 hipError_t launch_copy_heads_generic(const Problem& pb, const void* X, float* out, hipStream_t s);
-hipError_t launch_attn_generic(const Problem& pb, const float* q, const float* k, const float* v,
-                               void* out, hipStream_t s);
+hipError_t launch_attn_float(const Problem& pb, const float* q, const float* k, const float* v, void* out, hipStream_t s);
 hipError_t launch_sym_generic(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s);
 
 // ---- matrix-core path (bf16 storage, d_k 64 or 128, FULL and CAUSAL) --------
@@ -93,5 +92,7 @@ size_t sym_pair_workspace_floats(const Problem& pb);
 hipError_t launch_sym_pair(const Problem& pb, const h16_t* z, const h16_t* zt, float* work, bf16_t* out, hipStream_t s);
 // Physical score-block edge of the MFMA attention kernels (phys_br = phys_bc).
 enum { MFMA_BLOCK = 32 };
+// The same of the float attention kernel.
+enum { FLOAT_BLOCK = 16 };
 
 }  // namespace attnring

@@ -1,12 +1,6 @@
-// Float-compute kernels for every shape the MFMA path does not take: f32
-// storage, head sizes other than 64/128, and the q = k = v scheme.
-//
-// Mapping of the paper's ring onto the GPU: workgroup I is PE I.  It owns the
-// n/P query rows [I*b, (I+1)*b) (abstract: n divisible by the number of PEs)
-// and meets the key/value blocks in ring order J = I, I-1, ..., wrapping
-// (the order in which PE l holds block (l - j) mod m in Algorithm 1).  Blocks
-// that hold no needed pair are never touched: above the diagonal for masked
-// attention (Sec. 5.1), past the key length for padded batches.
+// Float path, for every shape the 16-bit matrix-core kernels do not take (f32 storage, head sizes
+// other than 64 and 128, unaligned pointers): the projections, and the q = k = v scheme.  The
+// attention kernel of the FULL and masked schemes is in attn_float.hip.
 #include "mfma_common.h"
 
 namespace attnring {
@@ -275,75 +269,6 @@ __device__ __forceinline__ void store_row(const RowState& st, T* out, size_t bas
     }
 }
 
-// len: key length of the batch item; rlen: the same limit for query rows when padded rows are left
-// out, else n.
-__device__ __forceinline__ bool pair_allowed(int scheme, int i, int j, int len, int rlen)
-{
-    return j < len && i < rlen && (scheme != SCHEME_CAUSAL || j <= i);
-}
-// A b x b tile holds a needed pair iff its first row's pair with its first key is allowed.
-__device__ __forceinline__ bool tile_needed(int scheme, int I, int J, int b, int len, int rlen)
-{
-    return J * b < len && I * b < rlen && (scheme != SCHEME_CAUSAL || J <= I);
-}
-
-// ---------------------------------------------------------------------------
-// Fused phases 1-3 for FULL and CAUSAL.  Grid (P, H, B); 4 wavefronts per PE,
-// row r of the PE goes to wavefront r % 4.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void attn_generic_kernel(Problem pb, const float* __restrict__ q,
-                                                           const float* __restrict__ k,
-                                                           const float* __restrict__ v, T* __restrict__ out)
-{
-    const int I = blockIdx.x, h = blockIdx.y, bb = blockIdx.z;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int N = pb.N, d = pb.d, b = pb.b, P = pb.P;
-    int len = N;
-    if (pb.lens) { len = pb.lens[bb]; len = len < 0 ? 0 : (len > N ? N : len); }
-    const int rlen = pb.skip_rows ? len : N;
-    const size_t head = ((size_t)bb * pb.H + h) * (size_t)N * d;
-    const float* qh = q + head;
-    const float* kh = k + head;
-    const float* vh = v + head;
-
-    if (threadIdx.x == 0) {  // tiles this PE works on (the same for each of its rows)
-        unsigned long long tiles = 0;
-        for (int t = 0; t < P; ++t) {
-            int J = I - t; if (J < 0) J += P;
-            if (pb.noskip || tile_needed(pb.scheme, I, J, b, len, rlen)) ++tiles;
-        }
-        count_add(pb.counters, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, tiles, tiles);
-    }
-
-    for (int r = wave; r < b; r += 4) {
-        const int i = I * b + r;
-        const float* qr = qh + (size_t)i * d;
-        RowState st;
-        st.m = -INFINITY; st.l = 0.f;
-#pragma unroll
-        for (int a = 0; a < MAX_ACC; ++a) st.o[a] = 0.f;
-        for (int t = 0; t < P; ++t) {  // ring order, own block first
-            int J = I - t; if (J < 0) J += P;
-            if (!pb.noskip && !tile_needed(pb.scheme, I, J, b, len, rlen)) continue;  // redundant tile: skipped
-            for (int c0 = 0; c0 < b; c0 += 64) {
-                const int cnt = (b - c0) < 64 ? (b - c0) : 64;
-                const int j = J * b + c0 + lane;
-                const bool valid = lane < cnt;
-                float s = 0.f;
-                if (valid) {
-                    const float* kr = kh + (size_t)j * d;
-                    for (int l = 0; l < d; ++l) s = fmaf(qr[l], kr[l], s);  // Eq. (1)
-                    s *= pb.scale;
-                }
-                fold_chunk(st, s, valid && pair_allowed(pb.scheme, i, j, len, rlen), J * b + c0, cnt, vh, d, lane);
-            }
-        }
-        store_row(st, out, ((size_t)bb * N + i) * ((size_t)pb.H * d) + (size_t)h * d, d, lane);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // q = k = v scheme (Sec. 4).  Phase 1 on tiles: PE I computes the tiles on the
 // circulant tile diagonals (I - J) mod P = 0 .. floor(P/2) (Sec. 4.2 applied to
@@ -460,17 +385,6 @@ hipError_t launch_copy_heads_generic(const Problem& pb, const void* X, float* ou
     else
         hipLaunchKernelGGL(copy_heads_kernel<float>, grid, dim3(256), 0, s, total, pb.N, pb.H, pb.d,
                            (const float*)X, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_attn_generic(const Problem& pb, const float* q, const float* k, const float* v, void* out,
-                               hipStream_t s)
-{
-    dim3 grid(pb.P, pb.H, pb.B);
-    if (pb.is_bf16)
-        hipLaunchKernelGGL(attn_generic_kernel<bf16_t>, grid, dim3(256), 0, s, pb, q, k, v, (bf16_t*)out);
-    else
-        hipLaunchKernelGGL(attn_generic_kernel<float>, grid, dim3(256), 0, s, pb, q, k, v, (float*)out);
     return hipGetLastError();
 }
 

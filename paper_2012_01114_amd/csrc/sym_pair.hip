@@ -286,11 +286,7 @@ hipError_t launch_sym_pair(const Problem& pb, const h16_t* z, const h16_t* zt, f
     float* part_m = work;
     float* part_l = work + rows;
     float* part_o = work + 2 * rows;
-    CountCfg cc;
-    cc.b = pb.b;
-    cc.b_shift = -1;
-    for (int sft = 0; sft < 31; ++sft)
-        if ((1 << sft) == pb.b) cc.b_shift = sft;
+    const CountCfg cc = count_cfg(pb.b);
     const float c2 = pb.scale * 1.4426950408889634f;
     const dim3 grid(pb.noskip ? T * T : T * (T + 1) / 2, pb.B * pb.H);
     if (pb.d == 64) {
