@@ -34,19 +34,39 @@ __device__ __forceinline__ f32x4 mfma16f(float a, float b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// Four floats at column `col` of a row of d; `whole`: rows are whole, aligned 16-byte pieces.
-__device__ __forceinline__ f32x4 load4(const float* __restrict__ row, int col, int d, bool whole)
+// Four floats at column `col` of a row of d, zeros past its end (and if not `there`).  No branch: a
+// load behind one would wait for all loads in flight.  WHOLE: pieces lie inside or outside the row,
+// and what is to be dropped is dropped by clip4 when the piece is used, since that waits for the load.
+template <bool WHOLE>
+__device__ __forceinline__ f32x4 load4(const float* __restrict__ row, int col, int d, bool there)
 {
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (whole) {
-        if (col < d) v = *(const f32x4*)(row + col);
+    f32x4 v;
+    if constexpr (WHOLE) {
+        v = *(const f32x4*)(row + (col < d ? col : 0));
     } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (col + j < d) v[j] = row[col + j];
+        for (int j = 0; j < 4; ++j) {
+            const bool in = col + j < d;
+            const float w = row[in ? col + j : 0];
+            v[j] = there && in ? w : 0.f;
+        }
     }
     return v;
 }
+
+template <bool WHOLE>
+__device__ __forceinline__ f32x4 clip4(f32x4 v, bool in)
+{
+    if constexpr (WHOLE) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = in ? v[j] : 0.f;
+    }
+    return v;
+}
+
+// exp(x), x <= 0, as a power of two: x * log2(e) is rounded once, which moves the result by |x| / 2 ulp
+// at most, where it is small against the row's largest weight of 1.
+__device__ __forceinline__ float exp_neg(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 
 // Four outputs of a row at column `col`.
 __device__ __forceinline__ void store4(void* out, size_t row_base, int col, int d, f32x4 y, bool bf16, bool whole)
@@ -68,45 +88,43 @@ __device__ __forceinline__ void store4(void* out, size_t row_base, int col, int 
 // A 64-row tile of K or V as float4 pieces in registers, then LDS rows of 16 NDB + 4 floats (the
 // pitch puts 16 rows, and rows 4 apart, on different banks); rows at or past `limit` and columns
 // at or past d are zeros.
-template <int NDB>
+template <int NDB, bool WHOLE>
 struct Tile {
     static constexpr int DP = 16 * NDB, PITCH = DP + 4, PPR = DP / 4, PER = KT * PPR / 256;
     f32x4 reg[PER];
-    __device__ __forceinline__ void fetch(const float* __restrict__ src, int j0, int limit, int d, bool whole, int tid)
+    __device__ __forceinline__ void fetch(const float* __restrict__ src, int j0, int limit, int d, int tid)
     {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int c = tid + 256 * u, r = c / PPR, col = (c % PPR) * 4;
-            reg[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (j0 + r < limit) reg[u] = load4(src + (size_t)(j0 + r) * d, col, d, whole);
+            const int j = j0 + r < limit ? j0 + r : (limit > 0 ? limit - 1 : 0);
+            reg[u] = load4<WHOLE>(src + (size_t)j * d, col, d, j0 + r < limit);
         }
     }
-    __device__ __forceinline__ void stage(float* dst, int tid) const
+    __device__ __forceinline__ void stage(float* dst, int j0, int limit, int d, int tid) const
     {
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             const int c = tid + 256 * u;
-            *(f32x4*)(dst + (c / PPR) * PITCH + (c % PPR) * 4) = reg[u];
+            const int r = c / PPR, col = (c % PPR) * 4;
+            *(f32x4*)(dst + r * PITCH + col) = clip4<WHOLE>(reg[u], j0 + r < limit && col < d);
         }
     }
 };
 
 // The lane's row as the B operand of the score MFMAs.
-template <int NDB>
-__device__ __forceinline__ void load_row(f32x4 (&qf)[NDB], const float* __restrict__ row, bool there, int g4, int d, bool whole)
+template <int NDB, bool WHOLE>
+__device__ __forceinline__ void load_row(f32x4 (&qf)[NDB], const float* __restrict__ row, int g4, int d)
 {
 #pragma unroll
-    for (int t = 0; t < NDB; ++t) {
-        qf[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (there) qf[t] = load4(row, 16 * t + 4 * g4, d, whole);
-    }
+    for (int t = 0; t < NDB; ++t) qf[t] = clip4<WHOLE>(load4<WHOLE>(row, 16 * t + 4 * g4, d, true), 16 * t + 4 * g4 < d);
 }
 
 // Phase 1 (Eq. (1), before the scale) of NB 16-key blocks from key row `kt` of an LDS tile.
 template <int NDB, int NB>
 __device__ __forceinline__ void score_blocks(f32x4* S, const float* kt, const f32x4 (&qf)[NDB], int ln, int g4)
 {
-    constexpr int PITCH = Tile<NDB>::PITCH;
+    constexpr int PITCH = Tile<NDB, true>::PITCH;
 #pragma unroll
     for (int b = 0; b < NB; ++b) S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -121,12 +139,12 @@ __device__ __forceinline__ void score_blocks(f32x4* S, const float* kt, const f3
     }
 }
 
-template <int NDB, bool KEYS>
+template <int NDB, bool KEYS, bool WHOLE>
 __global__ __launch_bounds__(256)
 void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, const float* __restrict__ k,
-                       const float* __restrict__ v, void* __restrict__ out, int n_rowtiles, bool whole, bool out_whole)
+                       const float* __restrict__ v, void* __restrict__ out, int n_rowtiles, bool out_whole)
 {
-    typedef Tile<NDB> TL;
+    typedef Tile<NDB, WHOLE> TL;
     constexpr int PITCH = TL::PITCH, DP = TL::DP;
     constexpr int ROWS = KEYS ? 16 : 64;  // query rows per workgroup
     constexpr int NB = KEYS ? 1 : 4;      // 16-key blocks of a tile that a wavefront takes
@@ -188,7 +206,7 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
     unsigned cnt_phys = 0;  // 16 x 16 score blocks; wave-uniform
 
     f32x4 qf[NDB], O[NDB];
-    load_row<NDB>(qf, q + head + (size_t)i * d, i < N, g4, d, whole);
+    load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);  // rows past the last: not stored
 #pragma unroll
     for (int db = 0; db < NDB; ++db) O[db] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;  // running maximum of the row; this lane's part of the row sum
@@ -199,19 +217,19 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
     TL tk, tv;
     if (nT > 0) {
         const int J = tile_of_step(0);
-        tk.fetch(k + head, J * KT, len, d, whole, tid);
-        tv.fetch(v + head, J * KT, len, d, whole, tid);
+        tk.fetch(k + head, J * KT, len, d, tid);
+        tv.fetch(v + head, J * KT, len, d, tid);
     }
     for (int t = 0; t < nT; ++t) {
         const int J = tile_of_step(t);
         __syncthreads();  // everyone is done with the tile before
-        tk.stage(ks, tid);
-        tv.stage(vs, tid);
+        tk.stage(ks, J * KT, len, d, tid);
+        tv.stage(vs, J * KT, len, d, tid);
         __syncthreads();
         if (t + 1 < nT) {
             const int Jn = tile_of_step(t + 1);
-            tk.fetch(k + head, Jn * KT, len, d, whole, tid);
-            tv.fetch(v + head, Jn * KT, len, d, whole, tid);
+            tk.fetch(k + head, Jn * KT, len, d, tid);
+            tv.fetch(v + head, Jn * KT, len, d, tid);
         }
         // 16-key blocks of the tile that hold a pair this wavefront needs: the first nk
         const int key0 = J * KT + (KEYS ? 16 * wave : 0);
@@ -253,14 +271,14 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
         const float ref = mx > -INFINITY ? mx : 0.f;
-        const float alpha = expf(m - ref);
+        const float alpha = exp_neg(m - ref);
         m = mx;
         float sum = 0.f;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                S[b][r] = expf(S[b][r] - ref);
+                S[b][r] = exp_neg(S[b][r] - ref);
                 sum += S[b][r];
             }
         l = l * alpha + sum;
@@ -304,7 +322,7 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
         const float ref = M > -INFINITY ? M : 0.f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            mw[w] = expf(mw[w] - ref);
+            mw[w] = exp_neg(mw[w] - ref);
             L += mw[w] * st_ml[2 * (16 * w + r) + 1];
         }
         const float inv = L > 0.f ? 1.f / L : 0.f;  // a row with no allowed pair is zero
@@ -333,12 +351,16 @@ hipError_t launch_attn_float(const Problem& pb, const float* q, const float* k, 
     const bool whole = pb.d % 4 == 0;  // the workspace is aligned
     const bool out_whole = whole && (reinterpret_cast<uintptr_t>(out) & (pb.is_bf16 ? 7 : 15)) == 0;
     const long heads = (long)pb.B * pb.H;
-    const bool keys = heads * ((pb.N + 63) / 64) < 4L * 256;
+    // Measured (us, rows / keys): 320 workgroups of 64 rows 55 / 46, 384 56 / 54 (masked 41 / 35), 768 85 / 105
+    // (masked 54 / 61); a single tile has no keys to share (256 workgroups 11 / 15).
+    const bool keys = pb.N > KT && heads * ((pb.N + 63) / 64) < 2L * 256;
     const int n_rowtiles = keys ? (pb.N + 15) / 16 : (pb.N + 63) / 64;
     const dim3 grid((unsigned)(heads * n_rowtiles));
+#define ATTN_FLOAT_LAUNCH(NDB_, K_, W_)                                                                                  \
+    hipLaunchKernelGGL((attn_float_kernel<NDB_, K_, W_>), grid, dim3(256), 0, s, pb, cc, q, k, v, out, n_rowtiles, out_whole)
 #define ATTN_FLOAT(NDB_)                                                                                               \
-    if (keys) hipLaunchKernelGGL((attn_float_kernel<NDB_, true>), grid, dim3(256), 0, s, pb, cc, q, k, v, out, n_rowtiles, whole, out_whole); \
-    else hipLaunchKernelGGL((attn_float_kernel<NDB_, false>), grid, dim3(256), 0, s, pb, cc, q, k, v, out, n_rowtiles, whole, out_whole)
+    if (whole) { if (keys) ATTN_FLOAT_LAUNCH(NDB_, true, true); else ATTN_FLOAT_LAUNCH(NDB_, false, true); }            \
+    else { if (keys) ATTN_FLOAT_LAUNCH(NDB_, true, false); else ATTN_FLOAT_LAUNCH(NDB_, false, false); }
     const int need = (pb.d + 15) / 16;
     if (need <= 1) { ATTN_FLOAT(1); }
     else if (need <= 2) { ATTN_FLOAT(2); }
@@ -351,6 +373,7 @@ hipError_t launch_attn_float(const Problem& pb, const float* q, const float* k, 
     else if (need <= 12) { ATTN_FLOAT(12); }
     else { ATTN_FLOAT(16); }
 #undef ATTN_FLOAT
+#undef ATTN_FLOAT_LAUNCH
     return hipGetLastError();
 }
 

@@ -1,6 +1,8 @@
 // Float path, for every shape the 16-bit matrix-core kernels do not take (f32 storage, head sizes
 // other than 64 and 128, unaligned pointers): the projections, and the q = k = v scheme.  The
 // attention kernel of the FULL and masked schemes is in attn_float.hip.
+#include <type_traits>
+
 #include "mfma_common.h"
 
 namespace attnring {
@@ -39,14 +41,17 @@ __device__ __forceinline__ float wave_sum(float x)
 // Bound by the matrix cores: float operands are contracted by v_mfma_f32_32x32x2_f32 (one fp32
 // fma per product, as an fmaf loop; 157 TFLOP/s on the chip, a large torch product reaches 153),
 // bfloat16 operands by v_mfma_f32_32x32x16_bf16 (products exact in float).  An MFMA of 64 (32)
-// cycles leaves room for its operand reads, so a tile is staged by plain loads: the next slice is
-// fetched into registers while the current one is contracted, and a CU holds several workgroups.
+// cycles leaves room for its operand reads, so tiles are small, 64 x 64, a 32 x 32 block for each
+// of 2 x 2 wavefronts: several workgroups share a CU and fill each other's waits, and small
+// products leave fewer CUs idle (4096 x 768 -> 2304 in f32: 136 us, 128 x 128 tiles 171; 1024 x 768
+// -> 768: 23 against 65).  Slices of k are fetched into registers three ahead, past the end of
+// d_model too, so that the wait for one leaves the others in flight, and pass through two LDS
+// buffers with one barrier each.
 //
-// 2 x 2 wavefronts, each RM x RN blocks of 32 x 32.  X rows lie k-contiguous in LDS and are read
-// 16 bytes at a time; the k a lane half contracts in one float MFMA are chosen to suit that read
-// (half g takes 8t + 4g + j in MFMA j), which only orders the sum.  W stays k-major: float columns
-// are read one by one, bfloat16 ones by the transposing read.  Row pitches put the rows that one
-// read touches on different banks.
+// X rows lie k-contiguous in LDS and are read 16 bytes at a time; the k a lane half contracts in
+// one float MFMA are chosen to suit that read (half g takes 8t + 4g + j in MFMA j), which only
+// orders the sum.  W stays k-major: float columns are read one by one, bfloat16 ones by the
+// transposing read.  Row pitches put the rows that one read touches on different banks.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct Slice;
@@ -70,100 +75,103 @@ struct ProjArgs {
     float* out[3];
 };
 
-// 16 bytes at element `col` of a row of `count` elements; `whole`: pieces are aligned and whole.
-template <typename T>
-__device__ __forceinline__ u32x4 load_piece(const T* __restrict__ row, int col, int count, bool whole)
+// 16 bytes at element `col` of a row of `count` elements, zeros past its end (and if not `there`).
+// No branch: what must not be read is read at the row's start instead; a load behind a branch would
+// wait for all loads in flight.  WHOLE: pieces are aligned and lie inside or outside, and what is to
+// be dropped is dropped by clip_piece when the piece is used, since that waits for the load.
+template <typename T, bool WHOLE>
+__device__ __forceinline__ u32x4 load_piece(const T* __restrict__ row, int col, int count, bool there)
 {
     constexpr int VEC = Slice<T>::VEC;
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (whole) {
-        if (col < count) v = *(const u32x4*)(row + col);
+    if constexpr (WHOLE) {
+        v = *(const u32x4*)(row + (col < count ? col : 0));
     } else {
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
-            if (col + j >= count) break;
-            if constexpr (sizeof(T) == 4) v[j] = __float_as_uint(row[col + j]);
-            else v[j >> 1] |= (unsigned)row[col + j] << (16 * (j & 1));
+            const bool in = col + j < count;
+            const T w = row[in ? col + j : 0];
+            if constexpr (sizeof(T) == 4) v[j] = there && in ? __float_as_uint(w) : 0u;
+            else v[j >> 1] |= there && in ? (unsigned)w << (16 * (j & 1)) : 0u;
         }
     }
     return v;
 }
 
-template <typename T, int RM, int RN>
+template <bool WHOLE>
+__device__ __forceinline__ u32x4 clip_piece(u32x4 v, bool in)
+{
+    if constexpr (WHOLE) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = in ? v[j] : 0u;
+    }
+    return v;
+}
+
+template <typename T, bool WHOLE>
 __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, int H, int d, const T* __restrict__ X,
-                                                         ProjArgs pa, int tiles_n, bool xwhole, bool wwhole)
+                                                         ProjArgs pa, int tiles_n)
 {
     typedef Slice<T> SL;
-    constexpr int BM = 64 * RM, BN = 64 * RN, KS = SL::KS, VEC = SL::VEC;
+    constexpr int BM = 64, BN = 64, KS = SL::KS, VEC = SL::VEC;
     constexpr int AP = SL::APITCH, BP = SL::bpitch(BN);
     constexpr int ACH = KS / VEC, BCH = BN / VEC;             // 16-byte pieces per row
     constexpr int NAL = BM * ACH / 256, NBL = KS * BCH / 256;  // pieces per thread
-    __shared__ __attribute__((aligned(16))) T As[BM * AP];
-    __shared__ __attribute__((aligned(16))) T Bs[KS * BP];
+    constexpr int PF = 3;  // slices fetched ahead, a set of registers each
+    __shared__ __attribute__((aligned(16))) T As2[2][BM * AP];
+    __shared__ __attribute__((aligned(16))) T Bs2[2][KS * BP];
     const int HD = H * d;
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = (wave >> 1) * 32 * RM, wn = (wave & 1) * 32 * RN;
+    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
     const int which = blockIdx.x / tiles_n;
     const int col0 = (blockIdx.x - which * tiles_n) * BN, row0 = blockIdx.y * BM;
     const T* __restrict__ W = (const T*)pa.W[which];
 
-    f32x16 acc[RM][RN];
+    f32x16 acc;
 #pragma unroll
-    for (int a = 0; a < RM; ++a)
-#pragma unroll
-        for (int b = 0; b < RN; ++b)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
 
-    u32x4 areg[NAL], breg[NBL];
-    auto fetch = [&](int k0) {
+    u32x4 areg[PF][NAL], breg[PF][NBL];
+    auto fetch = [&](int k0, auto set_) {
+        constexpr int SET = decltype(set_)::value;
 #pragma unroll
         for (int u = 0; u < NAL; ++u) {
             const int c = tid + 256 * u, r = c / ACH, kk = k0 + (c % ACH) * VEC;
-            areg[u] = u32x4{0u, 0u, 0u, 0u};
-            if (row0 + r < M) areg[u] = load_piece(X + (size_t)(row0 + r) * D, kk, D, xwhole);
+            // rows past the last are the last again: they are not stored
+            areg[SET][u] = load_piece<T, WHOLE>(X + (size_t)min(row0 + r, M - 1) * D, kk, D, true);
         }
 #pragma unroll
         for (int u = 0; u < NBL; ++u) {
             const int c = tid + 256 * u, kk = k0 + c / BCH, cc = col0 + (c % BCH) * VEC;
-            breg[u] = u32x4{0u, 0u, 0u, 0u};
-            if (kk < D) breg[u] = load_piece(W + (size_t)kk * HD, cc, HD, wwhole);
+            breg[SET][u] = load_piece<T, WHOLE>(W + (size_t)min(kk, D - 1) * HD, cc, HD, kk < D);
         }
     };
-    fetch(0);
-    for (int k0 = 0; k0 < D; k0 += KS) {
-        __syncthreads();  // everyone is done with the slice before
+    // Slice k0 goes from its register set to LDS buffer `buf`, which was last read two slices ago,
+    // on the other side of the barrier of the slice in between.
+    auto slice = [&](int k0, int buf, auto set_) {
+        constexpr int SET = decltype(set_)::value;
+        T* As = As2[buf];
+        T* Bs = Bs2[buf];
 #pragma unroll
         for (int u = 0; u < NAL; ++u) {
             const int c = tid + 256 * u;
-            *(u32x4*)(As + (c / ACH) * AP + (c % ACH) * VEC) = areg[u];
+            *(u32x4*)(As + (c / ACH) * AP + (c % ACH) * VEC) = clip_piece<WHOLE>(areg[SET][u], k0 + (c % ACH) * VEC < D);
         }
 #pragma unroll
         for (int u = 0; u < NBL; ++u) {
             const int c = tid + 256 * u;
-            *(u32x4*)(Bs + (c / BCH) * BP + (c % BCH) * VEC) = breg[u];
+            *(u32x4*)(Bs + (c / BCH) * BP + (c % BCH) * VEC) = clip_piece<WHOLE>(breg[SET][u], k0 + c / BCH < D);
         }
+        fetch(k0 + PF * KS, set_);  // unconditional (past d_model: dropped), so that waits can count the loads in flight
         __syncthreads();
-        if (k0 + KS < D) fetch(k0 + KS);
         if constexpr (sizeof(T) == 4) {
 #pragma unroll
             for (int t = 0; t < KS / 8; ++t) {
-                f32x4 af[RM];
-                float bf[RN][4];
-#pragma unroll
-                for (int a = 0; a < RM; ++a) af[a] = *(const f32x4*)(As + (wm + 32 * a + ln) * AP + 8 * t + 4 * g);
-#pragma unroll
-                for (int b = 0; b < RN; ++b)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) bf[b][j] = Bs[(8 * t + 4 * g + j) * BP + wn + 32 * b + ln];
+                const f32x4 af = *(const f32x4*)(As + (wm + ln) * AP + 8 * t + 4 * g);
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int a = 0; a < RM; ++a)
-#pragma unroll
-                        for (int b = 0; b < RN; ++b)
-                            acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[a][j], bf[b][j], acc[a][b], 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], Bs[(8 * t + 4 * g + j) * BP + wn + ln], acc, 0, 0, 0);
             }
         } else {
             // transposing read: 16 lanes hand in a 4 (k) x 16 (columns) patch, lane i gets column i
@@ -171,41 +179,37 @@ __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, in
             const int kr = 8 * g + (i16 >> 2), cb = wn + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
 #pragma unroll
             for (int ks = 0; ks < KS / 16; ++ks) {
-                u32x4 af[RM], bf[RN];
-#pragma unroll
-                for (int a = 0; a < RM; ++a) af[a] = *(const u32x4*)(As + (wm + 32 * a + ln) * AP + 16 * ks + 8 * g);
-#pragma unroll
-                for (int b = 0; b < RN; ++b) {
-                    const u32x2 lo = lds_read_tr16(Bs + (16 * ks + kr) * BP + cb + 32 * b);
-                    const u32x2 hi = lds_read_tr16(Bs + (16 * ks + kr + 4) * BP + cb + 32 * b);
-                    bf[b] = u32x4{lo[0], lo[1], hi[0], hi[1]};
-                }
-#pragma unroll
-                for (int a = 0; a < RM; ++a)
-#pragma unroll
-                    for (int b = 0; b < RN; ++b) acc[a][b] = mfma32(af[a], bf[b], acc[a][b]);
+                const u32x4 af = *(const u32x4*)(As + (wm + ln) * AP + 16 * ks + 8 * g);
+                const u32x2 lo = lds_read_tr16(Bs + (16 * ks + kr) * BP + cb);
+                const u32x2 hi = lds_read_tr16(Bs + (16 * ks + kr + 4) * BP + cb);
+                acc = mfma32(af, u32x4{lo[0], lo[1], hi[0], hi[1]}, acc);
             }
         }
+    };
+    fetch(0, std::integral_constant<int, 0>{});
+    fetch(KS, std::integral_constant<int, 1>{});
+    fetch(2 * KS, std::integral_constant<int, 2>{});
+    for (int k0 = 0, buf = 0;; k0 += PF * KS, buf ^= 1) {
+        slice(k0, buf, std::integral_constant<int, 0>{});
+        if (k0 + KS >= D) break;
+        slice(k0 + KS, buf ^ 1, std::integral_constant<int, 1>{});
+        if (k0 + 2 * KS >= D) break;
+        slice(k0 + 2 * KS, buf, std::integral_constant<int, 2>{});
+        if (k0 + 3 * KS >= D) break;
     }
-    // register r of a block: vector acc_row(r, g), column ln; 32 lanes write 128 consecutive bytes
+    // register r: vector acc_row(r, g), column ln; 32 lanes write 128 consecutive bytes
     float* __restrict__ out = pa.out[which];
+    const int gc = col0 + wn + ln;
+    if (gc >= HD) return;
+    const int h = gc / d, l = gc - h * d;
+    const int first = row0 + wm;
+    const int b0 = first / N, edge = (b0 + 1) * N;  // most blocks lie in one batch item
 #pragma unroll
-    for (int b = 0; b < RN; ++b) {
-        const int gc = col0 + wn + 32 * b + ln;
-        if (gc >= HD) continue;
-        const int h = gc / d, l = gc - h * d;
-#pragma unroll
-        for (int a = 0; a < RM; ++a) {
-            const int first = row0 + wm + 32 * a;
-            const int b0 = first / N, edge = (b0 + 1) * N;  // most blocks lie in one batch item
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int gr = first + acc_row(e, g);
-                if (gr >= M) continue;
-                const int bb = gr < edge ? b0 : gr / N;
-                out[(((size_t)bb * H + h) * N + (gr - bb * N)) * d + l] = acc[a][b][e];
-            }
-        }
+    for (int e = 0; e < 16; ++e) {
+        const int gr = first + acc_row(e, g);
+        if (gr >= M) continue;
+        const int bb = gr < edge ? b0 : gr / N;
+        out[(((size_t)bb * H + h) * N + (gr - bb * N)) * d + l] = acc[e];
     }
 }
 
@@ -336,28 +340,17 @@ __global__ __launch_bounds__(256) void sym_softmax_pv_kernel(Problem pb, const f
 
 namespace {
 
-template <typename T, int RM, int RN>
-void launch_proj_tile(const Problem& pb, const T* X, const ProjArgs& pa, int count, hipStream_t s)
+template <typename T>
+void launch_proj_type(const Problem& pb, const T* X, const ProjArgs& pa, int count, hipStream_t s)
 {
     const int M = pb.B * pb.N, HD = pb.H * pb.d;
-    const int tiles_n = (HD + 64 * RN - 1) / (64 * RN);
-    uintptr_t wbits = 0;
-    for (int m = 0; m < count; ++m) wbits |= reinterpret_cast<uintptr_t>(pa.W[m]);
-    const bool xwhole = pb.D % Slice<T>::VEC == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
-    const bool wwhole = HD % Slice<T>::VEC == 0 && (wbits & 15) == 0;
-    hipLaunchKernelGGL((proj_float_kernel<T, RM, RN>), dim3(tiles_n * count, (M + 64 * RM - 1) / (64 * RM)), dim3(256), 0,
-                       s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, xwhole, wwhole);
-}
-
-// Larger tiles read less of X and W per product; smaller ones leave fewer CUs idle.
-template <typename T>
-void launch_proj_pick(const Problem& pb, const T* X, const ProjArgs& pa, int count, hipStream_t s)
-{
-    const long M = (long)pb.B * pb.N, HD = (long)pb.H * pb.d;
-    auto tiles = [&](int rm, int rn) { return ((M + 64 * rm - 1) / (64 * rm)) * ((HD + 64 * rn - 1) / (64 * rn)) * count; };
-    if (tiles(2, 2) >= 4 * 256) launch_proj_tile<T, 2, 2>(pb, X, pa, count, s);
-    else if (tiles(1, 2) >= 4 * 256) launch_proj_tile<T, 1, 2>(pb, X, pa, count, s);
-    else launch_proj_tile<T, 1, 1>(pb, X, pa, count, s);
+    const int tiles_n = (HD + 63) / 64;
+    uintptr_t bits = reinterpret_cast<uintptr_t>(X);
+    for (int m = 0; m < count; ++m) bits |= reinterpret_cast<uintptr_t>(pa.W[m]);
+    const bool whole = pb.D % Slice<T>::VEC == 0 && HD % Slice<T>::VEC == 0 && (bits & 15) == 0;
+    const dim3 grid(tiles_n * count, (M + 63) / 64);
+    if (whole) hipLaunchKernelGGL((proj_float_kernel<T, true>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n);
+    else hipLaunchKernelGGL((proj_float_kernel<T, false>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n);
 }
 
 }  // namespace
@@ -370,8 +363,8 @@ hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* con
         pa.W[m] = W[m];
         pa.out[m] = out[m];
     }
-    if (pb.is_bf16) launch_proj_pick(pb, (const bf16_t*)X, pa, count, s);
-    else launch_proj_pick(pb, (const float*)X, pa, count, s);
+    if (pb.is_bf16) launch_proj_type(pb, (const bf16_t*)X, pa, count, s);
+    else launch_proj_type(pb, (const float*)X, pa, count, s);
     return hipGetLastError();
 }
 
