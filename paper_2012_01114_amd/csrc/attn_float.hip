@@ -22,12 +22,29 @@
 // The paper's ring: the walk starts at the rows' own tile and runs downwards, wrapping (the order
 // in which PE l meets block (l - j) mod m in Algorithm 1); tiles and, inside a tile, 16-key blocks
 // with no needed pair are left out (Sec. 5.1).
+//
+// q = k = v scheme (Sec. 4): a first kernel computes every score tile once and stores it at both
+// of its places of an n x n matrix per head, the same walk then reads its scores from there.
+#include <type_traits>
+
 #include "attn_common.h"
 
 namespace attnring {
 namespace {
 
 constexpr int KT = 64;  // keys per tile
+
+// Workgroups are numbered through a grid of rows of at most 2^22 (a grid dimension of more than
+// 2^32 threads does not exist); the numbers past the last do nothing.
+inline dim3 flat_grid(size_t count)
+{
+    const size_t row = (size_t)1 << 22;
+    return dim3((unsigned)(count < row ? count : row), (unsigned)((count + row - 1) / row));
+}
+__device__ __forceinline__ unsigned flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
+// Row pitch of the stored score matrices: whole 16-byte pieces.
+__host__ __device__ __forceinline__ int score_pitch(int n) { return (n + 3) & ~3; }
 
 __device__ __forceinline__ f32x4 mfma16f(float a, float b, f32x4 c)
 {
@@ -139,25 +156,31 @@ __device__ __forceinline__ void score_blocks(f32x4* S, const float* kt, const f3
     }
 }
 
-template <int NDB, bool KEYS, bool WHOLE>
+// STORED (q = k = v scheme): the scores come from `scores`, which sym_scores_float_kernel has filled,
+// instead of q and k, and have been counted there.
+template <int NDB, bool KEYS, bool WHOLE, bool STORED>
 __global__ __launch_bounds__(256)
 void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, const float* __restrict__ k,
-                       const float* __restrict__ v, void* __restrict__ out, int n_rowtiles, bool out_whole)
+                       const float* __restrict__ v, const float* __restrict__ scores, void* __restrict__ out,
+                       int n_rowtiles, bool out_whole)
 {
     typedef Tile<NDB, WHOLE> TL;
     constexpr int PITCH = TL::PITCH, DP = TL::DP;
     constexpr int ROWS = KEYS ? 16 : 64;  // query rows per workgroup
     constexpr int NB = KEYS ? 1 : 4;      // 16-key blocks of a tile that a wavefront takes
-    __shared__ __attribute__((aligned(16))) float ks[KT * PITCH];
+    __shared__ __attribute__((aligned(16))) float ks[STORED ? 4 : KT * PITCH];
     __shared__ __attribute__((aligned(16))) float vs[KT * PITCH];
+    __shared__ float st_ml[KEYS ? 2 * KT : 1];
 
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, g4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Consecutive workgroups take the heads in turn, the last row tiles (the most keys under the
     // mask) first, so that the long walks do not start last.
     const int heads = pb.B * pb.H;
-    const int bh = blockIdx.x % heads;
-    const int x = n_rowtiles - 1 - blockIdx.x / heads;
+    const unsigned item = flat_block();
+    if (item >= (unsigned)heads * (unsigned)n_rowtiles) return;
+    const int bh = (int)(item % (unsigned)heads);
+    const int x = n_rowtiles - 1 - (int)(item / (unsigned)heads);
     const int bb = bh / pb.H, h = bh - bb * pb.H;
     const int N = pb.N, d = pb.d;
     const bool causal = pb.scheme == SCHEME_CAUSAL;
@@ -188,7 +211,7 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
     };
 
     // logical tiles: row block I is counted by the workgroup that holds its first row
-    if (wave == 0) {
+    if (!STORED && wave == 0) {
         unsigned cnt = 0;
         const int I = (int)cdiv_b((unsigned)i0, cc) + lane;  // at most 64 row blocks start here
         if (I * cc.b < row_end) {
@@ -201,12 +224,12 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
         unsigned long long total = cnt;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
-        if (lane == 0) count_add(pb.counters, blockIdx.x, total, 0);
+        if (lane == 0) count_add(pb.counters, item, total, 0);
     }
     unsigned cnt_phys = 0;  // 16 x 16 score blocks; wave-uniform
 
     f32x4 qf[NDB], O[NDB];
-    load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);  // rows past the last: not stored
+    if constexpr (!STORED) load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);  // rows past the last: not stored
 #pragma unroll
     for (int db = 0; db < NDB; ++db) O[db] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;  // running maximum of the row; this lane's part of the row sum
@@ -214,23 +237,38 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
     if (causal) lim = min(lim, i);
     if (i >= rlen) lim = -1;
 
+    // the lane's stored scores of a tile: whole 16-byte pieces of its row (pitch SP)
+    const int SP = score_pitch(N);
+    const float* srow = STORED ? scores + ((size_t)bh * N + min(i, N - 1)) * SP : nullptr;
     TL tk, tv;
-    if (nT > 0) {
-        const int J = tile_of_step(0);
-        tk.fetch(k + head, J * KT, len, d, tid);
+    f32x4 sreg[NB];
+    auto fetch = [&](int t) {
+        const int J = tile_of_step(t);
+        if constexpr (STORED) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int col = J * KT + (KEYS ? 16 * wave : 16 * b) + 4 * g4;
+                sreg[b] = *(const f32x4*)(srow + (col < SP ? col : 0));
+            }
+        } else {
+            tk.fetch(k + head, J * KT, len, d, tid);
+        }
         tv.fetch(v + head, J * KT, len, d, tid);
-    }
+    };
+    if (nT > 0) fetch(0);
     for (int t = 0; t < nT; ++t) {
         const int J = tile_of_step(t);
+        f32x4 S[NB];
         __syncthreads();  // everyone is done with the tile before
-        tk.stage(ks, J * KT, len, d, tid);
+        if constexpr (STORED) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) S[b] = sreg[b];
+        } else {
+            tk.stage(ks, J * KT, len, d, tid);
+        }
         tv.stage(vs, J * KT, len, d, tid);
         __syncthreads();
-        if (t + 1 < nT) {
-            const int Jn = tile_of_step(t + 1);
-            tk.fetch(k + head, Jn * KT, len, d, tid);
-            tv.fetch(v + head, Jn * KT, len, d, tid);
-        }
+        if (t + 1 < nT) fetch(t + 1);
         // 16-key blocks of the tile that hold a pair this wavefront needs: the first nk
         const int key0 = J * KT + (KEYS ? 16 * wave : 0);
         int nk = 0;
@@ -240,23 +278,20 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
             nk = pb.noskip ? NB : max(0, min(NB, (keys + 15) >> 4));
         }
         if (nk == 0) continue;
-        cnt_phys += (unsigned)nk;
-        f32x4 S[NB];
-        const float* kt = ks + (KEYS ? 16 * wave * PITCH : 0);
-        if (nk == NB) {
-            score_blocks<NDB, NB>(S, kt, qf, ln, g4);
-        } else {
-            for (int b = 0; b < NB; ++b) {
-                f32x4 s1[1] = {{0.f, 0.f, 0.f, 0.f}};
-                if (b < nk) score_blocks<NDB, 1>(s1, kt + 16 * b * PITCH, qf, ln, g4);
-                // written out: S stays in registers
-                if (b == 0) S[0] = s1[0];
-                if constexpr (NB == 4) {
-                    if (b == 1) S[1] = s1[0];
-                    if (b == 2) S[2] = s1[0];
-                    if (b == 3) S[3] = s1[0];
+        if constexpr (!STORED) {
+            cnt_phys += (unsigned)nk;
+            const float* kt = ks + (KEYS ? 16 * wave * PITCH : 0);
+            if (nk == NB) {
+                score_blocks<NDB, NB>(S, kt, qf, ln, g4);
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (b < nk) score_blocks<NDB, 1>(&S[b], kt + 16 * b * PITCH, qf, ln, g4);
                 }
             }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) S[b] *= pb.scale;
         }
         // phase 2 (Eq. (2)), running maximum; a row that has met no allowed key keeps m = -inf
         float mx = m;
@@ -265,7 +300,7 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                S[b][r] = 16 * b + r <= rel ? S[b][r] * pb.scale : -INFINITY;
+                S[b][r] = 16 * b + r <= rel ? S[b][r] : -INFINITY;
                 mx = fmaxf(mx, S[b][r]);
             }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
@@ -303,8 +338,7 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
     if constexpr (KEYS) {
         // partial state of wavefront w, row r: m, l, then O
         __syncthreads();
-        float* st_o = ks;  // [4][16] rows of PITCH
-        float* st_ml = vs;
+        float* st_o = vs;  // [4][16] rows of PITCH
 #pragma unroll
         for (int db = 0; db < NDB; ++db) *(f32x4*)(st_o + (16 * wave + ln) * PITCH + 16 * db + 4 * g4) = O[db];
         if (g4 == 0) {
@@ -340,41 +374,160 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
             for (int db = 0; db < NDB; ++db)
                 store4(out, base + (size_t)(i - i0) * pitch, 16 * db + 4 * g4, d, O[db] * inv, pb.is_bf16, out_whole);
     }
-    if (lane == 0) count_add(pb.counters, blockIdx.x, 0, cnt_phys);
+    if (!STORED && lane == 0) count_add(pb.counters, item, 0, cnt_phys);
+}
+
+// Phase 1 of the q = k = v scheme (Sec. 4.1, Eq. (4)): one workgroup per unordered pair of 64-row
+// tiles of z computes S_AB = scale * z_A . z_B^T once and stores it at both places, w'_ji = w'_ij.
+// The paper's rule (Sec. 4.2: circulant diagonals 0 .. floor(P/2) of the P x P matrix of n/P-row
+// tiles, the middle one by both owners when P is even) fixes which of the two a ring of P
+// processing elements computes; the logical tiles it selects are counted over the regions the
+// workgroup covers (each position of the P x P matrix lies in exactly one use).  Products and their
+// order are the same in both orientations, so S is symmetric to the bit, and the debug mode, which
+// computes every ordered pair in its own orientation, gives the same bits.
+template <int NDB, bool WHOLE>
+__global__ __launch_bounds__(256)
+void sym_scores_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ z, float* __restrict__ scores, int T)
+{
+    typedef Tile<NDB, WHOLE> TL;
+    __shared__ __attribute__((aligned(16))) float ks[KT * TL::PITCH];
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = pb.N, d = pb.d, P = pb.P;
+    const unsigned pairs = pb.noskip ? (unsigned)(T * T) : (unsigned)(T * (T + 1) / 2), item = flat_block();
+    if (item >= pairs * (unsigned)(pb.B * pb.H)) return;
+    const int bh = (int)(item / pairs), pair = (int)(item - (unsigned)bh * pairs);
+    int A, B;
+    if (pb.noskip) {
+        A = pair / T;
+        B = pair - A * T;
+    } else {  // pair number A (A + 1) / 2 + B, A >= B
+        A = (int)((sqrtf(8.f * (float)pair + 1.f) - 1.f) * 0.5f);
+        while (A * (A + 1) / 2 > pair) --A;
+        while ((A + 1) * (A + 2) / 2 <= pair) ++A;
+        B = pair - A * (A + 1) / 2;
+    }
+    const bool twice = !pb.noskip && A != B;
+    const float* zh = z + (size_t)bh * N * d;
+    TL tk;
+    tk.fetch(zh, B * KT, N, d, tid);
+    const int i = A * KT + 16 * wave + ln;
+    f32x4 qf[NDB];
+    load_row<NDB, WHOLE>(qf, zh + (size_t)min(i, N - 1) * d, g4, d);
+
+    unsigned long long cnt = 0;
+    {
+        const int ia0 = (int)cdiv_b(A * KT, cc), ia1 = (int)cdiv_b(min((A + 1) * KT, N), cc);
+        const int ib0 = (int)cdiv_b(B * KT, cc), ib1 = (int)cdiv_b(min((B + 1) * KT, N), cc);
+        const int na = ia1 - ia0, nb = ib1 - ib0;
+        for (int e = tid; e < na * nb; e += 256) {
+            const int I = ia0 + e / nb, J = ib0 + e % nb;
+            const int gd = I >= J ? I - J : I - J + P;              // (I - J) mod P
+            cnt += (pb.noskip || 2 * gd <= P) ? 1u : 0u;            // region (A, B)
+            const int gt = gd ? P - gd : 0;
+            if (twice) cnt += (2 * gt <= P) ? 1u : 0u;              // region (B, A), filled by the mirrored store
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+    const int nk = min(4, (N - B * KT + 15) >> 4);  // 16-key blocks that hold a key
+    const bool rows = A * KT + 16 * wave < N;
+    if (lane == 0)
+        count_add(pb.counters, item * 4u + wave, cnt, rows ? (unsigned)nk : 0u);
+
+    tk.stage(ks, B * KT, N, d, tid);
+    __syncthreads();
+    if (!rows) return;
+    f32x4 S[4];
+    score_blocks<NDB, 4>(S, ks, qf, ln, g4);  // key rows past the last are zeros and not stored
+    const int SP = score_pitch(N);
+    float* Sh = scores + (size_t)bh * N * SP;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        S[b] *= pb.scale;
+        const int j = B * KT + 16 * b + 4 * g4;  // the lane's four keys
+        if (i < N && j < SP) *(f32x4*)(Sh + (size_t)i * SP + j) = S[b];
+        if (twice && i < N) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (j + r < N) Sh[(size_t)(j + r) * SP + i] = S[b][r];
+        }
+    }
+}
+
+}  // namespace
+
+namespace {
+
+// One row tile per workgroup of 64 rows, or of 16 rows with the keys shared by its wavefronts.
+// Measured (us, rows / keys): 320 workgroups of 64 rows 55 / 46, 384 56 / 54 (masked 41 / 35), 768 85 / 105
+// (masked 54 / 61); a single tile has no keys to share (256 workgroups 11 / 15).
+template <int NDB, bool WHOLE, bool STORED>
+void launch_rows(const Problem& pb, const float* q, const float* k, const float* v, const float* scores, void* out,
+                 hipStream_t s)
+{
+    const CountCfg cc = count_cfg(pb.b);
+    const bool out_whole = pb.d % 4 == 0 && (reinterpret_cast<uintptr_t>(out) & (pb.is_bf16 ? 7 : 15)) == 0;
+    const long heads = (long)pb.B * pb.H;
+    const bool keys = pb.N > KT && heads * ((pb.N + 63) / 64) < 2L * 256;
+    const int n_rowtiles = keys ? (pb.N + 15) / 16 : (pb.N + 63) / 64;
+    const dim3 grid = flat_grid((size_t)heads * n_rowtiles);
+    if (keys)
+        hipLaunchKernelGGL((attn_float_kernel<NDB, true, WHOLE, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
+                           out, n_rowtiles, out_whole);
+    else
+        hipLaunchKernelGGL((attn_float_kernel<NDB, false, WHOLE, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
+                           out, n_rowtiles, out_whole);
+}
+
+template <int NDB, bool WHOLE>
+hipError_t launch_sym(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s)
+{
+    const int T = (pb.N + KT - 1) / KT;
+    const dim3 grid = flat_grid((size_t)(pb.noskip ? T * T : T * (T + 1) / 2) * pb.B * pb.H);
+    hipLaunchKernelGGL((sym_scores_float_kernel<NDB, WHOLE>), grid, dim3(256), 0, s, pb, count_cfg(pb.b), z, scores, T);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    launch_rows<NDB, WHOLE, true>(pb, nullptr, nullptr, z, scores, out, s);
+    return hipGetLastError();
+}
+
+// f(NDB, WHOLE) for the number of 16-column blocks of d and whether rows are whole 16-byte pieces
+// (the workspace is aligned).
+template <class F>
+hipError_t with_size(int d, F&& f)
+{
+    auto pick = [&](auto ndb) { return d % 4 == 0 ? f(ndb, std::true_type{}) : f(ndb, std::false_type{}); };
+    const int need = (d + 15) / 16;
+    if (need <= 1) return pick(std::integral_constant<int, 1>{});
+    if (need <= 2) return pick(std::integral_constant<int, 2>{});
+    if (need <= 3) return pick(std::integral_constant<int, 3>{});
+    if (need <= 4) return pick(std::integral_constant<int, 4>{});
+    if (need <= 5) return pick(std::integral_constant<int, 5>{});
+    if (need <= 6) return pick(std::integral_constant<int, 6>{});
+    if (need <= 8) return pick(std::integral_constant<int, 8>{});
+    if (need <= 10) return pick(std::integral_constant<int, 10>{});
+    if (need <= 12) return pick(std::integral_constant<int, 12>{});
+    return pick(std::integral_constant<int, 16>{});
 }
 
 }  // namespace
 
 hipError_t launch_attn_float(const Problem& pb, const float* q, const float* k, const float* v, void* out, hipStream_t s)
 {
-    const CountCfg cc = count_cfg(pb.b);
-    const bool whole = pb.d % 4 == 0;  // the workspace is aligned
-    const bool out_whole = whole && (reinterpret_cast<uintptr_t>(out) & (pb.is_bf16 ? 7 : 15)) == 0;
-    const long heads = (long)pb.B * pb.H;
-    // Measured (us, rows / keys): 320 workgroups of 64 rows 55 / 46, 384 56 / 54 (masked 41 / 35), 768 85 / 105
-    // (masked 54 / 61); a single tile has no keys to share (256 workgroups 11 / 15).
-    const bool keys = pb.N > KT && heads * ((pb.N + 63) / 64) < 2L * 256;
-    const int n_rowtiles = keys ? (pb.N + 15) / 16 : (pb.N + 63) / 64;
-    const dim3 grid((unsigned)(heads * n_rowtiles));
-#define ATTN_FLOAT_LAUNCH(NDB_, K_, W_)                                                                                  \
-    hipLaunchKernelGGL((attn_float_kernel<NDB_, K_, W_>), grid, dim3(256), 0, s, pb, cc, q, k, v, out, n_rowtiles, out_whole)
-#define ATTN_FLOAT(NDB_)                                                                                               \
-    if (whole) { if (keys) ATTN_FLOAT_LAUNCH(NDB_, true, true); else ATTN_FLOAT_LAUNCH(NDB_, false, true); }            \
-    else { if (keys) ATTN_FLOAT_LAUNCH(NDB_, true, false); else ATTN_FLOAT_LAUNCH(NDB_, false, false); }
-    const int need = (pb.d + 15) / 16;
-    if (need <= 1) { ATTN_FLOAT(1); }
-    else if (need <= 2) { ATTN_FLOAT(2); }
-    else if (need <= 3) { ATTN_FLOAT(3); }
-    else if (need <= 4) { ATTN_FLOAT(4); }
-    else if (need <= 5) { ATTN_FLOAT(5); }
-    else if (need <= 6) { ATTN_FLOAT(6); }
-    else if (need <= 8) { ATTN_FLOAT(8); }
-    else if (need <= 10) { ATTN_FLOAT(10); }
-    else if (need <= 12) { ATTN_FLOAT(12); }
-    else { ATTN_FLOAT(16); }
-#undef ATTN_FLOAT
-#undef ATTN_FLOAT_LAUNCH
-    return hipGetLastError();
+    return with_size(pb.d, [&](auto ndb, auto whole) {
+        launch_rows<decltype(ndb)::value, decltype(whole)::value, false>(pb, q, k, v, nullptr, out, s);
+        return hipGetLastError();
+    });
+}
+
+size_t sym_float_score_floats(const Problem& pb) { return (size_t)pb.B * pb.H * pb.N * score_pitch(pb.N); }
+
+hipError_t launch_sym_float(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s)
+{
+    return with_size(pb.d, [&](auto ndb, auto whole) {
+        return launch_sym<decltype(ndb)::value, decltype(whole)::value>(pb, z, scores, out, s);
+    });
 }
 
 }  // namespace attnring

@@ -445,14 +445,14 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
             if (bytes > MAX_SCORE_BYTES)
                 return fail(ctx, ATTN_ERR_UNSUPPORTED, "attn_forward: q=k=v score scratch would exceed 1 GiB%s");
             if (!ctx->scores) {
-                e = hipMalloc((void**)&ctx->scores, bytes);
+                e = hipMalloc((void**)&ctx->scores, sym_float_score_floats(pb) * sizeof(float));
                 CHECK("hipMalloc(score scratch)");
             }
             if (Wq) e = launch_proj_generic(pb, X, &Wq, &ctx->qf, 1, s);
             else e = launch_copy_heads_generic(pb, X, ctx->qf, s);
             CHECK("launch projection (q=k=v)");
             MARK(2);
-            e = launch_sym_generic(pb, ctx->qf, ctx->scores, out, s);
+            e = launch_sym_float(pb, ctx->qf, ctx->scores, out, s);
             CHECK("launch q=k=v attention");
             ctx->last_proj_gemms = Wq ? 1 : 0;
         } else {
@@ -466,7 +466,7 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
             ctx->last_proj_gemms = 3;
         }
         MARK(3);
-        ctx->last_phys = scheme == ATTN_SCHEME_SYMMETRIC ? ctx->b : FLOAT_BLOCK;
+        ctx->last_phys = FLOAT_BLOCK;
     }
 #undef MARK
 #undef CHECK

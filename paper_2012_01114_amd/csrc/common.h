@@ -64,7 +64,9 @@ hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* con
                                hipStream_t s);
 hipError_t launch_copy_heads_generic(const Problem& pb, const void* X, float* out, hipStream_t s);
 hipError_t launch_attn_float(const Problem& pb, const float* q, const float* k, const float* v, void* out, hipStream_t s);
-hipError_t launch_sym_generic(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s);
+// q = k = v scheme; scores: sym_float_score_floats(pb) floats.
+size_t sym_float_score_floats(const Problem& pb);
+hipError_t launch_sym_float(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s);
 
 // ---- matrix-core path (bf16 storage, d_k 64 or 128, FULL and CAUSAL) --------
 // The projection contracts bf16 operands; q, k, v leave it in half precision (fp32 accumulators
@@ -92,7 +94,7 @@ size_t sym_pair_workspace_floats(const Problem& pb);
 hipError_t launch_sym_pair(const Problem& pb, const h16_t* z, const h16_t* zt, float* work, bf16_t* out, hipStream_t s);
 // Physical score-block edge of the MFMA attention kernels (phys_br = phys_bc).
 enum { MFMA_BLOCK = 32 };
-// The same of the float attention kernel.
+// The same of the float attention kernels.
 enum { FLOAT_BLOCK = 16 };
 
 }  // namespace attnring

@@ -1,6 +1,5 @@
 // Float path, for every shape the 16-bit matrix-core kernels do not take (f32 storage, head sizes
-// other than 64 and 128, unaligned pointers): the projections, and the q = k = v scheme.  The
-// attention kernel of the FULL and masked schemes is in attn_float.hip.
+// other than 64 and 128, unaligned pointers): the projections.  Phases 1-3 are in attn_float.hip.
 #include <type_traits>
 
 #include "mfma_common.h"
@@ -12,26 +11,6 @@ __device__ __forceinline__ float load_as_float(const float* p, size_t i) { retur
 __device__ __forceinline__ float load_as_float(const bf16_t* p, size_t i)
 {
     return __uint_as_float(((unsigned)p[i]) << 16);
-}
-__device__ __forceinline__ void store_from_float(float* p, size_t i, float v) { p[i] = v; }
-__device__ __forceinline__ void store_from_float(bf16_t* p, size_t i, float v)
-{
-    unsigned u = __float_as_uint(v);
-    u += 0x7fffu + ((u >> 16) & 1u);  // round to nearest even (inputs are finite)
-    p[i] = (bf16_t)(u >> 16);
-}
-
-__device__ __forceinline__ float wave_max(float x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-    return x;
-}
-__device__ __forceinline__ float wave_sum(float x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
 }
 
 // ---------------------------------------------------------------------------
@@ -225,121 +204,6 @@ __global__ void copy_heads_kernel(int total, int N, int H, int d, const T* __res
     out[(((size_t)bb * H + h) * N + i) * d + l] = load_as_float(X, (size_t)e);
 }
 
-// ---------------------------------------------------------------------------
-// Online row state of phases 2 and 3 (Eq. (2), Eq. (3)) for one query row held
-// by one wavefront: running maximum m, running sum l of exp(s - m), and the
-// un-normalised output o (lane L holds columns L, L+64, ...).
-// ---------------------------------------------------------------------------
-enum { MAX_ACC = 4 };  // d_k <= 256
-
-struct RowState {
-    float m, l;
-    float o[MAX_ACC];
-};
-
-// Fold up to 64 keys (one per lane) into the row state.  `s` is the lane's score,
-// `ok` whether its pair takes part; keys jbase .. jbase+cnt-1 of head `vh`.
-__device__ __forceinline__ void fold_chunk(RowState& st, float s, bool ok, int jbase, int cnt,
-                                           const float* __restrict__ vh, int d, int lane)
-{
-    s = ok ? s : -INFINITY;
-    const float m_new = fmaxf(st.m, wave_max(s));
-    if (m_new == -INFINITY) return;  // nothing allowed so far (uniform over the wave)
-    const float alpha = expf(st.m - m_new);
-    const float p = ok ? expf(s - m_new) : 0.f;
-    st.l = st.l * alpha + wave_sum(p);
-    st.m = m_new;
-#pragma unroll
-    for (int a = 0; a < MAX_ACC; ++a) st.o[a] *= alpha;
-    for (int jj = 0; jj < cnt; ++jj) {
-        const float pj = __shfl(p, jj, 64);
-        const float* vr = vh + (size_t)(jbase + jj) * d;
-#pragma unroll
-        for (int a = 0; a < MAX_ACC; ++a) {
-            int col = lane + 64 * a;
-            if (col < d) st.o[a] = fmaf(pj, vr[col], st.o[a]);
-        }
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void store_row(const RowState& st, T* out, size_t base, int d, int lane)
-{
-    const float inv = st.l > 0.f ? 1.f / st.l : 0.f;  // a row with no allowed pair is zero
-#pragma unroll
-    for (int a = 0; a < MAX_ACC; ++a) {
-        int col = lane + 64 * a;
-        if (col < d) store_from_float(out, base + col, st.o[a] * inv);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// q = k = v scheme (Sec. 4).  Phase 1 on tiles: PE I computes the tiles on the
-// circulant tile diagonals (I - J) mod P = 0 .. floor(P/2) (Sec. 4.2 applied to
-// the P x P tile matrix; for even P the middle diagonal is computed by both of
-// its owners, the paper's balance trade-off) and stores each score also at its
-// mirrored position, which is the reuse of w'_ij as w'_ji (Eq. (4)).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void sym_scores_kernel(Problem pb, const float* __restrict__ z,
-                                                         float* __restrict__ scores)
-{
-    const int I = blockIdx.x, h = blockIdx.y, bb = blockIdx.z;
-    const int N = pb.N, d = pb.d, b = pb.b, P = pb.P;
-    const size_t bh = (size_t)bb * pb.H + h;
-    const float* zh = z + bh * (size_t)N * d;
-    float* S = scores + bh * (size_t)N * N;
-    const int gmax = pb.noskip ? P - 1 : P / 2;
-    for (int g = 0; g <= gmax; ++g) {
-        int J = I - g; if (J < 0) J += P;
-        const bool mirror = !pb.noskip && g != 0 && !(P % 2 == 0 && g == P / 2);
-        for (int e = threadIdx.x; e < b * b; e += 256) {
-            const int i = I * b + e / b, j = J * b + e % b;
-            const float* zi = zh + (size_t)i * d;
-            const float* zj = zh + (size_t)j * d;
-            float s = 0.f;
-            for (int l = 0; l < d; ++l) s = fmaf(zi[l], zj[l], s);
-            s *= pb.scale;
-            S[(size_t)i * N + j] = s;
-            if (mirror) S[(size_t)j * N + i] = s;
-        }
-    }
-    if (threadIdx.x == 0) {
-        count_add(pb.counters, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x,
-                  (unsigned long long)(gmax + 1), (unsigned long long)(gmax + 1));
-    }
-}
-
-// Phases 2 and 3 of the q = k = v scheme: unchanged from the original definition
-// (Sec. 4.1), reading the stored scores.  One wavefront per row.
-template <typename T>
-__global__ __launch_bounds__(256) void sym_softmax_pv_kernel(Problem pb, const float* __restrict__ z,
-                                                             const float* __restrict__ scores, T* __restrict__ out)
-{
-    const int h = blockIdx.y, bb = blockIdx.z;
-    const int lane = threadIdx.x & 63;
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int N = pb.N, d = pb.d;
-    if (i >= N) return;
-    const size_t bh = (size_t)bb * pb.H + h;
-    const float* vh = z + bh * (size_t)N * d;
-    const float* Srow = scores + bh * (size_t)N * N + (size_t)i * N;
-    RowState st;
-    st.m = -INFINITY; st.l = 0.f;
-#pragma unroll
-    for (int a = 0; a < MAX_ACC; ++a) st.o[a] = 0.f;
-    for (int j0 = 0; j0 < N; j0 += 64) {
-        const int cnt = (N - j0) < 64 ? (N - j0) : 64;
-        const bool valid = lane < cnt;
-        const float s = valid ? Srow[j0 + lane] : 0.f;
-        fold_chunk(st, s, valid, j0, cnt, vh, d, lane);
-    }
-    store_row(st, out, ((size_t)bb * N + i) * ((size_t)pb.H * d) + (size_t)h * d, d, lane);
-}
-
-}  // namespace
-
-namespace {
-
 template <typename T>
 void launch_proj_type(const Problem& pb, const T* X, const ProjArgs& pa, int count, hipStream_t s)
 {
@@ -378,19 +242,6 @@ hipError_t launch_copy_heads_generic(const Problem& pb, const void* X, float* ou
     else
         hipLaunchKernelGGL(copy_heads_kernel<float>, grid, dim3(256), 0, s, total, pb.N, pb.H, pb.d,
                            (const float*)X, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_sym_generic(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s)
-{
-    hipLaunchKernelGGL(sym_scores_kernel, dim3(pb.P, pb.H, pb.B), dim3(256), 0, s, pb, z, scores);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    dim3 grid((pb.N + 3) / 4, pb.H, pb.B);
-    if (pb.is_bf16)
-        hipLaunchKernelGGL(sym_softmax_pv_kernel<bf16_t>, grid, dim3(256), 0, s, pb, z, scores, (bf16_t*)out);
-    else
-        hipLaunchKernelGGL(sym_softmax_pv_kernel<float>, grid, dim3(256), 0, s, pb, z, scores, (float*)out);
     return hipGetLastError();
 }
 

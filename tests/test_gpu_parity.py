@@ -75,6 +75,36 @@ def test_float_path_ragged(shape, scheme, dtype):
         _run_and_compare(w, scheme, 0.3, lens=lens)
 
 
+# ---- float path at the edges of its tiles: 64 x 64 GEMM tiles, 64-key tiles, 16-row and 16-column blocks,
+# and both ways of sharing a row tile's keys (512 row tiles of 64 rows is where they change)
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (1, 65, 33, 1, 17, 13),       # one row, one k and one column past a tile
+    (2, 64, 64, 2, 48, 8),        # whole tiles, a single key tile
+    (2, 192, 96, 2, 64, 24),      # keys shared by the wavefronts, whole tiles
+    (1, 129, 100, 3, 100, 43),    # rows of d in whole 16-byte pieces, last block partly used
+    (1, 80, 16, 1, 256, 5),       # the largest head
+    (32, 72, 20, 16, 12, 9),      # 1024 row tiles: a wavefront for every 16 rows
+    (64, 66, 16, 8, 33, 33),      # the same with unaligned rows
+])
+@pytest.mark.parametrize("scheme", [FULL, SYM, CAUSAL])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_float_path_tile_edges(shape, scheme, dtype):
+    B, n, D, H, d, p = shape
+    if dtype == "bf16" and d == 64:
+        D += 1                    # not a multiple of 8: off the 16-bit matrix-core path
+    w = hp.custom_workload("float_edges", B, n, D, H, d, p, dtype, scheme, 6100 + n)
+    _, stats = _run_and_compare(w, scheme, 0.0)
+    assert (stats["phys_br"], stats["phys_bc"]) == (16, 16)
+    if scheme == SYM:
+        assert stats["phys_tiles_executed"] == hp.expected_sym_blocks(w, tile=64, block=16)
+        return
+    assert stats["phys_tiles_executed"] == hp.expected_phys_blocks(w, scheme, block=16)
+    lens = np.random.default_rng(n).integers(0, n + 1, B).astype(np.int32)
+    lens[0] = 63 if n > 63 else n
+    _run_and_compare(w, scheme, 0.0, lens=lens)
+
+
 def test_symmetric_without_projection():
     w = hp.custom_workload("symx", 2, 20, 24, 2, 12, 5, "f32", SYM, 77)
     _, stats = _run_and_compare(w, SYM, 0.2, sym_no_proj=True)
