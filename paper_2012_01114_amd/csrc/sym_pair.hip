@@ -28,7 +28,15 @@ namespace attnring {
 namespace {
 
 constexpr int ST = 128;           // rows and keys of a score tile
-constexpr int SPITCH = ST + 4;    // floats per row of the staged tile: 16 lanes x 16 bytes meet 64 banks once
+
+// Float offset of element (row, col) of the staged 128 x 128 tile: rows of 512 bytes, their 16-byte
+// chunks XOR-ed with four bits of the row, so that the 16 rows one pass of the 16-byte reads takes
+// meet 64 different banks, and so do the two rows (4 apart) that a store instruction writes.
+__device__ __forceinline__ int staged(int row, int col)
+{
+    const int f = (row & 3) | (((row >> 3) & 1) << 2) | (((row >> 2) & 1) << 3);
+    return row * ST + ((((col >> 2) ^ f) << 2) | (col & 3));
+}
 
 template <int DK>
 struct Sym {
@@ -37,8 +45,10 @@ struct Sym {
     static constexpr int K_BYTES = ST * KROWB;       // K tile: 128 keys
     static constexpr int V_TILE = DK * 64 * 2;       // one 64-key block of V^T
     static constexpr int V_BYTES = 2 * V_TILE;
-    static constexpr int S_BYTES = ST * SPITCH * 4;
-    static constexpr int LDS_BYTES = K_BYTES + V_BYTES + S_BYTES;
+    static constexpr int S_BYTES = ST * ST * 4;
+    // The staged scores take the place of the K tile, which is no longer read by then: 80 KiB at
+    // d_k = 64, two workgroups per CU (with regions of their own one: 96 heads of 512, 44 against 29 us per launch).
+    static constexpr int LDS_BYTES = V_BYTES + S_BYTES;
 };
 
 // z rows [row0, row0 + 128) of one head as a K tile: rows of KROWB bytes, 16-byte chunks swizzled.
@@ -53,17 +63,27 @@ __device__ __forceinline__ void load_k_tile(unsigned char* dst, const h16_t* kh,
         *(u32x4*)(dst + row * (DK * 2) + swz<DK * 2>(p, row) * 16) = src[c];
     }
 }
-// V^T of the same rows: two 64-key blocks of [DK][64], rows of 128 bytes, chunks swizzled.
+// V^T of the same rows: two 64-key blocks of [DK][64], rows of 128 bytes, chunks swizzled; through
+// registers, so that the request can go out long before the tile in LDS is free.
 template <int DK>
-__device__ __forceinline__ void load_vt_tile(unsigned char* dst, const h16_t* vth, int row0, int tid)
-{
-    const u32x4* src = (const u32x4*)(vth + (size_t)(row0 >> 6) * DK * 64);
+struct VtTile {
+    static constexpr int PER = 2 * DK * 8 / 256;
+    u32x4 reg[PER];
+    __device__ __forceinline__ void fetch(const h16_t* vth, int row0, int tid)
+    {
+        const u32x4* src = (const u32x4*)(vth + (size_t)(row0 >> 6) * DK * 64);
 #pragma unroll
-    for (int c = tid; c < 2 * DK * 8; c += 256) {
-        const int row = c >> 3, p = c & 7;  // row: block * DK + column of v
-        *(u32x4*)(dst + row * 128 + swz<128>(p, row % DK) * 16) = src[c];
+        for (int u = 0; u < PER; ++u) reg[u] = src[tid + 256 * u];
     }
-}
+    __device__ __forceinline__ void stage(unsigned char* dst, int tid) const
+    {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int c = tid + 256 * u, row = c >> 3, p = c & 7;  // row: block * DK + column of v
+            *(u32x4*)(dst + row * 128 + swz<128>(p, row % DK) * 16) = reg[u];
+        }
+    }
+};
 
 // Phases 2 and 3 (Eq. (2), (3)) of 32 rows (one per lane pair) over the 128 keys of a tile whose
 // scores S[kb][r] are in accumulator layout (key kb * 32 + acc_row(r, g)); keys at or past
@@ -138,9 +158,9 @@ __global__ __launch_bounds__(256) void sym_pair_kernel(Problem pb, CountCfg cc, 
     typedef Sym<DK> Y;
     constexpr int NKS = Y::NKS;
     __shared__ __attribute__((aligned(16))) unsigned char lds[Y::LDS_BYTES];
-    unsigned char* kt = lds;
-    unsigned char* vt = lds + Y::K_BYTES;
-    float* sc = (float*)(lds + Y::K_BYTES + Y::V_BYTES);
+    unsigned char* vt = lds;
+    unsigned char* kt = lds + Y::V_BYTES;
+    float* sc = (float*)(lds + Y::V_BYTES);
 
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -160,6 +180,31 @@ __global__ __launch_bounds__(256) void sym_pair_kernel(Problem pb, CountCfg cc, 
     const h16_t* zth = zt + (size_t)bh * Npad * DK;
     const bool twice = !all_ordered && A != B;
 
+    // ---- phase 1 (Eq. (1)), once: S^T = z_B . z_A^T, the wavefront's 32 rows of A against 128 keys of B ----
+    VtTile<DK> vr;
+    vr.fetch(zth, B * ST, tid);
+    const int ia = A * ST + wave * 32 + ln;  // this lane's row of A
+    u32x4 qf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const u32x4*)(zh + (size_t)ia * DK + ks * 16 + g * 8);
+    load_k_tile<DK>(kt, zh, B * ST, tid);
+    vr.stage(vt, tid);
+    if (twice) vr.fetch(zth, A * ST, tid);  // V^T of A, for the second use
+    __syncthreads();
+    f32x16 S[4];
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) S[kb][e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+            const int row = kb * 32 + ln;
+            const u32x4 kf = *(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + g, row) * 16);
+            S[kb] = mfma32h(kf, qf[ks], S[kb]);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) S[kb][e] *= c2;  // scale and base-2 exponent, on the fp32 score
+    }
     // ---- counts: logical tiles the selection rule picks, over the regions this workgroup covers ----
     {
         unsigned long long cnt = 0;
@@ -180,32 +225,13 @@ __global__ __launch_bounds__(256) void sym_pair_kernel(Problem pb, CountCfg cc, 
         if (lane == 0) count_add(pb.counters, (unsigned)(blockIdx.y * gridDim.x + blockIdx.x) * 4u + wave, cnt, phys);
     }
 
-    // ---- phase 1 (Eq. (1)), once: S^T = z_B . z_A^T, the wavefront's 32 rows of A against 128 keys of B ----
-    load_k_tile<DK>(kt, zh, B * ST, tid);
-    load_vt_tile<DK>(vt, zth, B * ST, tid);
-    const int ia = A * ST + wave * 32 + ln;  // this lane's row of A
-    u32x4 qf[NKS];
+    if (twice) {
+        __syncthreads();  // nobody reads the K tile any more
+        // staged for the other orientation: sc[key of B][row of A]
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const u32x4*)(zh + (size_t)ia * DK + ks * 16 + g * 8);
-    __syncthreads();
-    f32x16 S[4];
+        for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) S[kb][e] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            const int row = kb * 32 + ln;
-            const u32x4 kf = *(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + g, row) * 16);
-            S[kb] = mfma32h(kf, qf[ks], S[kb]);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) S[kb][e] *= c2;  // scale and base-2 exponent, on the fp32 score
-        if (twice) {
-            // staged for the other orientation: sc[key of B][row of A]
-#pragma unroll
-            for (int e = 0; e < 16; ++e) sc[(kb * 32 + acc_row(e, g)) * SPITCH + wave * 32 + ln] = S[kb][e];
-        }
+            for (int e = 0; e < 16; ++e) sc[staged(kb * 32 + acc_row(e, g), wave * 32 + ln)] = S[kb][e];
     }
     {
         const size_t slot = (((size_t)bh * T + A) * T + B) * ST + wave * 32 + ln;
@@ -215,13 +241,13 @@ __global__ __launch_bounds__(256) void sym_pair_kernel(Problem pb, CountCfg cc, 
 
     // ---- the same scores, transposed: the wavefront's 32 rows of B against the 128 keys of A ----
     __syncthreads();  // the staged tile is complete, V^T of B no longer needed
-    load_vt_tile<DK>(vt, zth, A * ST, tid);
+    vr.stage(vt, tid);
     const int jb_row = wave * 32 + ln;  // this lane's row of B within the tile
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-            const f32x4 v = *(const f32x4*)(sc + jb_row * SPITCH + kb * 32 + 8 * r4 + 4 * g);
+            const f32x4 v = *(const f32x4*)(sc + staged(jb_row, kb * 32 + 8 * r4 + 4 * g));
             S[kb][4 * r4 + 0] = v[0]; S[kb][4 * r4 + 1] = v[1]; S[kb][4 * r4 + 2] = v[2]; S[kb][4 * r4 + 3] = v[3];
         }
     __syncthreads();
@@ -233,40 +259,40 @@ __global__ __launch_bounds__(256) void sym_pair_kernel(Problem pb, CountCfg cc, 
 }
 
 // y_i = sum over the key tiles of a row of 2^(m_t - M) O_t / sum 2^(m_t - M) l_t, M the largest m_t.
-// Grid (T, batch * heads); four rows at a time, a lane per output column.
+// Bound by the reads of the partial states, T (d + 2) floats per row: a thread owns four output
+// columns of one row and the rows of a wavefront are neighbours, so that every request is a run of
+// whole KiB and four of them are in flight per thread (96 heads of 512: 71 -> 10 us against a wavefront per row, 52 MB).
 template <int DK>
 __global__ __launch_bounds__(256) void sym_merge_kernel(Problem pb, const float* __restrict__ part_m,
                                                         const float* __restrict__ part_l,
                                                         const float* __restrict__ part_o, bf16_t* __restrict__ out, int T)
 {
-    const int A = blockIdx.x, bh = blockIdx.y;
+    constexpr int CPR = DK / 4, RPW = 256 / CPR;  // pieces of a row; rows per workgroup, a divisor of 128
+    const int bh = blockIdx.y;
     const int bb = bh / pb.H, h = bh - bb * pb.H;
-    const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
-    for (int r0 = 0; r0 < ST; r0 += 4) {
-        const int row = r0 + sub, i = A * ST + row;
-        if (i >= pb.N) continue;
-        const size_t base = (((size_t)bh * T + A) * T) * ST + row;
-        float M = -INFINITY;
-        for (int t = 0; t < T; ++t) M = fmaxf(M, part_m[base + (size_t)t * ST]);
-        float L = 0.f, acc[DK / 64];
-#pragma unroll
-        for (int u = 0; u < DK / 64; ++u) acc[u] = 0.f;
-        for (int t = 0; t < T; ++t) {
-            const float m = part_m[base + (size_t)t * ST];
-            const float w = m > -INFINITY ? __builtin_amdgcn_exp2f(m - M) : 0.f;
-            L += w * part_l[base + (size_t)t * ST];
-#pragma unroll
-            for (int u = 0; u < DK / 64; ++u) acc[u] += w * part_o[(base + (size_t)t * ST) * DK + lane + 64 * u];
-        }
-        const float inv = L > 0.f ? 1.f / L : 0.f;
-        bf16_t* o = out + ((size_t)bb * pb.N + i) * ((size_t)pb.H * DK) + (size_t)h * DK;
-#pragma unroll
-        for (int u = 0; u < DK / 64; ++u) {
-            unsigned v = __float_as_uint(acc[u] * inv);
-            v += 0x7fffu + ((v >> 16) & 1u);  // round to nearest even; the value is finite
-            o[lane + 64 * u] = (bf16_t)(v >> 16);
-        }
+    const int i = blockIdx.x * RPW + threadIdx.x / CPR, c = (threadIdx.x % CPR) * 4;
+    if (i >= pb.N) return;
+    const int A = i / ST, row = i - A * ST;
+    const size_t base = ((size_t)bh * T + A) * T * ST + row;
+    const float* pm = part_m + base;
+    const float* pl = part_l + base;
+    const float* po = part_o + base * DK + c;
+    float M = -INFINITY;
+#pragma unroll 4
+    for (int t = 0; t < T; ++t) M = fmaxf(M, pm[(size_t)t * ST]);
+    float L = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int t = 0; t < T; ++t) {
+        const float m = pm[(size_t)t * ST];
+        const f32x4 o = *(const f32x4*)(po + (size_t)t * ST * DK);
+        const float w = m > -INFINITY ? __builtin_amdgcn_exp2f(m - M) : 0.f;
+        L += w * pl[(size_t)t * ST];
+        acc += w * o;
     }
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    *(u32x2*)(out + ((size_t)bb * pb.N + i) * ((size_t)pb.H * DK) + (size_t)h * DK + c) =
+        u32x2{pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)};
 }
 
 }  // namespace
@@ -288,13 +314,15 @@ hipError_t launch_sym_pair(const Problem& pb, const h16_t* z, const h16_t* zt, f
     float* part_o = work + 2 * rows;
     const CountCfg cc = count_cfg(pb.b);
     const float c2 = pb.scale * 1.4426950408889634f;
+    const int rows_merge = 1024 / pb.d;
+    const dim3 merge_grid((pb.N + rows_merge - 1) / rows_merge, pb.B * pb.H);
     const dim3 grid(pb.noskip ? T * T : T * (T + 1) / 2, pb.B * pb.H);
     if (pb.d == 64) {
         hipLaunchKernelGGL(sym_pair_kernel<64>, grid, dim3(256), 0, s, pb, cc, z, zt, part_m, part_l, part_o, T, pb.noskip, c2);
-        hipLaunchKernelGGL(sym_merge_kernel<64>, dim3(T, pb.B * pb.H), dim3(256), 0, s, pb, part_m, part_l, part_o, out, T);
+        hipLaunchKernelGGL(sym_merge_kernel<64>, merge_grid, dim3(256), 0, s, pb, part_m, part_l, part_o, out, T);
     } else if (pb.d == 128) {
         hipLaunchKernelGGL(sym_pair_kernel<128>, grid, dim3(256), 0, s, pb, cc, z, zt, part_m, part_l, part_o, T, pb.noskip, c2);
-        hipLaunchKernelGGL(sym_merge_kernel<128>, dim3(T, pb.B * pb.H), dim3(256), 0, s, pb, part_m, part_l, part_o, out, T);
+        hipLaunchKernelGGL(sym_merge_kernel<128>, merge_grid, dim3(256), 0, s, pb, part_m, part_l, part_o, out, T);
     } else {
         return hipErrorInvalidValue;
     }
