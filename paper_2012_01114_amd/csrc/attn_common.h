@@ -9,27 +9,20 @@ namespace attnring {
 constexpr int BC = 64;  // keys per staged tile
 
 struct CountCfg {
-    int b;        // rows per logical PE
-    int b_shift;  // log2(b), or -1 when b is not a power of two
+    int b;       // rows per logical PE
+    FastDiv by;  // division by b
 };
 
-inline CountCfg count_cfg(int b)
-{
-    CountCfg cc = {b, -1};
-    for (int sft = 0; sft < 31; ++sft)
-        if ((1 << sft) == b) cc.b_shift = sft;
-    return cc;
-}
+inline CountCfg count_cfg(int b) { return CountCfg{b, fast_div((unsigned)b)}; }
 
 // ceil(x / b): the number of multiples of b in [0, x)
 __device__ __forceinline__ unsigned cdiv_b(unsigned x, const CountCfg& cc)
 {
-    const unsigned y = x + (unsigned)cc.b - 1u;
-    return cc.b_shift >= 0 ? (y >> cc.b_shift) : y / (unsigned)cc.b;
+    return x ? divide(x - 1u, cc.by) + 1u : 0u;
 }
 __device__ __forceinline__ bool is_multiple(int x, const CountCfg& cc)
 {
-    return cc.b_shift >= 0 ? (x & (cc.b - 1)) == 0 : (x % cc.b) == 0;
+    return (int)divide((unsigned)x, cc.by) * cc.b == x;
 }
 
 // Swizzled chunk position inside an LDS row of ROWB bytes (256 or 128).

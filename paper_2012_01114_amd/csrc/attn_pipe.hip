@@ -365,8 +365,9 @@ template <int DK, int WAVES, bool CAUSAL, bool FUSEQ>
 __global__ __launch_bounds__(64 * WAVES)
 __attribute__((amdgpu_waves_per_eu(Pipe<DK, WAVES, CAUSAL>::OCC, Pipe<DK, WAVES, CAUSAL>::OCC)))
 void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, const h16_t* __restrict__ k,
-                      const h16_t* __restrict__ vt, bf16_t* __restrict__ out, int n_qtiles, int per_head, int n_work,
-                      const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wq, float qscale, int single)
+                      const h16_t* __restrict__ vt, bf16_t* __restrict__ out, int n_qtiles, FastDiv per_head_d, int n_work,
+                      FastDiv heads_d, FastDiv per_xcd_heads, const bf16_t* __restrict__ X,
+                      const bf16_t* __restrict__ Wq, float qscale, int single)
 {
     typedef Pipe<DK, WAVES, CAUSAL> T;
     constexpr int NKS = T::NKS, NDB = T::NDB, BR = T::BR;
@@ -380,6 +381,7 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
     // Consecutive workgroup ids go to different XCDs; give each XCD a contiguous
     // run of work items so that the workgroups of one head share an L2.
     const int per_xcd = gridDim.x >> 3;
+    const int per_head = (int)per_head_d.d;
     int bh, x;
     if (CAUSAL && single) {
         // Masked scheme on a launch too small to give every CU several row-tile pairs: one row tile
@@ -391,13 +393,14 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
         const int r = j >> 5, c = j & 31;
         const int row_len = min(32, per_xcd - (r << 5));
         const int p = (r << 5) + ((r & 1) ? row_len - 1 - c : c);
-        const int nh = per_xcd / per_head;  // whole heads per XCD (the launcher sees to it)
-        bh = (blockIdx.x & 7) * nh + p % nh;
-        x = per_head - 1 - p / nh;
+        const int nh = (int)per_xcd_heads.d;  // whole heads per XCD (the launcher sees to it)
+        const int t = (int)divide((unsigned)p, per_xcd_heads);
+        bh = (blockIdx.x & 7) * nh + p - t * nh;
+        x = per_head - 1 - t;
     } else {
         const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
         if (work >= n_work) return;
-        bh = work / per_head;
+        bh = (int)divide((unsigned)work, per_head_d);
         x = work - bh * per_head;
         if (pb.skip_rows && ((pb.B * pb.H) & 7) == 0) {
             // With the padded rows left out the batch items differ in work by the square of their
@@ -407,12 +410,12 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
             // computed the items differ less and the same change gains nothing over a run of a
             // hundred calls: the kernel gets 6 % faster and the GEMM beside it as much slower - the
             // chip holds a power limit, and time follows the energy of a call, not its idle gaps.)
-            const int j = (blockIdx.x >> 3) / per_head;  // head number within the XCD
+            const int j = (int)divide(blockIdx.x >> 3, per_head_d);  // head number within the XCD
             x = (blockIdx.x >> 3) - j * per_head;
             bh = j * 8 + (blockIdx.x & 7);
         }
     }
-    const int bb = bh / pb.H, h = bh - bb * pb.H;
+    const int bb = (int)divide((unsigned)bh, heads_d), h = bh - bb * pb.H;
 
     const int N = pb.N, Npad = pb.Npad;
     int len = N;
@@ -441,7 +444,7 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
     const unsigned k_lane_off = dma_lane_offset<T::KROWB>(wave, lane);
     const unsigned v_lane_off = dma_lane_offset<BC * 2>(wave, lane);
 
-    unsigned long long cnt_logical = 0;  // per lane; summed over the wavefront at the end
+    unsigned cnt_logical = 0;  // per lane; summed over the wavefront at the end
     unsigned cnt_phys = 0;               // wave-uniform
 
     // Masked scheme: workgroup x takes row tiles T-1-x and x (Sec. 5.2).  With padded rows left
@@ -515,24 +518,10 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
         // ---- counts: logical tiles whose first pair is allowed ----
         if (n_first < NB) {
             cnt_phys += (unsigned)(NB - n_first);
-            const int rcnt = pb.noskip ? N : rlen;  // rows that anchor counted tiles
-            const unsigned nr_anchor = cdiv_b(min(i0w + 32, rcnt), cc) - cdiv_b(min(i0w, rcnt), cc);
-            if (pb.noskip) {
-                if (lane == 0) cnt_logical += (unsigned long long)nr_anchor * cdiv_b(N, cc);
-            } else {
-                // whole blocks below the diagonal block and below the key length: every pair allowed
-                int k_int = (len >> 5) << 5;
-                if (CAUSAL) k_int = k_int < i0w ? k_int : i0w;
-                if (k_int < 0) k_int = 0;
-                if (lane == 0) cnt_logical += (unsigned long long)nr_anchor * cdiv_b(k_int, cc);
-                // the rest (diagonal block, block cut by the key length): pair by pair
-                const int k_end = CAUSAL ? (len < i0w + 32 ? len : i0w + 32) : len;
-                if (g == 0 && i < rlen && is_multiple(i, cc)) {
-#pragma nounroll
-                    for (int j = (int)cdiv_b(k_int, cc) * cc.b; j < k_end; j += cc.b)
-                        cnt_logical += (!CAUSAL || j <= i) ? 1u : 0u;
-                }
-            }
+            // A row block is counted by the lane that holds its first row: the key blocks that start
+            // among the keys that row may meet.
+            if (g == 0 && i < (pb.noskip ? N : rlen) && is_multiple(i, cc))
+                cnt_logical += cdiv_b((unsigned)(pb.noskip ? N : CAUSAL ? min(len, i + 1) : len), cc);
         }
 
         typename T::Row r;
@@ -801,7 +790,7 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
         }
     }
 
-    // one atomic per wavefront
+    // one atomic per wavefront; p <= 46340 logical tiles per row block, 32 rows and four passes: 32 bits
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) cnt_logical += __shfl_xor(cnt_logical, o, 64);
     if (lane == 0) {
@@ -831,7 +820,7 @@ hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, c
     const CountCfg cc = count_cfg(pb.b);
 #define ATTN_LAUNCH(DK_, W_, C_, F_)                                                                                    \
     hipLaunchKernelGGL((attn_pipe_kernel<DK_, W_, C_, F_>), dim3(grid), dim3(64 * W_), 0, s, pb, cc, q, k, vt, out, \
-                       n_qtiles, per_head, n_work, X, Wq, qscale, single ? 1 : 0)
+                       n_qtiles, fast_div(per_head), n_work, fast_div(pb.H), fast_div(grid / 8 / per_head), X, Wq, qscale, single ? 1 : 0)
 #define ATTN_PICK(DK_, W_)                                                                  \
     do {                                                                                    \
         if (causal) { if (fuse) ATTN_LAUNCH(DK_, W_, true, true); else ATTN_LAUNCH(DK_, W_, true, false); }   \

@@ -43,6 +43,28 @@ __device__ __forceinline__ void count_add(unsigned long long* counters, unsigned
     if (phys) atomicAdd(&slot[CNT_PHYS], phys);
 }
 
+// Division by a number the host knows: n / d = (n * mul) >> (32 + shr) for n < 2^31, with
+// mul = ceil(2^(32 + shr) / d).  An integer division by a run-time value is some forty dependent
+// instructions, and a kernel's work-item arithmetic is a chain of them: 0.5 us before the first
+// request of a workgroup goes out.
+struct FastDiv {
+    unsigned d, mul, shr;  // mul 0: d is 1
+};
+inline FastDiv fast_div(unsigned d)
+{
+    FastDiv f = {d, 0u, 0u};
+    if (d <= 1) return f;
+    unsigned log2up = 1;
+    while (((uint64_t)1 << log2up) < d) ++log2up;
+    f.shr = log2up - 1;
+    f.mul = (unsigned)((((uint64_t)1 << (31 + log2up)) + d - 1) / d);
+    return f;
+}
+__device__ __forceinline__ unsigned divide(unsigned n, const FastDiv& f)
+{
+    return f.mul ? __umulhi(n, f.mul) >> f.shr : n;
+}
+
 // Row of the caller's x (and out) that holds vector i of batch item bb.  Padded layout: every item
 // has N rows.  Packed layout: item bb has rows row0[bb] .. row0[bb + 1] - 1 and nothing follows its
 // last vector; a vector at or past its length is in no allowed pair, and a read for it (whole tiles

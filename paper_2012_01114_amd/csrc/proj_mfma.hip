@@ -109,43 +109,69 @@ constexpr int ROWB = BK * 2 + 16;  // LDS bytes per tile row (padded)
 // ~32 tiles in flight on one XCD form a 4 x 8 patch that shares its operand
 // slices in that XCD's L2 instead of fetching 32 different x slices.
 constexpr int GROUP_W = 4;
-__device__ __forceinline__ void tile_of(int id, int tiles_x, int tiles_w, int& tw, int& tx, int group_w = GROUP_W)
+// What a kernel needs for its tile's place, with the divisions prepared on the host.
+struct TileMap {
+    int tiles_x, tiles_w, n_tiles;
+    int group_w;       // weight tiles walked together
+    FastDiv width;     // group_w * tiles_x
+    FastDiv per_item;  // x tiles per batch item (Npad / tile height)
+    int spread;        // matrices over which the column tiles are dealt (below), 0: not
+    int per_matrix;    // column tiles of one matrix
+    int mult;          // coprime to tiles_x
+    FastDiv by_x;      // tiles_x
+};
+__device__ __forceinline__ int small_div(int n, int d)  // d in 1..4
 {
-    const int width = group_w * tiles_x;
-    const int grp = id / width;
-    const int first_w = grp * group_w;
-    const int gsz = min(tiles_w - first_w, group_w);
-    const int local = id - grp * width;
-    tx = local / gsz;
-    tw = first_w + (local - tx * gsz);
+    return d == 4 ? n >> 2 : d == 2 ? n >> 1 : d == 1 ? n : (int)(__umulhi((unsigned)n, 0xAAAAAAABu) >> 1);
 }
 // With key lengths some k and v tiles return at once, and an XCD keeps the run of tiles it was
 // given: the order above would hand some XCDs q tiles only and others the short batch items.
 // Both tile indices are therefore permuted, so that every run holds q, k and v tiles in equal
 // parts (groups of three column tiles, dealt round-robin over the three matrices) and x tiles
 // from all over the batch (a multiplier that is coprime to their number).
-__device__ __forceinline__ void spread_tiles(int tiles_x, int tiles_w, int& tw, int& tx, int n_matrices = 3)
+__device__ __forceinline__ void tile_of(const TileMap& tm, int id, int& tw, int& tx)
 {
-    const int per_matrix = tiles_w / n_matrices;
-    tw = (tw % n_matrices) * per_matrix + tw / n_matrices;
-    int mult = tiles_x / 8 + 1;
-    while (true) {  // the next number coprime to tiles_x
-        int a = mult, b = tiles_x;
+    const int grp = (int)divide((unsigned)id, tm.width);
+    const int first_w = grp * tm.group_w;
+    const int gsz = min(tm.tiles_w - first_w, tm.group_w);
+    const int local = id - grp * (int)tm.width.d;
+    tx = small_div(local, gsz);
+    tw = first_w + (local - tx * gsz);
+    if (tm.spread) {
+        const int q = small_div(tw, tm.spread);
+        tw = (tw - q * tm.spread) * tm.per_matrix + q;
+        const long long t = (long long)tx * tm.mult;
+        tx = t <= 0x7fffffffLL ? (int)t - (int)divide((unsigned)t, tm.by_x) * tm.tiles_x : (int)(t % tm.tiles_x);
+    }
+}
+inline TileMap tile_map(const Problem& pb, int bt, int matrices, bool spread)
+{
+    TileMap tm;
+    tm.tiles_x = pb.B * pb.Npad / bt;
+    tm.tiles_w = matrices * pb.H * pb.d / bt;
+    tm.n_tiles = tm.tiles_x * tm.tiles_w;
+    tm.group_w = spread ? matrices : GROUP_W;
+    tm.width = fast_div((unsigned)(tm.group_w * tm.tiles_x));
+    tm.per_item = fast_div((unsigned)(pb.Npad / bt));
+    tm.spread = spread ? matrices : 0;
+    tm.per_matrix = tm.tiles_w / matrices;
+    tm.mult = tm.tiles_x / 8 + 1;
+    for (;; ++tm.mult) {
+        int a = tm.mult, b = tm.tiles_x;
         while (b) { const int r = a % b; a = b; b = r; }
         if (a == 1) break;
-        ++mult;
     }
-    tx = (int)(((long long)tx * mult) % tiles_x);
+    tm.by_x = fast_div((unsigned)tm.tiles_x);
+    return tm;
 }
 
-// Whether every row of the x tile that starts at flattened row x0 (Npad rows per batch item, a
-// multiple of the tile height) lies at or past the key length of its batch item.
-__device__ __forceinline__ bool past_key_length(const int* __restrict__ lens, int x0, int Npad, int N)
+// Whether every row of an x tile that starts at vector i0 of batch item bb lies at or past the
+// item's key length.
+__device__ __forceinline__ bool past_key_length(const int* __restrict__ lens, int bb, int i0, int N)
 {
-    const int bb = x0 / Npad;
     int len = lens[bb];
     len = len < 0 ? 0 : (len > N ? N : len);
-    return x0 - bb * Npad >= len;
+    return i0 >= len;
 }
 
 template <int BT>
@@ -153,7 +179,7 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
                                                         const bf16_t* __restrict__ X,
                                                         const bf16_t* __restrict__ Wt, h16_t* __restrict__ qo,
                                                         h16_t* __restrict__ ko, h16_t* __restrict__ vto,
-                                                        int tiles_x, int tiles_w, float qscale, const int* __restrict__ lens, bool skip_q_rows, bool no_q,
+                                                        TileMap tm, float qscale, const int* __restrict__ lens, bool skip_q_rows, bool no_q,
                                                         const int* __restrict__ row0)
 {
     constexpr int WT = BT / 2;          // wavefront tile edge
@@ -168,19 +194,21 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
     const int wr = wave >> 1, wc = wave & 1;
     const int HD = H * d;
 
-    const int n_tiles = tiles_x * tiles_w;
     const int per_xcd = gridDim.x >> 3;
     const int tile_id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (tile_id >= n_tiles) return;
+    if (tile_id >= tm.n_tiles) return;
     int tw, tx_;
-    tile_of(tile_id, tiles_x, tiles_w, tw, tx_);
+    tile_of(tm, tile_id, tw, tx_);
     const int x0 = tx_ * BT;   // first x-side row (padded vector index)
     const int w0 = tw * BT;    // first stacked output column
+    const int bb = (int)divide((unsigned)tx_, tm.per_item);  // Npad is a multiple of BT: one batch item per tile
+    const int i0 = x0 - bb * Npad;
+    if (i0 >= N) return;       // nothing but padding
     const bool is_v = w0 >= 2 * HD;
     // Keys past the key length of their batch item are in no allowed pair (Sec. 5.1 applied to
     // padding): their k and v rows are not computed.  (q rows are: every query row has an output.)
     // With padded rows left out as queries too, the same holds for their q rows.
-    if (lens != nullptr && (w0 >= HD || skip_q_rows) && past_key_length(lens, x0, Npad, N)) return;
+    if (lens != nullptr && (w0 >= HD || skip_q_rows) && past_key_length(lens, bb, i0, N)) return;
     if (no_q && w0 < HD) return;  // q = k = v scheme: the shared vectors are wanted as k and v^T only
 
     // per-thread source rows: chunk ch = tid + 256*u -> row ch/8, k-chunk ch%8
@@ -189,9 +217,7 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
 #pragma unroll
     for (int u = 0; u < NCH; ++u) {
         const int row = (tid >> 3) + 32 * u;
-        const int xr = x0 + row;
-        const int bb = xr / Npad;
-        xoff[u] = source_row(row0, Bsz, N, bb, xr - bb * Npad) * (unsigned)D;
+        xoff[u] = source_row(row0, Bsz, N, bb, i0 + row) * (unsigned)D;
         woff[u] = (unsigned)(w0 + row) * (unsigned)D;
     }
 
@@ -256,9 +282,7 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
         // A side = output columns (4 consecutive per register quad), B side = vectors.
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const int xr = x0 + wc * WT + 32 * b + ln;
-            const int bb = xr / Npad;
-            const int i = xr - bb * Npad;
+            const int i = i0 + wc * WT + 32 * b + ln;
             if (i >= N) continue;
 #pragma unroll
             for (int a = 0; a < NB; ++a)
@@ -286,9 +310,7 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
             for (int a = 0; a < NB; ++a)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
-                    const int xr = x0 + wr * WT + 32 * a + 8 * r4 + 4 * g;  // vector of register 4*r4
-                    const int bb = xr / Npad;
-                    const int i = xr - bb * Npad;
+                    const int i = i0 + wr * WT + 32 * a + 8 * r4 + 4 * g;  // vector of register 4*r4
                     if (i >= N) continue;
                     const int blk = i >> 6, r64 = i & 63;
                     const int slot = (r64 & 48) | vt_slot16(r64 & 15);
@@ -324,8 +346,8 @@ template <int BT, int WR, int WC>
 __global__ __launch_bounds__(64 * WR * WC, (WR * WC) / 4 * (BT == 256 ? 1 : 2))
 void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
                      const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
-                     h16_t* __restrict__ qo, h16_t* __restrict__ ko, h16_t* __restrict__ vto, int tiles_x,
-                     int tiles_w, float qscale, const int* __restrict__ lens, bool skip_q_rows, bool no_q,
+                     h16_t* __restrict__ qo, h16_t* __restrict__ ko, h16_t* __restrict__ vto, TileMap tm,
+                     float qscale, const int* __restrict__ lens, bool skip_q_rows, bool no_q,
                      const int* __restrict__ row0, unsigned long long* __restrict__ counters)
 {
     constexpr int NW = WR * WC;
@@ -351,25 +373,26 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     const int wr = wave / WC, wc = wave % WC;
     const int HD = H * d;
 
-    const int n_tiles = tiles_x * tiles_w;
     const int per_xcd = gridDim.x >> 3;
     const int tile_id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (tile_id >= n_tiles) return;
+    if (tile_id >= tm.n_tiles) return;
     int tw, tx_;
     // no_q (the queries are not wanted: q = k = v scheme, or projected by the attention kernel): the
     // grid holds the k and v column tiles only
-    tile_of(tile_id, tiles_x, tiles_w, tw, tx_, lens != nullptr ? (no_q ? 2 : 3) : GROUP_W);
-    if (lens != nullptr) spread_tiles(tiles_x, tiles_w, tw, tx_, no_q ? 2 : 3);
-    const int x0 = tx_ * BT, w0 = tw * BT + (no_q ? HD : 0);
+    tile_of(tm, tile_id, tw, tx_);
+    const int bb = (int)divide((unsigned)tx_, tm.per_item);  // Npad is a multiple of BT: one batch item per tile
+    const int i0 = tx_ * BT - bb * Npad;
+    if (i0 >= N) return;  // nothing but padding
+    const int w0 = tw * BT + (no_q ? HD : 0);
     const bool is_v = w0 >= 2 * HD;
     // Keys past the key length of their batch item are in no allowed pair (Sec. 5.1 applied to
     // padding): their k and v rows are not computed.  (q rows are: every query row has an output.)
     // With padded rows left out as queries too, the same holds for their q rows.
-    if (lens != nullptr && (w0 >= HD || skip_q_rows) && past_key_length(lens, x0, Npad, N)) return;
+    if (lens != nullptr && (w0 >= HD || skip_q_rows) && past_key_length(lens, bb, i0, N)) return;
 
     // The weights stay in the caller's layout, W[k][column]: this tile's columns of the one matrix
     // it lies in.
-    const int which = w0 / HD;
+    const int which = w0 >= 2 * HD ? 2 : w0 >= HD ? 1 : 0;
     const bf16_t* Wm = (which == 0 ? Wq : (which == 1 ? Wk : Wv)) + (w0 - which * HD);
 
     // Source byte offsets of this lane for its pieces.  32 bits hold them (attn_init bounds the
@@ -384,9 +407,7 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     for (int u = 0; u < XPW; ++u) {
         const int row = (wave + NW * u) * 8 + (lane >> 3);
         const int c = (lane & 7) ^ ((row >> 1) & 7);
-        const int xr = x0 + row;
-        const int bb = xr / Npad;
-        xoff[u] = 2u * (source_row(row0, Bsz, N, bb, xr - bb * Npad) * (unsigned)D + c * 8);
+        xoff[u] = 2u * (source_row(row0, Bsz, N, bb, i0 + row) * (unsigned)D + c * 8);
     }
 #pragma unroll
     for (int u = 0; u < WPW; ++u) {
@@ -612,8 +633,6 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     constexpr int NT = 64 * NW;
     constexpr int UNITS = BT * BT / 8;  // 16-byte pieces of the tile
     const int dsh = d == 128 ? 7 : 6;   // d is 64 or 128 on this path
-    const int bb = x0 / Npad;           // Npad is a multiple of BT: one batch element per tile
-    const int i0 = x0 - bb * Npad;
     if (!is_v) {
         // q and k: [head][vector][d], a staged row is one vector's d values of one head.
         const int which = w0 >= HD ? 1 : 0;
@@ -693,11 +712,11 @@ hipError_t launch_dma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, cons
                       h16_t* q, h16_t* k, h16_t* vt, hipStream_t s)
 {
     const float qscale = q_prescale(pb);
-    const int tiles_x = pb.B * pb.Npad / BT;
-    const int tiles_w = (pb.no_q ? 2 : 3) * pb.H * pb.d / BT;
-    const int grid = ((tiles_x * tiles_w + 7) / 8) * 8;
+    const int* lens = pb.noskip ? nullptr : pb.lens;
+    const TileMap tm = tile_map(pb, BT, pb.no_q ? 2 : 3, lens != nullptr);
+    const int grid = ((tm.n_tiles + 7) / 8) * 8;
     hipLaunchKernelGGL((proj_dma_kernel<BT, WR, WC>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad, pb.D,
-                       pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tiles_x, tiles_w, qscale, pb.noskip ? nullptr : pb.lens,
+                       pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens,
                        pb.skip_rows, pb.no_q, pb.row0, pb.counters);
     return hipGetLastError();
 }
@@ -707,11 +726,10 @@ hipError_t launch_bt(const Problem& pb, const bf16_t* X, const bf16_t* Wt, h16_t
                      hipStream_t s)
 {
     const float qscale = q_prescale(pb);
-    const int tiles_x = pb.B * pb.Npad / BT;
-    const int tiles_w = 3 * pb.H * pb.d / BT;
-    const int grid = ((tiles_x * tiles_w + 7) / 8) * 8;
+    const TileMap tm = tile_map(pb, BT, 3, false);
+    const int grid = ((tm.n_tiles + 7) / 8) * 8;
     hipLaunchKernelGGL(proj_mfma_kernel<BT>, dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X, Wt,
-                       q, k, vt, tiles_x, tiles_w, qscale, pb.noskip ? nullptr : pb.lens, pb.skip_rows, pb.no_q, pb.row0);
+                       q, k, vt, tm, qscale, pb.noskip ? nullptr : pb.lens, pb.skip_rows, pb.no_q, pb.row0);
     return hipGetLastError();
 }
 
