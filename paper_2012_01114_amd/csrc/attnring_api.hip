@@ -96,12 +96,6 @@ Problem make_problem(const attn_ctx* c, int scheme)
     return pb;
 }
 
-__global__ __launch_bounds__(1024) void zero_counters_kernel(unsigned long long* c)
-{
-    for (int w = 0; w < CNT_WORDS; ++w) c[(size_t)threadIdx.x * CNT_SLOT_WORDS + w] = 0ull;  // CNT_SLOTS threads
-    if (threadIdx.x < CNT_WORDS) c[CNT_TOTALS + threadIdx.x] = 0ull;
-}
-
 // totals[w] = sum over the slots; one workgroup of CNT_SLOTS threads
 __global__ __launch_bounds__(1024) void sum_counters_kernel(unsigned long long* c)
 {
@@ -237,7 +231,7 @@ attn_status static_scratch_on_current_device(unsigned char** out)
 }
 
 // Rows n .. Npad-1 of q and k, and the key slots of v^T that belong to them, of every (batch, head):
-// the kernels take them to be zero.  Grid (batch * heads, 3).
+// the debug mode that walks every block takes them to be zero.  Grid (batch * heads, 3).
 __global__ __launch_bounds__(256) void clear_pad_rows_kernel(int N, int Npad, int d, h16_t* __restrict__ q,
                                                              h16_t* __restrict__ k, h16_t* __restrict__ vt)
 {
@@ -398,14 +392,9 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
         e = hipMalloc((void**)&ctx->sym_work, sym_pair_workspace_floats(pb) * sizeof(float));
         if (e != hipSuccess) return hip_fail(ctx, "hipMalloc(partial row states)", e);
     }
-    if (!use_mfma) {  // the matrix-core path clears the counters in its first kernel
-        hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(CNT_SLOTS), 0, s, ctx->counters);
-        e = hipGetLastError();
-        CHECK("launch zero_counters");
-    }
     if (use_mfma) {
-        // the first kernel of the call clears the counter slots: the projection itself when it reads
-        // the weights in place, else the weight re-layout
+        // the first kernel of a call clears the counter slots; here the projection when it reads the
+        // weights in place, else the weight re-layout
         if (!proj_reads_weights_in_place(pb, (const bf16_t*)Wq, (const bf16_t*)Wk, (const bf16_t*)Wv)) {
             e = launch_transpose_w(pb, (const bf16_t*)Wq, (const bf16_t*)Wk, (const bf16_t*)Wv, ctx->wt, s);
             CHECK("launch transpose_w");
@@ -544,7 +533,10 @@ attn_status attn_forward_static(const attn_config* cfg, const int32_t* lens_dev,
 
     hipStream_t s = (hipStream_t)hip_stream;
     hipError_t e;
-    if (pb.Npad > pb.N) {  // whatever an earlier call left in the rows past n
+    // What an earlier call left in the rows past n: their q and k reach only scores that are masked,
+    // and the projection writes zeros into the rest of v^T's last 64-key block.  Only the debug mode
+    // that walks every block meets the blocks behind it.
+    if (pb.noskip && pb.Npad > pb.N) {
         hipLaunchKernelGGL(clear_pad_rows_kernel, dim3(pb.B * pb.H, 3), dim3(256), 0, s, pb.N, pb.Npad, pb.d, q, k, vt);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(nullptr, "launch clear_pad_rows", e);

@@ -43,6 +43,16 @@ __device__ __forceinline__ void count_add(unsigned long long* counters, unsigned
     if (phys) atomicAdd(&slot[CNT_PHYS], phys);
 }
 
+// The first kernel of a call clears the slots and totals: its first workgroup does.
+__device__ __forceinline__ void clear_counters(unsigned long long* counters)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
+        for (int sl = threadIdx.x; sl < CNT_SLOTS; sl += blockDim.x)
+            for (int w = 0; w < CNT_WORDS; ++w) counters[(size_t)sl * CNT_SLOT_WORDS + w] = 0ull;
+        if (threadIdx.x < CNT_WORDS) counters[CNT_TOTALS + threadIdx.x] = 0ull;
+    }
+}
+
 // Division by a number the host knows: n / d = (n * mul) >> (32 + shr) for n < 2^31, with
 // mul = ceil(2^(32 + shr) / d).  An integer division by a run-time value is some forty dependent
 // instructions, and a kernel's work-item arithmetic is a chain of them: 0.5 us before the first

@@ -89,8 +89,9 @@ __device__ __forceinline__ u32x4 clip_piece(u32x4 v, bool in)
 
 template <typename T, bool WHOLE>
 __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, int H, int d, const T* __restrict__ X,
-                                                         ProjArgs pa, int tiles_n)
+                                                         ProjArgs pa, int tiles_n, unsigned long long* __restrict__ counters)
 {
+    clear_counters(counters);
     typedef Slice<T> SL;
     constexpr int BM = 64, BN = 64, KS = SL::KS, VEC = SL::VEC;
     constexpr int AP = SL::APITCH, BP = SL::bpitch(BN);
@@ -194,8 +195,10 @@ __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, in
 
 // z = x split into heads, for the q = k = v scheme without a projection matrix.
 template <typename T>
-__global__ void copy_heads_kernel(int total, int N, int H, int d, const T* __restrict__ X, float* __restrict__ out)
+__global__ void copy_heads_kernel(int total, int N, int H, int d, const T* __restrict__ X, float* __restrict__ out,
+                                  unsigned long long* __restrict__ counters)
 {
+    clear_counters(counters);
     int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= total) return;
     int l = e % d, t = e / d;
@@ -213,8 +216,8 @@ void launch_proj_type(const Problem& pb, const T* X, const ProjArgs& pa, int cou
     for (int m = 0; m < count; ++m) bits |= reinterpret_cast<uintptr_t>(pa.W[m]);
     const bool whole = pb.D % Slice<T>::VEC == 0 && HD % Slice<T>::VEC == 0 && (bits & 15) == 0;
     const dim3 grid(tiles_n * count, (M + 63) / 64);
-    if (whole) hipLaunchKernelGGL((proj_float_kernel<T, true>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n);
-    else hipLaunchKernelGGL((proj_float_kernel<T, false>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n);
+    if (whole) hipLaunchKernelGGL((proj_float_kernel<T, true>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, pb.counters);
+    else hipLaunchKernelGGL((proj_float_kernel<T, false>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, pb.counters);
 }
 
 }  // namespace
@@ -238,10 +241,10 @@ hipError_t launch_copy_heads_generic(const Problem& pb, const void* X, float* ou
     dim3 grid((total + 255) / 256);
     if (pb.is_bf16)
         hipLaunchKernelGGL(copy_heads_kernel<bf16_t>, grid, dim3(256), 0, s, total, pb.N, pb.H, pb.d,
-                           (const bf16_t*)X, out);
+                           (const bf16_t*)X, out, pb.counters);
     else
         hipLaunchKernelGGL(copy_heads_kernel<float>, grid, dim3(256), 0, s, total, pb.N, pb.H, pb.d,
-                           (const float*)X, out);
+                           (const float*)X, out, pb.counters);
     return hipGetLastError();
 }
 

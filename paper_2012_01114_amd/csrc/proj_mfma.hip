@@ -21,15 +21,6 @@ namespace {
 // (0,0,0) also clears the counter slots of the call (every forward pass runs
 // this kernel first).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void clear_counters(unsigned long long* counters)
-{
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
-        for (int sl = threadIdx.x; sl < CNT_SLOTS; sl += blockDim.x)
-            for (int w = 0; w < CNT_WORDS; ++w) counters[(size_t)sl * CNT_SLOT_WORDS + w] = 0ull;
-        if (threadIdx.x < CNT_WORDS) counters[CNT_TOTALS + threadIdx.x] = 0ull;
-    }
-}
-
 __global__ __launch_bounds__(256) void transpose_w_kernel(int D, int HD, const bf16_t* __restrict__ Wq,
                                                           const bf16_t* __restrict__ Wk,
                                                           const bf16_t* __restrict__ Wv, bf16_t* __restrict__ Wt,
