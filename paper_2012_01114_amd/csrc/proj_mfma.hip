@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void transpose_w16_kernel(int D, int HD, const
 }
 
 // ---------------------------------------------------------------------------
-// Fallback GEMM (any d_model, any alignment), on transposed weights:
+// Fallback GEMM (an odd number of 64-wide heads, unaligned weights), on transposed weights:
 // C = A . B^T with both operands k-contiguous.  Square BT x BT tile per
 // workgroup, 2 x 2 wavefronts, 32x32x16 MFMA blocks, 64-deep k slices double
 // buffered in LDS.  The "x side" rows are vectors (with the per-batch row pitch
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
 }
 
 // ---------------------------------------------------------------------------
-// The GEMM for d_model a multiple of 64 and 16-byte aligned weights, with the operands
+// The GEMM for 16-byte aligned weights, with the operands
 // copied from global memory straight into LDS (buffer_load ... lds, 16 bytes per lane) and
 // the weights taken in the caller's layout.
 //
@@ -332,8 +332,12 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
 //            with the transposing LDS read (see the offset table in the kernel).  A slot is
 //            free half a slice after its first read.
 // Every request has at least one slice period to land.  WR x WC wavefronts share a BT x BT tile.
+// TAIL: d_model is a multiple of 8 only.  In the last slice the 16-byte pieces of a vector past its
+// end, and the k-rows past the last, are fetched from a piece of zeros, through per-lane addresses.
 // ---------------------------------------------------------------------------
-template <int BT, int WR, int WC>
+__device__ const u32x4 zero_piece = {0u, 0u, 0u, 0u};
+
+template <int BT, int WR, int WC, bool TAIL>
 __global__ __launch_bounds__(64 * WR * WC, (WR * WC) / 4 * (BT == 256 ? 1 : 2))
 void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
                      const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
@@ -411,14 +415,31 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)X, 0, -1, 0x00020000);
     const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Wm, 0, -1, 0x00020000);
     // piece u of the x side of the slice that starts at k0, into unit `unit`
+    typedef const __attribute__((address_space(1))) void* global_ptr;
+    typedef __attribute__((address_space(3))) void* lds_ptr;
     auto req_x = [&](int u, int k0, int unit) {
         unsigned char* dst = lds + unit * XU + (wave + NW * u) * 1024;
+        if (TAIL && k0 + 64 > D) {
+            const int c = (lane & 7) ^ ((((wave + NW * u) * 8 + (lane >> 3)) >> 1) & 7);
+            const void* src = k0 + 8 * c < D ? (const void*)((const unsigned char*)X + xoff[u] + 2u * (unsigned)k0)
+                                             : (const void*)&zero_piece;
+            __builtin_amdgcn_global_load_lds((global_ptr)src, (lds_ptr)dst, 16, 0, 0);
+            return;
+        }
         __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (__attribute__((address_space(3))) void*)dst, 16,
                                                  (int)xoff[u], (int)(2u * (unsigned)k0), 0, 0);
     };
     // piece u of half h of the weight side of the slice that starts at k0, into slot `slot`
     auto req_w = [&](int u, int k0, int h, int slot) {
         unsigned char* dst = lds + W_BASE + slot * WS + (wave + NW * u) * 1024;
+        if (TAIL && k0 + 64 > D) {
+            const int kr = k0 + 32 * h + (wave + NW * u) * WRPP + lane / WCPR;
+            const void* src = kr < D ? (const void*)((const unsigned char*)Wm + woff[u] +
+                                                     2u * ((unsigned)(k0 + 32 * h) * (unsigned)HD))
+                                     : (const void*)&zero_piece;
+            __builtin_amdgcn_global_load_lds((global_ptr)src, (lds_ptr)dst, 16, 0, 0);
+            return;
+        }
         __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (__attribute__((address_space(3))) void*)dst, 16,
                                                  (int)woff[u], (int)(2u * (unsigned)(k0 + 32 * h) * (unsigned)HD), 0, 0);
     };
@@ -578,7 +599,7 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
 
     // Prologue: slice 0 whole, and of slice 1 what steps 2-4 of a slice before slice 0 would
     // have sent (its last weight piece follows in step 1 of slice 0).
-    const int ns = D / 64;
+    const int ns = TAIL ? (D + 63) / 64 : D / 64;
     req_w(0, 0, 0, 0);
     req_w(1, 0, 0, 0);
 #pragma unroll
@@ -706,9 +727,12 @@ hipError_t launch_dma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, cons
     const int* lens = pb.noskip ? nullptr : pb.lens;
     const TileMap tm = tile_map(pb, BT, pb.no_q ? 2 : 3, lens != nullptr);
     const int grid = ((tm.n_tiles + 7) / 8) * 8;
-    hipLaunchKernelGGL((proj_dma_kernel<BT, WR, WC>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad, pb.D,
-                       pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens,
-                       pb.skip_rows, pb.no_q, pb.row0, pb.counters);
+    if (pb.D % 64 == 0)
+        hipLaunchKernelGGL((proj_dma_kernel<BT, WR, WC, false>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
+                           pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
+    else
+        hipLaunchKernelGGL((proj_dma_kernel<BT, WR, WC, true>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
+                           pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
     return hipGetLastError();
 }
 
@@ -741,14 +765,14 @@ hipError_t launch_transpose_w(const Problem& pb, const bf16_t* Wq, const bf16_t*
     return hipGetLastError();
 }
 
-// Whether the projection reads the weights where the caller has them (no W^T, no re-layout
-// kernel): d_model in whole 64-deep slices, and 16-byte aligned weights for the 16-byte copies.
+// Whether the projection reads the weights where the caller has them (no W^T, no re-layout kernel):
+// whole 128-column tiles in each matrix, and 16-byte aligned weights for the 16-byte copies.
 bool proj_reads_weights_in_place(const Problem& pb, const bf16_t* Wq, const bf16_t* Wk, const bf16_t* Wv)
 {
     const int HD = pb.H * pb.d;
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(Wq) | reinterpret_cast<uintptr_t>(Wk) |
                              reinterpret_cast<uintptr_t>(Wv)) & 15) == 0;
-    return pb.D % 64 == 0 && HD % 128 == 0 && aligned16;
+    return pb.D % 8 == 0 && HD % 128 == 0 && aligned16;
 }
 
 hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk,

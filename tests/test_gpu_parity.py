@@ -140,6 +140,38 @@ def test_mfma_path_small(shape, scheme, tiles, seed0):
     _run_and_compare(w, scheme, 0.0, lens=np.zeros(B, dtype=np.int32), flags=tiles)
 
 
+# ---- the projection's last slice of d_model when it is not 64 deep (vectors in whole 16-byte pieces) ----
+@pytest.mark.parametrize("d_model", [8, 56, 72, 136, 200])   # one slice, cut; then two to four with 8 .. 8 left
+@pytest.mark.parametrize("shape", [
+    # B, n, H, d, p
+    (2, 200, 2, 64, 25),          # 128 x 128 tiles
+    (8, 2048, 16, 128, 256),      # 256 x 256 tiles (512 of them and more)
+])
+def test_projection_with_a_cut_slice(shape, d_model):
+    B, n, H, d, p = shape
+    w = hp.custom_workload("cut_slice", B, n, d_model, H, d, p, "bf16", CAUSAL, 7700 + d_model)
+    if n <= 256:
+        _run_and_compare(w, CAUSAL, 0.0)
+        return
+    # values that follow a vector's end belong to the next one and must not reach it: rows of infinities
+    stored, f64 = inputs.make_inputs(w)
+    bad = [(0, n - 1), (3, 77), (7, n - 1)]
+    for b, i in bad:
+        stored["X"][b, i] = float("inf")
+    stored["lens"] = None
+    run = hp.GpuRun(w, stored)
+    try:
+        got, _ = run.forward(CAUSAL)
+    finally:
+        run.close()
+    for (b, h) in [(0, 0), (1, 5), (3, 15), (7, 8)]:
+        rows = [r for r in range(76 if b == 3 else n - 1) if r < 140 or r > n - 70]
+        ref = orc.head_rows(f64["X"], f64["Wq"], f64["Wk"], f64["Wv"], n_heads=H, d_k=d, p=p, scheme=CAUSAL,
+                            scale=hp.default_scale(w, 0.0), b=b, h=h, rows=rows)
+        clean = [k for k, r in enumerate(rows) if r // 32 * 32 + 32 <= (77 if b == 3 else n - 1)]  # a 32-row block before it
+        hp.tol_check(got[b, [rows[k] for k in clean], h * d:(h + 1) * d], ref[clean], w.dtype)
+
+
 # ---- queries projected inside the attention kernel (ATTN_FLAG_FUSE_Q_PROJECTION) ----------------------
 @pytest.mark.parametrize("shape", [
     (2, 320, 64, 2, 64, 40),      # two 32-row slices of Wq
