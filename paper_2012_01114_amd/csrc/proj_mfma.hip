@@ -135,15 +135,15 @@ __device__ __forceinline__ void tile_of(const TileMap& tm, int id, int& tw, int&
         tx = t <= 0x7fffffffLL ? (int)t - (int)divide((unsigned)t, tm.by_x) * tm.tiles_x : (int)(t % tm.tiles_x);
     }
 }
-inline TileMap tile_map(const Problem& pb, int bt, int matrices, bool spread)
+inline TileMap tile_map(const Problem& pb, int bx, int bw, int matrices, bool spread)
 {
     TileMap tm;
-    tm.tiles_x = pb.B * pb.Npad / bt;
-    tm.tiles_w = matrices * pb.H * pb.d / bt;
+    tm.tiles_x = pb.B * pb.Npad / bx;
+    tm.tiles_w = matrices * pb.H * pb.d / bw;
     tm.n_tiles = tm.tiles_x * tm.tiles_w;
     tm.group_w = spread ? matrices : GROUP_W;
     tm.width = fast_div((unsigned)(tm.group_w * tm.tiles_x));
-    tm.per_item = fast_div((unsigned)(pb.Npad / bt));
+    tm.per_item = fast_div((unsigned)(pb.Npad / bx));
     tm.spread = spread ? matrices : 0;
     tm.per_matrix = tm.tiles_w / matrices;
     tm.mult = tm.tiles_x / 8 + 1;
@@ -323,22 +323,24 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
 // A request for 64 KiB of operands takes longer to come back than the MFMAs of one
 // 64-deep slice take to run, so two slices have to be in flight, and LDS cannot hold
 // three 64-deep stages of a 256 x 256 tile.  The two sides are kept in rings of their own:
-//   x side   three units of BT rows x 128 bytes (64 k of a vector: a whole slice).  The vector
+//   x side   three units of BX rows x 128 bytes (64 k of a vector: a whole slice).  The vector
 //            cache works by 128-byte lines, and a request that takes 64 bytes from each of 16
 //            rows costs it twice the lines of one that takes 8 whole ones.  A unit is free when
 //            its slice is done; its 16-byte chunks are XOR-swizzled with bits 1..3 of the row
 //            index (128-bit operand reads of 16 consecutive rows fall on distinct banks).
-//   weights  four slots of 32 k-rows x BT columns (half a slice) as they lie in memory, read
+//   weights  four slots of 32 k-rows x BW columns (half a slice) as they lie in memory, read
 //            with the transposing LDS read (see the offset table in the kernel).  A slot is
 //            free half a slice after its first read.
-// Every request has at least one slice period to land.  WR x WC wavefronts share a BT x BT tile.
+// Every request has at least one slice period to land.  WR x WC wavefronts share a BX x BW tile.
+// The 128 x 256 tile has smaller rings (two x units, three weight slots: 80 KiB), so that two
+// workgroups share a CU; see slice_pair.
 // TAIL: d_model is a multiple of 8 only.  In the last slice the 16-byte pieces of a vector past its
 // end, and the k-rows past the last, are fetched from a piece of zeros, through per-lane addresses.
 // ---------------------------------------------------------------------------
 __device__ const u32x4 zero_piece = {0u, 0u, 0u, 0u};
 
-template <int BT, int WR, int WC, bool TAIL>
-__global__ __launch_bounds__(64 * WR * WC, (WR * WC) / 4 * (BT == 256 ? 1 : 2))
+template <int BX, int BW, int WR, int WC, bool TAIL>
+__global__ __launch_bounds__(64 * WR * WC, 2)
 void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
                      const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
                      h16_t* __restrict__ qo, h16_t* __restrict__ ko, h16_t* __restrict__ vto, TileMap tm,
@@ -346,17 +348,19 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
                      const int* __restrict__ row0, unsigned long long* __restrict__ counters)
 {
     constexpr int NW = WR * WC;
-    constexpr int TA = BT / WR, TB = BT / WC;    // wavefront tile: TA rows of the A side, TB of the B side
-    constexpr int NA = TA / 32, NBK = TB / 32;   // MFMA blocks per edge
-    constexpr int XU = BT * 128;                 // bytes of one x unit: BT rows x 64 k
-    constexpr int NXU = 3;
-    constexpr int WROWB = BT * 2;                // bytes of one k-row of the weight side in a slot
+    constexpr bool PAIR = BX != BW;              // 128 x 256 tile, two workgroups per CU
+    // A side: output columns for q and k tiles, vectors for v tiles.  MFMA blocks of a wavefront:
+    constexpr int NBLK = BX * BW / (1024 * NW);
+    constexpr int NX = PAIR ? BX / WC / 32 : 0, NWC = PAIR ? BW / WR / 32 : 0;  // PAIR: the same for both kinds
+    constexpr int XU = BX * 128;                 // bytes of one x unit: BX rows x 64 k
+    constexpr int NXU = PAIR ? 2 : 3;
+    constexpr int WROWB = BW * 2;                // bytes of one k-row of the weight side in a slot
     constexpr int WS = 32 * WROWB;               // bytes of one weight slot: 32 k-rows
-    constexpr int NWS = 4;
+    constexpr int NWS = PAIR ? 3 : 4;
     constexpr int W_BASE = NXU * XU;
-    constexpr int XPW = (BT / 8) / NW;           // x pieces (1 KiB: 8 rows x 128 bytes) per wavefront and slice
+    constexpr int XPW = (BX / 8) / NW;           // x pieces (1 KiB: 8 rows x 128 bytes) per wavefront and slice
     constexpr int WPW = (WS / 1024) / NW;        // weight pieces (1 KiB) per wavefront and half slice
-    static_assert(XPW == 4 && WPW == 2, "the request schedule below deals 4 + 2 + 2 requests per slice");
+    static_assert(XPW == 4 && WPW == (PAIR ? 4 : 2), "what the request schedules below deal out");
     constexpr int WCPR = WROWB / 16;             // 16-byte chunks of a weight k-row
     constexpr int WRPP = 64 / WCPR;              // k-rows per 1 KiB piece
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NXU * XU + NWS * WS];
@@ -376,9 +380,9 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     // grid holds the k and v column tiles only
     tile_of(tm, tile_id, tw, tx_);
     const int bb = (int)divide((unsigned)tx_, tm.per_item);  // Npad is a multiple of BT: one batch item per tile
-    const int i0 = tx_ * BT - bb * Npad;
+    const int i0 = tx_ * BX - bb * Npad;
     if (i0 >= N) return;  // nothing but padding
-    const int w0 = tw * BT + (no_q ? HD : 0);
+    const int w0 = tw * BW + (no_q ? HD : 0);
     const bool is_v = w0 >= 2 * HD;
     // Keys past the key length of their batch item are in no allowed pair (Sec. 5.1 applied to
     // padding): their k and v rows are not computed.  (q rows are: every query row has an output.)
@@ -394,7 +398,7 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     // element counts), which lets a request take a uniform 64-bit base and this offset.
     //   x side: rows are vectors, 128 bytes (64 k) each; piece m = wave + NW*u holds rows
     //           8m..8m+7; the lane lands at row 8m + lane/8, chunk position lane%8;
-    //   w side: rows are k, BT columns each; piece m holds k-rows m*WRPP..; the lane lands at
+    //   w side: rows are k, BW columns each; piece m holds k-rows m*WRPP..; the lane lands at
     //           k-row m*WRPP + lane/WCPR, chunk position lane%WCPR.
     // Either way it fetches the chunk that the swizzle of its row puts at that position.
     unsigned xoff[XPW], woff[WPW];
@@ -452,14 +456,16 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     //           addresses of a 4 (k) x 16 (columns) patch, four columns each, and lane i gets
     //           column i of the patch, its four k values.  Lanes 16..31 take the next 16 columns,
     //           the upper half of the wavefront the upper 8 k of the k-step; two reads (4 k each)
-    //           make one operand.  k-rows are BT*2 bytes apart, a multiple of the 256 bytes the
+    //           make one operand.  k-rows are BW*2 bytes apart, a multiple of the 256 bytes the
     //           banks span, and LDS serves 32 lanes (two patches, 4 k x 32 columns) at a time, so
     //           the chunks of k-row k are XOR-ed with 4*(k%4): the four 64-byte runs then fall on
     //           different banks.  That XOR reaches bits 2 and 3 of the chunk index, which is also
     //           where the 32-column block number sits: one table per block.
-    const int x_row0 = is_v ? wr * TA : wc * TB;  // first x row / first w column of this wavefront
-    const int w_col0 = is_v ? wc * TB : wr * TA;
-    constexpr int NWB = NA > NBK ? NA : NBK;  // 32-column blocks of the weight side of a wavefront
+    // Square tiles: the A side is split WR ways and the B side WC ways, whichever is which; the 128 x 256
+    // tile splits the columns WR ways and the vectors WC ways.
+    const int x_row0 = PAIR || !is_v ? wc * (BX / WC) : wr * (BX / WR);  // first x row / w column of this wavefront
+    const int w_col0 = PAIR || !is_v ? wr * (BW / WR) : wc * (BW / WC);
+    constexpr int NWB = BW / 32 / (WR < WC ? WR : WC);  // 32-column blocks of the weight side of a wavefront, at most
     int wfo[NWB];  // w side: k-step 0, first read; the others lie whole k-rows further (same k % 4)
     const int xfo0 = (x_row0 + ln) * 128 + ((g ^ ((ln >> 1) & 7)) << 4);  // x_row0 is a multiple of 32
 #pragma unroll
@@ -470,13 +476,11 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         wfo[blk] = k * WROWB + (((col >> 3) ^ (4 * (k & 3))) << 4) + ((col & 7) << 1);
     }
 
-    f32x16 acc[NA][NBK];
+    f32x16 acc[NBLK];  // [A block][B block]
 #pragma unroll
-    for (int a = 0; a < NA; ++a)
+    for (int e = 0; e < NBLK; ++e)
 #pragma unroll
-        for (int b = 0; b < NBK; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[e][r] = 0.f;
 
     // One k-step = the MFMAs of 16 k values on fragments that are already in registers.  Behind
     // the first MFMAs go, two at a time, the reads of the fragments of the following k-step (order
@@ -485,7 +489,11 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     // issues no MFMA meanwhile, and since all wavefronts do so at the same point the matrix pipe
     // would drain.  The order is pinned with scheduling fences; the group-barrier solver drops its
     // pattern as soon as memory requests are part of it.
-    u32x4 af[2][NA], bf[2][NBK];
+    // MFMA blocks of a wavefront on the A and on the B side
+    constexpr int NA_V = PAIR ? NX : BX / WR / 32, NB_V = NBLK / NA_V;
+    constexpr int NA_QK = PAIR ? NWC : BW / WR / 32, NB_QK = NBLK / NA_QK;
+    constexpr int NA_MAX = NA_V > NA_QK ? NA_V : NA_QK, NB_MAX = NB_V > NB_QK ? NB_V : NB_QK;
+    u32x4 af[2][NA_MAX], bf[2][NB_MAX];
     // ks4: k-step of the slice, 0..3
     auto x_frag = [&](const unsigned char* unit_base, int ks4, int blk) -> u32x4 {
         return *(const u32x4*)(unit_base + (xfo0 ^ (32 * ks4)) + blk * 4096);
@@ -505,9 +513,10 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     // fragment number r of a k-step, in the order a0, b0.., a1..; the weights are the A side of q and
     // k tiles and the B side of v tiles
     // hs: half slice 0 / 1 of x unit `unit` and weight slot `slot`; ks: k-step 0 / 1 of the half slice
-    auto read_frag = [&](auto is_v_, u32x4 (&fa)[NA], u32x4 (&fb)[NBK], int r, const unsigned char* unit_base,
+    auto read_frag = [&](auto is_v_, u32x4 (&fa)[NA_MAX], u32x4 (&fb)[NB_MAX], int r, const unsigned char* unit_base,
                          const unsigned char* slot_base, int hs, int ks) {
         constexpr bool IS_V = decltype(is_v_)::value;
+        constexpr int NBK = IS_V ? NB_V : NB_QK;
         if (r == 0 || r > NBK) {
             const int a = r == 0 ? 0 : r - NBK;
             fa[a] = IS_V ? x_frag(unit_base, 2 * hs + ks, a) : w_frag(slot_base, ks, a);
@@ -515,15 +524,18 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
             fb[r - 1] = IS_V ? w_frag(slot_base, ks, r - 1) : x_frag(unit_base, 2 * hs + ks, r - 1);
         }
     };
-    auto load_frags = [&](auto is_v_, u32x4 (&fa)[NA], u32x4 (&fb)[NBK], int unit, int slot, int hs, int ks) {
+    auto load_frags = [&](auto is_v_, u32x4 (&fa)[NA_MAX], u32x4 (&fb)[NB_MAX], int unit, int slot, int hs, int ks) {
+        constexpr bool IS_V = decltype(is_v_)::value;
 #pragma unroll
-        for (int r = 0; r < NA + NBK; ++r)
+        for (int r = 0; r < (IS_V ? NA_V + NB_V : NA_QK + NB_QK); ++r)
             read_frag(is_v_, fa, fb, r, lds + unit * XU, lds + W_BASE + slot * WS, hs, ks);
     };
     // `reqs(i)`, i = 0 .. ND-1: the requests that go out behind the MFMAs of this k-step
-    auto kstep = [&](auto is_v_, const u32x4 (&fa)[NA], const u32x4 (&fb)[NBK], u32x4 (&na)[NA], u32x4 (&nb)[NBK],
-                     int unit, int slot, int hs, int ks, auto nd_, auto&& reqs) {
+    auto kstep = [&](auto is_v_, const u32x4 (&fa)[NA_MAX], const u32x4 (&fb)[NB_MAX], u32x4 (&na)[NA_MAX],
+                     u32x4 (&nb)[NB_MAX], int unit, int slot, int hs, int ks, auto nd_, auto&& reqs) {
         constexpr int ND = decltype(nd_)::value;
+        constexpr bool IS_V = decltype(is_v_)::value;
+        constexpr int NA = IS_V ? NA_V : NA_QK, NBK = IS_V ? NB_V : NB_QK;
         constexpr int NRD = NA + NBK, NMF = NA * NBK;
         static_assert(NRD % 2 == 0 && NRD / 2 <= NMF, "read pairs fit behind the MFMAs of a k-step");
         static_assert(ND <= NMF, "at most one request per MFMA");
@@ -536,7 +548,7 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int b = 0; b < NBK; ++b) {
-                acc[a][b] = mfma32(fa[a], fb[b], acc[a][b]);
+                acc[a * NBK + b] = mfma32(fa[a], fb[b], acc[a * NBK + b]);
                 const int m = a * NBK + b + 1;  // MFMAs issued so far
                 if (m <= NRD / 2) {
                     read_frag(is_v_, na, nb, 2 * m - 2, unit_base, slot_base, hs, ks);
@@ -597,16 +609,59 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         wa = wc;
     };
 
+    // The 128 x 256 tile: two x units, three weight half slices (h = 2j, 2j + 1 of slice j, slot h mod 3), the
+    // same two barriers per slice.  Behind the first barrier (half slice 2j read) its slot takes half slice
+    // 2j + 3, two pieces in each of steps 2 and 3; behind the second, half slice 2j + 1's slot takes 2j + 4 and
+    // slice j's x unit takes x of slice j + 2, two pieces of either in step 4 and in step 1 of the next slice.
+    // Loads return in order: the first barrier of slice j wants half slice 2j + 1, sent in steps 2 and 3 of
+    // slice j - 1, and the eight requests sent since may be in flight; the second wants all that was sent
+    // up to step 1, four may be.  The other workgroup of the CU fills what these short distances leave.
+    auto slice_pair = [&](auto is_v_, auto var_, int j, int& ux, int& sa) {
+        constexpr int VAR = decltype(var_)::value;
+        constexpr bool E1 = VAR >= 1, E2 = VAR == 2;
+        const int sb = sa == 2 ? 0 : sa + 1, sc = sb == 2 ? 0 : sb + 1;  // slots of half slices 2j + 1 and 2j + 2
+        const int k1 = (j + 1) * 64, k2 = (j + 2) * 64;
+        const std::integral_constant<int, E1 ? 4 : 0> four{};
+        const std::integral_constant<int, E1 ? 2 : 0> two{};
+        const std::integral_constant<int, E2 ? 4 : 0> next_four{};
+        kstep(is_v_, af[0], bf[0], af[1], bf[1], ux, sa, 0, 1, four, [&](int i) {
+            if (i < 2) req_w(2 + i, k1, 0, sc);
+            else req_x(i, k1, ux ^ 1);
+        });
+        __builtin_amdgcn_s_waitcnt(0x0070 | (E1 ? 8 : 0));
+        __builtin_amdgcn_s_barrier();
+        kstep(is_v_, af[1], bf[1], af[0], bf[0], ux, sb, 1, 0, two, [&](int i) { req_w(i, k1, 1, sa); });
+        kstep(is_v_, af[0], bf[0], af[1], bf[1], ux, sb, 1, 1, two, [&](int i) { req_w(2 + i, k1, 1, sa); });
+        __builtin_amdgcn_s_waitcnt(0x0070 | (E1 ? 4 : 0));
+        __builtin_amdgcn_s_barrier();
+        kstep(is_v_, af[1], bf[1], af[0], bf[0], ux ^ 1, sc, 0, 0, next_four, [&](int i) {
+            if (i < 2) req_w(i, k2, 0, sb);
+            else req_x(i - 2, k2, ux);
+        });
+        ux ^= 1;
+        sa = sc;
+    };
+
     // Prologue: slice 0 whole, and of slice 1 what steps 2-4 of a slice before slice 0 would
     // have sent (its last weight piece follows in step 1 of slice 0).
     const int ns = TAIL ? (D + 63) / 64 : D / 64;
-    req_w(0, 0, 0, 0);
-    req_w(1, 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < WPW; ++u) req_w(u, 0, 0, 0);
 #pragma unroll
     for (int u = 0; u < XPW; ++u) req_x(u, 0, 0);
-    req_w(0, 0, 1, 1);
-    req_w(1, 0, 1, 1);
-    if (ns > 1) {
+#pragma unroll
+    for (int u = 0; u < WPW; ++u) req_w(u, 0, 1, 1);
+    if constexpr (PAIR) {  // and what step 4 of a slice before slice 0 would have sent
+        if (ns > 1) {
+            req_w(0, 64, 0, 2);
+            req_w(1, 64, 0, 2);
+            req_x(0, 64, 1);
+            req_x(1, 64, 1);
+            __builtin_amdgcn_s_waitcnt(0x0F70 | 8);  // x and the first half of the weights of slice 0 have landed
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+        }
+    } else if (ns > 1) {
         req_x(0, 64, 1);
         req_w(0, 64, 0, 2);
         req_x(1, 64, 1);
@@ -623,27 +678,31 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         load_frags(is_v_, af[0], bf[0], 0, 0, 0, 0);
         int ux = 0, wa = 0;
         int j = 0;
+        auto one = [&](auto var_) {
+            if constexpr (PAIR) slice_pair(is_v_, var_, j, ux, wa);
+            else slice(is_v_, var_, j, ux, wa);
+        };
 #pragma nounroll
-        for (; j + 2 < ns; ++j) slice(is_v_, two_req, j, ux, wa);
+        for (; j + 2 < ns; ++j) one(two_req);
 #pragma nounroll
-        for (; j + 1 < ns; ++j) slice(is_v_, one_req, j, ux, wa);
+        for (; j + 1 < ns; ++j) one(one_req);
 #pragma nounroll
-        for (; j < ns; ++j) slice(is_v_, no_req, j, ux, wa);
+        for (; j < ns; ++j) one(no_req);
     };
     if (is_v) all_slices(std::true_type{});
     else all_slices(std::false_type{});
     __builtin_amdgcn_s_waitcnt(0x0070);  // the fragments read ahead for a slice that does not exist are dropped
     __builtin_amdgcn_s_barrier();
 
-    // Epilogue.  acc[a][b][r]: A-side row wr*TA + 32a + acc_row(r,g), B-side row wc*TB + 32b + ln.
-    // A lane owns 8-byte runs whose neighbours in memory sit in other lanes' later registers, so
+    // Epilogue.  Register r of block (a, b): A-side row 32a + acc_row(r,g), B-side row 32b + ln of the
+    // wavefront's share.  A lane owns 8-byte runs whose neighbours in memory sit in other lanes' later registers, so
     // storing them directly would touch 64 cache lines per instruction.  The tile is staged in LDS
     // (free by now) in the order of the output arrays and leaves in 16-byte pieces, a full KiB of
     // consecutive addresses per wavefront and instruction.  Staged rows are XOR-swizzled by 16-byte
     // chunk like the operand tiles, which keeps both the 8-byte writes and the 16-byte reads spread
     // over the banks.
     constexpr int NT = 64 * NW;
-    constexpr int UNITS = BT * BT / 8;  // 16-byte pieces of the tile
+    constexpr int UNITS = BX * BW / 8;  // 16-byte pieces of the tile
     const int dsh = d == 128 ? 7 : 6;   // d is 64 or 128 on this path
     if (!is_v) {
         // q and k: [head][vector][d], a staged row is one vector's d values of one head.
@@ -651,27 +710,27 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         const float qs = which ? 1.f : qscale;  // q is stored pre-multiplied (see launch_proj_mfma)
         const int cmask = (d >> 3) - 1, rowb = 2 * d;
 #pragma unroll
-        for (int b = 0; b < NBK; ++b) {
-            const int v = wc * TB + 32 * b + ln;
+        for (int b = 0; b < NB_QK; ++b) {
+            const int v = x_row0 + 32 * b + ln;
 #pragma unroll
-            for (int a = 0; a < NA; ++a)
+            for (int a = 0; a < NA_QK; ++a)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
-                    const int ct = wr * TA + 32 * a + 8 * r4;  // tile column of register 4*r4 in half 0
+                    const int ct = w_col0 + 32 * a + 8 * r4;  // tile column of register 4*r4 in half 0
                     const int hc = ct >> dsh, c = (ct & (d - 1)) >> 3;
                     u32x2 w;
-                    w[0] = pack_f16_sat(acc[a][b][4 * r4 + 0] * qs, acc[a][b][4 * r4 + 1] * qs);
-                    w[1] = pack_f16_sat(acc[a][b][4 * r4 + 2] * qs, acc[a][b][4 * r4 + 3] * qs);
-                    *(u32x2*)(lds + (hc * BT + v) * rowb + ((c ^ (v & cmask)) << 4) + 8 * g) = w;
+                    w[0] = pack_f16_sat(acc[a * NB_QK + b][4 * r4 + 0] * qs, acc[a * NB_QK + b][4 * r4 + 1] * qs);
+                    w[1] = pack_f16_sat(acc[a * NB_QK + b][4 * r4 + 2] * qs, acc[a * NB_QK + b][4 * r4 + 3] * qs);
+                    *(u32x2*)(lds + (hc * BX + v) * rowb + ((c ^ (v & cmask)) << 4) + 8 * g) = w;
                 }
         }
         __syncthreads();
         h16_t* base = (which ? ko : qo) + ((size_t)bb * H + ((w0 - which * HD) >> dsh)) * Npad * d;
 #pragma unroll 4
         for (int e0 = tid; e0 < UNITS; e0 += NT) {
-            const int hv = e0 >> (dsh - 3);  // head-in-tile * BT + vector
+            const int hv = e0 >> (dsh - 3);  // head-in-tile * BX + vector
             const int c = e0 & cmask;
-            const int hc = hv / BT, v = hv - hc * BT;
+            const int hc = hv / BX, v = hv - hc * BX;
             if (i0 + v >= N) continue;  // rows past n stay zero
             const u32x4 val = *(const u32x4*)(lds + hv * rowb + ((c ^ (v & cmask)) << 4));
             *(u32x4*)(base + ((size_t)hc * Npad + i0 + v) * d + c * 8) = val;
@@ -680,21 +739,21 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         // v transposed: [head][64-key block][d][64 key slots], a staged row is the 64 slots of one
         // column; vectors past n are staged as zeros.
 #pragma unroll
-        for (int b = 0; b < NBK; ++b) {
-            const int cl = wc * TB + 32 * b + ln;
+        for (int b = 0; b < NB_V; ++b) {
+            const int cl = w_col0 + 32 * b + ln;
             const int hc = cl >> dsh, l = cl & (d - 1);
 #pragma unroll
-            for (int a = 0; a < NA; ++a)
+            for (int a = 0; a < NA_V; ++a)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
-                    const int vl = wr * TA + 32 * a + 8 * r4 + 4 * g;  // vector of register 4*r4
+                    const int vl = x_row0 + 32 * a + 8 * r4 + 4 * g;  // vector of register 4*r4
                     const int vb = vl >> 6, r64 = vl & 63;
                     const int slot = (r64 & 48) | vt_slot16(r64 & 15);
                     const int left = N - (i0 + vl);
                     u32x2 w;
-                    w[0] = pack_f16_sat(left > 0 ? acc[a][b][4 * r4 + 0] : 0.f, left > 1 ? acc[a][b][4 * r4 + 1] : 0.f);
-                    w[1] = pack_f16_sat(left > 2 ? acc[a][b][4 * r4 + 2] : 0.f, left > 3 ? acc[a][b][4 * r4 + 3] : 0.f);
-                    *(u32x2*)(lds + ((hc * (BT / 64) + vb) * d + l) * 128 + (((slot >> 3) ^ (l & 7)) << 4) +
+                    w[0] = pack_f16_sat(left > 0 ? acc[a * NB_V + b][4 * r4 + 0] : 0.f, left > 1 ? acc[a * NB_V + b][4 * r4 + 1] : 0.f);
+                    w[1] = pack_f16_sat(left > 2 ? acc[a * NB_V + b][4 * r4 + 2] : 0.f, left > 3 ? acc[a * NB_V + b][4 * r4 + 3] : 0.f);
+                    *(u32x2*)(lds + ((hc * (BX / 64) + vb) * d + l) * 128 + (((slot >> 3) ^ (l & 7)) << 4) +
                               2 * (slot & 7)) = w;
                 }
         }
@@ -705,7 +764,7 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
             const int ul = e0 >> 3;  // (head-in-tile * blocks + block) * d + column
             const int c = e0 & 7;
             const int u = ul >> dsh, l = ul & (d - 1);
-            const int hc = u / (BT / 64), vb = u - hc * (BT / 64);
+            const int hc = u / (BX / 64), vb = u - hc * (BX / 64);
             const int blk = (i0 >> 6) + vb;
             if (blk * 64 >= N) continue;  // blocks past n stay zero
             const u32x4 val = *(const u32x4*)(lds + ul * 128 + ((c ^ (l & 7)) << 4));
@@ -719,19 +778,19 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
 // half precision, so that the attention kernels get base-2 scores straight out of the MFMA.
 inline float q_prescale(const Problem& pb) { return pb.scale * 1.4426950408889634f; }
 
-template <int BT, int WR, int WC>
+template <int BX, int BW, int WR, int WC>
 hipError_t launch_dma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk, const bf16_t* Wv,
                       h16_t* q, h16_t* k, h16_t* vt, hipStream_t s)
 {
     const float qscale = q_prescale(pb);
     const int* lens = pb.noskip ? nullptr : pb.lens;
-    const TileMap tm = tile_map(pb, BT, pb.no_q ? 2 : 3, lens != nullptr);
+    const TileMap tm = tile_map(pb, BX, BW, pb.no_q ? 2 : 3, lens != nullptr);
     const int grid = ((tm.n_tiles + 7) / 8) * 8;
     if (pb.D % 64 == 0)
-        hipLaunchKernelGGL((proj_dma_kernel<BT, WR, WC, false>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
+        hipLaunchKernelGGL((proj_dma_kernel<BX, BW, WR, WC, false>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
                            pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
     else
-        hipLaunchKernelGGL((proj_dma_kernel<BT, WR, WC, true>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
+        hipLaunchKernelGGL((proj_dma_kernel<BX, BW, WR, WC, true>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
                            pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
     return hipGetLastError();
 }
@@ -741,7 +800,7 @@ hipError_t launch_bt(const Problem& pb, const bf16_t* X, const bf16_t* Wt, h16_t
                      hipStream_t s)
 {
     const float qscale = q_prescale(pb);
-    const TileMap tm = tile_map(pb, BT, 3, false);
+    const TileMap tm = tile_map(pb, BT, BT, 3, false);
     const int grid = ((tm.n_tiles + 7) / 8) * 8;
     hipLaunchKernelGGL(proj_mfma_kernel<BT>, dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X, Wt,
                        q, k, vt, tm, qscale, pb.noskip ? nullptr : pb.lens, pb.skip_rows, pb.no_q, pb.row0);
@@ -778,14 +837,20 @@ bool proj_reads_weights_in_place(const Problem& pb, const bf16_t* Wq, const bf16
 hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk,
                             const bf16_t* Wv, const bf16_t* Wt, h16_t* q, h16_t* k, h16_t* vt, hipStream_t s)
 {
-    // Largest square tile that divides the per-matrix column count (so a tile never
-    // mixes q, k and v columns) and still gives every CU a few tiles.
+    // Tile by the number of 256 x 256 tiles the product would have and by d_model.  Measured (us; 128 x 128,
+    // 256 x 256, 128 x 256 with two workgroups per CU; rows x d_model -> columns):
+    //   8192 x 768 -> 2304 (288)   36.4 / 45.2 / 36.1     16384 x 768 -> 2304 (576)    61 / 70 / 57
+    //   8192 x 1024 -> 3072 (384)  52 / 55 / 48           65536 x 1024 -> 3072 (3072)  435 / 374 / 377, with key
+    //   4096 x 4096 -> 12288 (768) 344 / 301 / 310        lengths 338 / 309 / 282, packed 266 / 249 / 224
+    // A workgroup's prologue and epilogue take as long as five slices and are hidden by the CU's other one, if
+    // there is one; 256 x 256 reads the least per product, which decides when d_model is long.  No tile mixes
+    // columns of two matrices.
     const int HD = pb.H * pb.d;
-    const long rows = (long)pb.B * pb.Npad;
-    const bool big = HD % 256 == 0 && rows % 256 == 0 && (rows / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) >= 512;
+    const long t256 = HD % 256 == 0 ? (long)pb.B * (pb.Npad / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
     if (proj_reads_weights_in_place(pb, Wq, Wk, Wv)) {  // operands go straight to LDS
-        if (big) return launch_dma<256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
-        return launch_dma<128, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        if (t256 >= 512 && pb.D >= 2048) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        if (t256 >= 320) return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        return launch_dma<128, 128, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
     }
     if (HD % 128 == 0) return launch_bt<128>(pb, X, Wt, q, k, vt, s);
     return launch_bt<64>(pb, X, Wt, q, k, vt, s);

@@ -145,17 +145,20 @@ def test_mfma_path_small(shape, scheme, tiles, seed0):
 @pytest.mark.parametrize("shape", [
     # B, n, H, d, p
     (2, 200, 2, 64, 25),          # 128 x 128 tiles
-    (8, 2048, 16, 128, 256),      # 256 x 256 tiles (512 of them and more)
+    (8, 2048, 16, 128, 256),      # 128 x 256 tiles
+    (1, 4096, 32, 128, 512),      # with 2048 added to d_model: 256 x 256 tiles
 ])
 def test_projection_with_a_cut_slice(shape, d_model):
     B, n, H, d, p = shape
+    if B == 1:
+        d_model += 2048
     w = hp.custom_workload("cut_slice", B, n, d_model, H, d, p, "bf16", CAUSAL, 7700 + d_model)
     if n <= 256:
         _run_and_compare(w, CAUSAL, 0.0)
         return
     # values that follow a vector's end belong to the next one and must not reach it: rows of infinities
     stored, f64 = inputs.make_inputs(w)
-    bad = [(0, n - 1), (3, 77), (7, n - 1)]
+    bad = [(0, n - 1), (3 % B, 77 if B > 1 else n - 1), (B - 1, n - 1)]
     for b, i in bad:
         stored["X"][b, i] = float("inf")
     stored["lens"] = None
@@ -165,6 +168,8 @@ def test_projection_with_a_cut_slice(shape, d_model):
     finally:
         run.close()
     for (b, h) in [(0, 0), (1, 5), (3, 15), (7, 8)]:
+        if b >= B:
+            continue
         rows = [r for r in range(76 if b == 3 else n - 1) if r < 140 or r > n - 70]
         ref = orc.head_rows(f64["X"], f64["Wq"], f64["Wk"], f64["Wv"], n_heads=H, d_k=d, p=p, scheme=CAUSAL,
                             scale=hp.default_scale(w, 0.0), b=b, h=h, rows=rows)
