@@ -14,14 +14,19 @@
 // are chosen so that an operand is a quarter of a 16-byte LDS read (lane group g4 holds columns
 // 16t + 4 g4 + j in MFMA j); both orders only order the fp32 sums.
 //
-// A wavefront owns 16 query rows.  Two ways to share the work of a workgroup's four wavefronts:
-//   rows  64 rows per workgroup, every wavefront walks all keys of the tile;
-//   keys  16 rows per workgroup, wavefront w takes the 16-key block w of every tile and the four
-//         partial states (m, l, O) are merged at the end: four times the workgroups, for launches
-//         that would leave CUs idle, for four times the reads of K and V (from L2).
-// The paper's ring: the walk starts at the rows' own tile and runs downwards, wrapping (the order
-// in which PE l meets block (l - j) mod m in Algorithm 1); tiles and, inside a tile, 16-key blocks
-// with no needed pair are left out (Sec. 5.1).
+// The columns of O that the MFMAs of a key hold are dealt so that an operand of four MFMAs is one
+// 16-byte read of a row of V (column 4i + e of a 64-column group in MFMA e), which makes the lane's
+// outputs runs of four columns as well.
+//
+// A wavefront owns 16 query rows.  Two kernels:
+//   rows  64 rows per workgroup, every wavefront walks all keys; K and V tiles of 64 keys pass
+//         through LDS, the next one fetched into registers meanwhile;
+//   keys  16 rows per workgroup, its four wavefronts take the 16-key blocks in turn, straight from
+//         memory (L2) into operand registers, and their partial states (m, l, O) are merged at the
+//         end: four times the wavefronts, no barrier in the walk, four times the reads of K and V.
+// The paper's ring: the walk of the rows kernel starts at the rows' own tile and runs downwards,
+// wrapping (the order in which PE l meets block (l - j) mod m in Algorithm 1); in both, blocks of
+// 16 keys with no needed pair are left out (Sec. 5.1).
 //
 // q = k = v scheme (Sec. 4): a first kernel computes every score tile once and stores it at both
 // of its places of an n x n matrix per head, the same walk then reads its scores from there.
@@ -137,165 +142,65 @@ __device__ __forceinline__ void load_row(f32x4 (&qf)[NDB], const float* __restri
     for (int t = 0; t < NDB; ++t) qf[t] = clip4<WHOLE>(load4<WHOLE>(row, 16 * t + 4 * g4, d, true), 16 * t + 4 * g4 < d);
 }
 
-// Phase 1 (Eq. (1), before the scale) of NB 16-key blocks from key row `kt` of an LDS tile.
-template <int NDB, int NB>
-__device__ __forceinline__ void score_blocks(f32x4* S, const float* kt, const f32x4 (&qf)[NDB], int ln, int g4)
-{
-    constexpr int PITCH = Tile<NDB, true>::PITCH;
+// The columns of a row of d in MFMA order: groups of 64, then one of 32, then one of 16.
+template <int NDB>
+struct Cols {
+    static constexpr int N4 = NDB / 4, N2 = (NDB % 4) / 2, N1 = NDB % 2;
+    static constexpr int C2 = 64 * N4, C1 = C2 + 32 * N2;
+    // lane ln's V operands of one key: column 64m + 4 ln + e in MFMA 4m + e, and so on
+    template <class L4, class L2, class L1>
+    static __device__ __forceinline__ void read(float (&v)[NDB], int ln, L4&& l4, L2&& l2, L1&& l1)
+    {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < N4; ++m) {
+            const f32x4 w = l4(64 * m + 4 * ln);
 #pragma unroll
-    for (int t = 0; t < NDB; ++t) {
-        f32x4 kf[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) kf[b] = *(const f32x4*)(kt + (16 * b + ln) * PITCH + 16 * t + 4 * g4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) S[b] = mfma16f(kf[b][j], qf[t][j], S[b]);
+            for (int e = 0; e < 4; ++e) v[4 * m + e] = w[e];
+        }
+        if constexpr (N2 != 0) {
+            const f32x2 w = l2(C2 + 2 * ln);
+            v[4 * N4] = w[0];
+            v[4 * N4 + 1] = w[1];
+        }
+        if constexpr (N1 != 0) v[NDB - 1] = l1(C1 + ln);
     }
-}
-
-// STORED (q = k = v scheme): the scores come from `scores`, which sym_scores_float_kernel has filled,
-// instead of q and k, and have been counted there.
-template <int NDB, bool KEYS, bool WHOLE, bool STORED>
-__global__ __launch_bounds__(256)
-void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, const float* __restrict__ k,
-                       const float* __restrict__ v, const float* __restrict__ scores, void* __restrict__ out,
-                       int n_rowtiles, bool out_whole)
-{
-    typedef Tile<NDB, WHOLE> TL;
-    constexpr int PITCH = TL::PITCH, DP = TL::DP;
-    constexpr int ROWS = KEYS ? 16 : 64;  // query rows per workgroup
-    constexpr int NB = KEYS ? 1 : 4;      // 16-key blocks of a tile that a wavefront takes
-    __shared__ __attribute__((aligned(16))) float ks[STORED ? 4 : KT * PITCH];
-    __shared__ __attribute__((aligned(16))) float vs[KT * PITCH];
-    __shared__ float st_ml[KEYS ? 2 * KT : 1];
-
-    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, g4 = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Consecutive workgroups take the heads in turn, the last row tiles (the most keys under the
-    // mask) first, so that the long walks do not start last.
-    const int heads = pb.B * pb.H;
-    const unsigned item = flat_block();
-    if (item >= (unsigned)heads * (unsigned)n_rowtiles) return;
-    const int bh = (int)(item % (unsigned)heads);
-    const int x = n_rowtiles - 1 - (int)(item / (unsigned)heads);
-    const int bb = bh / pb.H, h = bh - bb * pb.H;
-    const int N = pb.N, d = pb.d;
-    const bool causal = pb.scheme == SCHEME_CAUSAL;
-    int len = N;
-    if (pb.lens) { len = pb.lens[bb]; len = len < 0 ? 0 : (len > N ? N : len); }
-    const int rlen = pb.skip_rows ? len : N;  // query rows at or past it take part in no pair
-    const size_t head = (size_t)bh * N * d;
-    const int i0 = x * ROWS;                       // rows of the workgroup
-    const int i0w = KEYS ? i0 : i0 + 16 * wave;    // rows of the wavefront
-    const int i = i0w + ln;                        // the lane's query row
-    const int row_end = min(pb.noskip ? N : rlen, i0 + ROWS);       // rows that take part
-    const int wave_end = min(pb.noskip ? N : rlen, i0w + 16);
-
-    // needed tiles are 0 .. nJ-1, met from the own one downwards, wrapping; in debug mode the
-    // others follow and change nothing
-    const int n_all = (N + KT - 1) / KT;
-    int nJ = 0;
-    if (row_end > i0) {
-        nJ = (len + KT - 1) / KT;
-        if (causal) nJ = min(nJ, (row_end - 1) / KT + 1);
+    // f(column, four outputs) for the lane's pieces of its row
+    template <class F>
+    static __device__ __forceinline__ void pieces(const f32x4 (&O)[NDB], int g4, F&& f)
+    {
+#pragma unroll
+        for (int m = 0; m < N4; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                f(64 * m + 16 * g4 + 4 * r, f32x4{O[4 * m][r], O[4 * m + 1][r], O[4 * m + 2][r], O[4 * m + 3][r]});
+        if constexpr (N2 != 0) {
+            constexpr int b = 4 * N4;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                f(C2 + 8 * g4 + 4 * u, f32x4{O[b][2 * u], O[b + 1][2 * u], O[b][2 * u + 1], O[b + 1][2 * u + 1]});
+        }
+        if constexpr (N1 != 0) f(C1 + 4 * g4, O[NDB - 1]);
     }
-    const int nT = pb.noskip && row_end > i0 ? n_all : nJ;
-    const int Js = min((i0 + ROWS - 1) / KT, nJ - 1);
-    auto tile_of_step = [&](int t) -> int {
-        if (t >= nJ) return t;
-        const int J = Js - t;
-        return J < 0 ? J + nJ : J;
-    };
+};
 
-    // logical tiles: row block I is counted by the workgroup that holds its first row
-    if (!STORED && wave == 0) {
-        unsigned cnt = 0;
-        const int I = (int)cdiv_b((unsigned)i0, cc) + lane;  // at most 64 row blocks start here
-        if (I * cc.b < row_end) {
-            cnt = (unsigned)pb.P;
-            if (!pb.noskip) {
-                if (causal) cnt = min(cnt, (unsigned)I + 1u);
-                cnt = min(cnt, cdiv_b((unsigned)len, cc));
-            }
-        }
-        unsigned long long total = cnt;
+// Running state of the lane's row (m shared by the row's four lanes, l this lane's part).
+template <int NDB>
+struct Row {
+    f32x4 O[NDB];
+    float m, l;
+    __device__ __forceinline__ void clear()
+    {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
-        if (lane == 0) count_add(pb.counters, item, total, 0);
+        for (int db = 0; db < NDB; ++db) O[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m = -INFINITY;
+        l = 0.f;
     }
-    unsigned cnt_phys = 0;  // 16 x 16 score blocks; wave-uniform
-
-    f32x4 qf[NDB], O[NDB];
-    if constexpr (!STORED) load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);  // rows past the last: not stored
-#pragma unroll
-    for (int db = 0; db < NDB; ++db) O[db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m = -INFINITY, l = 0.f;  // running maximum of the row; this lane's part of the row sum
-    int lim = len - 1;             // the row's last allowed key
-    if (causal) lim = min(lim, i);
-    if (i >= rlen) lim = -1;
-
-    // the lane's stored scores of a tile: whole 16-byte pieces of its row (pitch SP)
-    const int SP = score_pitch(N);
-    const float* srow = STORED ? scores + ((size_t)bh * N + min(i, N - 1)) * SP : nullptr;
-    TL tk, tv;
-    f32x4 sreg[NB];
-    auto fetch = [&](int t) {
-        const int J = tile_of_step(t);
-        if constexpr (STORED) {
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int col = J * KT + (KEYS ? 16 * wave : 16 * b) + 4 * g4;
-                sreg[b] = *(const f32x4*)(srow + (col < SP ? col : 0));
-            }
-        } else {
-            tk.fetch(k + head, J * KT, len, d, tid);
-        }
-        tv.fetch(v + head, J * KT, len, d, tid);
-    };
-    if (nT > 0) fetch(0);
-    for (int t = 0; t < nT; ++t) {
-        const int J = tile_of_step(t);
-        f32x4 S[NB];
-        __syncthreads();  // everyone is done with the tile before
-        if constexpr (STORED) {
-#pragma unroll
-            for (int b = 0; b < NB; ++b) S[b] = sreg[b];
-        } else {
-            tk.stage(ks, J * KT, len, d, tid);
-        }
-        tv.stage(vs, J * KT, len, d, tid);
-        __syncthreads();
-        if (t + 1 < nT) fetch(t + 1);
-        // 16-key blocks of the tile that hold a pair this wavefront needs: the first nk
-        const int key0 = J * KT + (KEYS ? 16 * wave : 0);
-        int nk = 0;
-        if (wave_end > i0w) {
-            int keys = len - key0;
-            if (causal) keys = min(keys, wave_end - key0);
-            nk = pb.noskip ? NB : max(0, min(NB, (keys + 15) >> 4));
-        }
-        if (nk == 0) continue;
-        if constexpr (!STORED) {
-            cnt_phys += (unsigned)nk;
-            const float* kt = ks + (KEYS ? 16 * wave * PITCH : 0);
-            if (nk == NB) {
-                score_blocks<NDB, NB>(S, kt, qf, ln, g4);
-            } else {
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    if (b < nk) score_blocks<NDB, 1>(&S[b], kt + 16 * b * PITCH, qf, ln, g4);
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < NB; ++b) S[b] *= pb.scale;
-        }
-        // phase 2 (Eq. (2)), running maximum; a row that has met no allowed key keeps m = -inf
+    // Phase 2 (Eq. (2)) of NB blocks of scores: they become weights.  rel: the last allowed key,
+    // counted from the lane's first key.  A row that has met no allowed key keeps m = -inf.
+    template <int NB>
+    __device__ __forceinline__ void weights(f32x4 (&S)[NB], int rel)
+    {
         float mx = m;
-        const int rel = lim - key0 - 4 * g4;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -319,62 +224,357 @@ void attn_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, con
         l = l * alpha + sum;
 #pragma unroll
         for (int db = 0; db < NDB; ++db) O[db] *= alpha;
+    }
+    __device__ __forceinline__ float row_sum() const
+    {
+        float t = l + __shfl_xor(l, 16, 64);
+        return t + __shfl_xor(t, 32, 64);
+    }
+};
+
+// What both kernels need to know about a row tile.
+struct RowTile {
+    int bh, bb, h, i0, row_end, len, rlen;
+    bool there;
+    __device__ __forceinline__ RowTile(const Problem& pb, int rows, int n_rowtiles)
+    {
+        // Consecutive workgroups take the heads in turn, the last row tiles (the most keys under the
+        // mask) first, so that the long walks do not start last.
+        const unsigned heads = (unsigned)(pb.B * pb.H), item = flat_block();
+        there = item < heads * (unsigned)n_rowtiles;
+        bh = (int)(item % heads);
+        bb = bh / pb.H;
+        h = bh - bb * pb.H;
+        i0 = (n_rowtiles - 1 - (int)(item / heads)) * rows;
+        len = pb.N;
+        if (there && pb.lens) { len = pb.lens[bb]; len = len < 0 ? 0 : (len > pb.N ? pb.N : len); }
+        rlen = pb.skip_rows ? len : pb.N;                   // query rows at or past it take part in no pair
+        row_end = min(pb.noskip ? pb.N : rlen, i0 + rows);  // rows of the tile that take part
+    }
+    // Logical tiles: row block I is counted by the workgroup that holds its first row; called by one wavefront.
+    __device__ __forceinline__ void count(const Problem& pb, const CountCfg& cc, int lane) const
+    {
+        unsigned cnt = 0;
+        const int I = (int)cdiv_b((unsigned)i0, cc) + lane;  // at most 64 row blocks start here
+        if (I * cc.b < row_end) {
+            cnt = (unsigned)pb.P;
+            if (!pb.noskip) {
+                if (pb.scheme == SCHEME_CAUSAL) cnt = min(cnt, (unsigned)I + 1u);
+                cnt = min(cnt, cdiv_b((unsigned)len, cc));
+            }
+        }
+        unsigned long long total = cnt;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
+        if (lane == 0) count_add(pb.counters, flat_block(), total, 0);
+    }
+    // The row's last allowed key.
+    __device__ __forceinline__ int last_key(const Problem& pb, int i) const
+    {
+        if (i >= rlen) return -1;
+        return pb.scheme == SCHEME_CAUSAL ? min(len - 1, i) : len - 1;
+    }
+};
+
+// Phase 1 (Eq. (1), before the scale) of NB 16-key blocks from key row `kt` of an LDS tile.
+template <int NDB, int NB>
+__device__ __forceinline__ void score_blocks(f32x4* S, const float* kt, const f32x4 (&qf)[NDB], int ln, int g4)
+{
+    constexpr int PITCH = Tile<NDB, true>::PITCH;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NDB; ++t) {
+        f32x4 kf[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) kf[b] = *(const f32x4*)(kt + (16 * b + ln) * PITCH + 16 * t + 4 * g4);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) S[b] = mfma16f(kf[b][j], qf[t][j], S[b]);
+    }
+}
+
+// STORED (q = k = v scheme), in both kernels: the scores come from `scores`, which
+// sym_scores_float_kernel has filled, instead of q and k, and have been counted there.
+template <int NDB, bool WHOLE, bool STORED>
+__global__ __launch_bounds__(256, NDB <= 4 ? 3 : NDB <= 8 ? 2 : 1)
+void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, const float* __restrict__ k,
+                      const float* __restrict__ v, const float* __restrict__ scores, void* __restrict__ out,
+                      int n_rowtiles, bool out_whole)
+{
+    typedef Tile<NDB, WHOLE> TL;
+    typedef Cols<NDB> CL;
+    constexpr int PITCH = TL::PITCH, NB = 4;
+    __shared__ __attribute__((aligned(16))) float ks[STORED ? 4 : KT * PITCH];
+    __shared__ __attribute__((aligned(16))) float vs[KT * PITCH];
+
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const RowTile rt(pb, KT, n_rowtiles);
+    if (!rt.there) return;
+    const int N = pb.N, d = pb.d, len = rt.len;
+    const bool causal = pb.scheme == SCHEME_CAUSAL;
+    const size_t head = (size_t)rt.bh * N * d;
+    const int i0w = rt.i0 + 16 * wave, i = i0w + ln;  // rows of the wavefront, the lane's row
+    const int wave_end = min(rt.row_end, i0w + 16);
+
+    // needed tiles are 0 .. nJ-1, met from the own one downwards, wrapping; in debug mode the
+    // others follow and change nothing
+    int nJ = 0, nT = 0;
+    if (rt.row_end > rt.i0) {
+        nJ = (len + KT - 1) / KT;
+        if (causal) nJ = min(nJ, (rt.row_end - 1) / KT + 1);
+        nT = pb.noskip ? (N + KT - 1) / KT : nJ;
+    }
+    const int Js = min(rt.i0 / KT, nJ - 1);
+    auto tile_of_step = [&](int t) -> int {
+        if (t >= nJ) return t;
+        const int J = Js - t;
+        return J < 0 ? J + nJ : J;
+    };
+    if (!STORED && wave == 0) rt.count(pb, cc, lane);
+    unsigned cnt_phys = 0;  // 16 x 16 score blocks; wave-uniform
+
+    f32x4 qf[NDB];
+    if constexpr (!STORED) load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);  // rows past the last: not stored
+    Row<NDB> row;
+    row.clear();
+    const int lim = rt.last_key(pb, i) - 4 * g4;
+    // the lane's stored scores of a tile: whole 16-byte pieces of its row (pitch SP)
+    const int SP = score_pitch(N);
+    const float* srow = STORED ? scores + ((size_t)rt.bh * N + min(i, N - 1)) * SP : nullptr;
+    TL tk, tv;
+    f32x4 sreg[NB];
+    auto fetch = [&](int t) {
+        const int J = tile_of_step(t);
+        if constexpr (STORED) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const int col = J * KT + 16 * b + 4 * g4;
+                sreg[b] = *(const f32x4*)(srow + (col < SP ? col : 0));
+            }
+        } else {
+            tk.fetch(k + head, J * KT, len, d, tid);
+        }
+        tv.fetch(v + head, J * KT, len, d, tid);
+    };
+    if (nT > 0) fetch(0);
+    for (int t = 0; t < nT; ++t) {
+        const int J = tile_of_step(t);
+        f32x4 S[NB];
+        __syncthreads();  // everyone is done with the tile before
+        if constexpr (STORED) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) S[b] = sreg[b];
+        } else {
+            tk.stage(ks, J * KT, len, d, tid);
+        }
+        tv.stage(vs, J * KT, len, d, tid);
+        __syncthreads();
+        if (t + 1 < nT) fetch(t + 1);
+        // 16-key blocks of the tile that hold a pair this wavefront needs: the first nk
+        int nk = 0;
+        if (wave_end > i0w) {
+            int keys = len - J * KT;
+            if (causal) keys = min(keys, wave_end - J * KT);
+            nk = pb.noskip ? NB : max(0, min(NB, (keys + 15) >> 4));
+        }
+        if (nk == 0) continue;
+        if constexpr (!STORED) {
+            cnt_phys += (unsigned)nk;
+            if (nk == NB) {
+                score_blocks<NDB, NB>(S, ks, qf, ln, g4);
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    S[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (b < nk) score_blocks<NDB, 1>(&S[b], ks + 16 * b * PITCH, qf, ln, g4);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < NB; ++b) S[b] *= pb.scale;
+        }
+        row.weights(S, lim - J * KT);
         // phase 3 (Eq. (3))
-        const float* vt = vs + ((KEYS ? 16 * wave : 0) + 4 * g4) * PITCH + ln;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             if (b >= nk) break;
 #pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float* vrow = vs + (16 * b + 4 * g4 + r) * PITCH;
+                float vf[NDB];
+                CL::read(vf, ln, [&](int c) { return *(const f32x4*)(vrow + c); },
+                         [&](int c) { return *(const f32x2*)(vrow + c); }, [&](int c) { return vrow[c]; });
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) row.O[db] = mfma16f(vf[db], S[b][r], row.O[db]);
+            }
+        }
+    }
+    const float L = row.row_sum();
+    const float inv = L > 0.f ? 1.f / L : 0.f;  // a row with no allowed pair is zero
+    const size_t base = ((size_t)rt.bb * N + i) * ((size_t)pb.H * d) + (size_t)rt.h * d;
+    if (i < N) CL::pieces(row.O, g4, [&](int c, f32x4 y) { store4(out, base, c, d, y * inv, pb.is_bf16, out_whole); });
+    if (!STORED && lane == 0) count_add(pb.counters, flat_block(), 0, cnt_phys);
+}
+
+// EXACT: d is 16 NDB, no column is dropped.
+template <int NDB, bool WHOLE, bool EXACT, bool STORED>
+__global__ __launch_bounds__(256, NDB <= 4 ? 3 : NDB <= 6 ? 2 : 1)  // three wavefronts per SIMD at d = 64 rather than two
+void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, const float* __restrict__ k,
+                      const float* __restrict__ v, const float* __restrict__ scores, void* __restrict__ out,
+                      int n_rowtiles, bool out_whole)
+{
+    typedef Cols<NDB> CL;
+    constexpr int DP = 16 * NDB, PITCH = DP + 4;
+    __shared__ __attribute__((aligned(16))) float st_o[64 * PITCH];  // [4][16] rows
+    __shared__ float st_ml[2 * 64];
+
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const RowTile rt(pb, 16, n_rowtiles);
+    if (!rt.there) return;
+    const int N = pb.N, d = pb.d, len = rt.len, last = len > 0 ? len - 1 : 0;
+    const size_t head = (size_t)rt.bh * N * d;
+    const float *kh = k + head, *vh = v + head;
+    const int i = rt.i0 + ln;  // the lane's row
+    // blocks 0 .. nb-1 hold a needed pair; in debug mode the others follow and change nothing
+    int nb = 0;
+    if (rt.row_end > rt.i0) {
+        nb = (len + 15) / 16;
+        if (pb.scheme == SCHEME_CAUSAL) nb = min(nb, (rt.row_end - 1) / 16 + 1);
+        if (pb.noskip) nb = (N + 15) / 16;
+    }
+    f32x4 qf[NDB];
+    if constexpr (!STORED) load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);
+    const int SP = score_pitch(N);
+    const float* srow = STORED ? scores + ((size_t)rt.bh * N + min(i, N - 1)) * SP : nullptr;
+
+    // Operands of a block: the lane's pieces of key row ln, and of V rows 4 g4 .. 4 g4 + 3; what lies
+    // past the length or past d is read from a row that exists and dropped.
+    struct Block {
+        f32x4 k[STORED ? 1 : NDB];
+        float v[4][NDB];
+    };
+    auto load = [&](Block& x, int b) {
+        if constexpr (STORED) {
+            const int col = 16 * b + 4 * g4;
+            x.k[0] = *(const f32x4*)(srow + (col < SP ? col : 0));
+        } else {
+            const float* krow = kh + (size_t)min(16 * b + ln, last) * d;
+#pragma unroll
+            for (int t = 0; t < NDB; ++t) x.k[t] = load4<WHOLE>(krow, 16 * t + 4 * g4, d, true);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float* vrow = vh + (size_t)min(16 * b + 4 * g4 + r, last) * d;
+            CL::read(x.v[r], ln, [&](int c) { return load4<WHOLE>(vrow, c, d, true); },
+                     [&](int c) {
+                         if constexpr (WHOLE) return *(const f32x2*)(vrow + (c < d ? c : 0));
+                         else return f32x2{vrow[c < d ? c : 0], vrow[c + 1 < d ? c + 1 : 0]};
+                     },
+                     [&](int c) { return vrow[c < d ? c : 0]; });
+        }
+    };
+    Row<NDB> row;
+    row.clear();
+    unsigned cnt_phys = 0;
+    const int lim = rt.last_key(pb, i) - 4 * g4;
+    auto step = [&](Block& x, int b) {
+        f32x4 S[1] = {{0.f, 0.f, 0.f, 0.f}};
+        if constexpr (STORED) {
+            S[0] = x.k[0];
+        } else {
+            ++cnt_phys;
+            // two chains: a product waits for the one before it in its own
+            f32x4 s2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < NDB; ++t) {
+                const f32x4 kf = EXACT ? x.k[t] : clip4<WHOLE>(x.k[t], 16 * t + 4 * g4 < d);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (j & 1) s2 = mfma16f(kf[j], qf[t][j], s2);
+                    else S[0] = mfma16f(kf[j], qf[t][j], S[0]);
+                }
+            }
+            S[0] = (S[0] + s2) * pb.scale;
+        }
+        row.weights(S, lim - 16 * b);
+        if (16 * b + 16 <= len) {
+#pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int db = 0; db < NDB; ++db) O[db] = mfma16f(vt[(16 * b + r) * PITCH + 16 * db], S[b][r], O[db]);
-        }
-    }
-    l += __shfl_xor(l, 16, 64);
-    l += __shfl_xor(l, 32, 64);
-
-    const size_t pitch = (size_t)pb.H * d;
-    const size_t base = ((size_t)bb * N + i0) * pitch + (size_t)h * d;
-    if constexpr (KEYS) {
-        // partial state of wavefront w, row r: m, l, then O
-        __syncthreads();
-        float* st_o = vs;  // [4][16] rows of PITCH
+                for (int db = 0; db < NDB; ++db) row.O[db] = mfma16f(x.v[r][db], S[0][r], row.O[db]);
+        } else {  // keys past the length: nothing of them reaches O
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) *(f32x4*)(st_o + (16 * wave + ln) * PITCH + 16 * db + 4 * g4) = O[db];
-        if (g4 == 0) {
-            st_ml[2 * (16 * wave + ln)] = m;
-            st_ml[2 * (16 * wave + ln) + 1] = l;
-        }
-        __syncthreads();
-        const int r = tid >> 4;
-        float mw[4], M = -INFINITY, L = 0.f;
+            for (int r = 0; r < 4; ++r) {
+                const bool in = 16 * b + 4 * g4 + r < len;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            mw[w] = st_ml[2 * (16 * w + r)];
-            M = fmaxf(M, mw[w]);
-        }
-        const float ref = M > -INFINITY ? M : 0.f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            mw[w] = exp_neg(mw[w] - ref);
-            L += mw[w] * st_ml[2 * (16 * w + r) + 1];
-        }
-        const float inv = L > 0.f ? 1.f / L : 0.f;  // a row with no allowed pair is zero
-        if (i0 + r < N)
-            for (int c = tid & 15; c < DP / 4; c += 16) {
-                f32x4 y = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int w = 0; w < 4; ++w) y += mw[w] * *(const f32x4*)(st_o + (16 * w + r) * PITCH + 4 * c);
-                store4(out, base + (size_t)r * pitch, 4 * c, d, y * inv, pb.is_bf16, out_whole);
+                for (int db = 0; db < NDB; ++db) row.O[db] = mfma16f(in ? x.v[r][db] : 0.f, S[0][r], row.O[db]);
             }
-    } else {
-        const float inv = l > 0.f ? 1.f / l : 0.f;
-        if (i < N)
-#pragma unroll
-            for (int db = 0; db < NDB; ++db)
-                store4(out, base + (size_t)(i - i0) * pitch, 16 * db + 4 * g4, d, O[db] * inv, pb.is_bf16, out_whole);
+        }
+    };
+    if (wave < nb) {
+        int b = wave;
+        if constexpr (NDB <= 8) {
+            Block x0, x1;
+            load(x0, b);
+            while (true) {
+                // the requests stay in front: left alone, the compiler sinks each to where its wait stands
+                load(x1, b + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                step(x0, b);
+                __builtin_amdgcn_sched_barrier(0);
+                b += 4;
+                if (b >= nb) break;
+                load(x0, b + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                step(x1, b);
+                __builtin_amdgcn_sched_barrier(0);
+                b += 4;
+                if (b >= nb) break;
+            }
+        } else {  // two blocks would not fit the registers
+            for (; b < nb; b += 4) {
+                Block x;
+                load(x, b);
+                step(x, b);
+            }
+        }
     }
-    if (!STORED && lane == 0) count_add(pb.counters, item, 0, cnt_phys);
+    if (!STORED && wave == 0) rt.count(pb, cc, lane);
+    if (!STORED && lane == 0) count_add(pb.counters, flat_block(), 0, cnt_phys);
+
+    // partial state of wavefront w, row r: m, l, then O
+    const float L0 = row.row_sum();
+    CL::pieces(row.O, g4, [&](int c, f32x4 y) { *(f32x4*)(st_o + (16 * wave + ln) * PITCH + c) = y; });
+    if (g4 == 0) {
+        st_ml[2 * (16 * wave + ln)] = row.m;
+        st_ml[2 * (16 * wave + ln) + 1] = L0;
+    }
+    __syncthreads();
+    const int r = tid >> 4;
+    float mw[4], M = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        mw[w] = st_ml[2 * (16 * w + r)];
+        M = fmaxf(M, mw[w]);
+    }
+    const float ref = M > -INFINITY ? M : 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        mw[w] = exp_neg(mw[w] - ref);
+        L += mw[w] * st_ml[2 * (16 * w + r) + 1];
+    }
+    const float inv = L > 0.f ? 1.f / L : 0.f;  // a row with no allowed pair is zero
+    const size_t base = ((size_t)rt.bb * N + rt.i0 + r) * ((size_t)pb.H * d) + (size_t)rt.h * d;
+    if (rt.i0 + r < N)
+        for (int c = tid & 15; c < DP / 4; c += 16) {
+            f32x4 y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < 4; ++w) y += mw[w] * *(const f32x4*)(st_o + (16 * w + r) * PITCH + 4 * c);
+            store4(out, base, 4 * c, d, y * inv, pb.is_bf16, out_whole);
+        }
 }
 
 // Phase 1 of the q = k = v scheme (Sec. 4.1, Eq. (4)): one workgroup per unordered pair of 64-row
@@ -459,9 +659,9 @@ void sym_scores_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ 
 
 namespace {
 
-// One row tile per workgroup of 64 rows, or of 16 rows with the keys shared by its wavefronts.
-// Measured (us, rows / keys): 320 workgroups of 64 rows 55 / 46, 384 56 / 54 (masked 41 / 35), 768 85 / 105
-// (masked 54 / 61); a single tile has no keys to share (256 workgroups 11 / 15).
+// Rows or keys kernel.  Measured (us, rows / keys; f32, d = 64, by the number of 64-row tiles): 32 99 / 31,
+// 96 30 / 21, 192 31 / 28, 320 (d = 80, masked) 49 / 41, 384 48 / 47 (masked 35 / 31), 768 77 / 93 (masked
+// 48 / 53); a single key tile has no keys to share (256 row tiles 11 / 14).
 template <int NDB, bool WHOLE, bool STORED>
 void launch_rows(const Problem& pb, const float* q, const float* k, const float* v, const float* scores, void* out,
                  hipStream_t s)
@@ -473,10 +673,10 @@ void launch_rows(const Problem& pb, const float* q, const float* k, const float*
     const int n_rowtiles = keys ? (pb.N + 15) / 16 : (pb.N + 63) / 64;
     const dim3 grid = flat_grid((size_t)heads * n_rowtiles);
     if (keys)
-        hipLaunchKernelGGL((attn_float_kernel<NDB, true, WHOLE, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
+        hipLaunchKernelGGL(pb.d == 16 * NDB ? (attn_keys_kernel<NDB, WHOLE, WHOLE, STORED>) : (attn_keys_kernel<NDB, WHOLE, false, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
                            out, n_rowtiles, out_whole);
     else
-        hipLaunchKernelGGL((attn_float_kernel<NDB, false, WHOLE, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
+        hipLaunchKernelGGL((attn_rows_kernel<NDB, WHOLE, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
                            out, n_rowtiles, out_whole);
 }
 

@@ -32,21 +32,16 @@ __device__ __forceinline__ float load_as_float(const bf16_t* p, size_t i)
 // orders the sum.  W stays k-major: float columns are read one by one, bfloat16 ones by the
 // transposing read.  Row pitches put the rows that one read touches on different banks.
 // ---------------------------------------------------------------------------
-template <typename T>
-struct Slice;
-template <>
-struct Slice<float> {
-    static constexpr int KS = 32;              // k per slice
-    static constexpr int VEC = 4;              // elements of a 16-byte piece
-    static constexpr int APITCH = KS + 4;      // elements of an X row in LDS
-    static constexpr int bpitch(int bn) { return bn + 8; }
-};
-template <>
-struct Slice<bf16_t> {
-    static constexpr int KS = 64;
-    static constexpr int VEC = 8;
-    static constexpr int APITCH = KS + 8;
-    static constexpr int bpitch(int bn) { return bn + 32; }
+// WK = 1: 64 x 64 tile, 2 x 2 wavefronts.  WK = 4, for products that leave CUs idle: 32 x 32 tile, whose
+// four wavefronts take a quarter of every slice's k each, slices twice as deep, partial tiles added
+// through LDS at the end: four times the workgroups and a chain of products a quarter as long.
+template <typename T, int WK>
+struct Slice {
+    static constexpr int VEC = 16 / sizeof(T);                          // elements of a 16-byte piece
+    static constexpr int KS = (sizeof(T) == 4 ? 32 : 64) * (WK == 1 ? 1 : 2);  // k per slice
+    static constexpr int BT = WK == 1 ? 64 : 32;                        // tile edge
+    static constexpr int APITCH = KS + VEC;                             // elements of an X row in LDS
+    static constexpr int BPITCH = sizeof(T) == 4 ? BT + 8 : (WK == 1 ? BT + 32 : BT);
 };
 
 struct ProjArgs {
@@ -61,7 +56,7 @@ struct ProjArgs {
 template <typename T, bool WHOLE>
 __device__ __forceinline__ u32x4 load_piece(const T* __restrict__ row, int col, int count, bool there)
 {
-    constexpr int VEC = Slice<T>::VEC;
+    constexpr int VEC = 16 / sizeof(T);
     u32x4 v = {0u, 0u, 0u, 0u};
     if constexpr (WHOLE) {
         v = *(const u32x4*)(row + (col < count ? col : 0));
@@ -87,14 +82,14 @@ __device__ __forceinline__ u32x4 clip_piece(u32x4 v, bool in)
     return v;
 }
 
-template <typename T, bool WHOLE>
+template <typename T, bool WHOLE, int WK>
 __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, int H, int d, const T* __restrict__ X,
                                                          ProjArgs pa, int tiles_n, unsigned long long* __restrict__ counters)
 {
     clear_counters(counters);
-    typedef Slice<T> SL;
-    constexpr int BM = 64, BN = 64, KS = SL::KS, VEC = SL::VEC;
-    constexpr int AP = SL::APITCH, BP = SL::bpitch(BN);
+    typedef Slice<T, WK> SL;
+    constexpr int BM = SL::BT, BN = SL::BT, KS = SL::KS, VEC = SL::VEC;
+    constexpr int AP = SL::APITCH, BP = SL::BPITCH, KW = KS / WK;  // KW: k of a slice that a wavefront takes
     constexpr int ACH = KS / VEC, BCH = BN / VEC;             // 16-byte pieces per row
     constexpr int NAL = BM * ACH / 256, NBL = KS * BCH / 256;  // pieces per thread
     constexpr int PF = 3;  // slices fetched ahead, a set of registers each
@@ -103,7 +98,8 @@ __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, in
     const int HD = H * d;
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+    const int wm = WK == 1 ? (wave >> 1) * 32 : 0, wn = WK == 1 ? (wave & 1) * 32 : 0;
+    const int kw = WK == 1 ? 0 : wave * KW;
     const int which = blockIdx.x / tiles_n;
     const int col0 = (blockIdx.x - which * tiles_n) * BN, row0 = blockIdx.y * BM;
     const T* __restrict__ W = (const T*)pa.W[which];
@@ -147,21 +143,21 @@ __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, in
         __syncthreads();
         if constexpr (sizeof(T) == 4) {
 #pragma unroll
-            for (int t = 0; t < KS / 8; ++t) {
-                const f32x4 af = *(const f32x4*)(As + (wm + ln) * AP + 8 * t + 4 * g);
+            for (int t = 0; t < KW / 8; ++t) {
+                const f32x4 af = *(const f32x4*)(As + (wm + ln) * AP + kw + 8 * t + 4 * g);
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], Bs[(8 * t + 4 * g + j) * BP + wn + ln], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], Bs[(kw + 8 * t + 4 * g + j) * BP + wn + ln], acc, 0, 0, 0);
             }
         } else {
             // transposing read: 16 lanes hand in a 4 (k) x 16 (columns) patch, lane i gets column i
             const int i16 = lane & 15;
             const int kr = 8 * g + (i16 >> 2), cb = wn + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
 #pragma unroll
-            for (int ks = 0; ks < KS / 16; ++ks) {
-                const u32x4 af = *(const u32x4*)(As + (wm + ln) * AP + 16 * ks + 8 * g);
-                const u32x2 lo = lds_read_tr16(Bs + (16 * ks + kr) * BP + cb);
-                const u32x2 hi = lds_read_tr16(Bs + (16 * ks + kr + 4) * BP + cb);
+            for (int ks = 0; ks < KW / 16; ++ks) {
+                const u32x4 af = *(const u32x4*)(As + (wm + ln) * AP + kw + 16 * ks + 8 * g);
+                const u32x2 lo = lds_read_tr16(Bs + (kw + 16 * ks + kr) * BP + cb);
+                const u32x2 hi = lds_read_tr16(Bs + (kw + 16 * ks + kr + 4) * BP + cb);
                 acc = mfma32(af, u32x4{lo[0], lo[1], hi[0], hi[1]}, acc);
             }
         }
@@ -177,7 +173,20 @@ __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, in
         slice(k0 + 2 * KS, buf, std::integral_constant<int, 2>{});
         if (k0 + 3 * KS >= D) break;
     }
-    // register r: vector acc_row(r, g), column ln; 32 lanes write 128 consecutive bytes
+    // register r: vector acc_row(r, g), column ln; 32 lanes write 128 consecutive bytes.  WK = 4: a
+    // wavefront adds up and stores four of the sixteen registers.
+    int e0 = 0;
+    constexpr int NE = WK == 1 ? 16 : 4;
+    if constexpr (WK != 1) {
+        __shared__ float part[4][16][64];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) part[wave][e][lane] = acc[e];
+        __syncthreads();
+        e0 = 4 * wave;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[e] = (part[0][e0 + e][lane] + part[1][e0 + e][lane]) + (part[2][e0 + e][lane] + part[3][e0 + e][lane]);
+    }
     float* __restrict__ out = pa.out[which];
     const int gc = col0 + wn + ln;
     if (gc >= HD) return;
@@ -185,8 +194,8 @@ __global__ __launch_bounds__(256) void proj_float_kernel(int M, int N, int D, in
     const int first = row0 + wm;
     const int b0 = first / N, edge = (b0 + 1) * N;  // most blocks lie in one batch item
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int gr = first + acc_row(e, g);
+    for (int e = 0; e < NE; ++e) {
+        const int gr = first + acc_row(e0 + e, g);
         if (gr >= M) continue;
         const int bb = gr < edge ? b0 : gr / N;
         out[(((size_t)bb * H + h) * N + (gr - bb * N)) * d + l] = acc[e];
@@ -207,17 +216,29 @@ __global__ void copy_heads_kernel(int total, int N, int H, int d, const T* __res
     out[(((size_t)bb * H + h) * N + i) * d + l] = load_as_float(X, (size_t)e);
 }
 
+template <typename T, int WK>
+void launch_proj_tile(const Problem& pb, const T* X, const ProjArgs& pa, int count, bool whole, hipStream_t s)
+{
+    constexpr int BT = Slice<T, WK>::BT;
+    const int M = pb.B * pb.N, HD = pb.H * pb.d;
+    const int tiles_n = (HD + BT - 1) / BT;
+    const dim3 grid(tiles_n * count, (M + BT - 1) / BT);
+    if (whole) hipLaunchKernelGGL((proj_float_kernel<T, true, WK>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, pb.counters);
+    else hipLaunchKernelGGL((proj_float_kernel<T, false, WK>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, pb.counters);
+}
+
 template <typename T>
 void launch_proj_type(const Problem& pb, const T* X, const ProjArgs& pa, int count, hipStream_t s)
 {
-    const int M = pb.B * pb.N, HD = pb.H * pb.d;
-    const int tiles_n = (HD + 63) / 64;
+    const long M = (long)pb.B * pb.N, HD = pb.H * pb.d;
     uintptr_t bits = reinterpret_cast<uintptr_t>(X);
     for (int m = 0; m < count; ++m) bits |= reinterpret_cast<uintptr_t>(pa.W[m]);
-    const bool whole = pb.D % Slice<T>::VEC == 0 && HD % Slice<T>::VEC == 0 && (bits & 15) == 0;
-    const dim3 grid(tiles_n * count, (M + 63) / 64);
-    if (whole) hipLaunchKernelGGL((proj_float_kernel<T, true>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, pb.counters);
-    else hipLaunchKernelGGL((proj_float_kernel<T, false>), grid, dim3(256), 0, s, M, pb.N, pb.D, pb.H, pb.d, X, pa, tiles_n, pb.counters);
+    const bool whole = pb.D % (16 / sizeof(T)) == 0 && HD % (16 / sizeof(T)) == 0 && (bits & 15) == 0;
+    const long tiles = ((M + 63) / 64) * ((HD + 63) / 64) * count;
+    // Measured (us, 64 x 64 / 32 x 32 with k shared, f32): 48 tiles 18.1 / 9.8, 192 24.6 / 23.1, 288 38.0 / 33.9,
+    // 576 51 / 55; the larger tile reads half as much per product.
+    if (tiles < 300) launch_proj_tile<T, 4>(pb, X, pa, count, whole, s);
+    else launch_proj_tile<T, 1>(pb, X, pa, count, whole, s);
 }
 
 }  // namespace
