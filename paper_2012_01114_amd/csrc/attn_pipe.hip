@@ -383,7 +383,14 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
     const int per_xcd = gridDim.x >> 3;
     const int per_head = (int)per_head_d.d;
     int bh, x;
-    if (CAUSAL && single) {
+    if (CAUSAL && single == 2) {
+        // one row tile per workgroup, the heads in turn, the heaviest tiles first
+        const int heads = (int)per_xcd_heads.d;
+        const int t = (int)divide(blockIdx.x, per_xcd_heads);
+        if (t >= per_head) return;
+        bh = (int)blockIdx.x - t * heads;
+        x = per_head - 1 - t;
+    } else if (CAUSAL && single) {
         // Masked scheme on a launch too small to give every CU several row-tile pairs: one row tile
         // per workgroup (x is the tile itself), all of them resident at once, three to a CU.  The
         // tiles of an XCD's heads, heaviest first, are dealt over its 32 CUs in rows that run forth
@@ -808,19 +815,26 @@ hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, c
     const float qscale = pb.scale * 1.4426950408889634f;
     const int br = 32 * waves;
     const int n_qtiles = (pb.N + br - 1) / br;
-    // One row tile per workgroup instead of a pair when the pairs would not give every CU four
-    // workgroups (and the heads divide evenly over the eight XCDs, padded rows are not left out).
-    // Measured, 128-row workgroups: batch 8, n 1024, 12 heads 39.5 -> 32 us, batch 2 27 -> 23 us,
-    // even at 768 pairs; with 256-row workgroups the pairing stays ahead (d_k = 128, 512 pairs: +5 %).
-    const bool single = causal && waves == 4 && !pb.skip_rows && (pb.B * pb.H) % 8 == 0 &&
-                        (long)pb.B * pb.H * ((n_qtiles + 1) / 2) < 4L * 256;
+    // Masked scheme, padded rows not left out: one row tile per workgroup instead of a pair.
+    // d_k = 64, 128-row workgroups: when the pairs would not give every CU four workgroups.  Measured (us, pairs /
+    //   tiles dealt over the CUs of an XCD / heads in turn, heaviest tiles first): batch 8, 12 heads, n 512 21.5 /
+    //   17.7 / 17.6, n 1024 33.7 / 28.0 / 28.8; 20 x 15 heads, n 512 (600 pairs) 31.7 / - / 30.4; 480 heads, n 2048
+    //   319 / 330 / 335.  Dealing needs the heads to divide over the XCDs.
+    // d_k = 128 (one workgroup per CU): always, heads in turn: batch 8, 8 heads, n 512 35 / 24 / 24, n 1024 50 / 40 /
+    //   39, n 2048 (256 pairs) 91 / 98 / 86; 32 heads, n 8192 498 / 515 / 495.
+    const long pairs = (long)pb.B * pb.H * ((n_qtiles + 1) / 2);
+    int single = 0;
+    if (causal && !pb.skip_rows) {
+        if (pb.d == 128) single = 2;
+        else if (waves == 4 && pairs < 4L * 256) single = (pb.B * pb.H) % 8 == 0 ? 1 : 2;
+    }
     const int per_head = (causal && !single) ? (n_qtiles + 1) / 2 : n_qtiles;
     const int n_work = pb.B * pb.H * per_head;
     const int grid = ((n_work + 7) / 8) * 8;
     const CountCfg cc = count_cfg(pb.b);
 #define ATTN_LAUNCH(DK_, W_, C_, F_)                                                                                    \
     hipLaunchKernelGGL((attn_pipe_kernel<DK_, W_, C_, F_>), dim3(grid), dim3(64 * W_), 0, s, pb, cc, q, k, vt, out, \
-                       n_qtiles, fast_div(per_head), n_work, fast_div(pb.H), fast_div(grid / 8 / per_head), X, Wq, qscale, single ? 1 : 0)
+                       n_qtiles, fast_div(per_head), n_work, fast_div(pb.H), fast_div(single == 2 ? pb.B * pb.H : grid / 8 / per_head), X, Wq, qscale, single)
 #define ATTN_PICK(DK_, W_)                                                                  \
     do {                                                                                    \
         if (causal) { if (fuse) ATTN_LAUNCH(DK_, W_, true, true); else ATTN_LAUNCH(DK_, W_, true, false); }   \
