@@ -180,6 +180,12 @@ bool matrix_core_shape(const attn_config* cfg)
            effective_scale(cfg) > 0.f;
 }
 
+// Workgroup shape of the matrix-core attention kernel that the caller has asked for, in wavefronts of 32 rows.
+int asked_waves(const attn_config* cfg)
+{
+    return (cfg->flags & ATTN_FLAG_WIDE_TILES) ? 8 : (cfg->flags & ATTN_FLAG_NARROW_TILES) ? 4 : 0;
+}
+
 // The checks every entry point that takes a configuration starts with.
 attn_status validate_config(const attn_config* cfg)
 {
@@ -415,11 +421,8 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
             CHECK("launch q=k=v attention (mfma)");
             ctx->last_proj_gemms = 2;  // z = x.Wq, produced in the k and in the v^T layout
         } else {
-            // d_k = 64: 128-row workgroups of 4 wavefronts, three of them per CU; d_k = 128: 256 rows, 8 wavefronts
-            int waves = cf.d_k == 128 ? 8 : 4;
-            if (cf.d_k == 64 && (cf.flags & ATTN_FLAG_WIDE_TILES)) waves = 8;
-            e = launch_attn_pipe(pb, ctx->qb, ctx->kb, ctx->vtb, (bf16_t*)out, waves, s,
-                                 fuse_q ? (const bf16_t*)X : nullptr, fuse_q ? (const bf16_t*)Wq : nullptr);
+            e = launch_attn(pb, ctx->qb, ctx->kb, ctx->vtb, (bf16_t*)out, asked_waves(&cf), s,
+                            fuse_q ? (const bf16_t*)X : nullptr, fuse_q ? (const bf16_t*)Wq : nullptr);
             CHECK("launch attention (mfma)");
             ctx->last_proj_gemms = 3;
         }
@@ -545,9 +548,7 @@ attn_status attn_forward_static(const attn_config* cfg, const int32_t* lens_dev,
     e = launch_proj_mfma(pb, (const bf16_t*)X, (const bf16_t*)Wq, (const bf16_t*)Wk, (const bf16_t*)Wv, nullptr, q, k,
                          vt, s);
     if (e != hipSuccess) return hip_fail(nullptr, "launch proj_mfma", e);
-    int waves = cfg->d_k == 128 ? 8 : 4;
-    if (cfg->d_k == 64 && (cfg->flags & ATTN_FLAG_WIDE_TILES)) waves = 8;
-    e = launch_attn_pipe(pb, q, k, vt, (bf16_t*)out, waves, s);
+    e = launch_attn(pb, q, k, vt, (bf16_t*)out, asked_waves(cfg), s);
     if (e != hipSuccess) return hip_fail(nullptr, "launch attention (mfma)", e);
     return ATTN_OK;
 }

@@ -117,8 +117,11 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
 // 4 or 8 for d_k = 64, 8 for d_k = 128.
 // X and Wq given: the kernel projects its queries itself (q is not read).
 hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, const h16_t* vt,
-                            bf16_t* out, int waves, hipStream_t s, const bf16_t* X = nullptr,
-                            const bf16_t* Wq = nullptr);
+                            bf16_t* out, int waves, hipStream_t s, const bf16_t* X, const bf16_t* Wq);
+// Either of attn_pipe.hip and attn_split.hip, by the size of the launch; asked_waves: 4 or 8 when the
+// caller has asked for a workgroup shape of attn_pipe.hip, else 0.
+hipError_t launch_attn(const Problem& pb, const h16_t* q, const h16_t* k, const h16_t* vt, bf16_t* out, int asked_waves,
+                       hipStream_t s, const bf16_t* X = nullptr, const bf16_t* Wq = nullptr);
 // q = k = v scheme on the matrix cores: every 128 x 128 score tile computed once and used for both
 // of its row blocks, partial row states merged by a second kernel.  z, zt: the shared vectors in
 // the k and v^T layouts above; work: sym_pair_workspace_floats(pb) floats.

@@ -140,6 +140,55 @@ def test_mfma_path_small(shape, scheme, tiles, seed0):
     _run_and_compare(w, scheme, 0.0, lens=np.zeros(B, dtype=np.int32), flags=tiles)
 
 
+# ---- small launches: 32 rows per workgroup, its wavefronts share the keys (no tile flag) -------------------
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (1, 1, 64, 2, 64, 1),         # a single row and key
+    (1, 33, 64, 2, 64, 11),       # one row and one key past a block: three wavefronts without a block
+    (3, 96, 72, 2, 64, 12),       # whole blocks
+    (2, 200, 128, 3, 64, 25),     # more blocks than wavefronts, ragged
+    (2, 129, 64, 2, 128, 43),     # d_k = 128, one row in the last block
+    (1, 520, 64, 1, 128, 5),      # partitions larger than a row tile
+])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+def test_small_launches_share_the_keys(shape, scheme):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("split", B, n, D, H, d, p, "bf16", scheme, 8800 + n)
+    _run_and_compare(w, scheme, 0.0)
+    lens = np.random.default_rng(n + 3).integers(0, n + 1, B).astype(np.int32)
+    lens[-1] = n // 2 + 1
+    _run_and_compare(w, scheme, 0.0, lens=lens)
+    # padded rows left out: against the checker, and the same bits without skipping and in the packed layout
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = lens
+    outs = []
+    for noskip in (0, ar.ATTN_FLAG_NO_SKIP):
+        run = hp.GpuRun(w, stored, flags=ar.ATTN_FLAG_SKIP_PADDED_ROWS | noskip)
+        try:
+            got, stats = run.forward(scheme)
+            hp.check_counts(stats, hp.oracle_counts(w, scheme, lens, skip_padded_rows=True), noskip=bool(noskip))
+            outs.append(got)
+            if not noskip:
+                assert stats["phys_tiles_executed"] == hp.expected_phys_blocks(w, scheme, lens, skip_padded_rows=True)
+                outs.append(run.forward_packed(scheme, lens)[0])
+        finally:
+            run.close()
+    hp.tol_check(outs[0], hp.oracle_forward(w, f64, scheme, 0.0, lens=lens, skip_padded_rows=True), w.dtype)
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
+# ---- masked scheme, one row tile per workgroup with the heads in turn ------------------------------------
+@pytest.mark.parametrize("shape", [
+    (3, 700, 64, 13, 64, 100),    # d_k = 64, heads that do not divide by eight
+    (3, 1100, 64, 5, 128, 275),   # d_k = 128
+])
+def test_row_tiles_with_the_heads_in_turn(shape):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("in_turn", B, n, D, H, d, p, "bf16", CAUSAL, 9100 + n)
+    _run_and_compare(w, CAUSAL, 0.0)
+    _run_and_compare(w, CAUSAL, 0.0, lens=np.array([n, 1, n // 3], dtype=np.int32))
+
+
 # ---- the projection's last slice of d_model when it is not 64 deep (vectors in whole 16-byte pieces) ----
 @pytest.mark.parametrize("d_model", [8, 56, 72, 136, 200])   # one slice, cut; then two to four with 8 .. 8 left
 @pytest.mark.parametrize("shape", [
