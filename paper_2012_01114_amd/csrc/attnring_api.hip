@@ -407,9 +407,9 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
             MARK(1);
             prepared = true;
         }
-        // queries projected inside the attention kernel: when asked for, d_model comes in whole slices and the
-        // weights are read in place
-        const bool fuse_q = !sym && !row0 && (cf.flags & ATTN_FLAG_FUSE_Q_PROJECTION) != 0 && cf.d_model % 64 == 0 &&
+        // queries projected inside the attention kernel: when asked for, d_model comes in whole slices, the
+        // columns in whole 128s and the weights are read in place
+        const bool fuse_q = !sym && !row0 && (cf.flags & ATTN_FLAG_FUSE_Q_PROJECTION) != 0 && cf.d_model % 64 == 0 && hd % 128 == 0 &&
                             proj_reads_weights_in_place(pb, (const bf16_t*)Wq, (const bf16_t*)Wk, (const bf16_t*)Wv);
         if (fuse_q) pb.no_q = true;
         e = launch_proj_mfma(pb, (const bf16_t*)X, (const bf16_t*)Wq, (const bf16_t*)Wk, (const bf16_t*)Wv, ctx->wt,
@@ -513,7 +513,7 @@ attn_status attn_forward_static(const attn_config* cfg, const int32_t* lens_dev,
     pb.is_bf16 = true;
     pb.lens = lens_dev;
     pb.row0 = nullptr;
-    if (!matrix_core_shape(cfg) || cfg->d_model % 64 != 0 || !aligned_to(X, 16) || !aligned_to(out, 8) ||
+    if (!matrix_core_shape(cfg) || cfg->d_model % 64 != 0 || (cfg->n_heads * cfg->d_k) % 128 != 0 || !aligned_to(X, 16) || !aligned_to(out, 8) ||
         !proj_reads_weights_in_place(pb, (const bf16_t*)Wq, (const bf16_t*)Wk, (const bf16_t*)Wv))
         return fail(nullptr, ATTN_ERR_UNSUPPORTED,
                     "attn_forward_static: needs bfloat16, d_k 64 or 128, d_model a multiple of 64, n_heads*d_k a "

@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void transpose_w16_kernel(int D, int HD, const
 }
 
 // ---------------------------------------------------------------------------
-// Fallback GEMM (an odd number of 64-wide heads, unaligned weights), on transposed weights:
+// Fallback GEMM (unaligned weights), on transposed weights:
 // C = A . B^T with both operands k-contiguous.  Square BT x BT tile per
 // workgroup, 2 x 2 wavefronts, 32x32x16 MFMA blocks, 64-deep k slices double
 // buffered in LDS.  The "x side" rows are vectors (with the per-batch row pitch
@@ -773,6 +773,165 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     }
 }
 
+// ---------------------------------------------------------------------------
+// The GEMM for products of few tiles, and for columns that do not come in 128s (an odd number of
+// 64-wide heads): 64 x 64 tiles, four wavefronts of 32 x 32, operands copied straight into LDS.
+// What bounds a product that leaves CUs idle is its own chain of slices, so the ring is deep (five
+// 64-deep slices of x and W, 80 KiB: two workgroups share a CU) and a slice is one barrier, eight
+// LDS reads and four MFMAs per wavefront.  Both sides are rows of 128 bytes: x rows with their
+// chunks XOR-ed with bits 1..3 of the row, k-rows of W with 4 * bit 1 of k (transposing reads).
+// Stores go out from the accumulators, eight bytes per lane: four instructions per wavefront.
+// ---------------------------------------------------------------------------
+constexpr int SMALL_STAGES = 5;
+template <bool TAIL>
+__global__ __launch_bounds__(256, 2)
+void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
+                       const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
+                       h16_t* __restrict__ qo, h16_t* __restrict__ ko, h16_t* __restrict__ vto, TileMap tm,
+                       float qscale, const int* __restrict__ lens, bool skip_q_rows, bool no_q,
+                       const int* __restrict__ row0, unsigned long long* __restrict__ counters)
+{
+    constexpr int XB = 64 * 128, STAGE = 2 * XB;  // x: 64 rows x 64 k; W: 64 k-rows x 64 columns
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[SMALL_STAGES * STAGE];
+    clear_counters(counters);  // this is the first kernel of a forward pass on this path
+
+    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int HD = H * d;
+    const int per_xcd = gridDim.x >> 3;
+    const int tile_id = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile_id >= tm.n_tiles) return;
+    int tw, tx_;
+    tile_of(tm, tile_id, tw, tx_);
+    const int bb = (int)divide((unsigned)tx_, tm.per_item);
+    const int i0 = tx_ * 64 - bb * Npad;
+    if (i0 >= N) return;  // nothing but padding
+    const int w0 = tw * 64 + (no_q ? HD : 0);
+    if (lens != nullptr && (w0 >= HD || skip_q_rows) && past_key_length(lens, bb, i0, N)) return;  // see proj_dma_kernel
+    const int which = w0 >= 2 * HD ? 2 : w0 >= HD ? 1 : 0;
+    const int c0 = w0 - which * HD;  // first column in its matrix
+    const bf16_t* Wm = (which == 0 ? Wq : (which == 1 ? Wk : Wv)) + c0;
+
+    // pieces wave and wave + 4 of either side: rows 8 * piece + lane / 8, chunk position lane % 8
+    unsigned xoff[2], woff[2];
+    const int rl = lane >> 3, xc = (lane & 7) ^ ((rl >> 1) & 3);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int row = 8 * (wave + 4 * u) + rl;
+        const int cx = xc ^ (((row >> 3) & 1) << 2);  // chunk XOR (row >> 1) & 7
+        const int cw = (lane & 7) ^ (4 * ((row >> 1) & 1));
+        xoff[u] = 2u * (source_row(row0, Bsz, N, bb, i0 + row) * (unsigned)D + cx * 8);
+        woff[u] = 2u * ((unsigned)row * (unsigned)HD + cw * 8);
+    }
+    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)X, 0, -1, 0x00020000);
+    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Wm, 0, -1, 0x00020000);
+    typedef const __attribute__((address_space(1))) void* global_ptr;
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    auto request = [&](int j, int stage) {  // slice j: two x and two W pieces of this wavefront
+        const int k0 = 64 * j;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            unsigned char* xd = lds + stage * STAGE + (wave + 4 * u) * 1024;
+            unsigned char* wd = xd + XB;
+            if (TAIL && k0 + 64 > D) {
+                const int row = 8 * (wave + 4 * u) + rl, cx = xc ^ (((row >> 3) & 1) << 2);
+                const void* xs = k0 + 8 * cx < D ? (const void*)((const unsigned char*)X + xoff[u] + 2u * (unsigned)k0)
+                                                 : (const void*)&zero_piece;
+                const void* ws = k0 + row < D ? (const void*)((const unsigned char*)Wm + woff[u] +
+                                                              2u * ((unsigned)k0 * (unsigned)HD))
+                                              : (const void*)&zero_piece;
+                __builtin_amdgcn_global_load_lds((global_ptr)xs, (lds_ptr)xd, 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((global_ptr)ws, (lds_ptr)wd, 16, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_ptr)xd, 16, (int)xoff[u], (int)(2u * (unsigned)k0), 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_ptr)wd, 16, (int)woff[u],
+                                                         (int)(2u * (unsigned)k0 * (unsigned)HD), 0, 0);
+            }
+        }
+    };
+    // operand offsets within a stage: x row (wave >> 1) * 32 + ln, columns (wave & 1) * 32 ...
+    const int xr = (wave >> 1) * 32, wcol = (wave & 1) * 32;
+    const int xfo = (xr + ln) * 128 + ((g ^ ((ln >> 1) & 7)) << 4);
+    const int i16 = lane & 15, kr = 8 * g + (i16 >> 2);
+    const int col = wcol + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
+    const int wfo = XB + kr * 128 + (((col >> 3) ^ (4 * ((kr >> 1) & 1))) << 4) + ((col & 7) << 1);
+    const unsigned lds_addr = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)lds;
+
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    const int ns = TAIL ? (D + 63) / 64 : D / 64;
+    const int ahead = ns < SMALL_STAGES - 1 ? ns : SMALL_STAGES - 1;
+    for (int j = 0; j < ahead; ++j) request(j, j);
+    auto all_slices = [&](auto is_v_) {
+        constexpr bool IS_V = decltype(is_v_)::value;
+        int stage = 0;
+#pragma nounroll
+        for (int j = 0; j < ns; ++j) {
+            // slices j + 1 .. j + 3 may be in flight, four requests each; loads return in order
+            const int more = ns - 1 - j;
+            if (more >= 3) __builtin_amdgcn_s_waitcnt(0x0070 | 12);
+            else if (more == 2) __builtin_amdgcn_s_waitcnt(0x0070 | 8);
+            else if (more == 1) __builtin_amdgcn_s_waitcnt(0x0070 | 4);
+            else __builtin_amdgcn_s_waitcnt(0x0070);
+            // behind the barrier the slice is in LDS for everyone, and everyone has read the one before
+            // (its reads were waited for ahead of its MFMAs), whose stage takes slice j + 4
+            __builtin_amdgcn_s_barrier();
+            const int free_stage = stage == 0 ? SMALL_STAGES - 1 : stage - 1;
+            if (j + SMALL_STAGES - 1 < ns) request(j + SMALL_STAGES - 1, free_stage);
+            const unsigned char* base = lds + stage * STAGE;
+            const unsigned waddr = lds_addr + (unsigned)(stage * STAGE + wfo);
+            u32x4 xf[4];
+            u32x2 lo[4], hi[4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                xf[ks] = *(const u32x4*)(base + (xfo ^ (32 * ks)));
+                asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo[ks]) : "v"(waddr), "n"(16 * ks * 128));
+                asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi[ks]) : "v"(waddr), "n"((16 * ks + 4) * 128));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): hand-written reads are not counted by the compiler
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                const u32x4 wf = {lo[ks][0], lo[ks][1], hi[ks][0], hi[ks][1]};
+                acc = IS_V ? mfma32(xf[ks], wf, acc) : mfma32(wf, xf[ks], acc);
+            }
+            stage = stage == SMALL_STAGES - 1 ? 0 : stage + 1;
+        }
+    };
+    if (which == 2) all_slices(std::true_type{});
+    else all_slices(std::false_type{});
+
+    const int dsh = d == 128 ? 7 : 6;  // d is 64 or 128 on this path
+    if (which != 2) {
+        // A side = columns (four consecutive per register quad), B side = vectors
+        const int i = i0 + xr + ln;
+        const float qs = which ? 1.f : qscale;  // q is stored pre-multiplied (see launch_proj_mfma)
+        if (i < N) {
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const int cc = c0 + wcol + 8 * r4 + 4 * g, h = cc >> dsh, l = cc & (d - 1);
+                *(u32x2*)((which ? ko : qo) + (((size_t)bb * H + h) * Npad + i) * d + l) =
+                    u32x2{pack_f16_sat(acc[4 * r4] * qs, acc[4 * r4 + 1] * qs),
+                          pack_f16_sat(acc[4 * r4 + 2] * qs, acc[4 * r4 + 3] * qs)};
+            }
+        }
+    } else {
+        // A side = vectors (four consecutive key slots per register quad), B side = columns; the tile
+        // is one 64-key block, in which vectors past n are stored as zeros
+        const int cc = c0 + wcol + ln, h = cc >> dsh, l = cc & (d - 1);
+        h16_t* blk = vto + ((((size_t)bb * H + h) * (Npad >> 6) + (i0 >> 6)) * d + l) * 64;
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int r64 = xr + 8 * r4 + 4 * g, left = N - (i0 + r64);
+            *(u32x2*)(blk + ((r64 & 48) | vt_slot16(r64 & 15))) =
+                u32x2{pack_f16_sat(left > 0 ? acc[4 * r4] : 0.f, left > 1 ? acc[4 * r4 + 1] : 0.f),
+                      pack_f16_sat(left > 2 ? acc[4 * r4 + 2] : 0.f, left > 3 ? acc[4 * r4 + 3] : 0.f)};
+        }
+    }
+}
+
 // The stored q carries the score scale and the change to base-2 exponentials:
 // q' = q * scale * log2(e), applied to the fp32 accumulator before the one rounding to
 // half precision, so that the attention kernels get base-2 scores straight out of the MFMA.
@@ -792,6 +951,22 @@ hipError_t launch_dma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, cons
     else
         hipLaunchKernelGGL((proj_dma_kernel<BX, BW, WR, WC, true>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
                            pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
+    return hipGetLastError();
+}
+
+hipError_t launch_small(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk, const bf16_t* Wv,
+                        h16_t* q, h16_t* k, h16_t* vt, hipStream_t s)
+{
+    const float qscale = q_prescale(pb);
+    const int* lens = pb.noskip ? nullptr : pb.lens;
+    const TileMap tm = tile_map(pb, 64, 64, pb.no_q ? 2 : 3, lens != nullptr);
+    const int grid = ((tm.n_tiles + 7) / 8) * 8;
+    if (pb.D % 64 == 0)
+        hipLaunchKernelGGL(proj_small_kernel<false>, dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
+                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
+    else
+        hipLaunchKernelGGL(proj_small_kernel<true>, dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
+                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
     return hipGetLastError();
 }
 
@@ -825,13 +1000,12 @@ hipError_t launch_transpose_w(const Problem& pb, const bf16_t* Wq, const bf16_t*
 }
 
 // Whether the projection reads the weights where the caller has them (no W^T, no re-layout kernel):
-// whole 128-column tiles in each matrix, and 16-byte aligned weights for the 16-byte copies.
+// 16-byte aligned weights for the 16-byte copies.
 bool proj_reads_weights_in_place(const Problem& pb, const bf16_t* Wq, const bf16_t* Wk, const bf16_t* Wv)
 {
-    const int HD = pb.H * pb.d;
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(Wq) | reinterpret_cast<uintptr_t>(Wk) |
                              reinterpret_cast<uintptr_t>(Wv)) & 15) == 0;
-    return pb.D % 8 == 0 && HD % 128 == 0 && aligned16;
+    return pb.D % 8 == 0 && aligned16;
 }
 
 hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk,
@@ -848,6 +1022,10 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
     const int HD = pb.H * pb.d;
     const long t256 = HD % 256 == 0 ? (long)pb.B * (pb.Npad / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
     if (proj_reads_weights_in_place(pb, Wq, Wk, Wv)) {  // operands go straight to LDS
+        // Few tiles: 64 x 64 ones on a deeper ring.  Measured (us, 128 x 128 / 64 x 64, by the number of 128 x 128
+        // tiles): 24 9.9 / 8.2, 36 11.6 / 9.5, 72 12.5 / 11.6, 96 (d_model 3072) 25.7 / 23.2, 144 13.3 / 16.6.
+        const long t128 = (long)pb.B * (pb.Npad / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
+        if (HD % 128 != 0 || t128 <= 100) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 512 && pb.D >= 2048) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 320) return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         return launch_dma<128, 128, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);

@@ -193,7 +193,9 @@ def test_row_tiles_with_the_heads_in_turn(shape):
 @pytest.mark.parametrize("d_model", [8, 56, 72, 136, 200])   # one slice, cut; then two to four with 8 .. 8 left
 @pytest.mark.parametrize("shape", [
     # B, n, H, d, p
-    (2, 200, 2, 64, 25),          # 128 x 128 tiles
+    (2, 200, 2, 64, 25),          # 64 x 64 tiles
+    (2, 200, 3, 64, 25),          # the same with an odd number of 64-wide heads
+    (8, 256, 6, 64, 32),          # 128 x 128 tiles
     (8, 2048, 16, 128, 256),      # 128 x 256 tiles
     (1, 4096, 32, 128, 512),      # with 2048 added to d_model: 256 x 256 tiles
 ])
