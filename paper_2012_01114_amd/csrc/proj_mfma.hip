@@ -333,14 +333,15 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
 //            free half a slice after its first read.
 // Every request has at least one slice period to land.  WR x WC wavefronts share a BX x BW tile.
 // The 128 x 256 tile has smaller rings (two x units, three weight slots: 80 KiB), so that two
-// workgroups share a CU; see slice_pair.
+// workgroups share a CU (slice_pair); TRI are 128 x 128 tiles on rings of 48 KiB, three to a CU
+// (slice_tri).
 // TAIL: d_model is a multiple of 8 only.  In the last slice the 16-byte pieces of a vector past its
 // end, and the k-rows past the last, are fetched from a piece of zeros, through per-lane addresses.
 // ---------------------------------------------------------------------------
 __device__ const u32x4 zero_piece = {0u, 0u, 0u, 0u};
 
-template <int BX, int BW, int WR, int WC, bool TAIL>
-__global__ __launch_bounds__(64 * WR * WC, 2)
+template <int BX, int BW, int WR, int WC, bool TRI, bool TAIL>
+__global__ __launch_bounds__(64 * WR * WC, TRI ? 3 : 2)
 void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
                      const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
                      h16_t* __restrict__ qo, h16_t* __restrict__ ko, h16_t* __restrict__ vto, TileMap tm,
@@ -353,10 +354,10 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     constexpr int NBLK = BX * BW / (1024 * NW);
     constexpr int NX = PAIR ? BX / WC / 32 : 0, NWC = PAIR ? BW / WR / 32 : 0;  // PAIR: the same for both kinds
     constexpr int XU = BX * 128;                 // bytes of one x unit: BX rows x 64 k
-    constexpr int NXU = PAIR ? 2 : 3;
+    constexpr int NXU = PAIR || TRI ? 2 : 3;
     constexpr int WROWB = BW * 2;                // bytes of one k-row of the weight side in a slot
     constexpr int WS = 32 * WROWB;               // bytes of one weight slot: 32 k-rows
-    constexpr int NWS = PAIR ? 3 : 4;
+    constexpr int NWS = TRI ? 2 : PAIR ? 3 : 4;
     constexpr int W_BASE = NXU * XU;
     constexpr int XPW = (BX / 8) / NW;           // x pieces (1 KiB: 8 rows x 128 bytes) per wavefront and slice
     constexpr int WPW = (WS / 1024) / NW;        // weight pieces (1 KiB) per wavefront and half slice
@@ -642,6 +643,30 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         sa = sc;
     };
 
+    // TRI, 128 x 128 tiles with three workgroups per CU: two x units and two weight half slices (48 KiB).  Behind
+    // the first barrier half slice 2j's slot takes 2j + 2 (step 2), behind the second that of 2j + 1 takes
+    // 2j + 3 and slice j's unit takes x of slice j + 2 (steps 4 and 1).  The second barrier wants everything in,
+    // the first all but x of the next slice; the other two workgroups fill the waits.
+    auto slice_tri = [&](auto is_v_, auto var_, int j, int& ux, int&) {
+        constexpr int VAR = decltype(var_)::value;
+        constexpr bool E1 = VAR >= 1, E2 = VAR == 2;
+        const int k1 = (j + 1) * 64, k2 = (j + 2) * 64;
+        const std::integral_constant<int, E1 ? 2 : 0> two{};
+        const std::integral_constant<int, E2 ? 4 : E1 ? 2 : 0> last{};
+        kstep(is_v_, af[0], bf[0], af[1], bf[1], ux, 0, 0, 1, two, [&](int i) { req_x(2 + i, k1, ux ^ 1); });
+        __builtin_amdgcn_s_waitcnt(0x0070 | (E1 ? 4 : 0));
+        __builtin_amdgcn_s_barrier();
+        kstep(is_v_, af[1], bf[1], af[0], bf[0], ux, 1, 1, 0, two, [&](int i) { req_w(i, k1, 0, 0); });
+        kstep(is_v_, af[0], bf[0], af[1], bf[1], ux, 1, 1, 1, no_req, [&](int) {});
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __builtin_amdgcn_s_barrier();
+        kstep(is_v_, af[1], bf[1], af[0], bf[0], ux ^ 1, 0, 0, 0, last, [&](int i) {
+            if (i < 2) req_w(i, k1, 1, 1);
+            else req_x(i - 2, k2, ux);
+        });
+        ux ^= 1;
+    };
+
     // Prologue: slice 0 whole, and of slice 1 what steps 2-4 of a slice before slice 0 would
     // have sent (its last weight piece follows in step 1 of slice 0).
     const int ns = TAIL ? (D + 63) / 64 : D / 64;
@@ -651,7 +676,15 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     for (int u = 0; u < XPW; ++u) req_x(u, 0, 0);
 #pragma unroll
     for (int u = 0; u < WPW; ++u) req_w(u, 0, 1, 1);
-    if constexpr (PAIR) {  // and what step 4 of a slice before slice 0 would have sent
+    if constexpr (TRI) {
+        if (ns > 1) {
+            req_x(0, 64, 1);
+            req_x(1, 64, 1);
+            __builtin_amdgcn_s_waitcnt(0x0F70 | 4);
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0F70);
+        }
+    } else if constexpr (PAIR) {  // and what step 4 of a slice before slice 0 would have sent
         if (ns > 1) {
             req_w(0, 64, 0, 2);
             req_w(1, 64, 0, 2);
@@ -679,7 +712,8 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
         int ux = 0, wa = 0;
         int j = 0;
         auto one = [&](auto var_) {
-            if constexpr (PAIR) slice_pair(is_v_, var_, j, ux, wa);
+            if constexpr (TRI) slice_tri(is_v_, var_, j, ux, wa);
+            else if constexpr (PAIR) slice_pair(is_v_, var_, j, ux, wa);
             else slice(is_v_, var_, j, ux, wa);
         };
 #pragma nounroll
@@ -937,7 +971,7 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
 // half precision, so that the attention kernels get base-2 scores straight out of the MFMA.
 inline float q_prescale(const Problem& pb) { return pb.scale * 1.4426950408889634f; }
 
-template <int BX, int BW, int WR, int WC>
+template <int BX, int BW, int WR, int WC, bool TRI = false>
 hipError_t launch_dma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk, const bf16_t* Wv,
                       h16_t* q, h16_t* k, h16_t* vt, hipStream_t s)
 {
@@ -946,10 +980,10 @@ hipError_t launch_dma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, cons
     const TileMap tm = tile_map(pb, BX, BW, pb.no_q ? 2 : 3, lens != nullptr);
     const int grid = ((tm.n_tiles + 7) / 8) * 8;
     if (pb.D % 64 == 0)
-        hipLaunchKernelGGL((proj_dma_kernel<BX, BW, WR, WC, false>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
+        hipLaunchKernelGGL((proj_dma_kernel<BX, BW, WR, WC, TRI, false>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
                            pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
     else
-        hipLaunchKernelGGL((proj_dma_kernel<BX, BW, WR, WC, true>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
+        hipLaunchKernelGGL((proj_dma_kernel<BX, BW, WR, WC, TRI, true>), dim3(grid), dim3(64 * WR * WC), 0, s, pb.B, pb.N, pb.Npad,
                            pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
     return hipGetLastError();
 }
@@ -1028,6 +1062,11 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
         if (HD % 128 != 0 || t128 <= 100) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 512 && pb.D >= 2048) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 320) return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        // More 128 x 128 tiles than two per CU: three workgroups of them on a CU.  Measured (us, two / three per CU):
+        // 504 tiles 20.2 / 20.5, 576 24.8 / 23.0, 648 (d_model 1024) 32.1 / 28.3, 1152 37.8 / 37.5, 7680 (d_model
+        // 640) 214 / 203; 384 (d_model 4096) 57 / 63.
+        const long live = (long)pb.B * ((pb.N + 127) / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
+        if (live > 512) return launch_dma<128, 128, 2, 2, true>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         return launch_dma<128, 128, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
     }
     if (HD % 128 == 0) return launch_bt<128>(pb, X, Wt, q, k, vt, s);

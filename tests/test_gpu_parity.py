@@ -195,7 +195,8 @@ def test_row_tiles_with_the_heads_in_turn(shape):
     # B, n, H, d, p
     (2, 200, 2, 64, 25),          # 64 x 64 tiles
     (2, 200, 3, 64, 25),          # the same with an odd number of 64-wide heads
-    (8, 256, 6, 64, 32),          # 128 x 128 tiles
+    (8, 256, 6, 64, 32),          # 128 x 128 tiles, two workgroups per CU
+    (30, 256, 6, 64, 32),         # 540 of them: three workgroups per CU
     (8, 2048, 16, 128, 256),      # 128 x 256 tiles
     (1, 4096, 32, 128, 512),      # with 2048 added to d_model: 256 x 256 tiles
 ])
