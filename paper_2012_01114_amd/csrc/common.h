@@ -100,6 +100,9 @@ hipError_t launch_attn_float(const Problem& pb, const float* q, const float* k, 
 size_t sym_float_score_floats(const Problem& pb);
 hipError_t launch_sym_float(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s);
 
+bool launch_proj_small_float(const Problem& pb, const bf16_t* X, const bf16_t* const* W, float* const* out, int count,
+                             hipStream_t s);
+
 // ---- matrix-core path (bf16 storage, d_k 64 or 128, FULL and CAUSAL) --------
 // The projection contracts bf16 operands; q, k, v leave it in half precision (fp32 accumulators
 // rounded once to an 11-bit significand instead of bfloat16's 8: with bfloat16 there, the roundings

@@ -817,13 +817,17 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
 // Stores go out from the accumulators, eight bytes per lane: four instructions per wavefront.
 // ---------------------------------------------------------------------------
 constexpr int SMALL_STAGES = 5;
-template <bool TAIL>
+// FLOAT_OUT (the float path's bfloat16 storage): the product is written as floats, all three matrices
+// as [vector][d] rows of their heads, d a multiple of 4; the vectors of all batch items are one run of
+// rows (Bsz 1, N of them), `items` divides by an item's.
+template <bool TAIL, bool FLOAT_OUT>
 __global__ __launch_bounds__(256, 2)
 void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
                        const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
-                       h16_t* __restrict__ qo, h16_t* __restrict__ ko, h16_t* __restrict__ vto, TileMap tm,
+                       void* __restrict__ qo, void* __restrict__ ko, void* __restrict__ vto, TileMap tm,
                        float qscale, const int* __restrict__ lens, bool skip_q_rows, bool no_q,
-                       const int* __restrict__ row0, unsigned long long* __restrict__ counters)
+                       const int* __restrict__ row0, unsigned long long* __restrict__ counters, FastDiv items,
+                       FastDiv columns)
 {
     constexpr int XB = 64 * 128, STAGE = 2 * XB;  // x: 64 rows x 64 k; W: 64 k-rows x 64 columns
     __shared__ __attribute__((aligned(1024))) unsigned char lds[SMALL_STAGES * STAGE];
@@ -934,8 +938,23 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
             stage = stage == SMALL_STAGES - 1 ? 0 : stage + 1;
         }
     };
-    if (which == 2) all_slices(std::true_type{});
+    if (!FLOAT_OUT && which == 2) all_slices(std::true_type{});
     else all_slices(std::false_type{});
+
+    if constexpr (FLOAT_OUT) {
+        const int gr = i0 + xr + ln;
+        if (gr < N) {
+            const int item = (int)divide((unsigned)gr, items), i = gr - item * (int)items.d;
+            float* o = (float*)(which == 0 ? qo : (which == 1 ? ko : vto));
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const int cc = c0 + wcol + 8 * r4 + 4 * g, h = (int)divide((unsigned)cc, columns), l = cc - h * d;
+                *(f32x4*)(o + (((size_t)item * H + h) * items.d + i) * d + l) =
+                    f32x4{acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]};
+            }
+        }
+        return;
+    }
 
     const int dsh = d == 128 ? 7 : 6;  // d is 64 or 128 on this path
     if (which != 2) {
@@ -946,7 +965,7 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
 #pragma unroll
             for (int r4 = 0; r4 < 4; ++r4) {
                 const int cc = c0 + wcol + 8 * r4 + 4 * g, h = cc >> dsh, l = cc & (d - 1);
-                *(u32x2*)((which ? ko : qo) + (((size_t)bb * H + h) * Npad + i) * d + l) =
+                *(u32x2*)((h16_t*)(which ? ko : qo) + (((size_t)bb * H + h) * Npad + i) * d + l) =
                     u32x2{pack_f16_sat(acc[4 * r4] * qs, acc[4 * r4 + 1] * qs),
                           pack_f16_sat(acc[4 * r4 + 2] * qs, acc[4 * r4 + 3] * qs)};
             }
@@ -955,7 +974,7 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
         // A side = vectors (four consecutive key slots per register quad), B side = columns; the tile
         // is one 64-key block, in which vectors past n are stored as zeros
         const int cc = c0 + wcol + ln, h = cc >> dsh, l = cc & (d - 1);
-        h16_t* blk = vto + ((((size_t)bb * H + h) * (Npad >> 6) + (i0 >> 6)) * d + l) * 64;
+        h16_t* blk = (h16_t*)vto + ((((size_t)bb * H + h) * (Npad >> 6) + (i0 >> 6)) * d + l) * 64;
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
             const int r64 = xr + 8 * r4 + 4 * g, left = N - (i0 + r64);
@@ -995,12 +1014,13 @@ hipError_t launch_small(const Problem& pb, const bf16_t* X, const bf16_t* Wq, co
     const int* lens = pb.noskip ? nullptr : pb.lens;
     const TileMap tm = tile_map(pb, 64, 64, pb.no_q ? 2 : 3, lens != nullptr);
     const int grid = ((tm.n_tiles + 7) / 8) * 8;
+    const FastDiv none = {1u, 0u, 0u};
     if (pb.D % 64 == 0)
-        hipLaunchKernelGGL(proj_small_kernel<false>, dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
-                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
+        hipLaunchKernelGGL((proj_small_kernel<false, false>), dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
+                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters, none, none);
     else
-        hipLaunchKernelGGL(proj_small_kernel<true>, dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
-                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters);
+        hipLaunchKernelGGL((proj_small_kernel<true, false>), dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
+                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters, none, none);
     return hipGetLastError();
 }
 
@@ -1040,6 +1060,35 @@ bool proj_reads_weights_in_place(const Problem& pb, const bf16_t* Wq, const bf16
     const bool aligned16 = ((reinterpret_cast<uintptr_t>(Wq) | reinterpret_cast<uintptr_t>(Wk) |
                              reinterpret_cast<uintptr_t>(Wv)) & 15) == 0;
     return pb.D % 8 == 0 && aligned16;
+}
+
+// The float path's products of bfloat16 storage, where X and the weights come in whole 16-byte pieces and
+// the columns in whole 64s; false: not such a product.  W[0 .. count-1] -> out.
+bool launch_proj_small_float(const Problem& pb, const bf16_t* X, const bf16_t* const* W, float* const* out, int count,
+                             hipStream_t s)
+{
+    const int HD = pb.H * pb.d;
+    const long M = (long)pb.B * pb.N;
+    uintptr_t bits = reinterpret_cast<uintptr_t>(X);
+    for (int m = 0; m < count; ++m) bits |= reinterpret_cast<uintptr_t>(W[m]);
+    if (pb.D % 8 != 0 || HD % 64 != 0 || pb.d % 4 != 0 || (bits & 15) != 0 || M > 0x7fffffffL - 64) return false;
+    Problem rows = pb;  // all vectors as one item
+    rows.B = 1;
+    rows.N = (int)M;
+    rows.Npad = (int)((M + 63) / 64 * 64);
+    const TileMap tm = tile_map(rows, 64, 64, count, false);
+    const int grid = ((tm.n_tiles + 7) / 8) * 8;
+    const bf16_t* w[3] = {W[0], W[count > 1 ? 1 : 0], W[count > 2 ? 2 : 0]};
+    float* o[3] = {out[0], out[count > 1 ? 1 : 0], out[count > 2 ? 2 : 0]};
+    const FastDiv items = fast_div((unsigned)pb.N), columns = fast_div((unsigned)pb.d);
+#define PROJ_FLOAT(TAIL_)                                                                                                  \
+    hipLaunchKernelGGL((proj_small_kernel<TAIL_, true>), dim3(grid), dim3(256), 0, s, 1, rows.N, rows.Npad, pb.D, pb.H,    \
+                       pb.d, X, w[0], w[1], w[2], o[0], o[1], o[2], tm, 1.f, nullptr, false, false, nullptr, pb.counters, \
+                       items, columns)
+    if (pb.D % 64 == 0) PROJ_FLOAT(false);
+    else PROJ_FLOAT(true);
+#undef PROJ_FLOAT
+    return true;
 }
 
 hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk,

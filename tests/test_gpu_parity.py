@@ -84,6 +84,8 @@ def test_float_path_ragged(shape, scheme, dtype):
     (2, 192, 96, 2, 64, 24),      # keys shared by the wavefronts, whole tiles
     (1, 129, 100, 3, 100, 43),    # rows of d in whole 16-byte pieces, last block partly used
     (1, 80, 16, 1, 256, 5),       # the largest head
+    (3, 70, 72, 4, 48, 7),        # bf16: pieces straight into LDS, last slice of d_model cut, vectors as one run
+    (2, 130, 64, 2, 32, 13),      # the same with whole slices
     (32, 72, 20, 16, 12, 9),      # 1024 row tiles: a wavefront for every 16 rows
     (64, 66, 16, 8, 33, 33),      # the same with unaligned rows
 ])
