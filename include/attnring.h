@@ -75,7 +75,8 @@ typedef enum { ATTN_F32 = 0, ATTN_BF16 = 1 } attn_dtype;
 enum { ATTN_FLAG_NO_SKIP = 1u,
        /* Workgroup shape of the bf16 matrix-core path for d_k = 64, normally 128 query rows
         * (4 wavefronts): WIDE asks for 256 rows (8 wavefronts), NARROW for 128.  d_k = 128
-        * always takes 256 rows.  Results obey the same bars. */
+        * takes 256 rows.  Without either flag (and without FUSE_Q_PROJECTION) small launches take
+        * 32 rows per workgroup, for either d_k.  Results obey the same bars. */
        ATTN_FLAG_WIDE_TILES = 2u,
        ATTN_FLAG_NARROW_TILES = 4u,
        /* With key lengths: the padded vectors are left out as queries too.  A pair (i, j) of
@@ -112,7 +113,7 @@ typedef struct {
     uint64_t tiles_executed;      /* logical tiles the last attn_forward worked on; COUNTED ON THE DEVICE */
     uint64_t pairs_executed;      /* tiles_executed * (n/p)^2 */
     uint64_t phys_tiles_executed; /* score blocks of phys_br x phys_bc pairs the kernels issued; device-counted */
-    int32_t phys_br, phys_bc;
+    int32_t phys_br, phys_bc;     /* 32 x 32 on the matrix-core path, 16 x 16 on the float path */
     uint64_t proj_gemms;          /* 3; q = k = v scheme: 1 on the float path (0 when X is used unprojected),
                                      2 on the matrix-core path (z = x.Wq produced in two layouts) */
 } attn_stats_t;

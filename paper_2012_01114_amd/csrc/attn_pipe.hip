@@ -820,12 +820,13 @@ hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, c
     //   tiles dealt over the CUs of an XCD / heads in turn, heaviest tiles first): batch 8, 12 heads, n 512 21.5 /
     //   17.7 / 17.6, n 1024 33.7 / 28.0 / 28.8; 20 x 15 heads, n 512 (600 pairs) 31.7 / - / 30.4; 480 heads, n 2048
     //   319 / 330 / 335.  Dealing needs the heads to divide over the XCDs.
-    // d_k = 128 (one workgroup per CU): always, heads in turn: batch 8, 8 heads, n 512 35 / 24 / 24, n 1024 50 / 40 /
-    //   39, n 2048 (256 pairs) 91 / 98 / 86; 32 heads, n 8192 498 / 515 / 495.
+    // d_k = 128 (one workgroup per CU): when the pairs would not give every CU two, heads in turn: batch 8, 8 heads,
+    //   n 512 35 / 24 / 24, n 1024 50 / 40 / 39, n 2048 (256 pairs) 91 / 98 / 86; with 512 pairs the times are the
+    //   same (32 heads, n 8192 498 / 515 / 495) and the heads in turn fetch 1.7 times the bytes.
     const long pairs = (long)pb.B * pb.H * ((n_qtiles + 1) / 2);
     int single = 0;
     if (causal && !pb.skip_rows) {
-        if (pb.d == 128) single = 2;
+        if (pb.d == 128) single = pairs < 2L * 256 ? 2 : 0;
         else if (waves == 4 && pairs < 4L * 256) single = (pb.B * pb.H) % 8 == 0 ? 1 : 2;
     }
     const int per_head = (causal && !single) ? (n_qtiles + 1) / 2 : n_qtiles;
