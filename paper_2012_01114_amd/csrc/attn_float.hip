@@ -268,7 +268,7 @@ struct RowTile {
         for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
         if (lane == 0) count_add(pb.counters, flat_block(), total, 0);
     }
-    // The row's last allowed key.
+    // The row's last allowed key; -1: it has none, and its output is zero whatever its weights of zero met (0 * inf).
     __device__ __forceinline__ int last_key(const Problem& pb, int i) const
     {
         if (i >= rlen) return -1;
@@ -340,7 +340,7 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     if constexpr (!STORED) load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);  // rows past the last: not stored
     Row<NDB> row;
     row.clear();
-    const int lim = rt.last_key(pb, i) - 4 * g4;
+    const int last_allowed = rt.last_key(pb, i), lim = last_allowed - 4 * g4;
     // the lane's stored scores of a tile: whole 16-byte pieces of its row (pitch SP)
     const int SP = score_pitch(N);
     const float* srow = STORED ? scores + ((size_t)rt.bh * N + min(i, N - 1)) * SP : nullptr;
@@ -412,9 +412,13 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
         }
     }
     const float L = row.row_sum();
-    const float inv = L > 0.f ? 1.f / L : 0.f;  // a row with no allowed pair is zero
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
     const size_t base = ((size_t)rt.bb * N + i) * ((size_t)pb.H * d) + (size_t)rt.h * d;
-    if (i < N) CL::pieces(row.O, g4, [&](int c, f32x4 y) { store4(out, base, c, d, y * inv, pb.is_bf16, out_whole); });
+    if (i < N)
+        CL::pieces(row.O, g4, [&](int c, f32x4 y) {
+            store4(out, base, c, d, last_allowed < 0 ? zero : y * inv, pb.is_bf16, out_whole);
+        });
     if (!STORED && lane == 0) count_add(pb.counters, flat_block(), 0, cnt_phys);
 }
 
@@ -566,14 +570,17 @@ void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
         mw[w] = exp_neg(mw[w] - ref);
         L += mw[w] * st_ml[2 * (16 * w + r) + 1];
     }
-    const float inv = L > 0.f ? 1.f / L : 0.f;  // a row with no allowed pair is zero
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    const bool none = rt.last_key(pb, rt.i0 + r) < 0;
     const size_t base = ((size_t)rt.bb * N + rt.i0 + r) * ((size_t)pb.H * d) + (size_t)rt.h * d;
     if (rt.i0 + r < N)
         for (int c = tid & 15; c < DP / 4; c += 16) {
             f32x4 y = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < 4; ++w) y += mw[w] * *(const f32x4*)(st_o + (16 * w + r) * PITCH + 4 * c);
-            store4(out, base, 4 * c, d, y * inv, pb.is_bf16, out_whole);
+            y *= inv;
+            if (none) y = f32x4{0.f, 0.f, 0.f, 0.f};
+            store4(out, base, 4 * c, d, y, pb.is_bf16, out_whole);
         }
 }
 

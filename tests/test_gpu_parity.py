@@ -107,6 +107,44 @@ def test_float_path_tile_edges(shape, scheme, dtype):
     _run_and_compare(w, scheme, 0.0, lens=lens)
 
 
+# ---- float path, a vector that is not finite: rows that have no pair with it stay what they are -----------
+NOT_FINITE_SHAPES = [
+    # B, n, D, H, d, p
+    (2, 100, 24, 2, 20, 25),      # keys shared by the wavefronts of a row tile
+    (2, 48, 32, 3, 80, 12),       # a single key tile: a wavefront for every 16 rows
+    (64, 66, 16, 8, 33, 33),      # the same, two key tiles, unaligned rows
+]
+
+
+def _run_with_a_bad_vector(w, scheme, bad_row, lens=None, flags=0):
+    """The output with vector `bad_row` of every item infinite, and the checker's for the finite inputs."""
+    stored, f64 = inputs.make_inputs(w)
+    stored["X"][:, bad_row] = float("inf")
+    stored["lens"] = lens
+    run = hp.GpuRun(w, stored, flags=flags)
+    try:
+        got, _ = run.forward(scheme)
+    finally:
+        run.close()
+    skip = bool(flags & ar.ATTN_FLAG_SKIP_PADDED_ROWS)
+    return got, hp.oracle_forward(w, f64, scheme, 0.0, lens=lens, skip_padded_rows=skip)
+
+
+@pytest.mark.parametrize("shape", NOT_FINITE_SHAPES)
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("noskip", [0, ar.ATTN_FLAG_NO_SKIP])
+def test_left_out_rows_are_zeros_beside_infinite_keys(shape, scheme, dtype, noskip):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("left_out", B, n, D, H, d, p, dtype, scheme, 5200 + n)
+    lens = np.full(B, 41, dtype=np.int32)     # rows 41 .. 47 share a 16-row group with rows that are there
+    lens[-1] = 0
+    got, _ = _run_with_a_bad_vector(w, scheme, 35, lens, ar.ATTN_FLAG_SKIP_PADDED_ROWS | noskip)
+    for b, L in enumerate(lens):
+        assert np.all(got[b, L:] == 0.0)
+    assert not np.isfinite(got[:-1, 35:41]).any()   # rows that do attend the infinite key
+
+
 def test_symmetric_without_projection():
     w = hp.custom_workload("symx", 2, 20, 24, 2, 12, 5, "f32", SYM, 77)
     _, stats = _run_and_compare(w, SYM, 0.2, sym_no_proj=True)
