@@ -164,6 +164,13 @@ struct Cols {
         }
         if constexpr (N1 != 0) v[NDB - 1] = l1(C1 + ln);
     }
+    // column of register r of O[db]
+    static __device__ __forceinline__ int column(int db, int r, int g4)
+    {
+        if (db < 4 * N4) return 64 * (db / 4) + 16 * g4 + 4 * r + db % 4;
+        if (db < 4 * N4 + 2 * N2) return C2 + 8 * g4 + 2 * r + (db - 4 * N4);
+        return C1 + 4 * g4 + r;
+    }
     // f(column, four outputs) for the lane's pieces of its row
     template <class F>
     static __device__ __forceinline__ void pieces(const f32x4 (&O)[NDB], int g4, F&& f)
@@ -232,6 +239,53 @@ struct Row {
     }
 };
 
+// A weight of zero is no protection from a value that is not finite (0 * inf), so the 16-key block that
+// the diagonal cuts, if it holds such a value, stays out of the MFMAs: its weights are put aside and, behind
+// the walk, each row adds its allowed keys only, one by one.
+template <int NDB>
+struct CutBlock {
+    f32x4 w;
+    float m;   // the reference of the weights
+    int key0;  // first key of the block; -1: nothing was put aside
+    __device__ __forceinline__ void clear() { key0 = -1; }
+    // `poison` turns into NaN if a value is an infinity or NaN
+    static __device__ __forceinline__ float test(float poison, const float (&v)[NDB])
+    {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) poison = fmaf(v[db], 0.f, poison);
+        return poison;
+    }
+    // i0: the wavefront's first row; a block above the diagonal (debug mode) has nothing to add
+    __device__ __forceinline__ void put_aside(const f32x4& weights, float ref, int key, int i0)
+    {
+        if (key > i0) return;
+        w = weights;
+        m = ref;
+        key0 = key;
+    }
+    __device__ __forceinline__ void add(Row<NDB>& row, const float* __restrict__ vh, int d, int last_allowed, int ln, int g4) const
+    {
+        if (key0 < 0) return;
+        const float scale = exp_neg(m - (row.m > -INFINITY ? row.m : 0.f));
+#pragma nounroll
+        for (int key = 0; key < 16; ++key) {
+            const int r = key & 3;
+            const float p = scale * __shfl(r == 0 ? w[0] : r == 1 ? w[1] : r == 2 ? w[2] : w[3], 16 * (key >> 2) + ln, 64);
+            if (key0 + key > last_allowed) continue;
+            const float* vrow = vh + (size_t)(key0 + key) * d;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int c = Cols<NDB>::column(db, e, g4);
+                    row.O[db][e] = fmaf(p, vrow[c < d ? c : 0], row.O[db][e]);
+                }
+                __builtin_amdgcn_sched_barrier(0);  // rare: registers count, not time
+            }
+        }
+    }
+};
+
 // What both kernels need to know about a row tile.
 struct RowTile {
     int bh, bb, h, i0, row_end, len, rlen;
@@ -295,9 +349,14 @@ __device__ __forceinline__ void score_blocks(f32x4* S, const float* kt, const f3
     }
 }
 
+// CAUSAL, in both kernels: the masked scheme, or, of the large heads whose rows are no whole pieces, either
+// scheme (d = 190, FULL: 112 us, 140 with a kernel of its own, at the same registers).
+template <int NDB, bool WHOLE>
+constexpr bool EITHER = !WHOLE && NDB >= 12;
+
 // STORED (q = k = v scheme), in both kernels: the scores come from `scores`, which
 // sym_scores_float_kernel has filled, instead of q and k, and have been counted there.
-template <int NDB, bool WHOLE, bool STORED>
+template <int NDB, bool WHOLE, bool STORED, bool CAUSAL>
 __global__ __launch_bounds__(256, NDB <= 4 ? 3 : NDB <= 8 ? 2 : 1)
 void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, const float* __restrict__ k,
                       const float* __restrict__ v, const float* __restrict__ scores, void* __restrict__ out,
@@ -314,7 +373,7 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     const RowTile rt(pb, KT, n_rowtiles);
     if (!rt.there) return;
     const int N = pb.N, d = pb.d, len = rt.len;
-    const bool causal = pb.scheme == SCHEME_CAUSAL;
+    const bool causal = CAUSAL && (!EITHER<NDB, WHOLE> || pb.scheme == SCHEME_CAUSAL);
     const size_t head = (size_t)rt.bh * N * d;
     const int i0w = rt.i0 + 16 * wave, i = i0w + ln;  // rows of the wavefront, the lane's row
     const int wave_end = min(rt.row_end, i0w + 16);
@@ -340,6 +399,8 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     if constexpr (!STORED) load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);  // rows past the last: not stored
     Row<NDB> row;
     row.clear();
+    CutBlock<NDB> cut;
+    cut.clear();
     const int last_allowed = rt.last_key(pb, i), lim = last_allowed - 4 * g4;
     // the lane's stored scores of a tile: whole 16-byte pieces of its row (pitch SP)
     const int SP = score_pitch(N);
@@ -359,8 +420,14 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
         }
         tv.fetch(v + head, J * KT, len, d, tid);
     };
-    if (nT > 0) fetch(0);
-    for (int t = 0; t < nT; ++t) {
+    // The own tile, the only one with blocks that the diagonal cuts (values past the row tile's last row are
+    // staged as zeros), is met first; the other tiles then go without a look at their values, which keeps
+    // branches out of the loop (8 x 1024, 12 heads of 64: 142 -> 138 us).  At the large head sizes two
+    // copies of the body are not worth it.
+    constexpr bool FIRST_ALONE = CAUSAL && NDB <= 8;
+    const int v_end = causal ? min(len, rt.row_end) : len;
+    auto walk_tile = [&](int t, auto cut_) __attribute__((always_inline)) {
+        constexpr bool CUT = decltype(cut_)::value;
         const int J = tile_of_step(t);
         f32x4 S[NB];
         __syncthreads();  // everyone is done with the tile before
@@ -370,7 +437,7 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
         } else {
             tk.stage(ks, J * KT, len, d, tid);
         }
-        tv.stage(vs, J * KT, len, d, tid);
+        tv.stage(vs, J * KT, v_end, d, tid);
         __syncthreads();
         if (t + 1 < nT) fetch(t + 1);
         // 16-key blocks of the tile that hold a pair this wavefront needs: the first nk
@@ -380,7 +447,7 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
             if (causal) keys = min(keys, wave_end - J * KT);
             nk = pb.noskip ? NB : max(0, min(NB, (keys + 15) >> 4));
         }
-        if (nk == 0) continue;
+        if (nk == 0) return;
         if constexpr (!STORED) {
             cnt_phys += (unsigned)nk;
             if (nk == NB) {
@@ -400,17 +467,39 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
             if (b >= nk) break;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            auto read = [&](float (&vf)[NDB], int r) {
                 const float* vrow = vs + (16 * b + 4 * g4 + r) * PITCH;
-                float vf[NDB];
                 CL::read(vf, ln, [&](int c) { return *(const f32x4*)(vrow + c); },
                          [&](int c) { return *(const f32x2*)(vrow + c); }, [&](int c) { return vrow[c]; });
+            };
+            if (CUT && causal && J * KT + 16 * b + 15 > i0w) {
+                float poison = 0.f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float vf[NDB];
+                    read(vf, r);
+                    poison = CutBlock<NDB>::test(poison, vf);
+                }
+                if (__builtin_amdgcn_ballot_w64(poison != poison) != 0ull) {
+                    cut.put_aside(S[b], row.m, J * KT + 16 * b, i0w);
+                    continue;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float vf[NDB];
+                read(vf, r);
 #pragma unroll
                 for (int db = 0; db < NDB; ++db) row.O[db] = mfma16f(vf[db], S[b][r], row.O[db]);
             }
         }
+    };
+    if (nT > 0) {
+        fetch(0);
+        if constexpr (FIRST_ALONE) walk_tile(0, std::true_type{});
+        for (int t = FIRST_ALONE ? 1 : 0; t < nT; ++t) walk_tile(t, std::integral_constant<bool, CAUSAL && !FIRST_ALONE>{});
     }
+    if constexpr (!STORED) cut.add(row, v + head, d, last_allowed, ln, g4);
     const float L = row.row_sum();
     const float inv = L > 0.f ? 1.f / L : 0.f;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -423,7 +512,7 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
 }
 
 // EXACT: d is 16 NDB, no column is dropped.
-template <int NDB, bool WHOLE, bool EXACT, bool STORED>
+template <int NDB, bool WHOLE, bool EXACT, bool STORED, bool CAUSAL>
 __global__ __launch_bounds__(256, NDB <= 4 ? 3 : NDB <= 6 ? 2 : 1)  // three wavefronts per SIMD at d = 64 rather than two
 void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, const float* __restrict__ k,
                       const float* __restrict__ v, const float* __restrict__ scores, void* __restrict__ out,
@@ -442,11 +531,12 @@ void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     const size_t head = (size_t)rt.bh * N * d;
     const float *kh = k + head, *vh = v + head;
     const int i = rt.i0 + ln;  // the lane's row
+    const bool causal = CAUSAL && (!EITHER<NDB, WHOLE> || pb.scheme == SCHEME_CAUSAL);
     // blocks 0 .. nb-1 hold a needed pair; in debug mode the others follow and change nothing
     int nb = 0;
     if (rt.row_end > rt.i0) {
         nb = (len + 15) / 16;
-        if (pb.scheme == SCHEME_CAUSAL) nb = min(nb, (rt.row_end - 1) / 16 + 1);
+        if (causal) nb = min(nb, (rt.row_end - 1) / 16 + 1);
         if (pb.noskip) nb = (N + 15) / 16;
     }
     f32x4 qf[NDB];
@@ -482,9 +572,16 @@ void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     };
     Row<NDB> row;
     row.clear();
+    CutBlock<NDB> cut;
+    cut.clear();
     unsigned cnt_phys = 0;
-    const int lim = rt.last_key(pb, i) - 4 * g4;
-    auto step = [&](Block& x, int b) {
+    const int last_allowed = rt.last_key(pb, i), lim = last_allowed - 4 * g4;
+    // Blocks below plain_end hold allowed keys only; the others, cut by the diagonal or the length, follow:
+    // one at most, the last of the walk, but for the debug mode.  They have code of their own, which keeps
+    // branches out of the loop (4 x 600, 8 heads of 80, masked: 38.4 -> 36 us).
+    const int plain_end = (causal ? min(len, rt.i0) : len) >> 4;
+    // below_: the block ends below the tile's first row; inside_: below the length.
+    auto step = [&](Block& x, int b, auto below_, auto inside_) {
         f32x4 S[1] = {{0.f, 0.f, 0.f, 0.f}};
         if constexpr (STORED) {
             S[0] = x.k[0];
@@ -504,7 +601,16 @@ void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
             S[0] = (S[0] + s2) * pb.scale;
         }
         row.weights(S, lim - 16 * b);
-        if (16 * b + 16 <= len) {
+        if (CAUSAL && causal && !below_) {
+            float poison = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) poison = CutBlock<NDB>::test(poison, x.v[r]);
+            if (__builtin_amdgcn_ballot_w64(poison != poison) != 0ull) {
+                cut.put_aside(S[0], row.m, 16 * b, rt.i0);
+                return;
+            }
+        }
+        if (inside_) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -518,36 +624,69 @@ void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
             }
         }
     };
+    auto plain = [&](Block& x, int b) __attribute__((always_inline)) { step(x, b, std::true_type{}, std::true_type{}); };
+    auto edge = [&](Block& x, int b) __attribute__((always_inline)) { step(x, b, std::false_type{}, std::false_type{}); };
     if (wave < nb) {
         int b = wave;
         if constexpr (NDB <= 8) {
             Block x0, x1;
             load(x0, b);
-            while (true) {
-                // the requests stay in front: left alone, the compiler sinks each to where its wait stands
-                load(x1, b + 4);
-                __builtin_amdgcn_sched_barrier(0);
-                step(x0, b);
-                __builtin_amdgcn_sched_barrier(0);
-                b += 4;
-                if (b >= nb) break;
-                load(x0, b + 4);
-                __builtin_amdgcn_sched_barrier(0);
-                step(x1, b);
-                __builtin_amdgcn_sched_barrier(0);
-                b += 4;
-                if (b >= nb) break;
+            if constexpr (WHOLE || NDB <= 5) {
+                while (true) {
+                    if (b >= plain_end) {
+                        if (b < nb) edge(x0, b);
+                        break;
+                    }
+                    // the requests stay in front: left alone, the compiler sinks each to where its wait stands
+                    load(x1, b + 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                    plain(x0, b);
+                    __builtin_amdgcn_sched_barrier(0);
+                    b += 4;
+                    if (b >= plain_end) {
+                        if (b < nb) edge(x1, b);
+                        break;
+                    }
+                    load(x0, b + 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                    plain(x1, b);
+                    __builtin_amdgcn_sched_barrier(0);
+                    b += 4;
+                }
+                for (b += 4; b < nb; b += 4) {
+                    load(x0, b);
+                    edge(x0, b);
+                }
+            } else {  // rows in no whole pieces: one body with branches is the smaller one (d = 113: 57 us, 81 with two)
+                while (true) {
+                    load(x1, b + 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                    step(x0, b, 16 * b + 16 <= rt.i0, 16 * b + 16 <= len);
+                    __builtin_amdgcn_sched_barrier(0);
+                    b += 4;
+                    if (b >= nb) break;
+                    load(x0, b + 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                    step(x1, b, 16 * b + 16 <= rt.i0, 16 * b + 16 <= len);
+                    __builtin_amdgcn_sched_barrier(0);
+                    b += 4;
+                    if (b >= nb) break;
+                }
             }
         } else {  // two blocks would not fit the registers
             for (; b < nb; b += 4) {
                 Block x;
                 load(x, b);
-                step(x, b);
+                if constexpr (!WHOLE) step(x, b, 16 * b + 16 <= rt.i0, 16 * b + 16 <= len);
+                else if (b < plain_end) plain(x, b);
+                else edge(x, b);
             }
         }
     }
     if (!STORED && wave == 0) rt.count(pb, cc, lane);
     if (!STORED && lane == 0) count_add(pb.counters, flat_block(), 0, cnt_phys);
+
+    if constexpr (!STORED) cut.add(row, vh, d, last_allowed, ln, g4);
 
     // partial state of wavefront w, row r: m, l, then O
     const float L0 = row.row_sum();
@@ -679,12 +818,13 @@ void launch_rows(const Problem& pb, const float* q, const float* k, const float*
     const bool keys = pb.N > KT && heads * ((pb.N + 63) / 64) < 2L * 256;
     const int n_rowtiles = keys ? (pb.N + 15) / 16 : (pb.N + 63) / 64;
     const dim3 grid = flat_grid((size_t)heads * n_rowtiles);
-    if (keys)
-        hipLaunchKernelGGL(pb.d == 16 * NDB ? (attn_keys_kernel<NDB, WHOLE, WHOLE, STORED>) : (attn_keys_kernel<NDB, WHOLE, false, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
-                           out, n_rowtiles, out_whole);
-    else
-        hipLaunchKernelGGL((attn_rows_kernel<NDB, WHOLE, STORED>), grid, dim3(256), 0, s, pb, cc, q, k, v, scores,
-                           out, n_rowtiles, out_whole);
+    auto kernel = [&](auto causal) {
+        constexpr bool C = decltype(causal)::value;
+        if (!keys) return attn_rows_kernel<NDB, WHOLE, STORED, C>;
+        return pb.d == 16 * NDB ? attn_keys_kernel<NDB, WHOLE, WHOLE, STORED, C> : attn_keys_kernel<NDB, WHOLE, false, STORED, C>;
+    };
+    auto* const f = !STORED && (EITHER<NDB, WHOLE> || pb.scheme == SCHEME_CAUSAL) ? kernel(std::integral_constant<bool, !STORED>{}) : kernel(std::false_type{});
+    hipLaunchKernelGGL(f, grid, dim3(256), 0, s, pb, cc, q, k, v, scores, out, n_rowtiles, out_whole);
 }
 
 template <int NDB, bool WHOLE>

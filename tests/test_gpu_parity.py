@@ -145,6 +145,56 @@ def test_left_out_rows_are_zeros_beside_infinite_keys(shape, scheme, dtype, nosk
     assert not np.isfinite(got[:-1, 35:41]).any()   # rows that do attend the infinite key
 
 
+@pytest.mark.parametrize("shape", NOT_FINITE_SHAPES + [
+    (1, 100, 16, 1, 17, 100),     # one vector per partition, one column past a block
+    (1, 90, 40, 2, 100, 90),      # the lane's columns in a group of 64 and one of 32 and 16
+    (1, 64, 24, 2, 192, 64),      # the larger heads, both kernels
+    (1, 70, 24, 1, 256, 70),
+])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("bad_row", [21, 32, 47])
+def test_masked_infinite_vectors_reach_no_earlier_row(shape, dtype, bad_row):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("later_inf", B, n, D, H, d, p, dtype, CAUSAL, 5300 + n)
+    outs = []
+    for noskip in (0, ar.ATTN_FLAG_NO_SKIP):
+        got, ref = _run_with_a_bad_vector(w, CAUSAL, bad_row, None, noskip)
+        hp.tol_check(got[:, :bad_row], ref[:, :bad_row], dtype)
+        assert not np.isfinite(got[:, bad_row:]).any()      # every later row has a pair with it
+        outs.append(got)
+    # the block that is cut by the diagonal with a value that is not finite, and yet allowed for some rows:
+    # the same bits without skipping
+    assert np.array_equal(outs[0], outs[1], equal_nan=True)
+
+
+@pytest.mark.parametrize("shape", NOT_FINITE_SHAPES + [(1, 100, 16, 1, 17, 100)])
+def test_an_infinite_value_of_one_column_stays_in_it(shape):
+    """x with one component of its own, which only Wv takes, into column 0 of every head: v_j[0] infinite for one j,
+    all else finite.  Rows from j on have that infinity in column 0, everything else is the checker's."""
+    B, n, D, H, d, p = shape
+    j = 21
+    w = hp.custom_workload("one_inf", B, n, D, H, d, p, "f32", CAUSAL, 5400 + n)
+    stored, f64 = inputs.make_inputs(w)
+    for k in ("Wq", "Wk", "Wv"):
+        stored[k][0] = 0.0
+        stored[k][0, 0::d] = 1e30 if k == "Wv" else 0.0
+        f64[k][0] = 0.0
+    stored["X"][:, :, 0] = 0.0
+    stored["X"][:, j, 0] = 1e30               # 1e30 * 1e30 is an infinity in float, 1e30 * 0 is 0
+    stored["lens"] = None
+    run = hp.GpuRun(w, stored)
+    try:
+        got, _ = run.forward(CAUSAL)
+    finally:
+        run.close()
+    first = np.arange(H) * d
+    assert np.all(got[:, j:, first] == np.inf)
+    got[:, j:, first] = 0.0
+    ref = hp.oracle_forward(w, f64, CAUSAL, 0.0)
+    ref[:, j:, first] = 0.0
+    hp.tol_check(got, ref, "f32")
+
+
 def test_symmetric_without_projection():
     w = hp.custom_workload("symx", 2, 20, 24, 2, 12, 5, "f32", SYM, 77)
     _, stats = _run_and_compare(w, SYM, 0.2, sym_no_proj=True)
