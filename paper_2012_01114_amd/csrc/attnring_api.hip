@@ -431,8 +431,6 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
     } else {
         attn_status st = ensure_generic_workspace(ctx);
         if (st != ATTN_OK) return st;
-        MARK(1);
-        prepared = true;
         if (scheme == ATTN_SCHEME_SYMMETRIC) {
             const size_t bytes = (size_t)cf.batch * cf.n_heads * cf.n * cf.n * sizeof(float);
             if (bytes > MAX_SCORE_BYTES)

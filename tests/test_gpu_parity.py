@@ -436,6 +436,29 @@ def test_encoder_and_causal_full(name):
         assert stats["tiles_executed"] == 96 * 8256
 
 
+@pytest.mark.parametrize("dtype,scheme,unaligned", [("f32", FULL, False), ("f32", SYM, False), ("bf16", CAUSAL, False),
+                                                    ("bf16", CAUSAL, True)])
+def test_profile_reports_a_prepare_kernel_only_where_there_is_one(dtype, scheme, unaligned):
+    """Kernels ahead of the projection: the weight re-layout for unaligned weights, none elsewhere."""
+    import torch
+    w = hp.custom_workload("profile", 2, 96, 64, 1, 64 if dtype == "bf16" else 48, 12, dtype, scheme, 61)
+    stored, _ = inputs.make_inputs(w)
+    run = hp.GpuRun(w, stored)
+    try:
+        if unaligned:
+            for m in range(3):
+                room = torch.empty(run.W[m].numel() + 1, dtype=run.W[m].dtype, device=run.X.device)
+                run.W[m] = room[1:].view(run.W[m].shape).copy_(run.W[m])
+        ar.attn_profile(run.ctx, True)
+        for _ in range(3):
+            run.forward(scheme)
+        prof = ar.attn_profile_read(run.ctx)
+    finally:
+        run.close()
+    assert prof["calls"] == 3 and prof["ms_projection"] > 0.0 and prof["ms_attention"] > 0.0
+    assert (prof["ms_prepare"] > 0.0) == unaligned
+
+
 def test_repeat_calls_are_stable():
     """Back-to-back calls on one context give identical bits and identical counts."""
     w = inputs.WORKLOADS["causal"]
