@@ -48,8 +48,15 @@ inline dim3 flat_grid(size_t count)
 }
 __device__ __forceinline__ unsigned flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
 
-// Row pitch of the stored score matrices: whole 16-byte pieces.
-__host__ __device__ __forceinline__ int score_pitch(int n) { return (n + 3) & ~3; }
+// Row pitch of the stored score matrices: whole 16-byte pieces, unless only rows without a gap stay
+// within the bound.  Pieces then lie at any multiple of 4 bytes and a row's last one reaches into the row
+// behind it (the buffer has room for the last row's): what is read there is masked, nothing is written.
+__host__ __device__ __forceinline__ int score_pitch(const Problem& pb)
+{
+    const int whole = (pb.N + 3) & ~3;
+    return (size_t)pb.B * pb.H * pb.N * whole * sizeof(float) <= MAX_SCORE_BYTES ? whole : pb.N;
+}
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ f32x4 mfma16f(float a, float b, f32x4 c)
 {
@@ -403,7 +410,7 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     cut.clear();
     const int last_allowed = rt.last_key(pb, i), lim = last_allowed - 4 * g4;
     // the lane's stored scores of a tile: whole 16-byte pieces of its row (pitch SP)
-    const int SP = score_pitch(N);
+    const int SP = score_pitch(pb);
     const float* srow = STORED ? scores + ((size_t)rt.bh * N + min(i, N - 1)) * SP : nullptr;
     TL tk, tv;
     f32x4 sreg[NB];
@@ -413,7 +420,7 @@ void attn_rows_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 const int col = J * KT + 16 * b + 4 * g4;
-                sreg[b] = *(const f32x4*)(srow + (col < SP ? col : 0));
+                sreg[b] = *(const f32x4_any*)(srow + (col < SP ? col : 0));
             }
         } else {
             tk.fetch(k + head, J * KT, len, d, tid);
@@ -541,7 +548,7 @@ void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     }
     f32x4 qf[NDB];
     if constexpr (!STORED) load_row<NDB, WHOLE>(qf, q + head + (size_t)min(i, N - 1) * d, g4, d);
-    const int SP = score_pitch(N);
+    const int SP = score_pitch(pb);
     const float* srow = STORED ? scores + ((size_t)rt.bh * N + min(i, N - 1)) * SP : nullptr;
 
     // Operands of a block: the lane's pieces of key row ln, and of V rows 4 g4 .. 4 g4 + 3; what lies
@@ -553,7 +560,7 @@ void attn_keys_kernel(Problem pb, CountCfg cc, const float* __restrict__ q, cons
     auto load = [&](Block& x, int b) {
         if constexpr (STORED) {
             const int col = 16 * b + 4 * g4;
-            x.k[0] = *(const f32x4*)(srow + (col < SP ? col : 0));
+            x.k[0] = *(const f32x4_any*)(srow + (col < SP ? col : 0));
         } else {
             const float* krow = kh + (size_t)min(16 * b + ln, last) * d;
 #pragma unroll
@@ -786,13 +793,19 @@ void sym_scores_float_kernel(Problem pb, CountCfg cc, const float* __restrict__ 
     if (!rows) return;
     f32x4 S[4];
     score_blocks<NDB, 4>(S, ks, qf, ln, g4);  // key rows past the last are zeros and not stored
-    const int SP = score_pitch(N);
+    const int SP = score_pitch(pb);
     float* Sh = scores + (size_t)bh * N * SP;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         S[b] *= pb.scale;
         const int j = B * KT + 16 * b + 4 * g4;  // the lane's four keys
-        if (i < N && j < SP) *(f32x4*)(Sh + (size_t)i * SP + j) = S[b];
+        if (i < N && j + 4 <= SP) {
+            *(f32x4_any*)(Sh + (size_t)i * SP + j) = S[b];
+        } else if (i < N) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (j + r < SP) Sh[(size_t)i * SP + j + r] = S[b][r];
+        }
         if (twice && i < N) {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -868,7 +881,11 @@ hipError_t launch_attn_float(const Problem& pb, const float* q, const float* k, 
     });
 }
 
-size_t sym_float_score_floats(const Problem& pb) { return (size_t)pb.B * pb.H * pb.N * score_pitch(pb.N); }
+size_t sym_float_score_floats(const Problem& pb)
+{
+    const int pitch = score_pitch(pb);
+    return (size_t)pb.B * pb.H * pb.N * pitch + (pitch % 4 ? 3 : 0);
+}
 
 hipError_t launch_sym_float(const Problem& pb, const float* z, float* scores, void* out, hipStream_t s)
 {

@@ -56,7 +56,6 @@ namespace {
 
 thread_local char g_init_err[512] = "";
 constexpr int MAX_PROFILE_CALLS = 4096;
-constexpr size_t MAX_SCORE_BYTES = (size_t)1 << 30;
 
 attn_status fail(attn_ctx* ctx, attn_status st, const char* fmt, const char* detail = "")
 {

@@ -89,6 +89,9 @@ __device__ __forceinline__ unsigned source_row(const int* __restrict__ row0, int
     return (unsigned)(r < 0 ? 0 : r);
 }
 
+// What a workspace of the q = k = v scheme may take.
+constexpr size_t MAX_SCORE_BYTES = (size_t)1 << 30;
+
 // ---- generic float-compute path (any shape, f32 or bf16 storage) ----------
 // q/k/v workspace: float [B][H][N][d].
 // out[m] = X . W[m] for `count` (1..3) weight matrices in one launch.

@@ -201,6 +201,39 @@ def test_symmetric_without_projection():
     assert stats["proj_gemms"] == 0
 
 
+# ---- q = k = v on the float path, n no multiple of 4, close to the bound on the score matrices: rows in whole
+# 16-byte pieces would take more than the 1 GiB
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (12000, 13, 16, 128, 1, 13),  # a single key tile
+    (27391, 70, 8, 2, 4, 10),     # two tiles
+    (1, 9459, 16, 3, 16, 3),      # keys shared by the wavefronts
+])
+def test_symmetric_score_matrices_stay_within_their_bound(shape):
+    import torch
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("score_bound", B, n, D, H, d, p, "f32", SYM, 2700 + n)
+    assert B * H * n * n * 4 <= 1 << 30 < B * H * n * ((n + 3) & ~3) * 4
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = stored["Wk"] = stored["Wv"] = None
+    _run_and_compare(hp.custom_workload("loaded", 1, n, 16, 2, 16, 1, "f32", SYM, 5), SYM)   # the kernels are on the device
+    run = hp.GpuRun(w, stored)
+    try:
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        got, stats = run.forward(SYM)
+        taken = before - torch.cuda.mem_get_info()[0]
+    finally:
+        run.close()
+    assert taken <= (1 << 30) + (4 << 20)      # the device gives memory in pieces of 2 MiB
+    hp.check_counts(stats, hp.oracle_counts(w, SYM))
+    rows = sorted({r for r in (0, 1, n // 2, 63, 64, n - 65, n - 2, n - 1) if 0 <= r < n})
+    for (b, h) in {(0, 0), (B // 2, H // 2), (B - 1, H - 1)}:
+        ref = orc.head_rows(f64["X"], f64["Wq"], f64["Wk"], f64["Wv"], n_heads=H, d_k=d, p=p, scheme=SYM,
+                            scale=hp.default_scale(w, 0.0), b=b, h=h, rows=rows)
+        hp.tol_check(got[b, rows, h * d:(h + 1) * d], ref, "f32")
+
+
 # ---- bf16 MFMA path on small shapes: several tiles and a ragged tail -----------------------------
 @pytest.mark.parametrize("shape", [
     (2, 320, 64, 2, 64, 40),      # 2.5 row tiles
