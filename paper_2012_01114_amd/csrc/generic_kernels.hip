@@ -252,8 +252,8 @@ hipError_t launch_proj_generic(const Problem& pb, const void* X, const void* con
         pa.out[m] = out[m];
     }
     if (pb.is_bf16) {
-        // operands copied straight into LDS where they come in whole pieces: 2400 x 640 -> 1920 24 -> 22 us, 512 x 512 ->
-        // 1536 10.5 -> 9.3, 2048 x 1024 -> 3072 34 -> 29
+        // operands copied straight into LDS where they come in whole pieces: 2400 x 640 -> 1920 22.7 -> 18.4 us, 512 x 512 ->
+        // 1536 9.9 -> 8.8, 2048 x 1024 -> 3072 31.8 -> 26.3
         if (launch_proj_small_float(pb, (const bf16_t*)X, (const bf16_t* const*)W, out, count, s)) return hipGetLastError();
         launch_proj_type(pb, (const bf16_t*)X, pa, count, s);
     }

@@ -810,18 +810,21 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
 // ---------------------------------------------------------------------------
 // The GEMM for products of few tiles, and for columns that do not come in 128s (an odd number of
 // 64-wide heads): 64 x 64 tiles, four wavefronts of 32 x 32, operands copied straight into LDS.
-// What bounds a product that leaves CUs idle is its own chain of slices, so the ring is deep (five
-// 64-deep slices of x and W, 80 KiB: two workgroups share a CU) and a slice is one barrier, eight
-// LDS reads and four MFMAs per wavefront.  Both sides are rows of 128 bytes: x rows with their
-// chunks XOR-ed with bits 1..3 of the row, k-rows of W with 4 * bit 1 of k (transposing reads).
+// What bounds a product that leaves CUs idle is its own chain of slices, each one barrier, eight LDS
+// reads and four MFMAs per wavefront with the next slice on its way; what bounds a large one is how many
+// workgroups a CU holds against those barriers and the stores.  Three 64-deep slices of x and W (48 KiB,
+// three workgroups to a CU) suit both: with five (80 KiB, two to a CU) products of up to 384 tiles take
+// the same, 576 and more 5 to 25 % longer (8192 x 136 -> 2880 40 us where three take 31, 8192 x 960 -> 2880 85
+// and 75).  Both sides are rows of 128 bytes: x rows with their chunks XOR-ed with bits 1..3 of the row,
+// k-rows of W with 4 * bit 1 of k (transposing reads).
 // Stores go out from the accumulators, eight bytes per lane: four instructions per wavefront.
 // ---------------------------------------------------------------------------
-constexpr int SMALL_STAGES = 5;
+constexpr int SMALL_STAGES = 3;
 // FLOAT_OUT (the float path's bfloat16 storage): the product is written as floats, all three matrices
 // as [vector][d] rows of their heads, d a multiple of 4; the vectors of all batch items are one run of
 // rows (Bsz 1, N of them), `items` divides by an item's.
 template <bool TAIL, bool FLOAT_OUT>
-__global__ __launch_bounds__(256, 2)
+__global__ __launch_bounds__(256, 3)
 void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
                        const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
                        void* __restrict__ qo, void* __restrict__ ko, void* __restrict__ vto, TileMap tm,
@@ -906,14 +909,11 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
         int stage = 0;
 #pragma nounroll
         for (int j = 0; j < ns; ++j) {
-            // slices j + 1 .. j + 3 may be in flight, four requests each; loads return in order
-            const int more = ns - 1 - j;
-            if (more >= 3) __builtin_amdgcn_s_waitcnt(0x0070 | 12);
-            else if (more == 2) __builtin_amdgcn_s_waitcnt(0x0070 | 8);
-            else if (more == 1) __builtin_amdgcn_s_waitcnt(0x0070 | 4);
+            // slice j + 1 may be in flight, four requests; loads return in order
+            if (j + 1 < ns) __builtin_amdgcn_s_waitcnt(0x0070 | 4);
             else __builtin_amdgcn_s_waitcnt(0x0070);
             // behind the barrier the slice is in LDS for everyone, and everyone has read the one before
-            // (its reads were waited for ahead of its MFMAs), whose stage takes slice j + 4
+            // (its reads were waited for ahead of its MFMAs), whose stage takes slice j + 2
             __builtin_amdgcn_s_barrier();
             const int free_stage = stage == 0 ? SMALL_STAGES - 1 : stage - 1;
             if (j + SMALL_STAGES - 1 < ns) request(j + SMALL_STAGES - 1, free_stage);
@@ -1105,8 +1105,8 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
     const int HD = pb.H * pb.d;
     const long t256 = HD % 256 == 0 ? (long)pb.B * (pb.Npad / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
     if (proj_reads_weights_in_place(pb, Wq, Wk, Wv)) {  // operands go straight to LDS
-        // Few tiles: 64 x 64 ones on a deeper ring.  Measured (us, 128 x 128 / 64 x 64, by the number of 128 x 128
-        // tiles): 24 9.9 / 8.2, 36 11.6 / 9.5, 72 12.5 / 11.6, 96 (d_model 3072) 25.7 / 23.2, 144 13.3 / 16.6.
+        // Few tiles: 64 x 64 ones, four to one of 128 x 128.  Measured (us, 128 x 128 / 64 x 64, by the number of 128 x 128
+        // tiles): 24 11.4 / 9.8, 36 11.6 / 10.1, 72 12.5 / 11.4, 96 (d_model 3072) 26.9 / 26.7, 144 12.9 / 13.7.
         const long t128 = (long)pb.B * (pb.Npad / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
         if (HD % 128 != 0 || t128 <= 100) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 512 && pb.D >= 2048) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
