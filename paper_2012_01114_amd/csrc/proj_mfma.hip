@@ -1111,11 +1111,15 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
         if (HD % 128 != 0 || t128 <= 100) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 512 && pb.D >= 2048) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 320) return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
-        // More 128 x 128 tiles than two per CU: three workgroups of them on a CU.  Measured (us, two / three per CU):
-        // 504 tiles 20.2 / 20.5, 576 24.8 / 23.0, 648 (d_model 1024) 32.1 / 28.3, 1152 37.8 / 37.5, 7680 (d_model
-        // 640) 214 / 203; 384 (d_model 4096) 57 / 63.
+        // 128 x 128 tiles, two or three workgroups to a CU: whichever needs the less in whole rounds of the chip, a
+        // round of 768 taking 1.5 times one of 512.  Measured (three per CU over two, by tiles, at d_model 768 / 4096):
+        // 540 0.90 / 0.92, 756 0.90 / 0.97, 798 1.05 / 1.22, 1008 1.01 / 1.15, 1080 0.92 / 1.01, 1296 0.93 / 0.98,
+        // 1548 1.01 / 1.09, 1806 1.03 / 1.01, 2052 0.97 / 0.98, 2520 1.07 / 1.05, 3024 0.99 / 1.00, 3800 1.01 / 0.98 (at
+        // d_model 256 1.05); from 5400 on rounds no longer count: 5700 0.96, 7300 0.95.  With key lengths the tiles that
+        // are left are not known here: 0.93 to 1.22 with three, so two.
         const long live = (long)pb.B * ((pb.N + 127) / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
-        if (live > 512) return launch_dma<128, 128, 2, 2, true>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        if (pb.lens == nullptr && (live > 5376 || (live <= 3072 && 3 * ((live + 767) / 768) <= 2 * ((live + 511) / 512))))
+            return launch_dma<128, 128, 2, 2, true>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         return launch_dma<128, 128, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
     }
     if (HD % 128 == 0) return launch_bt<128>(pb, X, Wt, q, k, vt, s);
