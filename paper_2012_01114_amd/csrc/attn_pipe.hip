@@ -816,18 +816,26 @@ hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, c
     const int br = 32 * waves;
     const int n_qtiles = (pb.N + br - 1) / br;
     // Masked scheme, padded rows not left out: one row tile per workgroup instead of a pair.
-    // d_k = 64, 128-row workgroups: when the pairs would not give every CU four workgroups.  Measured (us, pairs /
+    // d_k = 64, 128-row workgroups, three to a CU: when the pairs would not give every CU four.  Measured (us, pairs /
     //   tiles dealt over the CUs of an XCD / heads in turn, heaviest tiles first): batch 8, 12 heads, n 512 21.5 /
-    //   17.7 / 17.6, n 1024 33.7 / 28.0 / 28.8; 20 x 15 heads, n 512 (600 pairs) 31.7 / - / 30.4; 480 heads, n 2048
-    //   319 / 330 / 335.  Dealing needs the heads to divide over the XCDs.
-    // d_k = 128 (one workgroup per CU): when the pairs would not give every CU two, heads in turn: batch 8, 8 heads,
-    //   n 512 35 / 24 / 24, n 1024 50 / 40 / 39, n 2048 (256 pairs) 91 / 98 / 86; with 512 pairs the times are the
-    //   same (32 heads, n 8192 498 / 515 / 495) and the heads in turn fetch 1.7 times the bytes.
-    const long pairs = (long)pb.B * pb.H * ((n_qtiles + 1) / 2);
+    //   17.7 / 17.6, n 1024 33.7 / 28.0 / 28.8; 800 pairs, n 1024 57.8 / 47.2 / 47.7; 1000 pairs, n 1024 59.9 / - / 65.2,
+    //   n 2048 94.5 / - / 103.2.  Dealing needs the heads to divide over the XCDs; the heads in turn stop at 896 pairs.
+    // d_k = 128, one workgroup per CU: heads in turn where the pairs leave much of their one or two rounds of the chip
+    //   idle.  Measured (us, pairs / heads in turn, by the share of the round slots that hold a pair's worth of rows):
+    //   one round, T row tiles per head: T 4 50 % 46.2 / 41.3, 69 % 50.2 / 50.9, 94 % 55.0 / 57.9, T 8 50 % 64.8 / 58.4,
+    //   81 % 73.1 / 74.2; odd T (one tile of a head has no partner) T 3 70 % 46.5 / 43.0, T 5 78 % 58.3 / 52.6, 83 %
+    //   59.0 / 60.2; two rounds: T 4 75 % 97 / 88, 88 % 101 / 104, 97 % 108 / 116, T 5 81 % 109 / 103, T 32 75 % 425 /
+    //   391, 100 % 498 / 498 and 1.7 times the bytes.
+    const long heads = (long)pb.B * pb.H, pairs = heads * ((n_qtiles + 1) / 2);
     int single = 0;
     if (causal && !pb.skip_rows) {
-        if (pb.d == 128) single = pairs < 2L * 256 ? 2 : 0;
-        else if (waves == 4 && pairs < 4L * 256) single = (pb.B * pb.H) % 8 == 0 ? 1 : 2;
+        if (pb.d == 128) {
+            const long rounds = (pairs + 255) / 256, percent = 100 * heads * n_qtiles / (2 * 256 * rounds);
+            if (rounds <= 2 && percent <= (rounds == 2 ? 82 : n_qtiles % 2 ? 78 : 50)) single = 2;
+        } else if (waves == 4) {
+            if (heads % 8 == 0) single = pairs < 4L * 256 ? 1 : 0;
+            else single = pairs <= 896 ? 2 : 0;
+        }
     }
     const int per_head = (causal && !single) ? (n_qtiles + 1) / 2 : n_qtiles;
     const int n_work = pb.B * pb.H * per_head;
