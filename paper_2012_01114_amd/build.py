@@ -17,7 +17,9 @@ LIB = os.path.join(HERE, "libattnring.so")
 PROBE_LIB = os.path.join(HERE, "libattnprobe.so")   # ceilings probe: instrumentation, its own library
 SOURCES = ["attnring_api.hip", "generic_kernels.hip", "attn_float.hip", "proj_mfma.hip", "attn_pipe.hip", "attn_split.hip", "sym_pair.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
+# Loops start on a 64-byte line: where the walk of attn_pipe_kernel<128, FULL> happened to start was worth 4 to 7 %
+# (one item of 4096 vectors, 4 heads: 94.8 -> 88.3 us, at the same instructions).
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-falign-loops=64",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
