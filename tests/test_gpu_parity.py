@@ -195,6 +195,67 @@ def test_an_infinite_value_of_one_column_stays_in_it(shape):
     hp.tol_check(got, ref, "f32")
 
 
+# ---- float path, steady states: many slices of d_model, many key tiles ----------------------------------------
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (8, 256, 200, 8, 80, 32),     # 64 x 64 GEMM tiles, seven slices of which the last is cut; walk: keys shared
+    (16, 200, 261, 8, 64, 25),    # the same on unaligned rows of x; 512 row tiles: K and V through LDS, four key tiles
+    (2, 200, 450, 2, 48, 25),     # 32 x 32 GEMM tiles that share k, eight slices (four in 16 bits)
+    (2, 200, 453, 2, 47, 25),     # the same, unaligned
+    (16, 200, 72, 8, 80, 25),     # K and V through LDS at the other head sizes
+    (16, 200, 24, 8, 96, 25),
+    (16, 200, 24, 8, 128, 25),
+    (16, 200, 24, 8, 90, 25),
+    (3, 64, 40, 2, 160, 8),       # a single key tile of the large heads
+    (3, 60, 40, 2, 192, 6),
+    (3, 33, 40, 2, 256, 11),
+    (3, 61, 40, 1, 250, 61),
+    (2, 300, 40, 2, 192, 30),     # their keys shared
+    (2, 300, 40, 2, 250, 30),
+    (16, 200, 24, 8, 160, 25),    # and through LDS
+])
+@pytest.mark.parametrize("scheme", [FULL, SYM, CAUSAL])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_float_path_steady_states(shape, scheme, dtype):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("float_steady", B, n, D, H, d, p, dtype, scheme, 6500 + n + d)
+    _run_and_compare(w, scheme, 0.0)
+    if scheme != SYM:
+        lens = np.random.default_rng(d).integers(0, n + 1, B).astype(np.int32)
+        lens[-1] = n - 1
+        _run_and_compare(w, scheme, 0.0, lens=lens)
+
+
+# ---- matrix-core projection, steady states and row subsets, by the GEMM that the size selects ---------------
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (1, 200, 768, 2, 64, 25),     # 64 x 64 tiles, twelve slices: the ring turns four times
+    (2, 200, 776, 3, 64, 25),     # the same with a cut slice and an odd number of heads
+    (6, 384, 136, 6, 64, 48),     # 128 x 128 tiles, two workgroups per CU, cut slice
+    (6, 400, 448, 6, 64, 50),     # the same, seven slices, ragged rows
+    (30, 200, 136, 6, 64, 25),    # 540 of them: three workgroups per CU (two with key lengths)
+    (30, 200, 448, 6, 64, 25),
+])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+def test_projection_steady_states_and_lengths(shape, scheme):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("proj_steady", B, n, D, H, d, p, "bf16", scheme, 7300 + D)
+    _run_and_compare(w, scheme, 0.0)
+    lens = np.random.default_rng(D).integers(0, n + 1, B).astype(np.int32)
+    lens[0] = n // 2 + 1
+    _run_and_compare(w, scheme, 0.0, lens=lens)
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = lens
+    run = hp.GpuRun(w, stored, flags=ar.ATTN_FLAG_SKIP_PADDED_ROWS)
+    try:
+        padded, _ = run.forward(scheme)
+        packed, _ = run.forward_packed(scheme, lens)
+    finally:
+        run.close()
+    hp.tol_check(padded, hp.oracle_forward(w, f64, scheme, 0.0, lens=lens, skip_padded_rows=True), w.dtype)
+    assert np.array_equal(padded, packed)
+
+
 def test_symmetric_without_projection():
     w = hp.custom_workload("symx", 2, 20, 24, 2, 12, 5, "f32", SYM, 77)
     _, stats = _run_and_compare(w, SYM, 0.2, sym_no_proj=True)
@@ -304,6 +365,9 @@ def test_small_launches_share_the_keys(shape, scheme):
 @pytest.mark.parametrize("shape", [
     (3, 700, 64, 13, 64, 100),    # d_k = 64, heads that do not divide by eight
     (3, 1100, 64, 5, 128, 275),   # d_k = 128
+    (3, 500, 64, 100, 128, 125),  # d_k = 128, 300 pairs: two rounds of the chip, half empty
+    (3, 700, 64, 70, 128, 100),   # 420 pairs of three row tiles per head
+    (3, 1000, 64, 40, 128, 125),  # 240 pairs fill one round: paired
 ])
 def test_row_tiles_with_the_heads_in_turn(shape):
     B, n, D, H, d, p = shape
@@ -330,11 +394,11 @@ def test_projection_with_a_cut_slice(shape, d_model):
     w = hp.custom_workload("cut_slice", B, n, d_model, H, d, p, "bf16", CAUSAL, 7700 + d_model)
     if n <= 256:
         _run_and_compare(w, CAUSAL, 0.0)
-        return
-    # values that follow a vector's end belong to the next one and must not reach it: rows of infinities
+    # values that follow a vector's end belong to the next one and must not reach it: a vector of infinities, and
+    # the rows up to the one directly before it
     stored, f64 = inputs.make_inputs(w)
-    bad = [(0, n - 1), (3 % B, 77 if B > 1 else n - 1), (B - 1, n - 1)]
-    for b, i in bad:
+    firsts = {b: 96 if b % 2 else n - 32 for b in range(B)}
+    for b, i in firsts.items():
         stored["X"][b, i] = float("inf")
     stored["lens"] = None
     run = hp.GpuRun(w, stored)
@@ -342,14 +406,11 @@ def test_projection_with_a_cut_slice(shape, d_model):
         got, _ = run.forward(CAUSAL)
     finally:
         run.close()
-    for (b, h) in [(0, 0), (1, 5), (3, 15), (7, 8)]:
-        if b >= B:
-            continue
-        rows = [r for r in range(76 if b == 3 else n - 1) if r < 140 or r > n - 70]
+    for (b, h) in {(0, 0), (min(1, B - 1), min(5, H - 1)), (min(3, B - 1), H - 1), (B - 1, H // 2)}:
+        rows = [r for r in range(firsts[b]) if r < 140 or r > n - 70]
         ref = orc.head_rows(f64["X"], f64["Wq"], f64["Wk"], f64["Wv"], n_heads=H, d_k=d, p=p, scheme=CAUSAL,
                             scale=hp.default_scale(w, 0.0), b=b, h=h, rows=rows)
-        clean = [k for k, r in enumerate(rows) if r // 32 * 32 + 32 <= (77 if b == 3 else n - 1)]  # a 32-row block before it
-        hp.tol_check(got[b, [rows[k] for k in clean], h * d:(h + 1) * d], ref[clean], w.dtype)
+        hp.tol_check(got[b, rows, h * d:(h + 1) * d], ref, w.dtype)
 
 
 # ---- queries projected inside the attention kernel (ATTN_FLAG_FUSE_Q_PROJECTION) ----------------------
@@ -402,7 +463,8 @@ def test_symmetric_on_matrix_cores(shape):
 # ---- row maxima that move along the walk: the running reference of Eq. (2)'s online form ----------
 @pytest.mark.parametrize("profile", ["ramp", "steps"])
 @pytest.mark.parametrize("scheme", [FULL, CAUSAL])
-@pytest.mark.parametrize("d_k,tiles", [(64, ar.ATTN_FLAG_NARROW_TILES), (64, ar.ATTN_FLAG_WIDE_TILES), (128, 0)])
+@pytest.mark.parametrize("d_k,tiles", [(64, ar.ATTN_FLAG_NARROW_TILES), (64, ar.ATTN_FLAG_WIDE_TILES), (64, 0), (128, 0),
+                                       (128, ar.ATTN_FLAG_WIDE_TILES)])
 def test_reference_moves_along_the_walk(profile, scheme, d_k, tiles):
     """Scores with a designed level per key (inputs.make_level_inputs): `ramp` adds 60 nats at key 0
     falling to 0 at the last key, so along a walk towards key 0 the row maximum outgrows any fixed
@@ -532,7 +594,9 @@ def test_key_lengths_change_between_calls(scheme):
     ("f32", 3, 48, 32, 2, 16, 6, 0),                                   # float path
     ("bf16", 3, 320, 64, 2, 64, 40, ar.ATTN_FLAG_NARROW_TILES),        # 128-row workgroups
     ("bf16", 3, 704, 128, 2, 64, 88, ar.ATTN_FLAG_WIDE_TILES),         # 256-row workgroups, d_k = 64
-    ("bf16", 3, 600, 192, 1, 128, 75, 0),                              # d_k = 128
+    ("bf16", 3, 600, 192, 1, 128, 75, 0),                              # d_k = 128, small launch
+    ("bf16", 3, 600, 192, 1, 128, 75, ar.ATTN_FLAG_WIDE_TILES),        # 256-row workgroups, d_k = 128
+    ("bf16", 3, 320, 64, 2, 64, 40, 0),                                # d_k = 64, small launch
 ])
 @pytest.mark.parametrize("scheme", [FULL, CAUSAL])
 def test_padded_rows_left_out(case, scheme):
@@ -581,8 +645,10 @@ def test_key_lengths_with_heads_dealt_over_the_xcds(scheme, flags):
 
 @pytest.mark.parametrize("case", [
     ("bf16", 3, 320, 64, 2, 64, 40, 0),
+    ("bf16", 3, 320, 64, 2, 64, 40, ar.ATTN_FLAG_NARROW_TILES),
     ("bf16", 3, 704, 128, 2, 64, 88, ar.ATTN_FLAG_WIDE_TILES),
     ("bf16", 3, 600, 192, 1, 128, 75, 0),
+    ("bf16", 3, 600, 192, 1, 128, 75, ar.ATTN_FLAG_WIDE_TILES),
     ("bf16", 3, 320, 72, 2, 64, 40, 0),      # d_model not in whole 64-deep slices: the other projection kernel
 ])
 @pytest.mark.parametrize("scheme", [FULL, CAUSAL])
