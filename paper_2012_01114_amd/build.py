@@ -17,15 +17,17 @@ LIB = os.path.join(HERE, "libattnring.so")
 PROBE_LIB = os.path.join(HERE, "libattnprobe.so")   # ceilings probe: instrumentation, its own library
 SOURCES = ["attnring_api.hip", "generic_kernels.hip", "attn_float.hip", "proj_mfma.hip", "attn_pipe.hip", "attn_split.hip", "sym_pair.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-# Loops start on a 64-byte line: where the walk of attn_pipe_kernel<128, FULL> happened to start was worth 4 to 7 %
-# (one item of 4096 vectors, 4 heads: 94.8 -> 88.3 us, at the same instructions).
-FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function", "-falign-loops=64",
+FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# Loops start on a 64-byte line: where the walk of attn_pipe_kernel<128, FULL> happened to start was worth 4 to 7 %
+# (one item of 4096 vectors, 4 heads: 94.8 -> 88.3 us, at the same instructions).  In the GEMMs it costs more than it
+# gives (960 x 1456 -> 1536: 20.7 -> 21.4).
+FLAGS_OF = {"attn_pipe.hip": ["-falign-loops=64"]}
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC] + FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC] + FLAGS + FLAGS_OF.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:
