@@ -810,21 +810,23 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
 // ---------------------------------------------------------------------------
 // The GEMM for products of few tiles, and for columns that do not come in 128s (an odd number of
 // 64-wide heads): 64 x 64 tiles, four wavefronts of 32 x 32, operands copied straight into LDS.
-// What bounds a product that leaves CUs idle is its own chain of slices, each one barrier, eight LDS
-// reads and four MFMAs per wavefront with the next slice on its way; what bounds a large one is how many
-// workgroups a CU holds against those barriers and the stores.  Three 64-deep slices of x and W (48 KiB,
-// three workgroups to a CU) suit both: with five (80 KiB, two to a CU) products of up to 384 tiles take
-// the same, 576 and more 5 to 25 % longer (8192 x 136 -> 2880 40 us where three take 31, 8192 x 960 -> 2880 85
-// and 75).  Both sides are rows of 128 bytes: x rows with their chunks XOR-ed with bits 1..3 of the row,
-// k-rows of W with 4 * bit 1 of k (transposing reads).
-// Stores go out from the accumulators, eight bytes per lane: four instructions per wavefront.
+// Both sides are rows of 128 bytes: x rows with their chunks XOR-ed with bits 1..3 of the row, k-rows of W
+// with 4 * bit 1 of k (transposing reads).  A slice is one barrier, eight LDS reads and four MFMAs per
+// wavefront.  Stores go out from the accumulators, eight bytes per lane: four instructions per wavefront.
+//
+// STAGES, the slices of x and W that the ring holds.  A product that leaves CUs idle is bound by its own
+// chain of slices and by what the first read of an input takes, so five (80 KiB, two workgroups share a CU):
+// 15 packed items of up to 536 vectors, 576 -> 192, on inputs new to every call 16.5 us the call, 17.4 with
+// three.  A product of more tiles than those 512 workgroups is bound by how many workgroups a CU holds
+// against the barriers and the stores, so three (48 KiB, three to a CU): 576 tiles and more 5 to 25 % less
+// time (8192 x 136 -> 2880 40 -> 31 us, 8192 x 960 -> 2880 85 -> 75, 2400 x 640 -> 1920 22 -> 18).
 // ---------------------------------------------------------------------------
-constexpr int SMALL_STAGES = 3;
+inline bool ring_of_three(long tiles) { return tiles > 512; }
 // FLOAT_OUT (the float path's bfloat16 storage): the product is written as floats, all three matrices
 // as [vector][d] rows of their heads, d a multiple of 4; the vectors of all batch items are one run of
 // rows (Bsz 1, N of them), `items` divides by an item's.
-template <bool TAIL, bool FLOAT_OUT>
-__global__ __launch_bounds__(256, 3)
+template <int STAGES, bool TAIL, bool FLOAT_OUT>
+__global__ __launch_bounds__(256, STAGES == 3 ? 3 : 2)
 void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t* __restrict__ X,
                        const bf16_t* __restrict__ Wq, const bf16_t* __restrict__ Wk, const bf16_t* __restrict__ Wv,
                        void* __restrict__ qo, void* __restrict__ ko, void* __restrict__ vto, TileMap tm,
@@ -833,7 +835,7 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
                        FastDiv columns)
 {
     constexpr int XB = 64 * 128, STAGE = 2 * XB;  // x: 64 rows x 64 k; W: 64 k-rows x 64 columns
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[SMALL_STAGES * STAGE];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[STAGES * STAGE];
     clear_counters(counters);  // this is the first kernel of a forward pass on this path
 
     const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, g = lane >> 5;
@@ -902,21 +904,24 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
     const int ns = TAIL ? (D + 63) / 64 : D / 64;
-    const int ahead = ns < SMALL_STAGES - 1 ? ns : SMALL_STAGES - 1;
+    const int ahead = ns < STAGES - 1 ? ns : STAGES - 1;
     for (int j = 0; j < ahead; ++j) request(j, j);
     auto all_slices = [&](auto is_v_) {
         constexpr bool IS_V = decltype(is_v_)::value;
         int stage = 0;
 #pragma nounroll
         for (int j = 0; j < ns; ++j) {
-            // slice j + 1 may be in flight, four requests; loads return in order
-            if (j + 1 < ns) __builtin_amdgcn_s_waitcnt(0x0070 | 4);
+            // slices j + 1 .. j + STAGES - 2 may be in flight, four requests each; loads return in order
+            const int more = min(ns - 1 - j, STAGES - 2);
+            if (more >= 3) __builtin_amdgcn_s_waitcnt(0x0070 | 12);
+            else if (more == 2) __builtin_amdgcn_s_waitcnt(0x0070 | 8);
+            else if (more == 1) __builtin_amdgcn_s_waitcnt(0x0070 | 4);
             else __builtin_amdgcn_s_waitcnt(0x0070);
             // behind the barrier the slice is in LDS for everyone, and everyone has read the one before
-            // (its reads were waited for ahead of its MFMAs), whose stage takes slice j + 2
+            // (its reads were waited for ahead of its MFMAs), whose stage takes slice j + STAGES - 1
             __builtin_amdgcn_s_barrier();
-            const int free_stage = stage == 0 ? SMALL_STAGES - 1 : stage - 1;
-            if (j + SMALL_STAGES - 1 < ns) request(j + SMALL_STAGES - 1, free_stage);
+            const int free_stage = stage == 0 ? STAGES - 1 : stage - 1;
+            if (j + STAGES - 1 < ns) request(j + STAGES - 1, free_stage);
             const unsigned char* base = lds + stage * STAGE;
             const unsigned waddr = lds_addr + (unsigned)(stage * STAGE + wfo);
             u32x4 xf[4];
@@ -935,7 +940,7 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
                 const u32x4 wf = {lo[ks][0], lo[ks][1], hi[ks][0], hi[ks][1]};
                 acc = IS_V ? mfma32(xf[ks], wf, acc) : mfma32(wf, xf[ks], acc);
             }
-            stage = stage == SMALL_STAGES - 1 ? 0 : stage + 1;
+            stage = stage == STAGES - 1 ? 0 : stage + 1;
         }
     };
     if (!FLOAT_OUT && which == 2) all_slices(std::true_type{});
@@ -1015,12 +1020,12 @@ hipError_t launch_small(const Problem& pb, const bf16_t* X, const bf16_t* Wq, co
     const TileMap tm = tile_map(pb, 64, 64, pb.no_q ? 2 : 3, lens != nullptr);
     const int grid = ((tm.n_tiles + 7) / 8) * 8;
     const FastDiv none = {1u, 0u, 0u};
-    if (pb.D % 64 == 0)
-        hipLaunchKernelGGL((proj_small_kernel<false, false>), dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
-                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters, none, none);
-    else
-        hipLaunchKernelGGL((proj_small_kernel<true, false>), dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X,
-                           Wq, Wk, Wv, q, k, vt, tm, qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters, none, none);
+    const bool tail = pb.D % 64 != 0;
+    auto* const kernel = ring_of_three((long)pb.B * ((pb.N + 63) / 64) * tm.tiles_w)
+                             ? (tail ? proj_small_kernel<3, true, false> : proj_small_kernel<3, false, false>)
+                             : (tail ? proj_small_kernel<5, true, false> : proj_small_kernel<5, false, false>);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, pb.B, pb.N, pb.Npad, pb.D, pb.H, pb.d, X, Wq, Wk, Wv, q, k, vt, tm,
+                       qscale, lens, pb.skip_rows, pb.no_q, pb.row0, pb.counters, none, none);
     return hipGetLastError();
 }
 
@@ -1081,13 +1086,12 @@ bool launch_proj_small_float(const Problem& pb, const bf16_t* X, const bf16_t* c
     const bf16_t* w[3] = {W[0], W[count > 1 ? 1 : 0], W[count > 2 ? 2 : 0]};
     float* o[3] = {out[0], out[count > 1 ? 1 : 0], out[count > 2 ? 2 : 0]};
     const FastDiv items = fast_div((unsigned)pb.N), columns = fast_div((unsigned)pb.d);
-#define PROJ_FLOAT(TAIL_)                                                                                                  \
-    hipLaunchKernelGGL((proj_small_kernel<TAIL_, true>), dim3(grid), dim3(256), 0, s, 1, rows.N, rows.Npad, pb.D, pb.H,    \
-                       pb.d, X, w[0], w[1], w[2], o[0], o[1], o[2], tm, 1.f, nullptr, false, false, nullptr, pb.counters, \
-                       items, columns)
-    if (pb.D % 64 == 0) PROJ_FLOAT(false);
-    else PROJ_FLOAT(true);
-#undef PROJ_FLOAT
+    const bool tail = pb.D % 64 != 0;
+    auto* const kernel = ring_of_three(tm.n_tiles)
+                             ? (tail ? proj_small_kernel<3, true, true> : proj_small_kernel<3, false, true>)
+                             : (tail ? proj_small_kernel<5, true, true> : proj_small_kernel<5, false, true>);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, 1, rows.N, rows.Npad, pb.D, pb.H, pb.d, X, w[0], w[1], w[2], o[0], o[1],
+                       o[2], tm, 1.f, nullptr, false, false, nullptr, pb.counters, items, columns);
     return true;
 }
 
@@ -1115,10 +1119,12 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
         // round of 768 taking 1.5 times one of 512.  Measured (three per CU over two, by tiles, at d_model 768 / 4096):
         // 540 0.90 / 0.92, 756 0.90 / 0.97, 798 1.05 / 1.22, 1008 1.01 / 1.15, 1080 0.92 / 1.01, 1296 0.93 / 0.98,
         // 1548 1.01 / 1.09, 1806 1.03 / 1.01, 2052 0.97 / 0.98, 2520 1.07 / 1.05, 3024 0.99 / 1.00, 3800 1.01 / 0.98 (at
-        // d_model 256 1.05); from 5400 on rounds no longer count: 5700 0.96, 7300 0.95.  With key lengths the tiles that
-        // are left are not known here: 0.93 to 1.22 with three, so two.
+        // d_model 256 1.05); from 5400 on rounds no longer count: 5700 0.96, 7300 0.95.  With key lengths the number of
+        // tiles that are left is not known here: three where all tiles would fit one round of them (29 x 224, d_model 2368
+        // -> 1536, padded rows left out, 696 tiles: 58 us the call, 65 with two), else 0.93 to 1.22 with three, so two.
         const long live = (long)pb.B * ((pb.N + 127) / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
-        if (pb.lens == nullptr && (live > 5376 || (live <= 3072 && 3 * ((live + 767) / 768) <= 2 * ((live + 511) / 512))))
+        const bool fewer_rounds = 3 * ((live + 767) / 768) <= 2 * ((live + 511) / 512);
+        if (live > 5376 || (fewer_rounds && live <= (pb.lens ? 768 : 3072)))
             return launch_dma<128, 128, 2, 2, true>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         return launch_dma<128, 128, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
     }

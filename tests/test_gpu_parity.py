@@ -202,6 +202,7 @@ def test_an_infinite_value_of_one_column_stays_in_it(shape):
     (16, 200, 261, 8, 64, 25),    # the same on unaligned rows of x; 512 row tiles: K and V through LDS, four key tiles
     (2, 200, 450, 2, 48, 25),     # 32 x 32 GEMM tiles that share k, eight slices (four in 16 bits)
     (2, 200, 453, 2, 47, 25),     # the same, unaligned
+    (2, 200, 456, 4, 48, 25),     # 16 bits: pieces straight into LDS, eight slices, the last cut
     (16, 200, 72, 8, 80, 25),     # K and V through LDS at the other head sizes
     (16, 200, 24, 8, 96, 25),
     (16, 200, 24, 8, 128, 25),
@@ -231,6 +232,7 @@ def test_float_path_steady_states(shape, scheme, dtype):
     # B, n, D, H, d, p
     (1, 200, 768, 2, 64, 25),     # 64 x 64 tiles, twelve slices: the ring turns four times
     (2, 200, 776, 3, 64, 25),     # the same with a cut slice and an odd number of heads
+    (6, 400, 456, 5, 64, 50),     # 630 of them: the shorter ring, eight slices
     (6, 384, 136, 6, 64, 48),     # 128 x 128 tiles, two workgroups per CU, cut slice
     (6, 400, 448, 6, 64, 50),     # the same, seven slices, ragged rows
     (30, 200, 136, 6, 64, 25),    # 540 of them: three workgroups per CU (two with key lengths)
