@@ -215,7 +215,7 @@ attn_status attn_profile_read(attn_ctx* ctx, attn_profile_t* out);
  *     130 KiB + 3 * batch * roundup(n, 256) * n_heads * d_k * 2 bytes
  * exceeds the array, returns UNSUPPORTED with the size needed in attn_last_error(NULL).
  * All calls on one GPU share that GPU's array, which keeps what the last call left: the call clears
- * what must start at zero (counter slots, the rows past n) itself, and two calls that overlap in time
+ * what must start at zero (counter slots, the values past n that a walk can meet) itself, and two calls that overlap in time
  * on one GPU - on different streams or from different threads - race.  Calls on one stream, or
  * otherwise ordered by the caller, are fine.  Results obey the same bars as attn_forward's.
  */

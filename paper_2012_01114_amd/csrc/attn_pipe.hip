@@ -542,7 +542,7 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
         r.l = 0.f;
 
         if (nT > 0) {
-            // Q rows of this wavefront as B operands (rows >= n of the workspace are zero).
+            // Q rows of this wavefront as B operands (what rows >= n hold reaches masked scores only: cut_rows).
             u32x4 qf[NKS];
             if constexpr (!FUSEQ) {
 #pragma unroll

@@ -8,18 +8,16 @@
 // The weights arrive as [D][H*d] (q = x.W), i.e. contiguous along the output
 // columns, while an MFMA operand register wants 8 consecutive values of the
 // contraction index.  The main kernel leaves them where they are and turns them
-// while reading LDS (ds_read_b64_tr_b16); the fallback kernel for shapes and
-// alignments that kernel does not take has a small kernel lay them out as
-// W^T [3*H*d][D] first.
+// while reading LDS (ds_read_b64_tr_b16); for weights that are not 16-byte aligned
+// a small kernel lays them out as W^T [3*H*d][D] first and the fallback GEMM reads that.
 #include "mfma_common.h"
 
 namespace attnring {
 namespace {
 
 // ---------------------------------------------------------------------------
-// W^T: 64 x 64 tiles through LDS; grid (HD/64, ceil(D/64), 3).  Workgroup
-// (0,0,0) also clears the counter slots of the call (every forward pass runs
-// this kernel first).
+// W^T: 64 x 64 tiles through LDS; grid (HD/64, ceil(D/64), 3).  Where it runs it is
+// the call's first kernel, so workgroup (0,0,0) clears the counter slots.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void transpose_w_kernel(int D, int HD, const bf16_t* __restrict__ Wq,
                                                           const bf16_t* __restrict__ Wk,
@@ -40,42 +38,6 @@ __global__ __launch_bounds__(256) void transpose_w_kernel(int D, int HD, const b
     for (int c = ty; c < 64; c += 4) {
         const int gk = r0 + tx;
         if (gk < D) dst[(size_t)(c0 + c) * D + gk] = tile[tx][c];
-    }
-}
-
-// The same for 16-byte aligned weights (D is a multiple of 8): 16 bytes per lane in and out.
-__global__ __launch_bounds__(256) void transpose_w16_kernel(int D, int HD, const bf16_t* __restrict__ Wq,
-                                                            const bf16_t* __restrict__ Wk,
-                                                            const bf16_t* __restrict__ Wv, bf16_t* __restrict__ Wt,
-                                                            unsigned long long* counters)
-{
-    constexpr int PITCH = 64 + 8;  // elements; keeps 16-byte alignment of the rows
-    __shared__ __attribute__((aligned(16))) bf16_t tile[64 * PITCH];
-    clear_counters(counters);
-    const bf16_t* W = blockIdx.z == 0 ? Wq : (blockIdx.z == 1 ? Wk : Wv);
-    bf16_t* dst = Wt + (size_t)blockIdx.z * HD * D;
-    const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int c = threadIdx.x + 256 * u;
-        const int row = c >> 3, cc = c & 7;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (r0 + row < D) v = *(const u32x4*)(W + (size_t)(r0 + row) * HD + c0 + 8 * cc);
-        *(u32x4*)(tile + row * PITCH + 8 * cc) = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int c = threadIdx.x + 256 * u;
-        const int n = c >> 3, kc = c & 7;
-        if (r0 + 8 * kc >= D) continue;
-        u32x4 v;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const unsigned lo = tile[(8 * kc + 2 * j) * PITCH + n], hi = tile[(8 * kc + 2 * j + 1) * PITCH + n];
-            v[j] = lo | (hi << 16);
-        }
-        *(u32x4*)(dst + (size_t)(c0 + n) * D + r0 + 8 * kc) = v;
     }
 }
 
@@ -765,7 +727,7 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
             const int hv = e0 >> (dsh - 3);  // head-in-tile * BX + vector
             const int c = e0 & cmask;
             const int hc = hv / BX, v = hv - hc * BX;
-            if (i0 + v >= N) continue;  // rows past n stay zero
+            if (i0 + v >= N) continue;  // rows past n are left as they are
             const u32x4 val = *(const u32x4*)(lds + hv * rowb + ((c ^ (v & cmask)) << 4));
             *(u32x4*)(base + ((size_t)hc * Npad + i0 + v) * d + c * 8) = val;
         }
@@ -800,7 +762,7 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
             const int u = ul >> dsh, l = ul & (d - 1);
             const int hc = u / (BX / 64), vb = u - hc * (BX / 64);
             const int blk = (i0 >> 6) + vb;
-            if (blk * 64 >= N) continue;  // blocks past n stay zero
+            if (blk * 64 >= N) continue;  // so are blocks past n
             const u32x4 val = *(const u32x4*)(lds + ul * 128 + ((c ^ (l & 7)) << 4));
             *(u32x4*)(vto + ((((size_t)bb * H + h0 + hc) * (Npad >> 6) + blk) * d + l) * 64 + c * 8) = val;
         }
@@ -1048,13 +1010,7 @@ hipError_t launch_transpose_w(const Problem& pb, const bf16_t* Wq, const bf16_t*
 {
     const int HD = pb.H * pb.d;
     const dim3 grid(HD / 64, (pb.D + 63) / 64, 3);
-    const bool aligned16 = ((reinterpret_cast<uintptr_t>(Wq) | reinterpret_cast<uintptr_t>(Wk) |
-                             reinterpret_cast<uintptr_t>(Wv) | reinterpret_cast<uintptr_t>(Wt)) & 15) == 0 &&
-                           pb.D % 8 == 0;
-    if (aligned16)
-        hipLaunchKernelGGL(transpose_w16_kernel, grid, dim3(256), 0, s, pb.D, HD, Wq, Wk, Wv, Wt, pb.counters);
-    else
-        hipLaunchKernelGGL(transpose_w_kernel, grid, dim3(256), 0, s, pb.D, HD, Wq, Wk, Wv, Wt, pb.counters);
+    hipLaunchKernelGGL(transpose_w_kernel, grid, dim3(256), 0, s, pb.D, HD, Wq, Wk, Wv, Wt, pb.counters);
     return hipGetLastError();
 }
 

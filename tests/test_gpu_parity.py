@@ -258,6 +258,41 @@ def test_projection_steady_states_and_lengths(shape, scheme):
     assert np.array_equal(padded, packed)
 
 
+# ---- weights that are not 16-byte aligned: laid out anew and read by the GEMM for transposed weights ----------
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (2, 320, 136, 2, 64, 40),     # 128 x 128 tiles, cut slice
+    (2, 200, 192, 3, 64, 25),     # 64 x 64 tiles (an odd number of 64-wide heads)
+    (1, 600, 64, 1, 128, 75),     # one slice, d_k = 128
+])
+@pytest.mark.parametrize("scheme", [FULL, SYM, CAUSAL])
+def test_unaligned_weights(shape, scheme):
+    import torch
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("unaligned", B, n, D, H, d, p, "bf16", scheme, 7900 + n)
+    stored, f64 = inputs.make_inputs(w)
+    lens = None
+    if scheme == SYM:
+        stored["Wk"] = stored["Wv"] = None
+    else:
+        lens = np.random.default_rng(n).integers(1, n + 1, B).astype(np.int32)
+    stored["lens"] = lens
+    run = hp.GpuRun(w, stored, flags=ar.ATTN_FLAG_SKIP_PADDED_ROWS)
+    try:
+        for m in range(3):
+            if run.W[m] is not None:
+                room = torch.empty(run.W[m].numel() + 1, dtype=run.W[m].dtype, device=run.X.device)
+                run.W[m] = room[1:].view(run.W[m].shape).copy_(run.W[m])
+        got, stats = run.forward(scheme)
+        hp.check_counts(stats, hp.oracle_counts(w, scheme, lens, skip_padded_rows=lens is not None))
+        packed = run.forward_packed(scheme, lens)[0] if lens is not None else got
+    finally:
+        run.close()
+    ref = hp.oracle_forward(w, f64, scheme, 0.0, lens=lens, skip_padded_rows=lens is not None)
+    hp.tol_check(got, ref, w.dtype)
+    assert np.array_equal(got, packed)
+
+
 def test_symmetric_without_projection():
     w = hp.custom_workload("symx", 2, 20, 24, 2, 12, 5, "f32", SYM, 77)
     _, stats = _run_and_compare(w, SYM, 0.2, sym_no_proj=True)
