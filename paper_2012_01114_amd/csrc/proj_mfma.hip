@@ -1059,6 +1059,8 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
     //   8192 x 768 -> 2304 (288)   36.4 / 45.2 / 36.1     16384 x 768 -> 2304 (576)    61 / 70 / 57
     //   8192 x 1024 -> 3072 (384)  52 / 55 / 48           65536 x 1024 -> 3072 (3072)  435 / 374 / 377, with key
     //   4096 x 4096 -> 12288 (768) 344 / 301 / 310        lengths 338 / 309 / 282, packed 266 / 249 / 224
+    //   4096 x 4096 -> 6144 (384)  182 / - / 165          7168 x 1536 -> 6144 (672)    - / 126 / 124
+    //                                                     7168 x 1984 -> 6144 (672)    - / 155 / 155
     // A workgroup's prologue and epilogue take as long as five slices and are hidden by the CU's other one, if
     // there is one; 256 x 256 reads the least per product, which decides when d_model is long.  No tile mixes
     // columns of two matrices.
@@ -1066,7 +1068,8 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
     const long t256 = HD % 256 == 0 ? (long)pb.B * (pb.Npad / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
     if (proj_reads_weights_in_place(pb, Wq, Wk, Wv)) {  // operands go straight to LDS
         // Few tiles: 64 x 64 ones, four to one of 128 x 128.  Measured (us, 128 x 128 / 64 x 64, by the number of 128 x 128
-        // tiles): 24 11.4 / 9.8, 36 11.6 / 10.1, 72 12.5 / 11.4, 96 (d_model 3072) 26.9 / 26.7, 144 12.9 / 13.7.
+        // tiles): 24 11.4 / 9.8, 36 11.6 / 10.1, 72 12.5 / 11.4, 96 (d_model 3072) 26.9 / 26.7, 144 12.9 / 13.7.  Columns not in
+        // 128s have no other tiles: 8192 x 960 -> 2880 78 us, 32768 x 1024 -> 2880 322, 32768 x 4096 -> 2880 1408.
         const long t128 = (long)pb.B * (pb.Npad / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
         if (HD % 128 != 0 || t128 <= 100) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 512 && pb.D >= 2048) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
