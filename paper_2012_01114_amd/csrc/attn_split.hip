@@ -229,8 +229,11 @@ hipError_t launch_attn(const Problem& pb, const h16_t* q, const h16_t* k, const 
     //               256 (n 4096) 56 / 36, 58 / 35         384 (n 512) 14.3 / 15.3, 14.1 / 13.1
     //               512 (n 2048) 32 / 36, 31 / 29         768 (n 512) 15 / 20, 15 / 17
     //   d_k = 128   256 (n 512) 21 / 16, 23 / 16          512 (n 2048) 52 / 67, 51 / 54
+    // masked, key lengths, every query row produced (the call): 384 (n 512) 21.1 / 21.0, 512 (n 1024) 24.6 / 26.1, 512 (n
+    // 512) 20.0 / 21.0: the walks that the split shortens are short already.
     const long split_wgs = (long)pb.B * pb.H * ((pb.N + 31) / 32);
-    const long most = pb.d == 64 && pb.scheme == SCHEME_CAUSAL ? 512 : 256;
+    const bool masked64 = pb.d == 64 && pb.scheme == SCHEME_CAUSAL;
+    const long most = !masked64 ? 256 : pb.lens && !pb.skip_rows ? 384 : 512;
     if (asked_waves == 0 && !fuse && split_wgs <= most)
         return launch_attn_split(pb, q, k, vt, out, s);
     // d_k = 64: 128-row workgroups of 4 wavefronts, three of them per CU; d_k = 128: 256 rows, 8 wavefronts
