@@ -299,6 +299,28 @@ def test_symmetric_without_projection():
     assert stats["proj_gemms"] == 0
 
 
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (3, 1000, 40, 12, 96, 125),   # K and V through LDS; own tile first in the walk: 8.4e-7
+    (2, 900, 64, 24, 64, 90),
+])
+def test_symmetric_float_sums_keep_their_precision(shape):
+    """q = k = v: a row's own weight outweighs the others together, and what is added to a float sum behind it is
+    rounded at that size.  2-norm of the error over 2-norm of the output; 2.5e-7 to 3.1e-7 measured, of which the
+    scores' own rounding (size |z|^2 / sqrt(d), some 10) is most."""
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("sym_precision", B, n, D, H, d, p, "f32", SYM, 2600 + n)
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = stored["Wk"] = stored["Wv"] = None
+    run = hp.GpuRun(w, stored)
+    try:
+        got, _ = run.forward(SYM)
+    finally:
+        run.close()
+    ref = hp.oracle_forward(w, f64, SYM, 0.0)
+    assert np.linalg.norm(got - ref) <= 5e-7 * np.linalg.norm(ref)
+
+
 # ---- q = k = v on the float path, n no multiple of 4, close to the bound on the score matrices: rows in whole
 # 16-byte pieces would take more than the 1 GiB
 @pytest.mark.parametrize("shape", [
