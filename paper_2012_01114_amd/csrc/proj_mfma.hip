@@ -1079,11 +1079,13 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
         // 540 0.90 / 0.92, 756 0.90 / 0.97, 798 1.05 / 1.22, 1008 1.01 / 1.15, 1080 0.92 / 1.01, 1296 0.93 / 0.98,
         // 1548 1.01 / 1.09, 1806 1.03 / 1.01, 2052 0.97 / 0.98, 2520 1.07 / 1.05, 3024 0.99 / 1.00, 3800 1.01 / 0.98 (at
         // d_model 256 1.05); from 5400 on rounds no longer count: 5700 0.96, 7300 0.95.  With key lengths the number of
-        // tiles that are left is not known here: three where all tiles would fit one round of them (29 x 224, d_model 2368
-        // -> 1536, padded rows left out, 696 tiles: 58 us the call, 65 with two), else 0.93 to 1.22 with three, so two.
+        // tiles that are left decides, 0.85 to 0.9 where it lies between 512 and 768 and 1.1 to 1.2 elsewhere, and is not
+        // known here: three for the counts whose tiles, some of them left out, mostly end up there.  Means over lengths
+        // uniform in n / 32 .. n, n 128 to 2000, d_model 512 and 2048: 600 tiles 1.09, 672 1.02, 714 0.88, 768 0.97, 798 0.93,
+        // 840 0.98, 864 0.97, 912 1.01, 960 1.04, 1008 1.07, 1104 1.06.
         const long live = (long)pb.B * ((pb.N + 127) / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
         const bool fewer_rounds = 3 * ((live + 767) / 768) <= 2 * ((live + 511) / 512);
-        if (live > 5376 || (fewer_rounds && live <= (pb.lens ? 768 : 3072)))
+        if (live > 5376 || (pb.lens ? live >= 680 && live <= 920 : fewer_rounds && live <= 3072))
             return launch_dma<128, 128, 2, 2, true>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         return launch_dma<128, 128, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
     }
