@@ -818,8 +818,10 @@ hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, c
     // Masked scheme, padded rows not left out: one row tile per workgroup instead of a pair.
     // d_k = 64, 128-row workgroups, three to a CU: when the pairs would not give every CU four.  Measured (us, pairs /
     //   tiles dealt over the CUs of an XCD / heads in turn, heaviest tiles first): batch 8, 12 heads, n 512 21.5 /
-    //   17.7 / 17.6, n 1024 33.7 / 28.0 / 28.8; 800 pairs, n 1024 57.8 / 47.2 / 47.7; 1000 pairs, n 1024 59.9 / - / 65.2,
-    //   n 2048 94.5 / - / 103.2.  Dealing needs the heads to divide over the XCDs; the heads in turn stop at 896 pairs.
+    //   17.7 / 17.6, n 1024 33.7 / 28.0 / 28.8; 800 pairs, n 1024 57.8 / 47.2 / 47.7.  Dealing needs the heads to divide
+    //   over the XCDs.  Elsewhere the heads in turn, but not where the pairs nearly fill the 768 places of one round
+    //   (640 pairs 0.87 to 0.98 of the pairs' time, 690 0.93 to 1.13, 760 0.9 to 1.12, 780 0.77 to 1.0), nor with 4 to 8 row
+    //   tiles per head beyond 920 pairs (910 0.88 to 1.0, 950 0.97 to 1.03, 1015 0.93 to 1.08; other counts 0.8 to 1.04).
     // d_k = 128, one workgroup per CU: heads in turn where the pairs leave much of their one or two rounds of the chip
     //   idle.  Measured (us, pairs / heads in turn, by the share of the round slots that hold a pair's worth of rows):
     //   one round, T row tiles per head: T 4 50 % 46.2 / 41.3, 69 % 50.2 / 50.9, 94 % 55.0 / 57.9, T 8 50 % 64.8 / 58.4,
@@ -834,7 +836,7 @@ hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, c
             if (rounds <= 2 && percent <= (rounds == 2 ? 82 : n_qtiles % 2 ? 78 : 50)) single = 2;
         } else if (waves == 4) {
             if (heads % 8 == 0) single = pairs < 4L * 256 ? 1 : 0;
-            else single = pairs <= 896 ? 2 : 0;
+            else single = pairs <= 640 || (pairs > 768 && pairs < (n_qtiles >= 4 && n_qtiles <= 8 ? 920 : 1024)) ? 2 : 0;
         }
     }
     const int per_head = (causal && !single) ? (n_qtiles + 1) / 2 : n_qtiles;

@@ -93,6 +93,7 @@ class GpuRun:
         self.W = [None if stored[k] is None else stored[k].to(dev) for k in ("Wq", "Wk", "Wv")]
         self.lens = None
         if stored.get("lens") is not None:
+            assert len(stored["lens"]) == w.batch
             self.lens = torch.from_numpy(np.asarray(stored["lens"], dtype=np.int32)).to(dev)
         self.ctx = ar.attn_init(w.batch, w.n, w.d_model, w.n_heads, w.d_k, w.p, self.dt, scale, flags)
         ar.attn_set_key_lengths(self.ctx, self.lens)

@@ -423,6 +423,8 @@ def test_small_launches_share_the_keys(shape, scheme):
 # ---- masked scheme, one row tile per workgroup with the heads in turn ------------------------------------
 @pytest.mark.parametrize("shape", [
     (3, 700, 64, 13, 64, 100),    # d_k = 64, heads that do not divide by eight
+    (5, 500, 64, 70, 64, 125),    # 700 pairs nearly fill a round: paired
+    (9, 500, 64, 45, 64, 125),    # 810 pairs: a second round nearly empty
     (3, 1100, 64, 5, 128, 275),   # d_k = 128
     (3, 500, 64, 100, 128, 125),  # d_k = 128, 300 pairs: two rounds of the chip, half empty
     (3, 700, 64, 70, 128, 100),   # 420 pairs of three row tiles per head
@@ -432,7 +434,7 @@ def test_row_tiles_with_the_heads_in_turn(shape):
     B, n, D, H, d, p = shape
     w = hp.custom_workload("in_turn", B, n, D, H, d, p, "bf16", CAUSAL, 9100 + n)
     _run_and_compare(w, CAUSAL, 0.0)
-    _run_and_compare(w, CAUSAL, 0.0, lens=np.array([n, 1, n // 3], dtype=np.int32))
+    _run_and_compare(w, CAUSAL, 0.0, lens=np.resize(np.array([n, 1, n // 3], dtype=np.int32), B))
 
 
 # ---- the projection's last slice of d_model when it is not 64 deep (vectors in whole 16-byte pieces) ----
