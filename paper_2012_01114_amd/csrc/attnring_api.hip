@@ -164,6 +164,22 @@ void try_planes(attn_ctx* c, const Problem& pb)
     (void)hipGetLastError();
 }
 
+bool overlap(const void* p, size_t p_bytes, const void* q, size_t q_bytes)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + q_bytes && b < a + p_bytes;
+}
+
+// Whether `out` shares memory with an input: the projection kernel has read them all before the attention kernel
+// writes, but in a single kernel one workgroup would write what others still read.
+bool out_over_inputs(const Problem& pb, const void* X, const void* const* W, const void* out)
+{
+    const size_t size = pb.is_bf16 ? sizeof(bf16_t) : sizeof(float), rows = (size_t)pb.B * pb.N, hd = (size_t)pb.H * pb.d;
+    bool over = overlap(out, rows * hd * size, X, rows * pb.D * size);
+    for (int m = 0; m < 3; ++m) over |= overlap(out, rows * hd * size, W[m], hd * pb.D * size);
+    return over;
+}
+
 bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
 // sum over batch items of f(len_b), key lengths copied from the device when set
@@ -474,7 +490,7 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
         } else {
             const void* const W[3] = {Wq, Wk, Wv};
             float* const qkv[3] = {ctx->qf, ctx->kf, ctx->vf};
-            const bool one_kernel = !planes && attn_takes_one_kernel(pb);
+            const bool one_kernel = !planes && attn_takes_one_kernel(pb) && !out_over_inputs(pb, X, W, out);
             if (one_kernel) e = hipSuccess;  // timed as attention
             else if (planes) e = launch_proj_split(pb, (const float*)X, (const float* const*)W, ctx->planes, 3, true, s);
             else e = launch_proj_generic(pb, X, W, qkv, 3, s);

@@ -295,6 +295,33 @@ def test_small_float_calls_in_one_kernel(shape, scheme):
         test_left_out_rows_are_zeros_beside_infinite_keys(shape, scheme, "f32", 0)
 
 
+@pytest.mark.parametrize("over", ["X", "X shifted", "Wv"])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+def test_small_float_call_over_its_own_inputs(over, scheme):
+    """`out` in the memory of X or of a weight matrix: every input is read before it is written over."""
+    import torch
+    B, n, D, H, d, p = 64, 16, 128, 8, 16, 8
+    if over == "Wv":
+        B, n = 16, 8              # as many floats as d_model * n_heads * d_k
+    w = hp.custom_workload("in_place", B, n, D, H, d, p, "f32", scheme, 7700 + n)
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = None
+    run = hp.GpuRun(w, stored)
+    try:
+        if over == "X":
+            run.out = run.X
+        elif over == "X shifted":
+            room = torch.empty(run.X.numel() + 40 * D, dtype=run.X.dtype, device=run.X.device)
+            run.X = room[:run.X.numel()].view(run.X.shape).copy_(run.X)
+            run.out = room[40 * D:].view(run.X.shape)
+        else:
+            run.out = run.W[2].view(B, n, D)
+        got, _ = run.forward(scheme)
+    finally:
+        run.close()
+    hp.tol_check(got, hp.oracle_forward(w, f64, scheme, 0.0), "f32")
+
+
 # ---- float path, steady states: many slices of d_model, many key tiles ----------------------------------------
 @pytest.mark.parametrize("shape", [
     # B, n, D, H, d, p
