@@ -268,6 +268,32 @@ def test_float_attention_on_planes_beside_values_not_finite(shape):
     test_an_infinite_value_of_one_column_stays_in_it(shape)
 
 
+@pytest.mark.parametrize("shape", [PLANE_SHAPES[1], PLANE_SHAPES[6]])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+@pytest.mark.parametrize("top,scale", [(2e8, 1.0), (2e9, 1.0), (2e9, -0.1), (2e10, 1.0), (1e12, 0.3), (1e30, 1.0), (3e38, 1.0), (3e38, 1e6)])
+def test_float_attention_on_planes_of_large_scores(shape, scheme, top, scale):
+    """score_ij = +-top x_i x_j, x growing from 1/n to 1: finite, and so far apart that a row's output is the value
+    vector of its largest score."""
+    import torch
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("large_scores", B, n, D, H, d, p, "f32", scheme, 7350 + n)
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = None
+    for k, size in (("Wq", 2.0), ("Wk", top / 2.0 / abs(scale))):
+        stored[k].zero_()
+        stored[k][0, 0::d] = size
+    stored["Wv"][0] = 0.0
+    stored["X"][:, :, 0] = torch.arange(1, n + 1) / n
+    for k in stored:
+        f64[k] = None if stored[k] is None else stored[k].double().numpy()
+    run = hp.GpuRun(w, stored, scale=scale)
+    try:
+        got, _ = run.forward(scheme)
+    finally:
+        run.close()
+    hp.tol_check(got, hp.oracle_forward(w, f64, scheme, scale), "f32")
+
+
 # ---- small float calls in one kernel: every number of row and column blocks, slices of d_model whole and cut
 @pytest.mark.parametrize("shape", [
     # B, n, D, H, d, p
