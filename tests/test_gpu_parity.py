@@ -294,6 +294,48 @@ def test_float_attention_on_planes_of_large_scores(shape, scheme, top, scale):
     hp.tol_check(got, hp.oracle_forward(w, f64, scheme, scale), "f32")
 
 
+# ---- float storage near the ends of float's range: X, Wq, Wk, Wv times powers of two.  Below 2^-109 a bfloat16 no longer
+# holds the last bits of a float, from 2^111 on its planes no longer hold the value
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (2, 24, 36, 3, 20, 8),        # one kernel
+    (2, 500, 296, 8, 64, 50),     # projection into floats
+    (32, 100, 24, 7, 73, 25),
+    (16, 250, 40, 8, 64, 25),     # and into planes
+    (16, 250, 136, 8, 128, 25),
+])
+@pytest.mark.parametrize("powers", [
+    (-122, 100, 100, 100),        # x
+    (0, -122, 100, 0),            # q
+    (0, 100, -122, 0),            # k
+    (0, 0, 0, -122),              # v and the output
+    (100, -100, -100, -100),
+    (125, -125, -125, -125),      # no planes of x
+    (0, 124, -124, 0),            # of q
+    (0, -124, 124, 0),            # of k
+    (0, 0, 0, 113),               # of v; sums of 500 of them before they are divided
+])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+def test_float_values_near_the_ends_of_the_range(shape, powers, scheme):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("range_ends", B, n, D, H, d, p, "f32", scheme, 7800 + n + D)
+    stored, f64 = inputs.make_inputs(w)
+    for k, e in zip(("X", "Wq", "Wk", "Wv"), powers):
+        stored[k] *= 2.0 ** e
+        f64[k] = stored[k].double().numpy()
+        assert np.isfinite(f64[k]).all()
+    stored["lens"] = None
+    scale = 2.0 ** -(2 * powers[0] + powers[1] + powers[2]) / np.sqrt(d)
+    if powers[0] == -122:
+        scale = 1.0               # a score is 2^-44: no larger scale than float has is needed
+    run = hp.GpuRun(w, stored, scale=scale)
+    try:
+        got, _ = run.forward(scheme)
+    finally:
+        run.close()
+    hp.tol_check(got, hp.oracle_forward(w, f64, scheme, scale), "f32")
+
+
 # ---- small float calls in one kernel: every number of row and column blocks, slices of d_model whole and cut
 @pytest.mark.parametrize("shape", [
     # B, n, D, H, d, p
