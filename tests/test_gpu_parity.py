@@ -336,6 +336,62 @@ def test_float_values_near_the_ends_of_the_range(shape, powers, scheme):
     hp.tol_check(got, hp.oracle_forward(w, f64, scheme, scale), "f32")
 
 
+# ---- float storage, key lengths: what the padding holds changes neither the other rows nor the time
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (32, 32, 128, 8, 32, 8),      # one kernel
+    (8, 200, 200, 7, 73, 25),     # projection into floats
+    (8, 512, 264, 12, 64, 64),    # and into planes
+    (8, 500, 264, 8, 128, 50),
+])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+@pytest.mark.parametrize("flags", [0, ar.ATTN_FLAG_SKIP_PADDED_ROWS])
+def test_float_padding_of_any_value(shape, scheme, flags):
+    import torch
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("padding", B, n, D, H, d, p, "f32", scheme, 7900 + n + D)
+    stored, f64 = inputs.make_inputs(w)
+    lens = np.asarray([n // 2 + 5 * b % (n // 2) for b in range(B)], dtype=np.int32)
+    lens[0] = n
+    stored["lens"] = lens
+    ref = hp.oracle_forward(w, f64, scheme, 0.0, lens=lens, skip_padded_rows=flags != 0)
+    run = hp.GpuRun(w, stored, flags=flags)
+    clean = run.X.clone()
+    first, times = None, {}
+    try:
+        for fill in (0.0, float("nan"), float("inf"), -3e38):
+            run.X.copy_(clean)
+            for b, L in enumerate(lens):
+                run.X[b, int(L):] = fill
+            got, _ = run.forward(scheme)
+            for b, L in enumerate(lens):
+                if flags:
+                    assert np.all(got[b, L:] == 0.0)
+                hp.tol_check(got[b, :L], ref[b, :L], "f32")
+            kept = [got[b, :L] for b, L in enumerate(lens)]
+            first = first or kept
+            # query rows of padding that are produced and not all NaN take their tile to float arithmetic: same values,
+            # other roundings, other times
+            alike = flags != 0 or fill == 0.0 or fill != fill
+            if alike:
+                assert all(np.array_equal(x, y) for x, y in zip(first, kept))
+            best = float("inf")
+            for _ in range(5):
+                ar.attn_profile(run.ctx, True)
+                for _ in range(10):
+                    ar.attn_forward(run.ctx, run.X, *run.W, scheme, run.out)
+                t = ar.attn_profile_read(run.ctx)
+                ar.attn_profile(run.ctx, False)
+                best = min(best, t["ms_projection"] + t["ms_attention"])
+            times[fill] = best
+            print(f"[padding] of {fill}: {best:.4f} ms", flush=True)
+            if alike:
+                assert best < 2.0 * times[0.0]      # 1.0 to 1.25 measured
+        torch.cuda.synchronize()
+    finally:
+        run.close()
+
+
 # ---- small float calls in one kernel: every number of row and column blocks, slices of d_model whole and cut
 @pytest.mark.parametrize("shape", [
     # B, n, D, H, d, p
