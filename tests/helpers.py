@@ -128,6 +128,15 @@ class GpuRun:
             full[b, :L] = host[offs[b]:offs[b] + L]
         return full, stats
 
+    def kernels(self, scheme):
+        """Names of the kernels that a forward pass launches, with their template arguments."""
+        from torch.profiler import ProfilerActivity, profile
+        self.torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            ar.attn_forward(self.ctx, self.X, self.W[0], self.W[1], self.W[2], scheme, self.out)
+            self.torch.cuda.synchronize()
+        return [e.name.replace("(anonymous namespace)::", "") for e in p.events() if "attnring::" in e.name]
+
     def close(self):
         if self.ctx is not None:
             self.torch.cuda.synchronize()

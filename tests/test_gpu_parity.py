@@ -195,27 +195,60 @@ def test_an_infinite_value_of_one_column_stays_in_it(shape):
     hp.tol_check(got, ref, "f32")
 
 
-# ---- float projection on products of bfloat16 planes: every tile that the size selects, slices of d_model cut and
-# whole, odd and even in number, columns in no whole pieces; then a value without planes in one of the rows
-@pytest.mark.parametrize("shape", [
-    # B, n, D, H, d, p
-    (1, 40, 33, 2, 30, 8),        # 32 x 32 tiles with shared slices
-    (2, 500, 296, 8, 64, 50),     # 64 x 64 ones, ten slices of which the last is cut
-    (2, 500, 260, 7, 73, 50),     # the same, 511 columns
-    (5, 600, 31, 8, 64, 60),      # one slice: a tile for every wavefront
-    (5, 600, 32, 6, 85, 60),
-    (3, 500, 40, 8, 64, 50),      # 64 x 128 tiles, one whole slice and a cut one
-    (3, 500, 128, 8, 64, 50),     # four slices
-    (2, 512, 70, 12, 64, 64),     # 128 x 96 tiles
-    (2, 512, 96, 11, 67, 64),     # 737 columns, three slices
-    (4, 300, 40, 8, 128, 30),     # 128 x 128 tiles
-    (4, 300, 192, 8, 128, 30),
-])
-def test_float_projection_tiles(shape):
+# ---- float projection on products of bfloat16 planes: every kernel that a size selects, for what it stores (floats in
+# 16-byte pieces, heads in no whole ones, planes), slices of d_model cut and whole, odd and even in number; then a value
+# without planes in one of the rows.  The kernel is part of the table: a rule that moves a shape elsewhere fails here
+FLOATS, ODD, PLANES = 0, 1, 2
+PROJECTIONS = [
+    # kernel, tile and k shared by the wavefronts; what it stores, even number of columns; B, n, D, H, d, p
+    ("strands 2, 1, true", FLOATS, True, (1, 40, 100, 2, 20, 8)),
+    ("strands 2, 1, true", ODD, True, (1, 40, 33, 2, 30, 8)),
+    ("strands 2, 1, true", ODD, False, (3, 50, 295, 1, 31, 10)),
+    ("strands 2, 1, true", ODD, False, (2, 30, 3, 3, 5, 10)),      # d_model below a piece
+    ("strands 4, 2, true", FLOATS, True, (2, 300, 296, 8, 64, 50)),
+    ("strands 4, 2, true", ODD, True, (2, 299, 288, 6, 85, 23)),
+    ("strands 4, 2, true", ODD, False, (2, 300, 261, 7, 73, 50)),
+    ("strands 2, 1, false", FLOATS, True, (5, 600, 31, 8, 64, 60)),
+    ("strands 2, 1, false", FLOATS, True, (5, 600, 64, 8, 60, 60)),
+    ("strands 2, 1, false", FLOATS, True, (16, 128, 104, 8, 64, 16)),
+    ("strands 2, 1, false", FLOATS, True, (16, 128, 96, 8, 64, 16)),
+    ("strands 2, 1, false", ODD, True, (5, 600, 32, 6, 85, 60)),
+    ("strands 2, 1, false", ODD, False, (5, 600, 50, 7, 73, 60)),
+    ("strands 2, 1, false", PLANES, True, (16, 250, 64, 8, 64, 25)),
+    ("strands 2, 1, false", PLANES, True, (16, 250, 23, 8, 40, 25)),
+    ("split 1, 4", FLOATS, True, (8, 128, 72, 8, 64, 16)),
+    ("split 1, 4", FLOATS, True, (8, 126, 192, 8, 60, 18)),
+    ("split 1, 4", ODD, True, (8, 126, 96, 8, 62, 18)),
+    ("split 1, 4", ODD, False, (8, 126, 193, 7, 73, 18)),
+    ("split 1, 4", PLANES, True, (16, 250, 168, 8, 64, 25)),
+    ("split 2, 3", FLOATS, True, (16, 125, 160, 12, 64, 25)),
+    ("split 2, 3", ODD, True, (16, 125, 190, 10, 75, 25)),
+    ("split 2, 3", ODD, False, (16, 125, 170, 11, 67, 25)),
+    ("split 2, 3", PLANES, True, (8, 250, 168, 16, 48, 25)),
+    ("split 2, 4", FLOATS, True, (4, 300, 192, 16, 64, 30)),
+    ("split 2, 4", ODD, True, (4, 300, 200, 14, 73, 30)),
+    ("split 2, 4", ODD, False, (4, 300, 161, 15, 67, 30)),
+    ("split 2, 4", PLANES, True, (8, 250, 200, 16, 32, 25)),
+]
+
+
+@pytest.mark.parametrize("kernel,stored_as,even,shape", PROJECTIONS)
+def test_float_projection_tiles(kernel, stored_as, even, shape):
     B, n, D, H, d, p = shape
     w = hp.custom_workload("proj_tiles", B, n, D, H, d, p, "f32", FULL, 7100 + n + D)
+    stored, _ = inputs.make_inputs(w)
+    run = hp.GpuRun(w, stored)
+    try:
+        names = run.kernels(FULL)
+    finally:
+        run.close()
+    kind, tile = kernel.split(" ", 1)
+    want = f"proj_split_{'strands_' if kind == 'strands' else ''}kernel<(attnring::Form){stored_as}, {str(even).lower()}, {tile}>"
+    assert want in names[0] and len(names) == 2, names
+    assert ("attn_planes_kernel" in names[1]) == (stored_as == PLANES), names
     _run_and_compare(w, FULL)
-    test_an_infinite_value_of_one_column_stays_in_it(shape)
+    if n > 21 and D > 3:
+        test_an_infinite_value_of_one_column_stays_in_it(shape)
 
 
 # ---- float attention on products of bfloat16 planes: head sizes that fill their 32-column steps and not, both tile
