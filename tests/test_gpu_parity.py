@@ -255,7 +255,7 @@ def test_float_projection_tiles(kernel, stored_as, even, shape):
 # shapes, last tiles whole and cut, then lengths, a negative scale, and vectors without planes
 PLANE_SHAPES = [
     # B, n, D, H, d, p
-    (32, 128, 16, 8, 8, 32),
+    (4, 1024, 16, 8, 8, 32),
     (16, 256, 24, 8, 32, 64),
     (30, 186, 24, 6, 40, 31),
     (16, 250, 40, 8, 64, 25),
@@ -271,6 +271,11 @@ PLANE_SHAPES = [
 def test_float_attention_on_planes(shape, scheme):
     B, n, D, H, d, p = shape
     w = hp.custom_workload("planes", B, n, D, H, d, p, "f32", scheme, 7300 + n + d)
+    run = hp.GpuRun(w, inputs.make_inputs(w)[0])
+    try:
+        assert "attn_planes_kernel" in run.kernels(scheme)[1]
+    finally:
+        run.close()
     _, stats = _run_and_compare(w, scheme)
     assert (stats["phys_br"], stats["phys_bc"]) == (16, 16)
     assert stats["phys_tiles_executed"] == hp.expected_phys_blocks(w, scheme, block=16)
