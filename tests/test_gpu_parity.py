@@ -436,8 +436,9 @@ def test_float_padding_of_any_value(shape, scheme, flags):
     (3, 1, 4, 2, 4, 1),
     (1, 16, 64, 1, 64, 4),
     (2, 24, 36, 3, 20, 8),
-    (5, 32, 128, 7, 48, 8),
-    (32, 30, 252, 4, 64, 10),
+    (5, 32, 64, 7, 48, 8),
+    (32, 30, 188, 4, 64, 10),
+    (64, 16, 252, 8, 64, 4),      # the longest d_model
     (128, 33, 100, 1, 36, 11),
     (16, 64, 128, 8, 64, 16),
     (33, 50, 8, 31, 16, 25),      # nearly a counter slot for every workgroup
@@ -446,6 +447,12 @@ def test_float_padding_of_any_value(shape, scheme, flags):
 def test_small_float_calls_in_one_kernel(shape, scheme):
     B, n, D, H, d, p = shape
     w = hp.custom_workload("one_kernel", B, n, D, H, d, p, "f32", scheme, 7500 + n + D)
+    run = hp.GpuRun(w, inputs.make_inputs(w)[0])
+    try:
+        names = run.kernels(scheme)
+        assert len(names) == 1 and "proj_attn_small_kernel" in names[0], names
+    finally:
+        run.close()
     _, stats = _run_and_compare(w, scheme)
     assert stats["phys_tiles_executed"] == hp.expected_phys_blocks(w, scheme, block=16)
     lens = np.asarray([(5 * b) % (n + 1) for b in range(B)], dtype=np.int32)
