@@ -125,28 +125,25 @@ __global__ __launch_bounds__(256) void lens_from_offsets_kernel(const int32_t* _
     lens[b] = len < 0 ? 0 : (len > N ? N : len);
 }
 
-attn_status ensure_generic_workspace(attn_ctx* c)
+// The first `count` of q, k and v as floats: the q = k = v scheme uses one.
+attn_status ensure_generic_workspace(attn_ctx* c, int count)
 {
-    if (c->qf && c->kf && c->vf) return ATTN_OK;
     const size_t bytes = (size_t)c->cfg.batch * c->cfg.n_heads * c->cfg.n * c->cfg.d_k * sizeof(float);
     float** dst[3] = {&c->qf, &c->kf, &c->vf};
-    for (auto p : dst) {
-        if (*p) continue;
-        hipError_t e = hipMalloc((void**)p, bytes);
+    for (int m = 0; m < count; ++m) {
+        if (*dst[m]) continue;
+        hipError_t e = hipMalloc((void**)dst[m], bytes);
         if (e != hipSuccess) {
-            // all three or none: a later call must not find a partial workspace
-            for (auto r : dst) {
-                if (*r) (void)hipFree(*r);
-                *r = nullptr;
-            }
+            *dst[m] = nullptr;  // what there is stays: a later call asks for the rest again
             return hip_fail(c, "hipMalloc(float q/k/v workspace)", e);
         }
     }
     return ATTN_OK;
 }
 
-// Planes of q, k and v: what no value goes to (rows past n, columns past d_k) is zeros for good.  Half as large again as
-// floats; where they do not fit, planes[0] stays nullptr and calls go by way of floats.
+// Planes of q, k and v: what no value goes to (rows past n, columns past d_k) is zeros for good.  Six bytes a value, rows
+// in whole 32 columns and 64 rows a tile: half as large again as floats at d_k 64, 2.4 times at 40, six times at 8.  Where
+// they do not fit, planes[0] stays nullptr and calls go by way of floats.
 void try_planes(attn_ctx* c, const Problem& pb)
 {
     const size_t bytes = plane_bytes(pb);
@@ -346,7 +343,7 @@ attn_status attn_init(const attn_config* cfg, attn_ctx** out_ctx)
         if (attn_takes_planes(pb)) try_planes(c, pb);
     }
     if (!c->mfma_shape && !c->planes[0]) {
-        attn_status st = ensure_generic_workspace(c);
+        attn_status st = ensure_generic_workspace(c, 3);
         if (st != ATTN_OK) {
             snprintf(g_init_err, sizeof(g_init_err), "%s", c->err);
             free_all(c);
@@ -470,7 +467,7 @@ static attn_status forward_on(attn_ctx* ctx, const int32_t* row0, const void* X,
         ctx->last_phys = MFMA_BLOCK;
     } else {
         const bool planes = !sym && ctx->planes[0] != nullptr;
-        attn_status st = planes ? ATTN_OK : ensure_generic_workspace(ctx);
+        attn_status st = planes ? ATTN_OK : ensure_generic_workspace(ctx, sym ? 1 : 3);
         if (st != ATTN_OK) return st;
         if (scheme == ATTN_SCHEME_SYMMETRIC) {
             const size_t bytes = (size_t)cf.batch * cf.n_heads * cf.n * cf.n * sizeof(float);
