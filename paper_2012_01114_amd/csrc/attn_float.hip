@@ -1,6 +1,7 @@
 // Phases 1-3 (Sec. 3.1, Eq. (1)-(3)) in float arithmetic, for every shape the 16-bit matrix-core
-// kernels do not take: f32 storage, head sizes other than 64 and 128, unaligned pointers, and the
-// q = k = v scheme on them.  q, k, v: float [B][H][N][d], d <= 256.
+// kernels do not take (f32 storage, head sizes other than 64 and 128, unaligned pointers, and the q = k = v scheme
+// on them) and that neither attn_planes.hip (larger f32 calls) nor proj_attn_small.hip (small ones, which walk their
+// one tile by attn_rows.h as well) takes.  q, k, v: float [B][H][N][d], d <= 256.
 //
 // Bound by the float matrix cores (v_mfma_f32_16x16x4_f32: one fp32 fma per product; 157 TFLOP/s on
 // the chip).  An MFMA takes 32 cycles, so one operand read from LDS and the vector work of the
