@@ -32,21 +32,20 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16, published
 
 # HBM/fabric bytes per launch from rocprofv3 counter runs (FETCH_SIZE + WRITE_SIZE, each scaled by what
 # the same counter reads for a plain 1 GiB device copy: x2.00 and x1.00; see profiles/).  They hold for
-# the kernel sources with the hash below; with other sources the bench line carries null.
-TRAFFIC_SOURCES_SHA256 = "4466b4109266aa2b63e2b1981f05b382f90d3a66c6d46a58e409652d61619bce"
+# the sources of these kernels with the hash below; with other sources the bench line carries null.
+TRAFFIC_SOURCES = ("proj_mfma.hip", "attn_pipe.hip", "attn_common.h", "mfma_common.h", "common.h")
+TRAFFIC_SOURCES_SHA256 = "645439d39ffe17ca1fea7dd6cbc107b15e5e6a542038ff3875cbd58a369aa9f8"
 TRAFFIC_BYTES = {
-    "long": {"projection": int((2 * 589947 + 196640) * 1024), "attention": int((2 * 138849 + 65792) * 1024)},
-    "causal": {"projection": int((2 * 38104 + 36896) * 1024), "attention": int((2 * 18697 + 12480) * 1024)},
+    "long": {"projection": int((2 * 589947 + 196640) * 1024), "attention": int((2 * 142036 + 65792) * 1024)},
+    "causal": {"projection": int((2 * 38104 + 36896) * 1024), "attention": int((2 * 18739 + 12480) * 1024)},
 }
 
 
 def kernel_sources_sha256() -> str:
-    """Hash of what libattnring.so is built from (the probe library's source is not part of it)."""
-    import glob
+    """Hash of the sources of the kernels that TRAFFIC_BYTES is about."""
     import hashlib
-    from paper_2012_01114_amd import build as libbuild
     csrc = os.path.join(ROOT, "paper_2012_01114_amd", "csrc")
-    files = sorted([os.path.join(csrc, f) for f in libbuild.SOURCES] + glob.glob(os.path.join(csrc, "*.h")))
+    files = [os.path.join(csrc, f) for f in TRAFFIC_SOURCES]
     h = hashlib.sha256()
     for f in files:
         h.update(os.path.basename(f).encode())
