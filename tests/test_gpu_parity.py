@@ -211,35 +211,35 @@ PROJECTIONS = [
     ("strands 2, 1, false", FLOATS, True, (5, 600, 31, 8, 64, 60)),
     ("strands 2, 1, false", FLOATS, True, (5, 600, 32, 8, 60, 60)),
     ("strands 2, 1, false", FLOATS, True, (8, 70, 63, 8, 60, 14)),
+    ("strands 2, 1, false", FLOATS, True, (5, 600, 64, 8, 60, 60)),
     ("strands 2, 1, false", FLOATS, True, (8, 63, 64, 8, 60, 21)),
     ("strands 2, 1, false", ODD, True, (5, 600, 32, 6, 85, 60)),
     ("strands 2, 1, false", ODD, False, (5, 600, 50, 7, 73, 60)),
     ("strands 2, 1, false", PLANES, True, (16, 250, 32, 8, 64, 25)),
     ("strands 2, 1, false", PLANES, True, (16, 250, 23, 8, 40, 25)),
     ("split 1, 4", FLOATS, True, (8, 128, 72, 8, 64, 16)),
-    ("split 1, 4", FLOATS, True, (5, 600, 64, 8, 60, 60)),
     ("split 1, 4", FLOATS, True, (10, 128, 39, 8, 64, 16)),       # one whole slice and a cut one
     ("split 1, 4", FLOATS, True, (8, 126, 192, 8, 60, 18)),
     ("split 1, 4", ODD, True, (8, 126, 96, 8, 62, 18)),
     ("split 1, 4", ODD, False, (8, 126, 193, 7, 73, 18)),
     ("split 1, 4", PLANES, True, (16, 250, 168, 8, 64, 25)),
     ("split 1, 4", PLANES, True, (16, 250, 40, 8, 64, 25)),
-    ("split 1, 4", PLANES, True, (8, 250, 60, 16, 48, 25)),
+    ("strands 2, 1, false", PLANES, True, (8, 250, 60, 16, 48, 25)),
     ("split 2, 3", FLOATS, True, (16, 125, 164, 12, 64, 25)),
     ("split 2, 3", FLOATS, True, (10, 100, 40, 12, 64, 25)),
     ("split 2, 3", FLOATS, True, (10, 100, 64, 12, 64, 25)),
     ("split 2, 3", ODD, True, (16, 125, 190, 10, 75, 25)),
     ("split 2, 3", ODD, False, (16, 125, 170, 11, 67, 25)),
     ("split 2, 3", PLANES, True, (8, 250, 168, 16, 48, 25)),
-    ("split 2, 3", PLANES, True, (16, 250, 64, 8, 96, 25)),
+    ("split 2, 3", PLANES, True, (16, 250, 60, 12, 64, 25)),
     ("split 2, 4", FLOATS, True, (4, 300, 192, 16, 64, 30)),
     ("split 2, 4", FLOATS, True, (16, 128, 104, 8, 64, 16)),
     ("split 2, 4", FLOATS, True, (16, 128, 96, 8, 64, 16)),
-    ("split 2, 4", FLOATS, True, (20, 100, 33, 8, 64, 25)),
+    ("split 2, 4", FLOATS, True, (32, 100, 33, 12, 64, 25)),
     ("split 2, 4", ODD, True, (4, 300, 200, 14, 73, 30)),
     ("split 2, 4", ODD, False, (4, 300, 161, 15, 67, 30)),
     ("split 2, 4", PLANES, True, (8, 250, 200, 16, 32, 25)),
-    ("split 2, 4", PLANES, True, (8, 250, 56, 16, 32, 25)),
+    ("split 2, 4", PLANES, True, (10, 250, 56, 16, 32, 25)),
 ]
 
 
