@@ -43,9 +43,9 @@
  *   - float storage: operands keep all their bits and sums are float, on the float matrix cores or as
  *     products of three bfloat16 planes a value on the bfloat16 ones (projections; attention of larger calls).
  *     Of the nine products of planes the six largest are summed: what is left out is at most 2^-24 of |x y|, and
- *     a sum is rounded less often than on the float matrix cores.  Values of 2^111 and more, sums beyond 2^95 and
- *     what is not finite have no planes: results they reach are formed again in float arithmetic, at several times
- *     the time.
+ *     a sum is rounded less often than on the float matrix cores.  Values of 2^111 and more (2^42 in a projected q
+ *     or k), sums beyond 2^95 and what is not finite have no planes: results they reach are formed again in float
+ *     arithmetic, at several times the time.
  */
 #ifndef ATTNRING_H
 #define ATTNRING_H

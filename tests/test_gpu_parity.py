@@ -343,6 +343,37 @@ def test_float_attention_on_planes_of_large_scores(shape, scheme, top, scale):
     hp.tol_check(got, hp.oracle_forward(w, f64, scheme, scale), "f32")
 
 
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_float_attention_on_planes_of_products_that_cancel(scheme, sign):
+    """Every third key has products of -3 * 2^95 in the first columns and 3 * 2^95 in later ones: its score is zero, which
+    a sum of planes, 2^32 times as large, leaves float's range before it gets to."""
+    B, n, D, H, d, p = 16, 250, 40, 8, 128, 25
+    w = hp.custom_workload("cancel", B, n, D, H, d, p, "f32", scheme, 7370)
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = None
+    X, Wq, Wk, Wv = (stored[k] for k in ("X", "Wq", "Wk", "Wv"))
+    X[:, :, 0], X[:, :, 1] = 1.0, 0.0
+    X[:, 1::3, 1], X[:, 1::3, 2] = 1.0, 0.0
+    Wq.zero_()
+    Wk.zero_()
+    Wv[:2] = 0.0
+    for col, size in ((0, -1.5), (1, -1.5), (32, 1.0), (64, 1.0), (96, 1.0)):
+        Wq[0, col::d] = 2.0 ** 48
+        Wk[1, col::d] = sign * size * 2.0 ** 47
+    Wq[0, 2::d] = 1.0
+    Wk[2, 2::d] = 1.0
+    for k in stored:
+        f64[k] = None if stored[k] is None else stored[k].double().numpy()
+    run = hp.GpuRun(w, stored, scale=1.0)
+    try:
+        assert "attn_planes_kernel" in run.kernels(scheme)[1]
+        got, _ = run.forward(scheme)
+    finally:
+        run.close()
+    hp.tol_check(got, hp.oracle_forward(w, f64, scheme, 1.0), "f32")
+
+
 # ---- float storage near the ends of float's range: X, Wq, Wk, Wv times powers of two.  Below 2^-109 a bfloat16 no longer
 # holds the last bits of a float, from 2^111 on its planes no longer hold the value
 @pytest.mark.parametrize("shape", [
