@@ -81,8 +81,9 @@ typedef enum { ATTN_F32 = 0, ATTN_BF16 = 1 } attn_dtype;
 enum { ATTN_FLAG_NO_SKIP = 1u,
        /* Workgroup shape of the bf16 matrix-core path for d_k = 64, normally 128 query rows
         * (4 wavefronts): WIDE asks for 256 rows (8 wavefronts), NARROW for 128.  d_k = 128
-        * takes 256 rows.  Without either flag (and without FUSE_Q_PROJECTION) small launches take
-        * 32 rows per workgroup, for either d_k.  Results obey the same bars. */
+        * takes 256 rows.  Without either flag (and without FUSE_Q_PROJECTION) launches that would
+        * leave the chip idle take 32 to 128 rows per workgroup, whose wavefronts share the keys, for
+        * either d_k.  Results obey the same bars. */
        ATTN_FLAG_WIDE_TILES = 2u,
        ATTN_FLAG_NARROW_TILES = 4u,
        /* With key lengths: the padded vectors are left out as queries too.  A pair (i, j) of

@@ -16,14 +16,15 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libattnring.so")
 PROBE_LIB = os.path.join(HERE, "libattnprobe.so")   # ceilings probe: instrumentation, its own library
 SOURCES = ["attnring_api.hip", "generic_kernels.hip", "proj_split.hip", "attn_float.hip", "attn_planes.hip", "proj_attn_small.hip",
-           "proj_mfma.hip", "attn_pipe.hip", "attn_split.hip", "sym_pair.hip"]
+           "proj_mfma.hip", "attn_pipe.hip", "attn_split.hip", "attn_strands.hip",
+           "sym_pair.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# Loops start on a 64-byte line: where the walk of attn_pipe_kernel<128, FULL> happened to start was worth 4 to 7 %
+# Loops start on a 64-byte line (the kernels that walk through LDS): where the walk of attn_pipe_kernel<128, FULL> happened to start was worth 4 to 7 %
 # (one item of 4096 vectors, 4 heads: 94.8 -> 88.3 us, at the same instructions).  In the GEMMs it costs more than it
 # gives (960 x 1456 -> 1536: 20.7 -> 21.4).
-FLAGS_OF = {"attn_pipe.hip": ["-falign-loops=64"]}
+FLAGS_OF = {"attn_pipe.hip": ["-falign-loops=64"], "attn_strands.hip": ["-falign-loops=64"]}
 
 
 def _compile(src: str) -> str:

@@ -8,8 +8,8 @@
 // takes the 32-key blocks w, w + 4, ... (the ring is met in four strands), straight from memory (L2)
 // into operand registers, the next block's operands on their way while one is worked on, no barrier;
 // the four partial states (m, l, O) are merged through LDS at the end.  Four times the row tiles, a
-// quarter of the walk, for four times the reads of K and V per row: the larger kernel stays ahead
-// where its own workgroups fill the CUs (launch_attn in this file draws the line).
+// quarter of the walk, for four times the reads of K and V per row: the larger kernels, which pass them
+// through LDS, stay ahead where their workgroups fill the CUs (launch_attn in this file draws the line).
 //
 // Blocks with no needed pair are left out (Sec. 5.1); pair by pair masking only in blocks cut by the
 // diagonal or the key length.  Scores are computed transposed (S^T = K.Q^T), so that a lane holds 16
@@ -224,18 +224,39 @@ hipError_t launch_attn(const Problem& pb, const h16_t* q, const h16_t* k, const 
                        hipStream_t s, const bf16_t* X, const bf16_t* Wq)
 {
     const bool fuse = X != nullptr && Wq != nullptr;
-    // Measured (us, attn_pipe / attn_split, by the number of 32-row workgroups; FULL, then masked):
-    //   d_k = 64    84 (n 200) 10.8 / 7.9, 15.4 / 7.9     192 (n 512) 13.6 / 10.4, 17.5 / 10.1
-    //               256 (n 4096) 56 / 36, 58 / 35         384 (n 512) 14.3 / 15.3, 14.1 / 13.1
-    //               512 (n 2048) 32 / 36, 31 / 29         768 (n 512) 15 / 20, 15 / 17
-    //   d_k = 128   256 (n 512) 21 / 16, 23 / 16          512 (n 2048) 52 / 67, 51 / 54
-    // masked, key lengths, every query row produced (the call): 384 (n 512) 21.1 / 21.0, 512 (n 1024) 24.6 / 26.1, 512 (n
-    // 512) 20.0 / 21.0: the walks that the split shortens are short already.
-    const long split_wgs = (long)pb.B * pb.H * ((pb.N + 31) / 32);
-    const bool masked64 = pb.d == 64 && pb.scheme == SCHEME_CAUSAL;
-    const long most = !masked64 ? 256 : pb.lens && !pb.skip_rows ? 384 : 512;
-    if (asked_waves == 0 && !fuse && split_wgs <= most)
-        return launch_attn_split(pb, q, k, vt, out, s);
+    // Measured (us, one kernel; W: 128-row tiles of all heads; split: attn_split, 2 3 4: attn_strands with so many strands).
+    //   d_k = 64, FULL           n 32 W 272 pipe 7.7 split 6.6    n 256 W 64 pipe 10.5 split 8.3 4: 9.4    W 128 10.7 / 11.6 / 9.8
+    //     n 512 W 64 13.4 / 10.1 / 10.7    W 256 pipe 14.9 3: 14.7    n 1024 W 64 20.1 / 13.6 / 13.3    W 128 19.6 / 22.2 / 13.8
+    //     W 256 pipe 21.0 3: 19.3    n 4096 W 64 54.6 / 34.9 / 28.8    W 128 55 / 64 / 30    W 256 pipe 56 3: 46    n 1024 W 288
+    //     pipe 24.7 3: 31.8 (a second round of one workgroup per CU; pipe has three)
+    //   d_k = 64, masked         n 128 W 128 pipe 10.1 split 9.1 4: 9.0    n 256 W 128 11.7 / 10.6 / 9.8    n 512 W 160 pipe 14.9 3: 13.9
+    //     n 1024 W 288 pipe 21.9 3: 19.9    W 384 22.2 / 24.2    n 2048 W 256 pipe 32.2 3: 26.1 4: 24.3    W 512 35.2 / 33.5    W 640
+    //     37.8 / 45.3    n 8192 W 384 103 / 76
+    //   d_k = 128, FULL          n 192 W 64 pipe 14.0 split 11.8 2: 13.2    W 128 14.4 / 18.0 / 13.5    n 512 W 256 pipe 22.1 2: 20.2
+    //     n 1024 W 128 30.4 / 39.3 / 24.6    n 4096 W 256 pipe 89 2: 78    W 288 n 1024 32 / 47
+    //   d_k = 128, masked        n 100 W 128 pipe 13.4 2: 12.2    n 512 W 320 24.7 / 24.0    n 1024 W 512 40.6 / 35.8    W 640 47.8 / 48.9
+    //     n 4096 W 512 99.7 / 84.3    W 768 117 / 129
+    if (asked_waves == 0 && !fuse) {
+        const int n = pb.N;
+        const bool masked = pb.scheme == SCHEME_CAUSAL;
+        const long heads = (long)pb.B * pb.H;
+        const long w32 = heads * ((n + 31) / 32), w64 = heads * ((n + 63) / 64), w128 = heads * ((n + 127) / 128);
+        bool split = w32 <= (n <= 32 ? 640 : 256);
+        int strands = 0;
+        if (pb.d == 64) {
+            split = split && n < 1024;
+            // key lengths, every query row produced: the walks that the split shortens are short already
+            split = split || (masked && n <= 128 && w32 <= (pb.lens && !pb.skip_rows ? 384 : 512));
+            if ((w64 <= 256 && n > 64) || (masked && n >= 2048 && w128 <= 256)) strands = 4;
+            else if (w128 <= 256 && n > (masked ? 256 : 512)) strands = 3;
+            else if (masked && w128 <= (n >= 2048 ? 512 : n >= 1024 ? 288 : 0)) strands = 3;
+        } else {
+            if (w128 <= 256 && n > (masked ? 64 : 128)) strands = 2;
+            else if (masked && w128 <= (n >= 1024 ? 512 : n >= 512 ? 320 : 0)) strands = 2;
+        }
+        if (split) return launch_attn_split(pb, q, k, vt, out, s);
+        if (strands) return launch_attn_strands(pb, q, k, vt, out, strands, s);
+    }
     // d_k = 64: 128-row workgroups of 4 wavefronts, three of them per CU; d_k = 128: 256 rows, 8 wavefronts
     const int waves = pb.d == 128 ? 8 : asked_waves == 8 ? 8 : 4;
     return launch_attn_pipe(pb, q, k, vt, out, waves, s, X, Wq);

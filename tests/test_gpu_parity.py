@@ -788,6 +788,46 @@ def test_small_launches_share_the_keys(shape, scheme):
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
 
 
+# ---- launches that leave the chip idle otherwise: strands of wavefronts share the keys (no tile flag) ------
+@pytest.mark.parametrize("strands,shape", [
+    # B, n, D, H, d, p
+    (4, (1, 1030, 64, 3, 64, 103)),    # five tiles for the first strand, four for the others; six rows in the last
+    (4, (9, 140, 64, 9, 64, 35)),      # three tiles: a strand has none
+    (3, (2, 516, 64, 19, 64, 129)),    # nine tiles; partitions larger than a row tile
+    (2, (1, 1100, 64, 8, 128, 275)),   # d_k = 128
+    (2, (3, 150, 64, 20, 128, 30)),    # three tiles, two strands
+    (2, (3, 1030, 64, 11, 128, 103)),  # masked: 297 row tiles, a second round; heads that do not divide by eight
+])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+def test_strands_share_the_keys(strands, shape, scheme):
+    B, n, D, H, d, p = shape
+    if scheme == FULL and B * H * ((n + 127) // 128) > 256:
+        H = 8
+    w = hp.custom_workload("strands", B, n, D, H, d, p, "bf16", scheme, 8900 + n)
+    _run_and_compare(w, scheme, 0.0)
+    lens = np.random.default_rng(n + 3).integers(0, n + 1, B).astype(np.int32)
+    lens[-1] = n // 2 + 1
+    _run_and_compare(w, scheme, 0.0, lens=lens)
+    # padded rows left out: against the checker, and the same bits without skipping and in the packed layout
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = lens
+    outs = []
+    for noskip in (0, ar.ATTN_FLAG_NO_SKIP):
+        run = hp.GpuRun(w, stored, flags=ar.ATTN_FLAG_SKIP_PADDED_ROWS | noskip)
+        try:
+            got, stats = run.forward(scheme)
+            hp.check_counts(stats, hp.oracle_counts(w, scheme, lens, skip_padded_rows=True), noskip=bool(noskip))
+            outs.append(got)
+            if not noskip:
+                assert stats["phys_tiles_executed"] == hp.expected_phys_blocks(w, scheme, lens, skip_padded_rows=True)
+                outs.append(run.forward_packed(scheme, lens)[0])
+                assert any(f"attn_strands_kernel<{d}, {strands}," in k for k in run.kernels(scheme))
+        finally:
+            run.close()
+    hp.tol_check(outs[0], hp.oracle_forward(w, f64, scheme, 0.0, lens=lens, skip_padded_rows=True), w.dtype)
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
 # ---- masked scheme, one row tile per workgroup with the heads in turn ------------------------------------
 @pytest.mark.parametrize("shape", [
     (3, 700, 64, 13, 64, 100),    # d_k = 64, heads that do not divide by eight
