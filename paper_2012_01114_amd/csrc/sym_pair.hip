@@ -2,16 +2,30 @@
 //
 // Eq. (4): with one set of vectors z in all three roles, w'_ij = w'_ji, so phase 1 needs one
 // element of every symmetric pair; phases 2 and 3 do not share it (Sec. 4.1).  Here the unit of
-// reuse is a 128 x 128 score tile.  Workgroup (A, B), A >= B, computes S_AB = z_A . z_B^T once with
-// MFMAs and uses it twice:
+// reuse is a 128 x 128 score tile.  S_AB = z_A . z_B^T is computed once with MFMAs and used twice:
 //     as it stands      for the rows of A against the keys of B   (phases 2 and 3 of row block A)
 //     transposed        for the rows of B against the keys of A   (phases 2 and 3 of row block B)
-// The transposition goes through LDS: the tile is stored as fp32 while the first use runs from
-// registers, and read back in the accumulator layout of the other orientation, so the second use
-// runs the very code of the first.  Each use yields a partial row state (m, l, O) over 128 keys;
-// the T = n/128 partial states of a row block (one per key tile, whichever workgroup made them) are
-// merged by a second kernel.  The scores never leave the chip; what does is 128 (d + 2) floats per
-// use.  Tiles on the diagonal (A == B) are used once.
+// A workgroup owns row tile A and meets a run of its partners A, A + 1, .. (mod T = n/128; every
+// unordered pair of tiles has one owner, a circulant choice).  The first use adds to sums it keeps in
+// registers over the whole run, the second yields a partial row state (m, l, O) of B over the 128 keys
+// of A; a second kernel merges the states of a row block.  The scores never leave the chip; what does
+// is 128 (d + 2) floats per second use and per run.  Tiles on the diagonal (A == B) are used once.
+//
+// Both uses take their exponentials from the accumulators: the reference of a row is its own score
+// |z_i|^2 (known ahead of any product, and among the row's largest: s_ij <= |z_i| |z_j|) less 4, so no
+// maximum is searched for, and a row has one reference in every workgroup.  The weight of the row's own
+// score is 2^4; a score that exceeds it by 11 (base 2) makes a weight of 2^15, towards the end of half
+// precision, and then the reference is raised to the largest score of the tile (first use: before the
+// exponentials are taken; second: they are taken again).  Weights so small that half precision loses bits of them are
+// 2^-18 of the own score's or less.
+// The exponentials of the second use are stored to LDS in half precision, [row of A][row of B], and
+// read back as operands by the transposing read.  Row sums are MFMAs with ones: sums of the weights
+// as rounded, the same for either use.
+//
+// What bounds it: exponentials (16 cycles per 64 pairs and use) and the partial states.  96 heads of
+// 512 at d_k = 64, us (pairs, merge): 30.9, 10.3 with a workgroup per pair of tiles, scores staged in fp32,
+// maxima and a state per use, 22.2, 7.3 so; 32 heads of 2048 159 -> 93 together, 8 heads of 2048 at d_k = 128
+// 97 -> 62.  Of that the barriers that leave memory alone gave 4, addresses recomputed per tile (no spills) 4.
 //
 // The paper's selection rule (Sec. 4.2: circulant diagonals 0 .. floor(P/2) of the P x P matrix of
 // (n/P)-row tiles, the middle one computed by both owners when P is even) fixes WHICH element of a
@@ -22,20 +36,22 @@
 // Both operands of the score MFMAs are the same half-precision z (the scale is applied to the
 // fp32 scores), so S_AB and S_BA^T are equal bit for bit, as Eq. (4) has it; with every tile
 // computed in its own orientation instead (the debug mode) the outputs are the same bits.
+#include <type_traits>
+
 #include "attn_common.h"
 
 namespace attnring {
 namespace {
 
 constexpr int ST = 128;           // rows and keys of a score tile
+constexpr float OWN_WEIGHT = 4.f; // base-2 logarithm of the weight of a row's own score
 
-// Float offset of element (row, col) of the staged 128 x 128 tile: rows of 512 bytes, their 16-byte
-// chunks XOR-ed with four bits of the row, so that the 16 rows one pass of the 16-byte reads takes
-// meet 64 different banks, and so do the two rows (4 apart) that a store instruction writes.
-__device__ __forceinline__ int staged(int row, int col)
+// Byte offset of the weight of (row of A, row of B) in LDS: rows of 256 bytes, their 16-byte chunks XOR-ed with four bits
+// of the row: 16 rows of one 8-byte store meet all banks, and the four rows of a transposing read four pairs of chunks.
+__device__ __forceinline__ int weight_at(int row, int col)
 {
-    const int f = (row & 3) | (((row >> 3) & 1) << 2) | (((row >> 2) & 1) << 3);
-    return row * ST + ((((col >> 2) ^ f) << 2) | (col & 3));
+    const int f = ((row & 7) << 1) | ((row >> 3) & 1);
+    return row * 256 + (((col >> 3) ^ f) << 4) + ((col & 7) << 1);
 }
 
 template <int DK>
@@ -43,26 +59,35 @@ struct Sym {
     static constexpr int NKS = DK / 16, NDB = DK / 32;
     static constexpr int KROWB = DK * 2;             // bytes of a key row in LDS
     static constexpr int K_BYTES = ST * KROWB;       // K tile: 128 keys
-    static constexpr int V_TILE = DK * 64 * 2;       // one 64-key block of V^T
-    static constexpr int V_BYTES = 2 * V_TILE;
-    static constexpr int S_BYTES = ST * ST * 4;
-    // The staged scores take the place of the K tile, which is no longer read by then: 80 KiB at
-    // d_k = 64, two workgroups per CU (with regions of their own one: 96 heads of 512, 44 against 29 us per launch).
-    static constexpr int LDS_BYTES = V_BYTES + S_BYTES;
+    static constexpr int V_BYTES = 2 * DK * 64 * 2;  // V^T of 128 keys, two 64-key blocks
+    static constexpr int W_BYTES = ST * ST * 2;      // the weights of the second use, in the place of the K tile
+    // d_k = 64: V^T of A stays, and the next tiles wait in registers.  d_k = 128: V^T of A takes the place of that of B, and
+    // nothing waits (256 registers).  Two workgroups per CU either way.
+    static constexpr bool RESIDENT = DK == 64;
+    static constexpr int KW_BYTES = K_BYTES > W_BYTES ? K_BYTES : W_BYTES;
+    static constexpr int LDS_BYTES = KW_BYTES + (RESIDENT ? 2 : 1) * V_BYTES;
 };
 
 // z rows [row0, row0 + 128) of one head as a K tile: rows of KROWB bytes, 16-byte chunks swizzled.
 template <int DK>
-__device__ __forceinline__ void load_k_tile(unsigned char* dst, const h16_t* kh, int row0, int tid)
-{
-    constexpr int CPR = DK / 8;
-    const u32x4* src = (const u32x4*)(kh + (size_t)row0 * DK);
+struct KTile {
+    static constexpr int CPR = DK / 8, PER = ST * CPR / 256;
+    u32x4 reg[PER];
+    __device__ __forceinline__ void fetch(const h16_t* kh, int row0, int tid)
+    {
+        const u32x4* src = (const u32x4*)(kh + (size_t)row0 * DK);
 #pragma unroll
-    for (int c = tid; c < ST * CPR; c += 256) {
-        const int row = c / CPR, p = c % CPR;
-        *(u32x4*)(dst + row * (DK * 2) + swz<DK * 2>(p, row) * 16) = src[c];
+        for (int u = 0; u < PER; ++u) reg[u] = src[tid + 256 * u];
     }
-}
+    __device__ __forceinline__ void stage(unsigned char* dst, int tid) const
+    {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int c = tid + 256 * u, row = c / CPR, p = c % CPR;
+            *(u32x4*)(dst + row * (DK * 2) + swz<DK * 2>(p, row) * 16) = reg[u];
+        }
+    }
+};
 // V^T of the same rows: two 64-key blocks of [DK][64], rows of 128 bytes, chunks swizzled; through
 // registers, so that the request can go out long before the tile in LDS is free.
 template <int DK>
@@ -85,177 +110,392 @@ struct VtTile {
     }
 };
 
-// Phases 2 and 3 (Eq. (2), (3)) of 32 rows (one per lane pair) over the 128 keys of a tile whose
-// scores S[kb][r] are in accumulator layout (key kb * 32 + acc_row(r, g)); keys at or past
-// `keys_left` are not there.  V^T of the tile in LDS at vt.  Writes the partial state.
-template <int DK>
-__device__ __forceinline__ void softmax_pv_store(f32x16 (&S)[4], int keys_left, const unsigned char* vt, int ln, int g,
-                                                 bool row_live, float* __restrict__ pm, float* __restrict__ pl,
-                                                 float* __restrict__ po)
+// A workgroup barrier that orders LDS only: __syncthreads would also wait for the tiles on their way from memory and for
+// the stores of states, 1 to 2 us each.
+__device__ __forceinline__ void lds_barrier()
 {
-    constexpr int NDB = DK / 32;
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = kb * 32 + acc_row(r, g);
-            S[kb][r] = key < keys_left ? S[kb][r] : -INFINITY;
-            mx = fmaxf(mx, S[kb][r]);
-        }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float ref = mx > -INFINITY ? mx : 0.f;
-    float l = 0.f;
-    f32x16 O[NDB];
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) O[db][e] = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-        u32x4 P[2];
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float p0 = __builtin_amdgcn_exp2f(S[kb][8 * hf + 2 * w] - ref);
-                const float p1 = __builtin_amdgcn_exp2f(S[kb][8 * hf + 2 * w + 1] - ref);
-                P[hf][w] = pack_f16(p0, p1);
-                l += p0 + p1;
-            }
-        const unsigned char* blk = vt + (kb >> 1) * (DK * 128);
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-            for (int db = 0; db < NDB; ++db) {
-                const int row = db * 32 + ln;
-                const int chunk = swz<128>(2 * hf + g, row) ^ (4 * (kb & 1));
-                const u32x4 vf = *(const u32x4*)(blk + row * 128 + chunk * 16);
-                O[db] = mfma32h(vf, P[hf], O[db]);
-            }
-    }
-    l += __shfl_xor(l, 32, 64);
-    if (row_live) {
-        if (g == 0) { *pm = mx; *pl = l; }
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                f32x4 v = {O[db][4 * r4 + 0], O[db][4 * r4 + 1], O[db][4 * r4 + 2], O[db][4 * r4 + 3]};
-                *(f32x4*)(po + db * 32 + 8 * r4 + 4 * g) = v;
-            }
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Grid: (pairs, batch * heads).  all_ordered: every ordered pair of tiles computed in its own
-// orientation, nothing reused (the debug mode); else the unordered pairs A >= B.
+// Adds the squares of eight half-precision values, in order.
+__device__ __forceinline__ float add_squares(u32x4 v, float x)
+{
+    const f16x8 h = __builtin_bit_cast(f16x8, v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x = fmaf((float)h[e], (float)h[e], x);
+    return x;
+}
+
+// V^T of one 16-key group, group 2 kb + hf of the 128 keys in LDS at vt, as operands.
 template <int DK>
-__global__ __launch_bounds__(256) void sym_pair_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ z,
-                                                       const h16_t* __restrict__ zt, float* __restrict__ part_m,
-                                                       float* __restrict__ part_l, float* __restrict__ part_o,
-                                                       int T, bool all_ordered, float c2)
+__device__ __forceinline__ void read_group(u32x4 (&vf)[DK / 32], const unsigned char* vt, int kb, int hf, int ln, int g)
+{
+#pragma unroll
+    for (int db = 0; db < DK / 32; ++db) {
+        const int row = db * 32 + ln;
+        const int chunk = swz<128>(2 * hf + g, row) ^ (4 * (kb & 1));
+        vf[db] = *(const u32x4*)(vt + (kb >> 1) * (DK * 128) + row * 128 + chunk * 16);
+    }
+}
+// Ones for the keys of such a group that are there, `keys` of the 128, zeros for the others (whose rows of V^T are zeros, and
+// whose weights are finite).
+__device__ __forceinline__ u32x4 ones_of_group(int keys, int kb, int hf, int g)
+{
+    constexpr unsigned ONES = 0x3C003C00u;
+    u32x4 ones = {ONES, ONES, ONES, ONES};
+    if (keys < ST)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const int left = keys - (kb * 32 + acc_row(8 * hf + 2 * w, g));
+            ones[w] = left > 1 ? ONES : left == 1 ? ONES & 0xFFFFu : 0u;
+        }
+    return ones;
+}
+// O += V^T.P^T and l += 1.P^T (Eq. (3), (2)) of such a group.
+template <int DK>
+__device__ __forceinline__ void add_group(f32x16 (&O)[DK / 32], f32x16& l, u32x4 P, const u32x4 (&vf)[DK / 32], u32x4 ones)
+{
+    l = mfma32h(ones, P, l);
+#pragma unroll
+    for (int db = 0; db < DK / 32; ++db) O[db] = mfma32h(vf[db], P, O[db]);
+}
+
+__device__ __forceinline__ unsigned max_f16(unsigned a, unsigned b)
+{
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b)));
+}
+// Whether one of two weights (not negative) is 2^15 or more.
+__device__ __forceinline__ bool too_large(unsigned m) { return (m & 0xFFFFu) >= 0x7800u || m >= 0x78000000u; }
+
+template <int DK>
+__device__ __forceinline__ void store_state(const f32x16 (&O)[DK / 32], float m, float l, int g, float* __restrict__ pm,
+                                            float* __restrict__ pl, float* __restrict__ po)
+{
+    if (g == 0) { *pm = m; *pl = l; }
+#pragma unroll
+    for (int db = 0; db < DK / 32; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+            *(f32x4*)(po + db * 32 + 8 * r4 + 4 * g) = f32x4{O[db][4 * r4], O[db][4 * r4 + 1], O[db][4 * r4 + 2], O[db][4 * r4 + 3]};
+}
+
+// Partners of row tile A that it owns: A .. A + owned(A, T) - 1 (mod T).
+__device__ __forceinline__ int owned(int A, int T) { return (T + 1) / 2 + (T % 2 == 0 && A < T / 2 ? 1 : 0); }
+
+// Work items: (head, row tile, run of `run` partners), runs in turn.  all_ordered: every ordered pair of tiles computed in
+// its own orientation, nothing reused (the debug mode): the runs are followed by the tiles of other owners, one by one.
+template <int DK>
+__global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ z,
+                                                          const h16_t* __restrict__ zt, float* __restrict__ part_m,
+                                                          float* __restrict__ part_l, float* __restrict__ part_o,
+                                                          bf16_t* __restrict__ out, int T, int runs, int run, bool all_ordered, float c2, int heads)
 {
     typedef Sym<DK> Y;
-    constexpr int NKS = Y::NKS;
+    constexpr int NKS = Y::NKS, NDB = Y::NDB;
     __shared__ __attribute__((aligned(16))) unsigned char lds[Y::LDS_BYTES];
-    unsigned char* vt = lds;
-    unsigned char* kt = lds + Y::V_BYTES;
-    float* sc = (float*)(lds + Y::V_BYTES);
+    __shared__ __attribute__((aligned(16))) float ref_b[ST];
+    __shared__ float max_b[4][ST], weight_b[4][ST];
+    __shared__ unsigned raised;
+    unsigned char* const kt = lds;  // K tile of B, then the weights
+    unsigned char* const vt = lds + Y::KW_BYTES;
+    unsigned char* const vt_a = Y::RESIDENT ? vt + Y::V_BYTES : vt;
 
-    const int tid = threadIdx.x, lane = tid & 63, ln = lane & 31, g = lane >> 5;
+    const int tid0 = threadIdx.x, tid = tid0, lane = tid & 63, ln = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int bh = blockIdx.y;
-    int A, B;
-    if (all_ordered) {
-        A = blockIdx.x / T;
-        B = blockIdx.x - A * T;
-    } else {
-        A = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
-        while (A * (A + 1) / 2 > (int)blockIdx.x) --A;
-        while ((A + 1) * (A + 2) / 2 <= (int)blockIdx.x) ++A;
-        B = blockIdx.x - A * (A + 1) / 2;
+    // Where the heads divide over the XCDs an XCD has whole heads; the row tiles with the most partners first.
+    const int nh = heads % 8 == 0 ? heads / 8 : heads, p = heads % 8 == 0 ? blockIdx.x >> 3 : blockIdx.x;
+    const int item = p / nh, bh = (heads % 8 == 0 ? (blockIdx.x & 7) * nh : 0) + p - item * nh;
+    const int A = item / runs, turn = item - A * runs;
+    if (A >= T) return;
+    const int mine = owned(A, T), own_runs = all_ordered ? runs - T : runs;
+    int j0 = turn * run, j1 = min(j0 + run, mine);
+    if (all_ordered && turn >= own_runs) {
+        j0 = mine + turn - own_runs;
+        j1 = min(j0 + 1, T);
     }
+    if (j0 >= j1) return;
+
     const int N = pb.N, Npad = pb.Npad;
     const h16_t* zh = z + (size_t)bh * Npad * DK;
     const h16_t* zth = zt + (size_t)bh * Npad * DK;
-    const bool twice = !all_ordered && A != B;
+    auto partner = [&](int j) { return A + j < T ? A + j : A + j - T; };
 
-    // ---- phase 1 (Eq. (1)), once: S^T = z_B . z_A^T, the wavefront's 32 rows of A against 128 keys of B ----
+    KTile<DK> kr;
     VtTile<DK> vr;
-    vr.fetch(zth, B * ST, tid);
     const int ia = A * ST + wave * 32 + ln;  // this lane's row of A
     u32x4 qf[NKS];
+    auto fetch_q = [&](int at) {
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const u32x4*)(zh + (size_t)ia * DK + ks * 16 + g * 8);
-    load_k_tile<DK>(kt, zh, B * ST, tid);
+        for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const u32x4*)(zh + at + ks * 16);
+    };
+    kr.fetch(zh, partner(j0) * ST, tid);
+    vr.fetch(zth, partner(j0) * ST, tid);
+    fetch_q(ia * DK + g * 8);
+    if constexpr (Y::RESIDENT) {
+        VtTile<DK> va;
+        va.fetch(zth, A * ST, tid);
+        __builtin_amdgcn_sched_barrier(0);
+        va.stage(vt_a, tid);
+    }
+    kr.stage(kt, tid);
     vr.stage(vt, tid);
-    if (twice) vr.fetch(zth, A * ST, tid);  // V^T of A, for the second use
-    __syncthreads();
-    f32x16 S[4];
+    if (tid == 0) raised = 0u;
+    float ref = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
+    for (int ks = 0; ks < NKS; ++ks) ref = add_squares(qf[ks], ref);
+    ref = fmaf(c2, ref + __shfl_xor(ref, 32, 64), -OWN_WEIGHT);
+    f32x16 O[NDB], l;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) S[kb][e] = 0.f;
+    for (int e = 0; e < 16; ++e) {
+        l[e] = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            const int row = kb * 32 + ln;
-            const u32x4 kf = *(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + g, row) * 16);
-            S[kb] = mfma32h(kf, qf[ks], S[kb]);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) S[kb][e] *= c2;  // scale and base-2 exponent, on the fp32 score
+        for (int db = 0; db < NDB; ++db) O[db][e] = 0.f;
     }
-    // ---- counts: logical tiles the selection rule picks, over the regions this workgroup covers ----
-    {
-        unsigned long long cnt = 0;
-        const int ia0 = (int)cdiv_b(A * ST, cc), ia1 = (int)cdiv_b(min((A + 1) * ST, N), cc);
-        const int ib0 = (int)cdiv_b(B * ST, cc), ib1 = (int)cdiv_b(min((B + 1) * ST, N), cc);
-        const int na = ia1 - ia0, nb = ib1 - ib0, P = pb.P;
-        for (int e = tid; e < na * nb; e += 256) {
-            const int I = ia0 + e / nb, J = ib0 + e % nb;
-            const int gd = ((I - J) % P + P) % P, gt = ((J - I) % P + P) % P;
-            cnt += (all_ordered || 2 * gd <= P) ? 1u : 0u;          // region (A, B)
-            if (twice) cnt += (2 * gt <= P) ? 1u : 0u;              // region (B, A), met transposed
-        }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-        // 32 x 32 score blocks issued: the key blocks that hold a key, for a wavefront that holds a row
-        unsigned phys = 0;
-        if (A * ST + wave * 32 < N) phys = (unsigned)min(4, (N - B * ST + 31) / 32);
-        if (lane == 0) count_add(pb.counters, (unsigned)(blockIdx.y * gridDim.x + blockIdx.x) * 4u + wave, cnt, phys);
-    }
+    unsigned long long cnt = 0;
+    unsigned phys = 0;
 
-    if (twice) {
-        __syncthreads();  // nobody reads the K tile any more
-        // staged for the other orientation: sc[key of B][row of A]
+#pragma nounroll
+    for (int j = j0; j < j1; ++j) {
+        // Addresses that depend on the thread only, from an opaque copy of its number: else they are kept over the loop, more
+        // of them than there are registers.
+        int tid = tid0;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, ln = lane & 31, g = lane >> 5;
+        const int B = partner(j);
+        const bool twice = !all_ordered && j > 0;
+        const int keys_left = N - B * ST;
+        if constexpr (!Y::RESIDENT) {  // not kept over a tile: the registers are wanted
+            int at = ia * DK + g * 8;
+            asm volatile("" : "+v"(at));
+            fetch_q(at);
+        }
+        lds_barrier();  // the tiles of B are there
+        if (twice) {      // references of the rows of B, as a wavefront takes those of its own rows
+            const int row = tid >> 1, half = tid & 1;
+            float x = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks)
+                x = add_squares(*(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + half, row) * 16), x);
+            x = fmaf(c2, x + __shfl_xor(x, 1, 64), -OWN_WEIGHT);
+            if (half == 0) ref_b[row] = x;
+        }
+        // ---- phase 1 (Eq. (1)), once: S^T = z_B . z_A^T, the wavefront's 32 rows of A against 128 keys of B ----
+        f32x16 S[4];
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) sc[staged(kb * 32 + acc_row(e, g), wave * 32 + ln)] = S[kb][e];
-    }
-    {
-        const size_t slot = (((size_t)bh * T + A) * T + B) * ST + wave * 32 + ln;
-        softmax_pv_store<DK>(S, N - B * ST, vt, ln, g, ia < N, part_m + slot, part_l + slot, part_o + slot * DK);
-    }
-    if (!twice) return;
-
-    // ---- the same scores, transposed: the wavefront's 32 rows of B against the 128 keys of A ----
-    __syncthreads();  // the staged tile is complete, V^T of B no longer needed
-    vr.stage(vt, tid);
-    const int jb_row = wave * 32 + ln;  // this lane's row of B within the tile
+            for (int e = 0; e < 16; ++e) S[kb][e] = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
+        for (int ks = 0; ks < NKS; ++ks)
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            const f32x4 v = *(const f32x4*)(sc + staged(jb_row, kb * 32 + 8 * r4 + 4 * g));
-            S[kb][4 * r4 + 0] = v[0]; S[kb][4 * r4 + 1] = v[1]; S[kb][4 * r4 + 2] = v[2]; S[kb][4 * r4 + 3] = v[3];
+            for (int kb = 0; kb < 4; ++kb) {
+                if (kb == 0) __builtin_amdgcn_sched_barrier(0);
+                const int row = kb * 32 + ln;
+                S[kb] = mfma32h(*(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + g, row) * 16), qf[ks], S[kb]);
+            }
+        // ---- counts: logical tiles the selection rule picks, over the regions of this tile, and 32 x 32 score blocks
+        // issued: the key blocks that hold a key, for a wavefront that holds a row ----
+        {
+            const int ia0 = (int)cdiv_b(A * ST, cc), ia1 = (int)cdiv_b(min((A + 1) * ST, N), cc);
+            const int ib0 = (int)cdiv_b(B * ST, cc), ib1 = (int)cdiv_b(min((B + 1) * ST, N), cc);
+            const int na = ia1 - ia0, nb = ib1 - ib0, P = pb.P;
+            for (int e = tid; e < na * nb; e += 256) {
+                const int I = ia0 + e / nb, J = ib0 + e % nb;
+                const int gd = I >= J ? I - J : I - J + P, gt = I > J ? J - I + P : J - I;
+                cnt += (all_ordered || 2 * gd <= P) ? 1u : 0u;          // region (A, B)
+                if (twice) cnt += (2 * gt <= P) ? 1u : 0u;              // region (B, A), met transposed
+            }
+            if (A * ST + wave * 32 < N) phys += (unsigned)min(4, (keys_left + 31) / 32);
         }
-    __syncthreads();
-    {
-        const size_t slot = (((size_t)bh * T + B) * T + A) * ST + wave * 32 + ln;
-        softmax_pv_store<DK>(S, N - A * ST, vt, ln, g, B * ST + jb_row < N, part_m + slot, part_l + slot,
-                             part_o + slot * DK);
+        lds_barrier();  // nobody reads the K tile any more; the references are there
+        if (j + 1 < j1 && Y::RESIDENT) {
+            kr.fetch(zh, partner(j + 1) * ST, tid);
+            vr.fetch(zth, partner(j + 1) * ST, tid);
+        } else if (!Y::RESIDENT && twice) {
+            vr.fetch(zth, A * ST, tid);
+        }
+        // ---- weights of the second use: rows of B against keys of A ----
+        auto store_weights = [&]() {
+            unsigned most = 0u;
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    if ((r4 & 1) == 0) __builtin_amdgcn_sched_barrier(0);
+                    const f32x4 rb = *(const f32x4*)(ref_b + kb * 32 + 8 * r4 + 4 * g);
+                    float p[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        p[e] = __builtin_amdgcn_exp2f(fmaf(S[kb][4 * r4 + e], c2, -rb[e]));
+                    }
+                    const u32x2 w = {pack_f16(p[0], p[1]), pack_f16(p[2], p[3])};
+                    most = max_f16(most, max_f16(w[0], w[1]));
+                    *(u32x2*)(kt + weight_at(wave * 32 + ln, kb * 32 + 8 * r4 + 4 * g)) = w;
+                }
+            return too_large(most);
+        };
+        if (twice) {
+            const bool over = store_weights();
+            if (__builtin_amdgcn_ballot_w64(over) != 0ull && lane == 0) raised = 1u;
+        }
+        // ---- first use: phases 2 and 3 of the rows of A over the keys of B ----
+        {
+            float most = S[0][0];
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) most = fmaxf(most, S[kb][e]);
+            // (a scale below zero: always looked at; in the own tile also weights all below one: scores so large, 10^7 and more,
+            // that the reference misses the row's own by more than half precision holds)
+            const float heaviest = __builtin_amdgcn_exp2f(fmaf(most, c2, -ref));
+            const bool over = c2 < 0.f || too_large(pack_f16(heaviest, 0.f)) || (j == 0 && heaviest < 1.f);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(over) != 0ull, 0)) {
+                float mx = -INFINITY, w = 0.f;
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        mx = fmaxf(mx, S[kb][e] * c2);
+                        w = fmaxf(w, __builtin_amdgcn_exp2f(fmaf(S[kb][e], c2, -ref)));
+                    }
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                w = fmaxf(w, __shfl_xor(w, 32, 64));
+                const bool raise = too_large(pack_f16(w, 0.f)) || (j == 0 && w < 1.f);
+                const float alpha = raise ? __builtin_amdgcn_exp2f(ref - mx) : 1.f;
+                ref = raise ? mx : ref;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    l[e] *= alpha;
+#pragma unroll
+                    for (int db = 0; db < NDB; ++db) O[db][e] *= alpha;
+                }
+            }
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    u32x4 P, vf[NDB];
+                    read_group<DK>(vf, vt, kb, hf, ln, g);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const float p0 = __builtin_amdgcn_exp2f(fmaf(S[kb][8 * hf + 2 * w], c2, -ref));
+                        const float p1 = __builtin_amdgcn_exp2f(fmaf(S[kb][8 * hf + 2 * w + 1], c2, -ref));
+                        P[w] = pack_f16(p0, p1);
+                    }
+                    add_group<DK>(O, l, P, vf, ones_of_group(keys_left, kb, hf, g));
+                }
+        }
+        lds_barrier();  // the weights of the second use are complete, V^T of B no longer needed
+        if (twice && __builtin_expect(raised != 0u, 0)) {
+            // some row of B has a score too large for its reference: its largest score of the tile takes the place
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = kb * 32 + acc_row(e, g);
+                    float mx = S[kb][e] * c2;
+                    float w = __builtin_amdgcn_exp2f(fmaf(S[kb][e], c2, -ref_b[row]));
+#pragma unroll
+                    for (int o = 16; o > 0; o >>= 1) {
+                        mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+                        w = fmaxf(w, __shfl_xor(w, o, 64));
+                    }
+                    if (ln == 0) {
+                        max_b[wave][row] = mx;
+                        weight_b[wave][row] = w;
+                    }
+                }
+            lds_barrier();
+            if (tid == 0) raised = 0u;
+            if (tid < ST) {
+                const float mx = fmaxf(fmaxf(max_b[0][tid], max_b[1][tid]), fmaxf(max_b[2][tid], max_b[3][tid]));
+                const float w = fmaxf(fmaxf(weight_b[0][tid], weight_b[1][tid]), fmaxf(weight_b[2][tid], weight_b[3][tid]));
+                if (too_large(pack_f16(w, 0.f))) ref_b[tid] = mx;
+            }
+            lds_barrier();
+            store_weights();
+            lds_barrier();
+        }
+        if constexpr (Y::RESIDENT) {
+            if (j + 1 < j1) vr.stage(vt, tid);
+        } else if (twice) {
+            vr.stage(vt, tid);
+            lds_barrier();
+        }
+        if (twice) {
+            // ---- second use: the wavefront's 32 rows of B over the 128 keys of A ----
+            f32x16 Ob[NDB], lb;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                lb[e] = 0.f;
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) Ob[db][e] = 0.f;
+            }
+            const int i16 = lane & 15, col = wave * 32 + 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
+            u32x2 lo[2], hi[2];
+            u32x4 vf[2][NDB];
+            auto read = [&](int n) {  // group n of the keys of A, which V^T has in the order 0..3, 8..11 (lower half of the lanes),
+                                      // 4..7, 12..15 (upper half)
+                const int row = n * 16 + 4 * g + (i16 >> 2);
+                lo[n & 1] = lds_read_tr16(kt + weight_at(row, col));
+                hi[n & 1] = lds_read_tr16(kt + weight_at(row + 8, col));
+                read_group<DK>(vf[n & 1], vt_a, n >> 1, n & 1, ln, g);
+            };
+            read(0);
+#pragma unroll
+            for (int n = 0; n < 8; ++n) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (n < 7) read(n + 1);
+                add_group<DK>(Ob, lb, u32x4{lo[n & 1][0], lo[n & 1][1], hi[n & 1][0], hi[n & 1][1]}, vf[n & 1],
+                              ones_of_group(N - A * ST, n >> 1, n & 1, g));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            const int jb = wave * 32 + ln;  // this lane's row of B within the tile
+            if (B * ST + jb < N) {
+                const size_t slot = (((size_t)bh * T + B) * T + A) * ST + jb;
+                store_state<DK>(Ob, ref_b[jb], lb[0], g, part_m + slot, part_l + slot, part_o + slot * DK);
+            }
+        }
+        if (j + 1 < j1) {
+            if constexpr (!Y::RESIDENT) {
+                kr.fetch(zh, partner(j + 1) * ST, tid);
+                vr.fetch(zth, partner(j + 1) * ST, tid);
+            }
+            lds_barrier();  // nobody reads the weights (or V^T of A in the place of that of B) any more
+            kr.stage(kt, tid);
+            if constexpr (!Y::RESIDENT) vr.stage(vt, tid);
+        }
     }
+    if (T == 1) {
+        // the only state of its rows: y_i = O_i / l_i, through LDS (nobody reads the K tile any more), so that whole rows leave
+        constexpr int CPR = DK / 8;
+        const float inv = 1.f / l[0];
+        unsigned char* const stage = kt + wave * (32 * DK * 2);
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4)
+                *(u32x2*)(stage + ln * (DK * 2) + (((4 * db + r4) ^ (ln & (CPR - 1))) << 4) + 8 * g) =
+                    u32x2{pack_bf16(O[db][4 * r4] * inv, O[db][4 * r4 + 1] * inv), pack_bf16(O[db][4 * r4 + 2] * inv, O[db][4 * r4 + 3] * inv)};
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): only this wavefront reads what it wrote
+        const int bb = bh / pb.H, h = bh - bb * pb.H;
+#pragma unroll
+        for (int it = 0; it < 32 * CPR / 64; ++it) {
+            const int row = it * (64 / CPR) + lane / CPR, c = lane % CPR;
+            const u32x4 v = *(const u32x4*)(stage + row * (DK * 2) + ((c ^ (row & (CPR - 1))) << 4));
+            if (wave * 32 + row < N) *(u32x4*)(out + ((size_t)bb * N + wave * 32 + row) * ((size_t)pb.H * DK) + (size_t)h * DK + c * 8) = v;
+        }
+    } else if (ia < N) {
+        const size_t slot = (((size_t)bh * T + A) * T + partner(j0)) * ST + wave * 32 + ln;
+        store_state<DK>(O, ref, l[0], g, part_m + slot, part_l + slot, part_o + slot * DK);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+    if (lane == 0) count_add(pb.counters, blockIdx.x * 4u + wave, cnt, phys);
 }
 
 // y_i = sum over the key tiles of a row of 2^(m_t - M) O_t / sum 2^(m_t - M) l_t, M the largest m_t.
@@ -265,7 +505,7 @@ __global__ __launch_bounds__(256) void sym_pair_kernel(Problem pb, CountCfg cc, 
 template <int DK>
 __global__ __launch_bounds__(256) void sym_merge_kernel(Problem pb, const float* __restrict__ part_m,
                                                         const float* __restrict__ part_l,
-                                                        const float* __restrict__ part_o, bf16_t* __restrict__ out, int T)
+                                                        const float* __restrict__ part_o, bf16_t* __restrict__ out, int T, int run)
 {
     constexpr int CPR = DK / 4, RPW = 256 / CPR;  // pieces of a row; rows per workgroup, a divisor of 128
     const int bh = blockIdx.y;
@@ -277,18 +517,36 @@ __global__ __launch_bounds__(256) void sym_merge_kernel(Problem pb, const float*
     const float* pm = part_m + base;
     const float* pl = part_l + base;
     const float* po = part_o + base * DK + c;
-    float M = -INFINITY;
-#pragma unroll 4
-    for (int t = 0; t < T; ++t) M = fmaxf(M, pm[(size_t)t * ST]);
-    float L = 0.f;
+    // the states there are: one for every run of own partners, in the place of its first, and one for every other tile
+    const int mine = owned(A, T), own_states = (mine + run - 1) / run, states = own_states + T - mine;
+    auto place = [&](int s) -> size_t {
+        const int t = A + (s < own_states ? s * run : mine + s - own_states);
+        return (size_t)(t < T ? t : t - T) * ST;
+    };
+    float M = -INFINITY, L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int t = 0; t < T; ++t) {
-        const float m = pm[(size_t)t * ST];
-        const f32x4 o = *(const f32x4*)(po + (size_t)t * ST * DK);
-        const float w = m > -INFINITY ? __builtin_amdgcn_exp2f(m - M) : 0.f;
-        L += w * pl[(size_t)t * ST];
-        acc += w * o;
+    for (int s0 = 0; s0 < states; s0 += 4) {
+        float m[4], lt[4];
+        f32x4 o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // past the last: its state once more, with weight zero
+            const size_t t = place(min(s0 + u, states - 1));
+            m[u] = pm[t];
+            lt[u] = pl[t];
+            o[u] = *(const f32x4*)(po + t * DK);
+        }
+        const float before = M;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) M = fmaxf(M, m[u]);
+        const float alpha = __builtin_amdgcn_exp2f(before - M);
+        L *= alpha;
+        acc *= alpha;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float w = s0 + u < states ? __builtin_amdgcn_exp2f(m[u] - M) : 0.f;
+            L += w * lt[u];
+            acc += w * o[u];
+        }
     }
     const float inv = L > 0.f ? 1.f / L : 0.f;
     *(u32x2*)(out + ((size_t)bb * pb.N + i) * ((size_t)pb.H * DK) + (size_t)h * DK + c) =
@@ -316,13 +574,21 @@ hipError_t launch_sym_pair(const Problem& pb, const h16_t* z, const h16_t* zt, f
     const float c2 = pb.scale * 1.4426950408889634f;
     const int rows_merge = 1024 / pb.d;
     const dim3 merge_grid((pb.N + rows_merge - 1) / rows_merge, pb.B * pb.H);
-    const dim3 grid(pb.noskip ? T * T : T * (T + 1) / 2, pb.B * pb.H);
+    const int most = T / 2 + 1;  // partners of a row tile
+    // Runs of a row tile's partners: as many as give every CU a workgroup, for every one writes a state of its own.  Measured
+    // (us, both kernels; one run, two, three): 384 row tiles of d_k = 64, T 4 32.6 / 37.1 / -; 192, T 3 24.7 / 26.4; 128, T 16 63 /
+    // 43.5 / 43.2; d_k = 128 128, T 4 36.7 / 29.9 / 31.5, T 16 90 / 62 / 63.
+    const long tiles = (long)pb.B * pb.H * T;
+    const int want = tiles < 256 ? (int)(256 / tiles) : 1;
+    const int run = (most + want - 1) / want;
+    const int runs = (most + run - 1) / run + (pb.noskip ? T : 0);
+    const dim3 grid((unsigned)((tiles * runs + 7) / 8 * 8));
     if (pb.d == 64) {
-        hipLaunchKernelGGL(sym_pair_kernel<64>, grid, dim3(256), 0, s, pb, cc, z, zt, part_m, part_l, part_o, T, pb.noskip, c2);
-        hipLaunchKernelGGL(sym_merge_kernel<64>, merge_grid, dim3(256), 0, s, pb, part_m, part_l, part_o, out, T);
+        hipLaunchKernelGGL(sym_pair_kernel<64>, grid, dim3(256), 0, s, pb, cc, z, zt, part_m, part_l, part_o, out, T, runs, run, pb.noskip, c2, pb.B * pb.H);
+        if (T > 1) hipLaunchKernelGGL(sym_merge_kernel<64>, merge_grid, dim3(256), 0, s, pb, part_m, part_l, part_o, out, T, run);
     } else if (pb.d == 128) {
-        hipLaunchKernelGGL(sym_pair_kernel<128>, grid, dim3(256), 0, s, pb, cc, z, zt, part_m, part_l, part_o, T, pb.noskip, c2);
-        hipLaunchKernelGGL(sym_merge_kernel<128>, merge_grid, dim3(256), 0, s, pb, part_m, part_l, part_o, out, T);
+        hipLaunchKernelGGL(sym_pair_kernel<128>, grid, dim3(256), 0, s, pb, cc, z, zt, part_m, part_l, part_o, out, T, runs, run, pb.noskip, c2, pb.B * pb.H);
+        if (T > 1) hipLaunchKernelGGL(sym_merge_kernel<128>, merge_grid, dim3(256), 0, s, pb, part_m, part_l, part_o, out, T, run);
     } else {
         return hipErrorInvalidValue;
     }

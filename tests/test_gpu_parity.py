@@ -1,6 +1,8 @@
 """GPU parity: the HIP library, called through its C ABI, against the float64 CPU
 checker on the same seeded inputs.  Bars: f32 |g-r| <= 1e-5|r| + 1e-5 max|r|;
 bf16 |g-r| <= 2e-2; every count bit-exact."""
+import math
+
 import numpy as np
 import pytest
 
@@ -927,6 +929,70 @@ def test_symmetric_on_matrix_cores(shape):
     half = p * (p + 1) // 2 if p % 2 else p * (p + 2) // 2      # Sec. 4.2, on the tile matrix
     assert stats["tiles_executed"] == B * H * half
     _run_and_compare(w, SYM, 1.0 / 32)
+
+
+def _sym_both_ways(w, stored, scale):
+    """q = k = v with reuse and with every tile computed in its own orientation: the same bits."""
+    outs = []
+    for flags in (0, ar.ATTN_FLAG_NO_SKIP):
+        run = hp.GpuRun(w, stored, scale=scale, flags=flags)
+        try:
+            got, stats = run.forward(SYM)
+        finally:
+            run.close()
+        hp.check_counts(stats, hp.oracle_counts(w, SYM), noskip=bool(flags))
+        if not flags:
+            assert stats["phys_tiles_executed"] == hp.expected_sym_blocks(w)
+        outs.append(got)
+    assert np.array_equal(outs[0], outs[1])
+    return outs[0]
+
+
+# ---- the same: a row tile's partners in runs of several lengths, and references that its own score does not give
+@pytest.mark.parametrize("shape", [
+    # B, n, D, H, d, p
+    (2, 90, 64, 2, 64, 10),       # one tile: no states to merge
+    (1, 600, 64, 3, 64, 75),      # five tiles, runs of one partner
+    (8, 500, 64, 16, 64, 125),    # four tiles, one run of three or two partners; ragged
+    (8, 300, 64, 16, 128, 75),    # three tiles of d_k = 128, one run of two partners
+    (1, 1500, 64, 8, 128, 150),   # twelve tiles, runs of three
+])
+@pytest.mark.parametrize("rows", ["normal", "other rows heavier", "huge"])
+def test_symmetric_references(shape, rows):
+    """`other rows heavier`: all vectors point one way, with lengths 0.3 to 1.6, so that short rows have scores up to 16
+    nats above their own, across tiles.  z is rounded to half precision, 2^-12 of a score of up to 60 spread over d products:
+    2e-3 of a weight, on top of the output's own rounding (below 8).  `huge`: scores of 1e8, where the sum of squares and the
+    product differ by more than half precision holds; every row attends to itself."""
+    import torch
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("sym_refs", B, n, D, H, d, p, "bf16", SYM, 2900 + n)
+    scale = {"normal": 0.0, "other rows heavier": 2.0 / math.sqrt(d), "huge": 0.0}[rows]
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = stored["Wk"] = stored["Wv"] = None
+    if rows != "normal":
+        X = stored["X"].float()
+        if rows == "huge":
+            X = 3000.0 * X
+        else:
+            g = np.random.default_rng(n)
+            way = X[:, :1] * (8.0 / X[:, :1].norm(dim=-1, keepdim=True))
+            X = way * torch.from_numpy(g.uniform(0.3, 1.6, (B, n, 1))).float() + 0.02 * X
+        stored["X"] = X.to(torch.bfloat16)
+        f64["X"] = stored["X"].double().numpy()
+    got = _sym_both_ways(w, stored, scale)
+    if B * H > 32:  # a few heads
+        heads = [(0, 0), (B // 2, H - 1), (B - 1, H // 2)]
+        ref = np.stack([orc.head_rows(f64["X"], f64["Wq"], f64["Wq"], f64["Wq"], n_heads=H, d_k=d, p=p, scheme=SYM,
+                                      scale=hp.default_scale(w, scale), b=b, h=h, rows=range(n)) for b, h in heads])
+        got = np.stack([got[b, :, h * d:(h + 1) * d] for b, h in heads])
+    else:
+        ref = hp.oracle_forward(w, f64, SYM, scale)
+    if rows == "huge":
+        # half an ulp of the output, at most 2^-8 of it, and of z in half precision, 2^-11; where z's 64 products of some 300
+        # cancel, the roundings of their sums: 2^-24 of 2e4 each
+        assert np.all(np.abs(got - ref) <= (2.0 ** -8 + 2.0 ** -11) * np.abs(ref) + 2e-2)
+    else:
+        hp.tol_check(got, ref, w.dtype)
 
 
 # ---- row maxima that move along the walk: the running reference of Eq. (2)'s online form ----------
