@@ -12,12 +12,10 @@
 // is 128 (d + 2) floats per second use and per run.  Tiles on the diagonal (A == B) are used once.
 //
 // Both uses take their exponentials from the accumulators: the reference of a row is its own score
-// |z_i|^2 (known ahead of any product, and among the row's largest: s_ij <= |z_i| |z_j|) less 4, so no
-// maximum is searched for, and a row has one reference in every workgroup.  The weight of the row's own
-// score is 2^4; a score that exceeds it by 11 (base 2) makes a weight of 2^15, towards the end of half
-// precision, and then the reference is raised to the largest score of the tile (first use: before the
-// exponentials are taken; second: they are taken again).  Weights so small that half precision loses bits of them are
-// 2^-18 of the own score's or less.
+// |z_i|^2 (known ahead of any product, and among the row's largest: s_ij <= |z_i| |z_j|), so no maximum
+// is searched for, and a row has one reference in every workgroup.  A score that exceeds it by 16 (base
+// 2, 11 nats) makes a weight at the end of half precision, and then the reference is raised to the
+// largest score of the tile (first use: before the exponentials are taken; second: they are taken again).
 // The exponentials of the second use are stored to LDS in half precision, [row of A][row of B], and
 // read back as operands by the transposing read.  Row sums are MFMAs with ones: sums of the weights
 // as rounded, the same for either use.
@@ -26,6 +24,8 @@
 // 512 at d_k = 64, us (pairs, merge): 30.9, 10.3 with a workgroup per pair of tiles, scores staged in fp32,
 // maxima and a state per use, 22.2, 7.3 so; 32 heads of 2048 159 -> 93 together, 8 heads of 2048 at d_k = 128
 // 97 -> 62.  Of that the barriers that leave memory alone gave 4, addresses recomputed per tile (no spills) 4.
+// One vector in 50 four times as long as the others, so that most tiles raise a reference: 8 heads of 2048
+// 44 -> 53 us.
 //
 // The paper's selection rule (Sec. 4.2: circulant diagonals 0 .. floor(P/2) of the P x P matrix of
 // (n/P)-row tiles, the middle one computed by both owners when P is even) fixes WHICH element of a
@@ -44,7 +44,6 @@ namespace attnring {
 namespace {
 
 constexpr int ST = 128;           // rows and keys of a score tile
-constexpr float OWN_WEIGHT = 4.f; // base-2 logarithm of the weight of a row's own score
 
 // Byte offset of the weight of (row of A, row of B) in LDS: rows of 256 bytes, their 16-byte chunks XOR-ed with four bits
 // of the row: 16 rows of one 8-byte store meet all banks, and the four rows of a transposing read four pairs of chunks.
@@ -167,8 +166,24 @@ __device__ __forceinline__ unsigned max_f16(unsigned a, unsigned b)
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b)));
 }
-// Whether one of two weights (not negative) is 2^15 or more.
-__device__ __forceinline__ bool too_large(unsigned m) { return (m & 0xFFFFu) >= 0x7800u || m >= 0x78000000u; }
+// Whether one of two weights (not negative) is the largest of half precision, or infinite.
+__device__ __forceinline__ bool too_large(unsigned m) { return (m & 0xFFFFu) >= 0x7BFFu || m >= 0x7BFF0000u; }
+
+// The largest value of the 32 lanes of a half, in its last 16 lanes.
+__device__ __forceinline__ float max_of_half(float x)
+{
+    auto step = [&](auto control) {
+        constexpr int C = decltype(control)::value;
+        const int i = __builtin_bit_cast(int, x);
+        x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, C, 0xF, 0xF, false)));
+    };
+    step(std::integral_constant<int, 0xB1>{});   // lane ^ 1
+    step(std::integral_constant<int, 0x4E>{});   // lane ^ 2
+    step(std::integral_constant<int, 0x141>{});  // mirrored in 8 lanes
+    step(std::integral_constant<int, 0x140>{});  // mirrored in 16 lanes
+    step(std::integral_constant<int, 0x142>{});  // the last lane of 16 to the next 16
+    return x;
+}
 
 template <int DK>
 __device__ __forceinline__ void store_state(const f32x16 (&O)[DK / 32], float m, float l, int g, float* __restrict__ pm,
@@ -246,7 +261,7 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
     float ref = 0.f;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) ref = add_squares(qf[ks], ref);
-    ref = fmaf(c2, ref + __shfl_xor(ref, 32, 64), -OWN_WEIGHT);
+    ref = c2 * (ref + __shfl_xor(ref, 32, 64));
     f32x16 O[NDB], l;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -279,7 +294,7 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks)
                 x = add_squares(*(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + half, row) * 16), x);
-            x = fmaf(c2, x + __shfl_xor(x, 1, 64), -OWN_WEIGHT);
+            x = c2 * (x + __shfl_xor(x, 1, 64));
             if (half == 0) ref_b[row] = x;
         }
         // ---- phase 1 (Eq. (1)), once: S^T = z_B . z_A^T, the wavefront's 32 rows of A against 128 keys of B ----
@@ -348,10 +363,11 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) most = fmaxf(most, S[kb][e]);
-            // (a scale below zero: always looked at; in the own tile also weights all below one: scores so large, 10^7 and more,
+            most = fmaxf(most, __shfl_xor(most, 32, 64));
+            // (a scale below zero: always looked at; in the own tile also weights that are all small: scores so large, 10^7 and more,
             // that the reference misses the row's own by more than half precision holds)
             const float heaviest = __builtin_amdgcn_exp2f(fmaf(most, c2, -ref));
-            const bool over = c2 < 0.f || too_large(pack_f16(heaviest, 0.f)) || (j == 0 && heaviest < 1.f);
+            const bool over = c2 < 0.f || too_large(pack_f16(heaviest, 0.f)) || (j == 0 && heaviest < 0.0625f);
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(over) != 0ull, 0)) {
                 float mx = -INFINITY, w = 0.f;
 #pragma unroll
@@ -363,7 +379,7 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
                     }
                 mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
                 w = fmaxf(w, __shfl_xor(w, 32, 64));
-                const bool raise = too_large(pack_f16(w, 0.f)) || (j == 0 && w < 1.f);
+                const bool raise = too_large(pack_f16(w, 0.f)) || (j == 0 && w < 0.0625f);
                 const float alpha = raise ? __builtin_amdgcn_exp2f(ref - mx) : 1.f;
                 ref = raise ? mx : ref;
 #pragma unroll
@@ -399,12 +415,9 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
                     const int row = kb * 32 + acc_row(e, g);
                     float mx = S[kb][e] * c2;
                     float w = __builtin_amdgcn_exp2f(fmaf(S[kb][e], c2, -ref_b[row]));
-#pragma unroll
-                    for (int o = 16; o > 0; o >>= 1) {
-                        mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-                        w = fmaxf(w, __shfl_xor(w, o, 64));
-                    }
-                    if (ln == 0) {
+                    mx = max_of_half(mx);
+                    w = max_of_half(w);
+                    if (ln == 31) {
                         max_b[wave][row] = mx;
                         weight_b[wave][row] = w;
                     }
