@@ -1072,8 +1072,20 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
         // 128s have no other tiles: 8192 x 960 -> 2880 78 us, 32768 x 1024 -> 2880 322, 32768 x 4096 -> 2880 1408.
         const long t128 = (long)pb.B * (pb.Npad / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
         if (HD % 128 != 0 || t128 <= 100) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
-        if (t256 >= 512 && pb.D >= 2048) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        // At long d_model 256 x 256 where its tiles, one to a CU, fill four fifths of their rounds of the chip (256 x 256 /
+        // 128 x 256: 432 tiles 110 / 112, 576 157 / 140, d_model 2048).
+        if (t256 >= 512 && pb.D >= 2048 && 5 * t256 >= 4 * 256 * ((t256 + 255) / 256))
+            return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         if (t256 >= 320) return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        // One round of either: more 128 x 128 tiles than the chip holds at three per CU, and no more than 256 of 256 x 256 (two
+        // of 128 x 256 to a CU).  Measured (128 x 128 two, three per CU / 128 x 256 / 256 x 256): d_model 768, 864 tiles 34.0 /
+        // 35.6 / 29.2 / 29.5, 1024 40.2 / 43.1 / 33.7 / 33.2, 768 (still three per CU) 27.4 / 26.4 / 28.5 / 28.2; d_model 2048, 864 64.8
+        // / 75.1 / 59.4 / 56.8.  With key lengths the tiles that are left are not known here.
+        const long live256 = HD % 256 == 0 ? (long)pb.B * ((pb.N + 127) / 128) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
+        if (!pb.lens && live256 > 384 && live256 <= 512) {
+            if (pb.D >= 2048 && t256 <= 256) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+            return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        }
         // 128 x 128 tiles, two or three workgroups to a CU: whichever needs the less in whole rounds of the chip, a
         // round of 768 taking 1.5 times one of 512.  Measured (three per CU over two, by tiles, at d_model 768 / 4096):
         // 540 0.90 / 0.92, 756 0.90 / 0.97, 798 1.05 / 1.22, 1008 1.01 / 1.15, 1080 0.92 / 1.01, 1296 0.93 / 0.98,

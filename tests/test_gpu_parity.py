@@ -884,6 +884,33 @@ def test_projection_with_a_cut_slice(shape, d_model):
         hp.tol_check(got[b, rows, h * d:(h + 1) * d], ref, w.dtype)
 
 
+# ---- products of one round of large tiles, and of large tiles that fill their rounds badly ------------------------
+@pytest.mark.parametrize("tile,shape", [
+    # B, n, D, H, d, p
+    ("128, 256", (11, 500, 64, 12, 64, 125)),     # 792 tiles of 128 x 128, ragged
+    ("128, 256", (18, 250, 72, 8, 128, 125)),     # d_k = 128; a cut slice
+    ("256, 256", (6, 1020, 2056, 12, 64, 255)),    # d_model from 2048 on, 216 of 256 x 256
+    ("128, 256", (24, 500, 2048, 16, 64, 125)),   # 576 of 256 x 256 in three rounds
+    ("128, 128", (8, 512, 64, 24, 64, 64)),       # 1152 of 128 x 128: as before
+])
+def test_projection_rounds_of_large_tiles(tile, shape):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("rounds", B, n, D, H, d, p, "bf16", CAUSAL, 7750 + n)
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = None
+    run = hp.GpuRun(w, stored)
+    try:
+        assert any(f"proj_dma_kernel<{tile}," in k for k in run.kernels(CAUSAL))
+        got, _ = run.forward(CAUSAL)
+    finally:
+        run.close()
+    rows = sorted({0, 1, 127, 128, n // 2, n - 2, n - 1})
+    for (b, h) in {(0, 0), (B // 2, H // 2), (B - 1, H - 1)}:
+        ref = orc.head_rows(f64["X"], f64["Wq"], f64["Wk"], f64["Wv"], n_heads=H, d_k=d, p=p, scheme=CAUSAL,
+                            scale=hp.default_scale(w, 0.0), b=b, h=h, rows=rows)
+        hp.tol_check(got[b, rows, h * d:(h + 1) * d], ref, w.dtype)
+
+
 # ---- queries projected inside the attention kernel (ATTN_FLAG_FUSE_Q_PROJECTION) ----------------------
 @pytest.mark.parametrize("shape", [
     (2, 320, 64, 2, 64, 40),      # two 32-row slices of Wq
