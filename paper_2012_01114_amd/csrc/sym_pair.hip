@@ -587,13 +587,14 @@ hipError_t launch_sym_pair(const Problem& pb, const h16_t* z, const h16_t* zt, f
     const float c2 = pb.scale * 1.4426950408889634f;
     const int rows_merge = 1024 / pb.d;
     const dim3 merge_grid((pb.N + rows_merge - 1) / rows_merge, pb.B * pb.H);
-    const int most = T / 2 + 1;  // partners of a row tile
-    // Runs of a row tile's partners: as many as give every CU a workgroup, for every one writes a state of its own.  Measured
-    // (us, both kernels; one run, two, three): 384 row tiles of d_k = 64, T 4 32.6 / 37.1 / -; 192, T 3 24.7 / 26.4; 128, T 16 63 /
-    // 43.5 / 43.2; d_k = 128 128, T 4 36.7 / 29.9 / 31.5, T 16 90 / 62 / 63.
-    const long tiles = (long)pb.B * pb.H * T;
-    const int want = tiles < 256 ? (int)(256 / tiles) : 1;
-    const int run = (most + want - 1) / want;
+    // Runs of a row tile's partners: as short as one workgroup per CU allows, two with six row tiles and more per head, for
+    // every run writes a state of its own.  Measured (us, both kernels; runs per row tile one, two, three): 384 row tiles of
+    // d_k = 64, T 4 32.6 / 37.1 / -; 192, T 3 24.7 / 26.4; 128, T 16 63 / 43.5 / 43.2; d_k = 128 128, T 4 36.7 / 29.9 / 31.5, T 16 90 / 62 /
+    // 63.  Runs of one against two partners: 96 row tiles, T 4 (240 runs) 21.3 / 22.0; 72, T 12 (468 runs) 27.3 / 32.8.
+    const long tiles = (long)pb.B * pb.H * T, more = T % 2 == 0 ? tiles / 2 : 0;  // `more` of them have one partner more
+    const int least = (T + 1) / 2, most = T / 2 + 1;
+    int run = 1;
+    while (run < most && more * ((most + run - 1) / run) + (tiles - more) * ((least + run - 1) / run) > (T >= 6 ? 512 : 256)) ++run;
     const int runs = (most + run - 1) / run + (pb.noskip ? T : 0);
     const dim3 grid((unsigned)((tiles * runs + 7) / 8 * 8));
     if (pb.d == 64) {
