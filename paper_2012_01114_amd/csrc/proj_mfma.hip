@@ -67,7 +67,7 @@ struct TileMap {
     int tiles_x, tiles_w, n_tiles;
     int group_w;       // weight tiles walked together
     FastDiv width;     // group_w * tiles_x
-    FastDiv per_item;  // x tiles per batch item (Npad / tile height)
+    FastDiv per_item;  // x tiles per batch item that hold a vector
     int spread;        // matrices over which the column tiles are dealt (below), 0: not
     int per_matrix;    // column tiles of one matrix
     int mult;          // coprime to tiles_x
@@ -100,12 +100,15 @@ __device__ __forceinline__ void tile_of(const TileMap& tm, int id, int& tw, int&
 inline TileMap tile_map(const Problem& pb, int bx, int bw, int matrices, bool spread)
 {
     TileMap tm;
-    tm.tiles_x = pb.B * pb.Npad / bx;
+    // Only tiles that hold a vector are launched: of a short item's 256 padded rows a grid of 64-row tiles was three quarters
+    // empty, and the workgroups that had a tile came to lie two to a CU (64 x 2048 -> 6144 29.5 -> 18 us).
+    const int per_item = (pb.N + bx - 1) / bx;
+    tm.tiles_x = pb.B * per_item;
     tm.tiles_w = matrices * pb.H * pb.d / bw;
     tm.n_tiles = tm.tiles_x * tm.tiles_w;
     tm.group_w = spread ? matrices : GROUP_W;
     tm.width = fast_div((unsigned)(tm.group_w * tm.tiles_x));
-    tm.per_item = fast_div((unsigned)(pb.Npad / bx));
+    tm.per_item = fast_div((unsigned)per_item);
     tm.spread = spread ? matrices : 0;
     tm.per_matrix = tm.tiles_w / matrices;
     tm.mult = tm.tiles_x / 8 + 1;
@@ -152,11 +155,9 @@ __global__ __launch_bounds__(256) void proj_mfma_kernel(int Bsz, int N, int Npad
     if (tile_id >= tm.n_tiles) return;
     int tw, tx_;
     tile_of(tm, tile_id, tw, tx_);
-    const int x0 = tx_ * BT;   // first x-side row (padded vector index)
     const int w0 = tw * BT;    // first stacked output column
-    const int bb = (int)divide((unsigned)tx_, tm.per_item);  // Npad is a multiple of BT: one batch item per tile
-    const int i0 = x0 - bb * Npad;
-    if (i0 >= N) return;       // nothing but padding
+    const int bb = (int)divide((unsigned)tx_, tm.per_item);  // one batch item per tile
+    const int i0 = (tx_ - bb * (int)tm.per_item.d) * BT;
     const bool is_v = w0 >= 2 * HD;
     // Keys past the key length of their batch item are in no allowed pair (Sec. 5.1 applied to
     // padding): their k and v rows are not computed.  (q rows are: every query row has an output.)
@@ -342,9 +343,8 @@ void proj_dma_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16_t
     // no_q (the queries are not wanted: q = k = v scheme, or projected by the attention kernel): the
     // grid holds the k and v column tiles only
     tile_of(tm, tile_id, tw, tx_);
-    const int bb = (int)divide((unsigned)tx_, tm.per_item);  // Npad is a multiple of BT: one batch item per tile
-    const int i0 = tx_ * BX - bb * Npad;
-    if (i0 >= N) return;  // nothing but padding
+    const int bb = (int)divide((unsigned)tx_, tm.per_item);  // one batch item per tile
+    const int i0 = (tx_ - bb * (int)tm.per_item.d) * BX;
     const int w0 = tw * BW + (no_q ? HD : 0);
     const bool is_v = w0 >= 2 * HD;
     // Keys past the key length of their batch item are in no allowed pair (Sec. 5.1 applied to
@@ -809,8 +809,7 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
     int tw, tx_;
     tile_of(tm, tile_id, tw, tx_);
     const int bb = (int)divide((unsigned)tx_, tm.per_item);
-    const int i0 = tx_ * 64 - bb * Npad;
-    if (i0 >= N) return;  // nothing but padding
+    const int i0 = (tx_ - bb * (int)tm.per_item.d) * 64;
     const int w0 = tw * 64 + (no_q ? HD : 0);
     if (lens != nullptr && (w0 >= HD || skip_q_rows) && past_key_length(lens, bb, i0, N)) return;  // see proj_dma_kernel
     const int which = w0 >= 2 * HD ? 2 : w0 >= HD ? 1 : 0;
@@ -1054,7 +1053,7 @@ bool launch_proj_small_float(const Problem& pb, const bf16_t* X, const bf16_t* c
 hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq, const bf16_t* Wk,
                             const bf16_t* Wv, const bf16_t* Wt, h16_t* q, h16_t* k, h16_t* vt, hipStream_t s)
 {
-    // Tile by the number of 256 x 256 tiles the product would have and by d_model.  Measured (us; 128 x 128,
+    // Tile by the number of tiles that hold a vector and by d_model.  Measured (us; 128 x 128,
     // 256 x 256, 128 x 256 with two workgroups per CU; rows x d_model -> columns):
     //   8192 x 768 -> 2304 (288)   36.4 / 45.2 / 36.1     16384 x 768 -> 2304 (576)    61 / 70 / 57
     //   8192 x 1024 -> 3072 (384)  52 / 55 / 48           65536 x 1024 -> 3072 (3072)  435 / 374 / 377, with key
@@ -1065,24 +1064,26 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
     // there is one; 256 x 256 reads the least per product, which decides when d_model is long.  No tile mixes
     // columns of two matrices.
     const int HD = pb.H * pb.d;
-    const long t256 = HD % 256 == 0 ? (long)pb.B * (pb.Npad / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
+    const long t256 = HD % 256 == 0 ? (long)pb.B * ((pb.N + 255) / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
     if (proj_reads_weights_in_place(pb, Wq, Wk, Wv)) {  // operands go straight to LDS
-        // Few tiles: 64 x 64 ones, four to one of 128 x 128.  Measured (us, 128 x 128 / 64 x 64, by the number of 128 x 128
-        // tiles): 24 11.4 / 9.8, 36 11.6 / 10.1, 72 12.5 / 11.4, 96 (d_model 3072) 26.9 / 26.7, 144 12.9 / 13.7.  Columns not in
-        // 128s have no other tiles: 8192 x 960 -> 2880 78 us, 32768 x 1024 -> 2880 322, 32768 x 4096 -> 2880 1408.
-        const long t128 = (long)pb.B * (pb.Npad / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
-        if (HD % 128 != 0 || t128 <= 100) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        // Few tiles: 64 x 64 ones, where they find a CU each, or at short d_model half of one.  Measured (us, 128 x 128 / 64 x 64,
+        // by the number of 64 x 64 tiles): d_model 768, 144 11.3 / 9.3, 288 11.8 / 11.2, 432 (1024) 13.5 / 12.5, 480 (1096) 17.7 / 16.1, 576
+        // 12.9 / 13.7, 900 15.8 / 17.4; d_model 2048, 384 28.2 / 29.9, 26.7 / 29.5; 3072, 384 26.9 / 26.7; 4096, 192 45.3 / 33.1.
+        // Columns not in 128s have no other tiles: 8192 x 960 -> 2880 78 us, 32768 x 1024 -> 2880 322, 32768 x 4096 -> 2880 1408.
+        const long cols = (pb.no_q ? 2L : 3L) * HD;
+        const long t64 = (long)pb.B * ((pb.N + 63) / 64) * (cols / 64);
+        if (HD % 128 != 0 || t64 <= 256 || (t64 <= 512 && pb.D <= 1280)) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        const long t128x256 = HD % 256 == 0 ? (long)pb.B * ((pb.N + 127) / 128) * (cols / 256) : 0;
         // At long d_model 256 x 256 where its tiles, one to a CU, fill four fifths of their rounds of the chip (256 x 256 /
         // 128 x 256: 432 tiles 110 / 112, 576 157 / 140, d_model 2048).
         if (t256 >= 512 && pb.D >= 2048 && 5 * t256 >= 4 * 256 * ((t256 + 255) / 256))
             return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
-        if (t256 >= 320) return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        if (t128x256 >= 640) return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         // One round of either: more 128 x 128 tiles than the chip holds at three per CU, and no more than 256 of 256 x 256 (two
         // of 128 x 256 to a CU).  Measured (128 x 128 two, three per CU / 128 x 256 / 256 x 256): d_model 768, 864 tiles 34.0 /
         // 35.6 / 29.2 / 29.5, 1024 40.2 / 43.1 / 33.7 / 33.2, 768 (still three per CU) 27.4 / 26.4 / 28.5 / 28.2; d_model 2048, 864 64.8
         // / 75.1 / 59.4 / 56.8.  With key lengths the tiles that are left are not known here.
-        const long live256 = HD % 256 == 0 ? (long)pb.B * ((pb.N + 127) / 128) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
-        if (!pb.lens && live256 > 384 && live256 <= 512) {
+        if (!pb.lens && t128x256 > 384 && t128x256 <= 512) {
             if (pb.D >= 2048 && t256 <= 256) return launch_dma<256, 256, 2, 4>(pb, X, Wq, Wk, Wv, q, k, vt, s);
             return launch_dma<128, 256, 2, 2>(pb, X, Wq, Wk, Wv, q, k, vt, s);
         }
@@ -1095,7 +1096,7 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
         // known here: three for the counts whose tiles, some of them left out, mostly end up there.  Means over lengths
         // uniform in n / 32 .. n, n 128 to 2000, d_model 512 and 2048: 600 tiles 1.09, 672 1.02, 714 0.88, 768 0.97, 798 0.93,
         // 840 0.98, 864 0.97, 912 1.01, 960 1.04, 1008 1.07, 1104 1.06.
-        const long live = (long)pb.B * ((pb.N + 127) / 128) * ((pb.no_q ? 2L : 3L) * HD / 128);
+        const long live = (long)pb.B * ((pb.N + 127) / 128) * (cols / 128);
         const bool fewer_rounds = 3 * ((live + 767) / 768) <= 2 * ((live + 511) / 512);
         if (live > 5376 || (pb.lens ? live >= 680 && live <= 920 : fewer_rounds && live <= 3072))
             return launch_dma<128, 128, 2, 2, true>(pb, X, Wq, Wk, Wv, q, k, vt, s);
