@@ -245,8 +245,11 @@ hipError_t launch_attn(const Problem& pb, const h16_t* q, const h16_t* k, const 
         int strands = 0;
         if (pb.d == 64) {
             split = split && n < 1024;
-            // key lengths, every query row produced: the walks that the split shortens are short already
-            split = split || (masked && n <= 128 && w32 <= (pb.lens && !pb.skip_rows ? 384 : 512));
+            // masked, beyond 256 tiles of 32 rows: up to 128 vectors, or, where items differ in length and padded rows are left
+            // out, some more (lengths uniform in n / 32 .. n, split / 4: 48 items of 232 9.1 / 9.3, 32 of 300 9.4 / 10.0, of 500
+            // 12.8 / 11.0).  Key lengths with every query row produced: the walks that the split shortens are short already.
+            split = split || (masked && (pb.lens && pb.skip_rows ? n <= 320 && w32 <= (n <= 128 ? 512 : 400)
+                                                                  : n <= 128 && w32 <= (pb.lens ? 384 : 512)));
             if ((w64 <= 256 && n > 64) || (masked && n >= 2048 && w128 <= 256)) strands = 4;
             else if (w128 <= 256 && n > (masked ? 256 : 512)) strands = 3;
             else if (masked && w128 <= (n >= 2048 ? 512 : n >= 1024 ? 288 : 0)) strands = 3;
