@@ -908,16 +908,22 @@ void proj_small_kernel(int Bsz, int N, int Npad, int D, int H, int d, const bf16
     else all_slices(std::false_type{});
 
     if constexpr (FLOAT_OUT) {
-        const int gr = i0 + xr + ln;
-        if (gr < N) {
-            const int item = (int)divide((unsigned)gr, items), i = gr - item * (int)items.d;
-            float* o = (float*)(which == 0 ? qo : (which == 1 ? ko : vto));
+        // through LDS, so that 16 lanes store a row's 64 columns: from the accumulators it would be 32 bytes of a line at a time
+        constexpr int PITCH = 64 + 4;
+        float* const stage = (float*)lds;
+        __builtin_amdgcn_s_barrier();  // everyone has read the last slice (and waited for that)
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4) {
-                const int cc = c0 + wcol + 8 * r4 + 4 * g, h = (int)divide((unsigned)cc, columns), l = cc - h * d;
-                *(f32x4*)(o + (((size_t)item * H + h) * items.d + i) * d + l) =
-                    f32x4{acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]};
-            }
+        for (int r4 = 0; r4 < 4; ++r4)
+            *(f32x4*)(stage + (xr + ln) * PITCH + wcol + 8 * r4 + 4 * g) = f32x4{acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]};
+        __syncthreads();
+        float* o = (float*)(which == 0 ? qo : (which == 1 ? ko : vto));
+        const int cl = (tid & 15) * 4, cc = c0 + cl, h = (int)divide((unsigned)cc, columns), l = cc - h * d;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int row = 16 * it + (tid >> 4), gr = i0 + row;
+            if (gr >= N) break;
+            const int item = (int)divide((unsigned)gr, items), i = gr - item * (int)items.d;
+            *(f32x4*)(o + (((size_t)item * H + h) * items.d + i) * d + l) = *(const f32x4*)(stage + row * PITCH + cl);
         }
         return;
     }
