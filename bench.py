@@ -34,10 +34,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16, published
 # the same counter reads for a plain 1 GiB device copy: x2.00 and x1.00; see profiles/).  They hold for
 # the sources of these kernels with the hash below; with other sources the bench line carries null.
 TRAFFIC_SOURCES = ("proj_mfma.hip", "attn_pipe.hip", "attn_walk.h", "attn_common.h", "mfma_common.h", "common.h")
-TRAFFIC_SOURCES_SHA256 = "645439d39ffe17ca1fea7dd6cbc107b15e5e6a542038ff3875cbd58a369aa9f8"
+TRAFFIC_SOURCES_SHA256 = "007151e3fc0b78480c8603f89c3a9c07c786cf8c37f76d0c4e8bdc122f9afed7"
 TRAFFIC_BYTES = {
-    "long": {"projection": int((2 * 589947 + 196640) * 1024), "attention": int((2 * 142036 + 65792) * 1024)},
-    "causal": {"projection": int((2 * 38104 + 36896) * 1024), "attention": int((2 * 18739 + 12480) * 1024)},
+    "long": {"projection": int((2 * 589944 + 196640) * 1024), "attention": int((2 * 137374 + 65792) * 1024)},
+    "causal": {"projection": int((2 * 38104 + 36896) * 1024), "attention": int((2 * 18772 + 12480) * 1024)},
 }
 
 
