@@ -12,10 +12,12 @@
 // is 128 (d + 2) floats per second use and per run.  Tiles on the diagonal (A == B) are used once.
 //
 // Both uses take their exponentials from the accumulators: the reference of a row is its own score
-// |z_i|^2 (known ahead of any product, and among the row's largest: s_ij <= |z_i| |z_j|), so no maximum
-// is searched for, and a row has one reference in every workgroup.  A score that exceeds it by 16 (base
-// 2, 11 nats) makes a weight at the end of half precision, and then the reference is raised to the
-// largest score of the tile (first use: before the exponentials are taken; second: they are taken again).
+// |z_i|^2 (among the row's largest: s_ij <= |z_i| |z_j|), so no maximum is searched for, and a row has one
+// reference in every workgroup.  It comes from the MFMAs that form the scores, in their order of sums, and
+// is rounded as they are, so that a row's own weight is 1 exactly, whatever its size (a sum of squares of
+// another order misses a score of 1e9 by hundreds).  A score that exceeds it by 15.5 (base 2, 10.7 nats) makes
+// a weight near the end of half precision, and then the reference is raised to the largest score of the tile
+// (first use: before the exponentials are taken; second: they are taken again).
 // The exponentials of the second use are stored to LDS in half precision, [row of A][row of B], and
 // read back as operands by the transposing read.  Row sums are MFMAs with ones: sums of the weights
 // as rounded, the same for either use.
@@ -24,8 +26,8 @@
 // 512 at d_k = 64, us (pairs, merge): 30.9, 10.3 with a workgroup per pair of tiles, scores staged in fp32,
 // maxima and a state per use, 22.2, 7.3 so; 32 heads of 2048 159 -> 93 together, 8 heads of 2048 at d_k = 128
 // 97 -> 62.  Of that the barriers that leave memory alone gave 4, addresses recomputed per tile (no spills) 4.
-// One vector in 50 four times as long as the others, so that most tiles raise a reference: 8 heads of 2048
-// 44 -> 53 us.
+// One vector in 50 four times as long as the others, so that most tiles raise a reference: 8 heads of 2048,
+// whole calls, 42 -> 45 us.
 //
 // The paper's selection rule (Sec. 4.2: circulant diagonals 0 .. floor(P/2) of the P x P matrix of
 // (n/P)-row tiles, the middle one computed by both owners when P is even) fixes WHICH element of a
@@ -118,13 +120,21 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Adds the squares of eight half-precision values, in order.
-__device__ __forceinline__ float add_squares(u32x4 v, float x)
+// Score of row ln with itself out of the product of 32 rows with themselves, in the lanes whose half holds it: register
+// 4 (ln / 8) + ln % 4 of half (ln / 4) % 2 (acc_row).
+__device__ __forceinline__ bool holds_diagonal(int ln, int g) { return ((ln >> 2) & 1) == g; }
+__device__ __forceinline__ float diagonal(const f32x16& D, int ln)
 {
-    const f16x8 h = __builtin_bit_cast(f16x8, v);
+    // by masks: written as conditions, each choice becomes an element with a number known at run time, 16 comparisons
+    auto pick = [](float a, float b, int bit) {  // b where the bit is set
+        const unsigned m = 0u - (unsigned)bit;
+        return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, b) & m) | (__builtin_bit_cast(unsigned, a) & ~m));
+    };
+    const int b0 = ln & 1, b1 = (ln >> 1) & 1, b3 = (ln >> 3) & 1, b4 = (ln >> 4) & 1;
+    float x[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x = fmaf((float)h[e], (float)h[e], x);
-    return x;
+    for (int r4 = 0; r4 < 4; ++r4) x[r4] = pick(pick(D[4 * r4], D[4 * r4 + 1], b0), pick(D[4 * r4 + 2], D[4 * r4 + 3], b0), b1);
+    return pick(pick(x[0], x[1], b3), pick(x[2], x[3], b3), b4);
 }
 
 // V^T of one 16-key group, group 2 kb + hf of the 128 keys in LDS at vt, as operands.
@@ -166,8 +176,10 @@ __device__ __forceinline__ unsigned max_f16(unsigned a, unsigned b)
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b)));
 }
-// Whether one of two weights (not negative) is the largest of half precision, or infinite.
-__device__ __forceinline__ bool too_large(unsigned m) { return (m & 0xFFFFu) >= 0x7BFFu || m >= 0x7BFF0000u; }
+// Scores above a row's reference by more raise it; their weights are at most 2^15.5, and one of two weights (not negative)
+// that are such says so here.
+constexpr float RAISE = 15.5f;
+__device__ __forceinline__ bool near_the_end(unsigned m) { return (m & 0xFFFFu) >= 0x7800u || m >= 0x78000000u; }
 
 // The largest value of the 32 lanes of a half, in its last 16 lanes.
 __device__ __forceinline__ float max_of_half(float x)
@@ -208,11 +220,12 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
                                                           float* __restrict__ part_l, float* __restrict__ part_o,
                                                           bf16_t* __restrict__ out, int T, int runs, int run, bool all_ordered, float c2, int heads)
 {
+#pragma clang fp contract(off)  // scores are rounded before references are taken from them
     typedef Sym<DK> Y;
     constexpr int NKS = Y::NKS, NDB = Y::NDB;
     __shared__ __attribute__((aligned(16))) unsigned char lds[Y::LDS_BYTES];
     __shared__ __attribute__((aligned(16))) float ref_b[ST];
-    __shared__ float max_b[4][ST], weight_b[4][ST];
+    __shared__ float max_b[4][ST];
     __shared__ unsigned raised;
     unsigned char* const kt = lds;  // K tile of B, then the weights
     unsigned char* const vt = lds + Y::KW_BYTES;
@@ -258,11 +271,14 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
     kr.stage(kt, tid);
     vr.stage(vt, tid);
     if (tid == 0) raised = 0u;
-    float ref = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) ref = add_squares(qf[ks], ref);
-    ref = c2 * (ref + __shfl_xor(ref, 32, 64));
     f32x16 O[NDB], l;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) l[e] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks) l = mfma32h(qf[ks], qf[ks], l);
+    float ref = diagonal(l, ln) * c2;
+    const float other = __shfl_xor(ref, 32, 64);
+    if (!holds_diagonal(ln, g)) ref = other;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         l[e] = 0.f;
@@ -289,13 +305,17 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
         }
         lds_barrier();  // the tiles of B are there
         if (twice) {      // references of the rows of B, as a wavefront takes those of its own rows
-            const int row = tid >> 1, half = tid & 1;
-            float x = 0.f;
+            const int row = wave * 32 + ln;
+            f32x16 own;
 #pragma unroll
-            for (int ks = 0; ks < NKS; ++ks)
-                x = add_squares(*(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + half, row) * 16), x);
-            x = c2 * (x + __shfl_xor(x, 1, 64));
-            if (half == 0) ref_b[row] = x;
+            for (int e = 0; e < 16; ++e) own[e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < NKS; ++ks) {
+                const u32x4 f = *(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + g, row) * 16);
+                own = mfma32h(f, f, own);
+            }
+            const float x = diagonal(own, ln) * c2;
+            if (holds_diagonal(ln, g)) ref_b[row] = x;
         }
         // ---- phase 1 (Eq. (1)), once: S^T = z_B . z_A^T, the wavefront's 32 rows of A against 128 keys of B ----
         f32x16 S[4];
@@ -311,6 +331,12 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
                 const int row = kb * 32 + ln;
                 S[kb] = mfma32h(*(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + g, row) * 16), qf[ks], S[kb]);
             }
+        // scale and base-2 exponent, rounded here once: a product and difference in one step would leave as much of a score as
+        // the rounding of its reference has taken away, 2^64 and more at 1e9
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) S[kb][e] *= c2;
         // ---- counts: logical tiles the selection rule picks, over the regions of this tile, and 32 x 32 score blocks
         // issued: the key blocks that hold a key, for a wavefront that holds a row ----
         {
@@ -344,13 +370,13 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
                     float p[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        p[e] = __builtin_amdgcn_exp2f(fmaf(S[kb][4 * r4 + e], c2, -rb[e]));
+                        p[e] = __builtin_amdgcn_exp2f(S[kb][4 * r4 + e] - rb[e]);
                     }
                     const u32x2 w = {pack_f16(p[0], p[1]), pack_f16(p[2], p[3])};
                     most = max_f16(most, max_f16(w[0], w[1]));
                     *(u32x2*)(kt + weight_at(wave * 32 + ln, kb * 32 + 8 * r4 + 4 * g)) = w;
                 }
-            return too_large(most);
+            return near_the_end(most);
         };
         if (twice) {
             const bool over = store_weights();
@@ -364,24 +390,10 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
 #pragma unroll
                 for (int e = 0; e < 16; ++e) most = fmaxf(most, S[kb][e]);
             most = fmaxf(most, __shfl_xor(most, 32, 64));
-            // (a scale below zero: always looked at; in the own tile also weights that are all small: scores so large, 10^7 and more,
-            // that the reference misses the row's own by more than half precision holds)
-            const float heaviest = __builtin_amdgcn_exp2f(fmaf(most, c2, -ref));
-            const bool over = c2 < 0.f || too_large(pack_f16(heaviest, 0.f)) || (j == 0 && heaviest < 0.0625f);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(over) != 0ull, 0)) {
-                float mx = -INFINITY, w = 0.f;
-#pragma unroll
-                for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        mx = fmaxf(mx, S[kb][e] * c2);
-                        w = fmaxf(w, __builtin_amdgcn_exp2f(fmaf(S[kb][e], c2, -ref)));
-                    }
-                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-                w = fmaxf(w, __shfl_xor(w, 32, 64));
-                const bool raise = too_large(pack_f16(w, 0.f)) || (j == 0 && w < 0.0625f);
-                const float alpha = raise ? __builtin_amdgcn_exp2f(ref - mx) : 1.f;
-                ref = raise ? mx : ref;
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(most - ref > RAISE) != 0ull, 0)) {
+                const bool raise = most - ref > RAISE;
+                const float alpha = raise ? __builtin_amdgcn_exp2f(ref - most) : 1.f;
+                ref = raise ? most : ref;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     l[e] *= alpha;
@@ -398,8 +410,8 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
                     read_group<DK>(vf, vt, kb, hf, ln, g);
 #pragma unroll
                     for (int w = 0; w < 4; ++w) {
-                        const float p0 = __builtin_amdgcn_exp2f(fmaf(S[kb][8 * hf + 2 * w], c2, -ref));
-                        const float p1 = __builtin_amdgcn_exp2f(fmaf(S[kb][8 * hf + 2 * w + 1], c2, -ref));
+                        const float p0 = __builtin_amdgcn_exp2f(S[kb][8 * hf + 2 * w] - ref);
+                        const float p1 = __builtin_amdgcn_exp2f(S[kb][8 * hf + 2 * w + 1] - ref);
                         P[w] = pack_f16(p0, p1);
                     }
                     add_group<DK>(O, l, P, vf, ones_of_group(keys_left, kb, hf, g));
@@ -412,22 +424,14 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
-                    const int row = kb * 32 + acc_row(e, g);
-                    float mx = S[kb][e] * c2;
-                    float w = __builtin_amdgcn_exp2f(fmaf(S[kb][e], c2, -ref_b[row]));
-                    mx = max_of_half(mx);
-                    w = max_of_half(w);
-                    if (ln == 31) {
-                        max_b[wave][row] = mx;
-                        weight_b[wave][row] = w;
-                    }
+                    const float mx = max_of_half(S[kb][e]);
+                    if (ln == 31) max_b[wave][kb * 32 + acc_row(e, g)] = mx;
                 }
             lds_barrier();
             if (tid == 0) raised = 0u;
             if (tid < ST) {
                 const float mx = fmaxf(fmaxf(max_b[0][tid], max_b[1][tid]), fmaxf(max_b[2][tid], max_b[3][tid]));
-                const float w = fmaxf(fmaxf(weight_b[0][tid], weight_b[1][tid]), fmaxf(weight_b[2][tid], weight_b[3][tid]));
-                if (too_large(pack_f16(w, 0.f))) ref_b[tid] = mx;
+                if (mx - ref_b[tid] > RAISE) ref_b[tid] = mx;
             }
             lds_barrier();
             store_weights();
@@ -574,8 +578,9 @@ size_t sym_pair_workspace_floats(const Problem& pb)
     return (size_t)pb.B * pb.H * T * T * ST * (size_t)(pb.d + 2);
 }
 
-// z: [B][H][Npad][d] half precision; zt: the same vectors in the transposed layout of the
-// attention kernels; work: sym_pair_workspace_floats(pb) floats.
+// z: [B][H][Npad][d] half precision, rows past N zeros; zt: the same vectors in the transposed layout of the
+// attention kernels; work: sym_pair_workspace_floats(pb) floats.  The scale has to be above zero (as it is wherever the
+// matrix-core kernels are taken): a row's own score is then not below the zeros of the keys past N, whose weights stay finite.
 hipError_t launch_sym_pair(const Problem& pb, const h16_t* z, const h16_t* zt, float* work, bf16_t* out, hipStream_t s)
 {
     const int T = (pb.N + ST - 1) / ST;

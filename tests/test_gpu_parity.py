@@ -984,22 +984,24 @@ def _sym_both_ways(w, stored, scale):
     (8, 300, 64, 16, 128, 75),    # three tiles of d_k = 128, one run of two partners
     (1, 1500, 64, 8, 128, 150),   # twelve tiles, runs of three
 ])
-@pytest.mark.parametrize("rows", ["normal", "other rows heavier", "huge"])
+@pytest.mark.parametrize("rows", ["normal", "other rows heavier", "huge", "huger", "hugest"])
 def test_symmetric_references(shape, rows):
     """`other rows heavier`: all vectors point one way, with lengths 0.3 to 1.6, so that short rows have scores up to 15
     nats (d_k = 64; 22 at 128) above their own, across tiles, where 11 raise the reference.  z is rounded to half precision, 2^-12
     of a score of up to 90 spread over d products: 3e-3 of a weight, on top of the output's own rounding (below 8).  `huge`: scores of 1e8, where the sum of squares and the
-    product differ by more than half precision holds; every row attends to itself."""
+    product differ by more than half precision holds; every row attends to itself.  `huger`, `hugest`: of 1e9 and 1e10, where
+    they would differ by more than a float's exponent holds, and so would a score and its reference, rounded apart."""
     import torch
     B, n, D, H, d, p = shape
     w = hp.custom_workload("sym_refs", B, n, D, H, d, p, "bf16", SYM, 2900 + n)
-    scale = {"normal": 0.0, "other rows heavier": 3.0 / math.sqrt(d), "huge": 0.0}[rows]
+    scale = {"other rows heavier": 3.0 / math.sqrt(d), "hugest": 1.0}.get(rows, 0.0)
+    length = {"huge": 3000.0, "huger": 10000.0, "hugest": 10000.0}.get(rows)
     stored, f64 = inputs.make_inputs(w)
     stored["lens"] = stored["Wk"] = stored["Wv"] = None
     if rows != "normal":
         X = stored["X"].float()
-        if rows == "huge":
-            X = 3000.0 * X
+        if length:
+            X = length * X
         else:
             g = np.random.default_rng(n)
             way = X[:, :1] * (8.0 / X[:, :1].norm(dim=-1, keepdim=True))
@@ -1014,10 +1016,10 @@ def test_symmetric_references(shape, rows):
         got = np.stack([got[b, :, h * d:(h + 1) * d] for b, h in heads])
     else:
         ref = hp.oracle_forward(w, f64, SYM, scale)
-    if rows == "huge":
+    if length:
         # half an ulp of the output, at most 2^-8 of it, and of z in half precision, 2^-11; where z's 64 products of some 300
-        # cancel, the roundings of their sums: 2^-24 of 2e4 each
-        assert np.all(np.abs(got - ref) <= (2.0 ** -8 + 2.0 ** -11) * np.abs(ref) + 2e-2)
+        # (a tenth of the length) cancel, the roundings of their sums: 2^-24 of 2e4 each
+        assert np.all(np.abs(got - ref) <= (2.0 ** -8 + 2.0 ** -11) * np.abs(ref) + 2e-2 * (length / 3000.0))
     else:
         hp.tol_check(got, ref, w.dtype)
 
