@@ -39,7 +39,8 @@
  *   - bfloat16 storage: the matrix-core kernels (d_k 64 or 128, d_model a multiple of 8) contract
  *     bfloat16 operands in the projection and keep the projected q, k, v and the exponentials in half
  *     precision (same matrix-core rate, three more significand bits; values beyond its range
- *     saturate), with float accumulation throughout; out is rounded once to bfloat16.
+ *     saturate), with float accumulation throughout; out is rounded once to bfloat16.  The sum of a row's
+ *     exponentials is over floats, with ATTN_SCHEME_SYMMETRIC over their half-precision values, those that multiply v.
  *   - float storage: operands keep all their bits and sums are float, on the float matrix cores or as
  *     products of three bfloat16 planes a value on the bfloat16 ones (projections; attention of larger calls).
  *     Of the nine products of planes the six largest are summed: what is left out is at most 2^-24 of |x y|, and

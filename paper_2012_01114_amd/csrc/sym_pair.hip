@@ -11,23 +11,29 @@
 // of A; a second kernel merges the states of a row block.  The scores never leave the chip; what does
 // is 128 (d + 2) floats per second use and per run.  Tiles on the diagonal (A == B) are used once.
 //
-// Both uses take their exponentials from the accumulators: the reference of a row is its own score
-// |z_i|^2 (among the row's largest: s_ij <= |z_i| |z_j|), so no maximum is searched for, and a row has one
-// reference in every workgroup.  It comes from the MFMAs that form the scores, in their order of sums, and
-// is rounded as they are, so that a row's own weight is 1 exactly, whatever its size (a sum of squares of
-// another order misses a score of 1e9 by hundreds).  A score that exceeds it by 15.5 (base 2, 10.7 nats) makes
-// a weight near the end of half precision, and then the reference is raised to the largest score of the tile
-// (first use: before the exponentials are taken; second: they are taken again).
+// Both uses take their exponentials from the accumulators: the reference of a row is 8 (base 2) below its own
+// score |z_i|^2 (among the row's largest: s_ij <= |z_i| |z_j|), so no maximum is searched for, and a row has one
+// reference in every workgroup.  The own score comes from the MFMAs that form the scores, in their order of sums,
+// and is rounded as they are, so that a row's own weight is the same exactly in all of them, whatever its size (a
+// sum of squares of another order misses a score of 1e9 by hundreds).  A score that exceeds the reference by 15.5
+// makes a weight near the end of half precision, and then the reference is set 8 below the largest score of the
+// tile (first use: before the exponentials are taken; second: they are taken again).
+//
+// The 8 keep weights down to 2^-22 of the own one at all bits of half precision and to 2^-33 off zero: the others
+// of vectors from N(0, 1) lie around 2^-12 of it at d_k = 64 and 2^-16 at 128.  A model in 64 bits of the roundings
+// between z and out (n 200 .. 16384, z of rms 0.3 .. 1.4) has errors of 1.0 to 1.4 times those of a maximum per tile
+// with sums of unrounded weights where either is above 1e-6 (out rounds by 1.7e-3); 6 to 380 times without the 8 at
+// rms 1.2 to 1.4 and n 8192 and more.
 // The exponentials of the second use are stored to LDS in half precision, [row of A][row of B], and
-// read back as operands by the transposing read.  Row sums are MFMAs with ones: sums of the weights
-// as rounded, the same for either use.
+// read back as operands by the transposing read.  Row sums are MFMAs with ones: float sums of the weights
+// as rounded (what multiplies V is what is summed), the same for either use.
 //
 // What bounds it: exponentials (16 cycles per 64 pairs and use) and the partial states.  96 heads of
 // 512 at d_k = 64, us (pairs, merge): 30.9, 10.3 with a workgroup per pair of tiles, scores staged in fp32,
 // maxima and a state per use, 22.2, 7.3 so; 32 heads of 2048 159 -> 93 together, 8 heads of 2048 at d_k = 128
 // 97 -> 62.  Of that the barriers that leave memory alone gave 4, addresses recomputed per tile (no spills) 4.
 // One vector in 50 four times as long as the others, so that most tiles raise a reference: 8 heads of 2048,
-// whole calls, 42 -> 45 us.
+// whole calls, 43 -> 48 us.
 //
 // The paper's selection rule (Sec. 4.2: circulant diagonals 0 .. floor(P/2) of the P x P matrix of
 // (n/P)-row tiles, the middle one computed by both owners when P is even) fixes WHICH element of a
@@ -179,23 +185,10 @@ __device__ __forceinline__ unsigned max_f16(unsigned a, unsigned b)
 // Scores above a row's reference by more raise it; their weights are at most 2^15.5, and one of two weights (not negative)
 // that are such says so here.
 constexpr float RAISE = 15.5f;
+constexpr float BELOW = 8.f;
+// A row's reference by the score at hand.  From 2^26 on scores are 8 and more apart, and a step of 8 could become one of 16.
+__device__ __forceinline__ float reference(float score) { return score < 0x1p26f ? score - BELOW : score; }
 __device__ __forceinline__ bool near_the_end(unsigned m) { return (m & 0xFFFFu) >= 0x7800u || m >= 0x78000000u; }
-
-// The largest value of the 32 lanes of a half, in its last 16 lanes.
-__device__ __forceinline__ float max_of_half(float x)
-{
-    auto step = [&](auto control) {
-        constexpr int C = decltype(control)::value;
-        const int i = __builtin_bit_cast(int, x);
-        x = fmaxf(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, C, 0xF, 0xF, false)));
-    };
-    step(std::integral_constant<int, 0xB1>{});   // lane ^ 1
-    step(std::integral_constant<int, 0x4E>{});   // lane ^ 2
-    step(std::integral_constant<int, 0x141>{});  // mirrored in 8 lanes
-    step(std::integral_constant<int, 0x140>{});  // mirrored in 16 lanes
-    step(std::integral_constant<int, 0x142>{});  // the last lane of 16 to the next 16
-    return x;
-}
 
 template <int DK>
 __device__ __forceinline__ void store_state(const f32x16 (&O)[DK / 32], float m, float l, int g, float* __restrict__ pm,
@@ -225,8 +218,8 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
     constexpr int NKS = Y::NKS, NDB = Y::NDB;
     __shared__ __attribute__((aligned(16))) unsigned char lds[Y::LDS_BYTES];
     __shared__ __attribute__((aligned(16))) float ref_b[ST];
-    __shared__ float max_b[4][ST];
-    __shared__ unsigned raised;
+    __shared__ float high_b[ST];
+    __shared__ unsigned raised, raised_rows[ST / 32];
     unsigned char* const kt = lds;  // K tile of B, then the weights
     unsigned char* const vt = lds + Y::KW_BYTES;
     unsigned char* const vt_a = Y::RESIDENT ? vt + Y::V_BYTES : vt;
@@ -259,24 +252,29 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) qf[ks] = *(const u32x4*)(zh + at + ks * 16);
     };
+    fetch_q(ia * DK + g * 8);
     kr.fetch(zh, partner(j0) * ST, tid);
     vr.fetch(zth, partner(j0) * ST, tid);
-    fetch_q(ia * DK + g * 8);
+    f32x16 O[NDB], l;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) l[e] = 0.f;
+    auto own_scores = [&]() __attribute__((always_inline)) {  // behind the requests of the tiles
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) l = mfma32h(qf[ks], qf[ks], l);
+    };
     if constexpr (Y::RESIDENT) {
         VtTile<DK> va;
         va.fetch(zth, A * ST, tid);
-        __builtin_amdgcn_sched_barrier(0);
+        own_scores();
         va.stage(vt_a, tid);
+    } else {
+        own_scores();
     }
     kr.stage(kt, tid);
     vr.stage(vt, tid);
     if (tid == 0) raised = 0u;
-    f32x16 O[NDB], l;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) l[e] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) l = mfma32h(qf[ks], qf[ks], l);
-    float ref = diagonal(l, ln) * c2;
+    float ref = reference(diagonal(l, ln) * c2);
     const float other = __shfl_xor(ref, 32, 64);
     if (!holds_diagonal(ln, g)) ref = other;
 #pragma unroll
@@ -314,8 +312,8 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
                 const u32x4 f = *(const u32x4*)(kt + row * Y::KROWB + swz<Y::KROWB>(2 * ks + g, row) * 16);
                 own = mfma32h(f, f, own);
             }
-            const float x = diagonal(own, ln) * c2;
-            if (holds_diagonal(ln, g)) ref_b[row] = x;
+            const float x = reference(diagonal(own, ln) * c2);
+            if (holds_diagonal(ln, g)) ref_b[row] = high_b[row] = x;
         }
         // ---- phase 1 (Eq. (1)), once: S^T = z_B . z_A^T, the wavefront's 32 rows of A against 128 keys of B ----
         f32x16 S[4];
@@ -359,28 +357,25 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
             vr.fetch(zth, A * ST, tid);
         }
         // ---- weights of the second use: rows of B against keys of A ----
-        auto store_weights = [&]() {
+        auto store_group = [&](int kb, int r4) __attribute__((always_inline)) -> unsigned {  // the largest, in either half
+            const f32x4 rb = *(const f32x4*)(ref_b + kb * 32 + 8 * r4 + 4 * g);
+            float p[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(S[kb][4 * r4 + e] - rb[e]);
+            const u32x2 w = {pack_f16(p[0], p[1]), pack_f16(p[2], p[3])};
+            *(u32x2*)(kt + weight_at(wave * 32 + ln, kb * 32 + 8 * r4 + 4 * g)) = w;
+            return max_f16(w[0], w[1]);
+        };
+        if (twice) {
             unsigned most = 0u;
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
                 for (int r4 = 0; r4 < 4; ++r4) {
                     if ((r4 & 1) == 0) __builtin_amdgcn_sched_barrier(0);
-                    const f32x4 rb = *(const f32x4*)(ref_b + kb * 32 + 8 * r4 + 4 * g);
-                    float p[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        p[e] = __builtin_amdgcn_exp2f(S[kb][4 * r4 + e] - rb[e]);
-                    }
-                    const u32x2 w = {pack_f16(p[0], p[1]), pack_f16(p[2], p[3])};
-                    most = max_f16(most, max_f16(w[0], w[1]));
-                    *(u32x2*)(kt + weight_at(wave * 32 + ln, kb * 32 + 8 * r4 + 4 * g)) = w;
+                    most = max_f16(most, store_group(kb, r4));
                 }
-            return near_the_end(most);
-        };
-        if (twice) {
-            const bool over = store_weights();
-            if (__builtin_amdgcn_ballot_w64(over) != 0ull && lane == 0) raised = 1u;
+            if (__builtin_amdgcn_ballot_w64(near_the_end(most)) != 0ull && lane == 0) raised = 1u;
         }
         // ---- first use: phases 2 and 3 of the rows of A over the keys of B ----
         {
@@ -392,8 +387,9 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
             most = fmaxf(most, __shfl_xor(most, 32, 64));
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(most - ref > RAISE) != 0ull, 0)) {
                 const bool raise = most - ref > RAISE;
-                const float alpha = raise ? __builtin_amdgcn_exp2f(ref - most) : 1.f;
-                ref = raise ? most : ref;
+                const float higher = raise ? reference(most) : ref;
+                const float alpha = __builtin_amdgcn_exp2f(ref - higher);
+                ref = higher;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     l[e] *= alpha;
@@ -419,22 +415,34 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
         }
         lds_barrier();  // the weights of the second use are complete, V^T of B no longer needed
         if (twice && __builtin_expect(raised != 0u, 0)) {
-            // some row of B has a score too large for its reference: its largest score of the tile takes the place
+            // some rows of B have scores too large for their references: 8 below the largest of the tile take the places
 #pragma unroll
             for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float mx = max_of_half(S[kb][e]);
-                    if (ln == 31) max_b[wave][kb * 32 + acc_row(e, g)] = mx;
+                for (int r4 = 0; r4 < 4; ++r4) {
+                    const int row = kb * 32 + 8 * r4 + 4 * g;
+                    const f32x4 rb = *(const f32x4*)(ref_b + row);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (S[kb][4 * r4 + e] - rb[e] > RAISE) atomicMax(high_b + row + e, S[kb][4 * r4 + e]);
                 }
             lds_barrier();
             if (tid == 0) raised = 0u;
             if (tid < ST) {
-                const float mx = fmaxf(fmaxf(max_b[0][tid], max_b[1][tid]), fmaxf(max_b[2][tid], max_b[3][tid]));
-                if (mx - ref_b[tid] > RAISE) ref_b[tid] = mx;
+                const float mx = high_b[tid];
+                const bool raise = mx - ref_b[tid] > RAISE;
+                if (raise) ref_b[tid] = reference(mx);
+                const unsigned long long rows = __builtin_amdgcn_ballot_w64(raise);
+                if (ln == 0) raised_rows[tid >> 5] = (unsigned)(rows >> (32 * g));
             }
             lds_barrier();
-            store_weights();
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) {
+                const unsigned rows = __builtin_amdgcn_readfirstlane(raised_rows[kb]);
+#pragma unroll
+                for (int r4 = 0; r4 < 4; ++r4)
+                    if ((rows >> (8 * r4)) & 0xFFu) store_group(kb, r4);
+            }
             lds_barrier();
         }
         if constexpr (Y::RESIDENT) {

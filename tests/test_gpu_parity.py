@@ -1024,6 +1024,30 @@ def test_symmetric_references(shape, rows):
         hp.tol_check(got, ref, w.dtype)
 
 
+@pytest.mark.parametrize("n,d", [(90, 64), (256, 64), (250, 128), (1500, 64)])   # one tile; two, both uses; runs of several
+def test_symmetric_small_weights_keep_their_bits(n, d):
+    """z = X.  Some fifty long vectors each along an axis of their own, whose own scores are 16 to 24 (base 2), among others
+    that have one in the last column and score 0 against them.  A long row's last column is the sum of weights of 2^-16 to
+    2^-24 of its own one.  Bound: the output's rounding, 2^-8 of it, and that of a weight in half precision, 2^-11, and of
+    their sum and the row's, 2^-11."""
+    import torch
+    c2 = math.log2(math.e) / math.sqrt(d)
+    w = hp.custom_workload("sym_small", 1, n, d, 1, d, 1, "bf16", SYM, 2950 + n)
+    X = torch.zeros(1, n, d)
+    X[:, :, d - 1] = 1.0
+    long_rows = range(0, n, -(-n // 50))
+    for axis, i in enumerate(long_rows):
+        X[0, i] = 0.0
+        X[0, i, axis] = math.sqrt((16.0 + 8.0 * (axis % 17) / 16.0) / c2)
+    stored = {"X": X.to(torch.bfloat16), "Wq": torch.eye(d).to(torch.bfloat16), "Wk": None, "Wv": None, "lens": None}
+    X, eye = stored["X"].double().numpy(), np.eye(d)
+    ref = hp.oracle_forward(w, {"X": X, "Wq": eye, "Wk": eye, "Wv": eye}, SYM, 0.0)
+    got = _sym_both_ways(w, stored, 0.0)
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-3)
+    got, ref = got[0, list(long_rows), d - 1], ref[0, list(long_rows), d - 1]
+    assert np.all(ref > 0.0) and np.all(np.abs(got - ref) <= (2.0 ** -8 + 2.0 ** -10) * ref), f"{np.abs(got / ref - 1.0).max():.2e}"
+
+
 # ---- row maxima that move along the walk: the running reference of Eq. (2)'s online form ----------
 @pytest.mark.parametrize("profile", ["ramp", "steps"])
 @pytest.mark.parametrize("scheme", [FULL, CAUSAL])
