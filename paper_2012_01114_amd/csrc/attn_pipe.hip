@@ -635,7 +635,7 @@ void attn_pipe_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, cons
             for (int it = 0; it < 32 * CPR / 64; ++it) {
                 const int row = it * (64 / CPR) + le / CPR, c = le % CPR;
                 const u32x4 v = *(const u32x4*)(stage + row * (DK * 2) + ((c ^ (row & (CPR - 1))) << 4));
-                if (i0w + row < n_out) *(u32x4*)(obase + (size_t)row * ((size_t)pb.H * DK) + c * 8) = v;
+                if (i0w + row < n_out) *(u32x4_out*)(obase + (size_t)row * ((size_t)pb.H * DK) + c * 8) = v;
             }
             if (pass + 1 < n_pass) {
                 // the next pass refills the ring: every wavefront has to be done with its staging first

@@ -347,7 +347,7 @@ void attn_strands_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, c
         y0 *= inv;
         y1 *= inv;
         if (I * BR + row < n_out)
-            *(u32x4*)(out + (out_row0 + I * BR + row) * ((size_t)pb.H * DK) + (size_t)h * DK + c0) =
+            *(u32x4_out*)(out + (out_row0 + I * BR + row) * ((size_t)pb.H * DK) + (size_t)h * DK + c0) =
                 u32x4{pack_bf16(y0[0], y0[1]), pack_bf16(y0[2], y0[3]), pack_bf16(y1[0], y1[1]), pack_bf16(y1[2], y1[3])};
     }
 }

@@ -12,6 +12,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4_out __attribute__((ext_vector_type(4), aligned(8)));  // 16 bytes of `out`, which starts at a multiple of 8
 
 // v_mfma_f32_32x32x16_bf16: D[32x32] += A[32x16] * B[16x32], one wavefront.
 // Lane L supplies row (L % 32) of A and column (L % 32) of B, eight consecutive

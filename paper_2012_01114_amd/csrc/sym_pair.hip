@@ -512,7 +512,7 @@ __global__ __launch_bounds__(256, 2) void sym_pair_kernel(Problem pb, CountCfg c
         for (int it = 0; it < 32 * CPR / 64; ++it) {
             const int row = it * (64 / CPR) + lane / CPR, c = lane % CPR;
             const u32x4 v = *(const u32x4*)(stage + row * (DK * 2) + ((c ^ (row & (CPR - 1))) << 4));
-            if (wave * 32 + row < N) *(u32x4*)(out + ((size_t)bb * N + wave * 32 + row) * ((size_t)pb.H * DK) + (size_t)h * DK + c * 8) = v;
+            if (wave * 32 + row < N) *(u32x4_out*)(out + ((size_t)bb * N + wave * 32 + row) * ((size_t)pb.H * DK) + (size_t)h * DK + c * 8) = v;
         }
     } else if (ia < N) {
         const size_t slot = (((size_t)bh * T + A) * T + partner(j0)) * ST + wave * 32 + ln;

@@ -1048,6 +1048,41 @@ def test_symmetric_small_weights_keep_their_bits(n, d):
     assert np.all(ref > 0.0) and np.all(np.abs(got - ref) <= (2.0 ** -8 + 2.0 ** -10) * ref), f"{np.abs(got / ref - 1.0).max():.2e}"
 
 
+# ---- `out` need not start at a multiple of 16 bytes: 8 are enough on the matrix-core path ------------------
+@pytest.mark.parametrize("kernel,scheme,tiles,shape", [
+    # kernel, scheme, tile flag, (B, n, D, H, d, p)
+    ("attn_split_kernel<64,", FULL, 0, (2, 200, 64, 2, 64, 25)),
+    ("attn_split_kernel<128,", CAUSAL, 0, (2, 130, 64, 2, 128, 13)),
+    ("attn_strands_kernel<64, 4,", CAUSAL, 0, (1, 1030, 64, 3, 64, 103)),
+    ("attn_strands_kernel<64, 3,", FULL, 0, (2, 516, 64, 19, 64, 129)),
+    ("attn_strands_kernel<128, 2,", CAUSAL, 0, (1, 1100, 64, 8, 128, 275)),
+    ("attn_pipe_kernel<64, 4,", CAUSAL, ar.ATTN_FLAG_NARROW_TILES, (2, 300, 64, 2, 64, 75)),
+    ("attn_pipe_kernel<64, 8,", FULL, ar.ATTN_FLAG_WIDE_TILES, (2, 300, 64, 2, 64, 75)),
+    ("attn_pipe_kernel<128, 8,", FULL, ar.ATTN_FLAG_WIDE_TILES, (2, 300, 64, 1, 128, 75)),
+    ("sym_pair_kernel<64>", SYM, 0, (2, 90, 64, 2, 64, 10)),      # one tile: stored by the pair kernel
+    ("sym_pair_kernel<128>", SYM, 0, (2, 90, 64, 1, 128, 10)),
+    ("sym_merge_kernel<64>", SYM, 0, (2, 300, 64, 2, 64, 75)),
+])
+def test_out_at_a_multiple_of_8_bytes(kernel, scheme, tiles, shape):
+    import torch
+    w = hp.custom_workload("out_8", *shape, "bf16", scheme, 3300)
+    stored, _ = inputs.make_inputs(w)
+    run = hp.GpuRun(w, stored, flags=tiles)
+    try:
+        aligned, _ = run.forward(scheme)
+        room = torch.full((run.out.numel() + 16,), 7.0, dtype=run.out.dtype, device=run.out.device)
+        for first in (4, 12):
+            run.out = room[first:first + aligned.size].view(aligned.shape)
+            assert run.out.data_ptr() % 16 == 8
+            run.out.fill_(float("nan"))
+            assert any(kernel in k for k in run.kernels(scheme))
+            assert np.array_equal(run.forward(scheme)[0], aligned)
+            assert torch.all(room[:first] == 7.0) and torch.all(room[first + aligned.size:] == 7.0)
+            room.fill_(7.0)
+    finally:
+        run.close()
+
+
 # ---- row maxima that move along the walk: the running reference of Eq. (2)'s online form ----------
 @pytest.mark.parametrize("profile", ["ramp", "steps"])
 @pytest.mark.parametrize("scheme", [FULL, CAUSAL])
