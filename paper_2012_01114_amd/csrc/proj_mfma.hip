@@ -106,7 +106,13 @@ inline TileMap tile_map(const Problem& pb, int bx, int bw, int matrices, bool sp
     tm.tiles_x = pb.B * per_item;
     tm.tiles_w = matrices * pb.H * pb.d / bw;
     tm.n_tiles = tm.tiles_x * tm.tiles_w;
-    tm.group_w = spread ? matrices : GROUP_W;
+    // 64 x 64 tiles that are more than the CUs, two workgroups to some of them: groups of three.  What tiles come to share a CU
+    // (32 apart in an XCD's run) decides, in groups of four often tiles of the same x rows; measured, whole calls, four / three
+    // (rows, d_model -> columns): 256 x 4096 -> 4608 40.2 / 31.8, 512 x 4096 -> 2304 34.7 / 30.3, 360 x 4096 -> 4608 40.5 / 35.1, 128 x
+    // 4096 -> 12288 54.3 / 49.7, 384 x 768 -> 4608 17.1 / 16.4, 400 x 1024 -> 3072 18.1 / 18.0; the other way 320 x 4096 -> 6144 38.3 /
+    // 41.2, 4096 x 1024 -> 384 22.0 / 22.2.  Up to 256 tiles within 1 %.
+    const bool shared = bx == 64 && tm.n_tiles > 256 && tm.n_tiles <= 512;
+    tm.group_w = spread ? matrices : shared ? 3 : GROUP_W;
     tm.width = fast_div((unsigned)(tm.group_w * tm.tiles_x));
     tm.per_item = fast_div((unsigned)per_item);
     tm.spread = spread ? matrices : 0;
@@ -1072,13 +1078,14 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
     const int HD = pb.H * pb.d;
     const long t256 = HD % 256 == 0 ? (long)pb.B * ((pb.N + 255) / 256) * ((pb.no_q ? 2L : 3L) * HD / 256) : 0;
     if (proj_reads_weights_in_place(pb, Wq, Wk, Wv)) {  // operands go straight to LDS
-        // Few tiles: 64 x 64 ones, where they find a CU each, or at short d_model half of one.  Measured (us, 128 x 128 / 64 x 64,
-        // by the number of 64 x 64 tiles): d_model 768, 144 11.3 / 9.3, 288 11.8 / 11.2, 432 (1024) 13.5 / 12.5, 480 (1096) 17.7 / 16.1, 576
-        // 12.9 / 13.7, 900 15.8 / 17.4; d_model 2048, 384 28.2 / 29.9, 26.7 / 29.5; 3072, 384 26.9 / 26.7; 4096, 192 45.3 / 33.1.
+        // Few tiles: 64 x 64 ones, up to two to a CU.  Measured (us, 128 x 128 / 64 x 64, by the number of 64 x 64 tiles), the kernel
+        // at d_model 768: 144 11.3 / 9.3, 288 11.8 / 11.2, 576 12.9 / 13.7, 900 15.8 / 17.4; whole calls of 128 to 640 rows at d_model
+        // 4096: -> 3072 columns 288 37.8 / 30.9, 384 38.9 / 36.1, 432 37.9 / 31.8; -> 4608 288 38.9 / 31.8, 360 40.2 / 38.9, 432 38.5 / 35.1; ->
+        // 6144 288 34.6 / 28.0, 384 37.7 / 33.5, 480 40.3 / 41.2; -> 9216 288 38.9 / 35.8, 432 39.6 / 36.9; -> 2304 360 43.8 / 40.0.
         // Columns not in 128s have no other tiles: 8192 x 960 -> 2880 78 us, 32768 x 1024 -> 2880 322, 32768 x 4096 -> 2880 1408.
         const long cols = (pb.no_q ? 2L : 3L) * HD;
         const long t64 = (long)pb.B * ((pb.N + 63) / 64) * (cols / 64);
-        if (HD % 128 != 0 || t64 <= 256 || (t64 <= 512 && pb.D <= 1280)) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
+        if (HD % 128 != 0 || t64 <= 512) return launch_small(pb, X, Wq, Wk, Wv, q, k, vt, s);
         const long t128x256 = HD % 256 == 0 ? (long)pb.B * ((pb.N + 127) / 128) * (cols / 256) : 0;
         // At long d_model 256 x 256 where its tiles, one to a CU, fill four fifths of their rounds of the chip (256 x 256 /
         // 128 x 256: 432 tiles 110 / 112, 576 157 / 140, d_model 2048).

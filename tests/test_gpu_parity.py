@@ -911,6 +911,31 @@ def test_projection_rounds_of_large_tiles(tile, shape):
         hp.tol_check(got[b, rows, h * d:(h + 1) * d], ref, w.dtype)
 
 
+# ---- 64 x 64 tiles that are more than the CUs: groups of three column tiles --------------------------------------
+@pytest.mark.parametrize("scheme,lens,shape", [
+    # B, n, D, H, d, p
+    (CAUSAL, False, (2, 150, 1288, 16, 64, 25)),   # 288 tiles, 24 in the last row tile; a cut slice
+    (FULL, True, (3, 150, 1344, 12, 64, 25)),      # 324, with key lengths (dealt over the matrices)
+    (FULL, False, (1, 340, 64, 14, 128, 85)),      # 504
+    (SYM, False, (1, 900, 64, 10, 64, 225)),       # 300; 20 column tiles, two in the last group
+    (FULL, False, (1, 600, 640, 8, 80, 75)),       # 300, left as floats
+])
+def test_projection_of_small_tiles_that_share_cus(scheme, lens, shape):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload("shared", B, n, D, H, d, p, "bf16", scheme, 7790 + n)
+    stored, f64 = inputs.make_inputs(w)
+    stored["lens"] = np.resize(np.array([n, 70, 1], dtype=np.int32), B) if lens else None
+    if scheme == SYM:
+        f64["Wk"] = f64["Wv"] = f64["Wq"]
+    run = hp.GpuRun(w, stored)
+    try:
+        assert any("proj_small_kernel<5," in k for k in run.kernels(scheme))
+        got, _ = run.forward(scheme)
+    finally:
+        run.close()
+    hp.tol_check(got, hp.oracle_forward(w, f64, scheme, 0.0, lens=stored["lens"]), w.dtype)
+
+
 # ---- queries projected inside the attention kernel (ATTN_FLAG_FUSE_Q_PROJECTION) ----------------------
 @pytest.mark.parametrize("shape", [
     (2, 320, 64, 2, 64, 40),      # two 32-row slices of Wq
