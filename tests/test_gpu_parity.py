@@ -1139,6 +1139,33 @@ def test_reference_moves_along_the_walk(profile, scheme, d_k, tiles):
         hp.check_counts(stats, hp.oracle_counts(w, scheme, lens))
 
 
+# ---- the same in the kernels whose wavefronts share the keys: every strand has references of its own ----------
+@pytest.mark.parametrize("profile", ["ramp", "steps"])
+@pytest.mark.parametrize("scheme", [FULL, CAUSAL])
+@pytest.mark.parametrize("kernel,shape", [
+    # kernel, B, n, D, H, d, p
+    ("attn_split_kernel<64,", (2, 900, 64, 2, 64, 225)),
+    ("attn_split_kernel<128,", (2, 900, 64, 2, 128, 225)),
+    ("attn_strands_kernel<64, 4,", (2, 1100, 64, 2, 64, 275)),
+    ("attn_strands_kernel<64, 3,", (2, 900, 64, 10, 64, 225)),
+    ("attn_strands_kernel<128, 2,", (2, 1100, 64, 4, 128, 275)),
+])
+def test_reference_moves_along_shared_walks(profile, scheme, kernel, shape):
+    B, n, D, H, d, p = shape
+    w = hp.custom_workload(f"shared_levels_{profile}", B, n, D, H, d, p, "bf16", scheme, 950 + d)
+    stored, f64 = inputs.make_level_inputs(w, profile, hp.default_scale(w, 0.0))
+    for lens in (None, np.array([n, 700], dtype=np.int32)):
+        stored["lens"] = lens
+        run = hp.GpuRun(w, stored)
+        try:
+            assert any(kernel in k for k in run.kernels(scheme))
+            got, stats = run.forward(scheme)
+        finally:
+            run.close()
+        hp.tol_check(got, hp.oracle_forward(w, f64, scheme, 0.0, lens=lens), w.dtype)
+        hp.check_counts(stats, hp.oracle_counts(w, scheme, lens))
+
+
 # ---- the -inf practice (Sec. 5.1) against skipping: identical bits ------------------------------
 @pytest.mark.parametrize("case", [
     ("f32", 1, 48, 32, 2, 16, 6, 0),
