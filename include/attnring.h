@@ -162,7 +162,8 @@ attn_status attn_set_key_lengths(attn_ctx* ctx, const int32_t* lens_dev);
  * (may be NULL); Wq == NULL means z = x and needs d_model == n_heads*d_k.  On the
  * matrix-core path (bfloat16, d_k 64 or 128, Wq given) every 128 x 128 score tile is
  * computed once and used for both of its row blocks (Sec. 4.1, Eq. (4)), the scores stay
- * on chip and 128 (d_k + 2) floats of partial row state per use go through device memory;
+ * on chip, and 128 (d_k + 2) floats of partial row state go through device memory for every second use of a
+ * tile and for every run of tiles that a workgroup adds up (none where n is at most 128);
  * elsewhere one score matrix per (batch, head) does.  Either workspace is bounded by
  * 1 GiB; a shape beyond it on both paths is refused (UNSUPPORTED).
  * Errors: INVALID (NULL ctx/X/out, NULL weights where needed, bad scheme),

@@ -35,7 +35,8 @@ __device__ __forceinline__ int swz(int chunk, int row)
 // One wavefront copies 1 KiB pieces of a [rows][ROWB] tile from global memory to
 // LDS: piece m holds rows m*RPP .. ; lane L lands at byte 16*L of the piece and
 // fetches the chunk that belongs there under the swizzle.  With the pieces of a
-// wavefront 4 or 8 apart, the lane's byte offset inside its piece does not depend
+// wavefront whole periods of the swizzle (16 rows: 2 pieces of 128-byte rows, 4 of
+// 256-byte ones) apart, the lane's byte offset inside its piece does not depend
 // on the piece, so it is computed once (dma_lane_offset) and every copy is a
 // uniform base (buffer descriptor and scalar offset) plus that offset.
 template <int ROWB>

@@ -2,7 +2,7 @@
 // between the small ones of attn_split.hip and those that fill the chip with attn_pipe.hip's workgroups.
 //
 // What bounds such a launch is the length of one wavefront's walk on a chip that is partly idle: attn_pipe.hip
-// gives a CU 256 rows (d_k = 128) or 128 (d_k = 64) and every wavefront all keys of its rows.  Here the eight
+// gives a CU 256 rows (d_k = 128) or 128 (d_k = 64) and every wavefront all keys of its rows.  Here the eight or twelve
 // wavefronts of a workgroup are KS strands of RW: a wavefront owns 32 query rows, the wavefronts of a strand
 // the RW * 32 rows of the workgroup, and strand s takes tiles s, s + KS, ... of the walk (the ring is met in KS
 // strands).  Half (a quarter) of the rows per workgroup, half (a quarter) of the walk, for the same operand
@@ -10,12 +10,12 @@
 // LDS at the end.  The walk itself, block by block, is that of attn_pipe.hip (attn_walk.h).
 //
 // Order of phases.  Wavefronts w and w + 4 share a SIMD; step t is tile t of every strand:
-//     wavefronts 0..3:  | E(2t)     M(2t)  E(2t+1)  M(2t+1)  | ...
-//     wavefronts 4..7:  | M(2t-1)   E(2t)  M(2t)    E(2t+1)  | M(2t+1) ...
+//     wavefronts 0..3 (and 8..11):  | E(2t)     M(2t)  E(2t+1)  M(2t+1)  | ...
+//     wavefronts 4..7:              | M(2t-1)   E(2t)  M(2t)    E(2t+1)  | M(2t+1) ...
 // with the workgroup barrier of step t at the bar: one side is in a vector phase while the other is in a matrix
 // phase.  LDS is read in vector phases only (K of the next block, V^T of this one), so that behind barrier t every
-// wavefront reads V^T of step t, K of steps t and t + 1: K needs one ring stage more than V^T, and 96 + 64 KiB
-// hold the rings of 128-row workgroups at d_k = 128.
+// wavefront reads V^T of step t, K of steps t and t + 1: three ring stages of K and two of V^T, 160 KiB in all with two
+// strands at d_k = 128 and four at 64, 120 with three.  Every barrier waits for all copies sent behind the one before.
 //
 // d_k = 128: two strands of four wavefronts (two per SIMD, 234 registers); d_k = 64: three of four (three per SIMD) or,
 // where 64-row workgroups still find a CU each, four of two.  Measured against attn_pipe.hip: 3 x 1100 rows, 8 heads of 128,
@@ -38,15 +38,14 @@ struct Strands : Walk<DK> {
     static constexpr int BR = 32 * RW;                     // rows per workgroup
     static constexpr int KPIECES = K_BYTES / 1024 / RW;    // 1 KiB copy pieces per wavefront and tile
     static constexpr int VPIECES = V_BYTES / 1024 / RW;
-    static constexpr int PPW = KPIECES + VPIECES;
     static constexpr int K_STAGE = KS * K_BYTES, V_STAGE = KS * V_BYTES;
-    static constexpr int NK = (160 * 1024 + V_STAGE) / (K_STAGE + V_STAGE);  // 3 to 5 stages of K, one less of V^T
-    static constexpr int NV = NK - 1;
+    static constexpr int NK = 3, NV = 2;
     static constexpr int V_BASE = NK * K_STAGE;
     static constexpr int PITCH = DK + 4;                   // floats per row of a partial state in LDS
     static constexpr int MERGE = KS * BR * (PITCH + 2) * 4;
     static constexpr int LDS = V_BASE + NV * V_STAGE;
     static_assert(LDS <= 160 * 1024 && MERGE <= LDS, "what a CU holds");
+    static_assert(RW * 1024 / (DK * 2) % 16 == 0 && RW * 1024 / (BC * 2) % 16 == 0, "dma_lane_offset: whole periods of the swizzle");
 };
 
 template <int DK, int KS, int RW, bool CAUSAL>
@@ -183,28 +182,23 @@ void attn_strands_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, c
             v_slot = v_slot + T::V_STAGE == T::NV * T::V_STAGE ? 0 : v_slot + T::V_STAGE;
         };
         // Barrier of step t: behind it K of steps t and t + 1 and V^T of step t are in LDS, and the stages of K of
-        // step t - 1 and of V^T of step t - 1, which nobody reads any more, take the next requests.  Those of the
-        // last NK - 3 barriers may still be in flight, where each of them has sent all of its pieces.
-        auto step_sync = [&](int t) {
-            if (T::NK > 3 && t + T::NK - 2 < n_own)
-                __builtin_amdgcn_s_waitcnt(0x0F70 | ((T::NK - 3) * T::PPW));
-            else
-                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-            __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wavefront's LDS reads are done
+        // step t - 1 and of V^T of step t - 1, which nobody reads any more, take the next requests.
+        auto step_sync = [&]() {
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront's LDS reads are done
             __builtin_amdgcn_s_barrier();
-            request_k();  // of step t + NK - 1
-            request_v();  // of step t + NV - 1
+            request_k();  // of step t + 2
+            request_v();  // of step t + 1
         };
-        static_assert((T::NK - 3) * T::PPW < 16, "the low bits of the wait count");
 #pragma unroll
         for (int t = 0; t < T::NV; ++t) {
             request_k();
             if (t < T::NV - 1) request_v();
         }
-        step_sync(0);
+        step_sync();
         int next_sync = 1;
         const int t_first = n_first >> 1;
-        for (; next_sync <= t_first && next_sync < n_steps; ++next_sync) step_sync(next_sync);
+        for (; next_sync <= t_first && next_sync < n_steps; ++next_sync) step_sync();
 
         if (n_first < NB) {
             typename T::Frags fr;
@@ -268,7 +262,7 @@ void attn_strands_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, c
             const std::integral_constant<int, 1> upper{};
             const std::integral_constant<int, 0> lower{};
             auto end_of_step = [&]() {  // between the two phases of a tile's lower block
-                if (late && next_sync == t + 1 && next_sync < n_steps) { step_sync(next_sync); ++next_sync; }
+                if (late && next_sync == t + 1 && next_sync < n_steps) { step_sync(); ++next_sync; }
                 phase_m();
                 ++t;
                 kst = kst + T::K_STAGE == T::V_BASE ? 0 : kst + T::K_STAGE;
@@ -278,7 +272,7 @@ void attn_strands_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, c
 #pragma nounroll
                 while (t < t_end) {
                     const int J = masked ? tile_of_step(t) : 0;
-                    if (!late && next_sync == t) { step_sync(t); ++next_sync; }
+                    if (!late && next_sync == t) { step_sync(); ++next_sync; }
                     phase_e(upper, masked, J);
                     phase_m();
                     phase_e(lower, masked, J);
@@ -294,7 +288,7 @@ void attn_strands_kernel(Problem pb, CountCfg cc, const h16_t* __restrict__ q, c
             run_steps(t_edge_end < n_own ? t_edge_end : n_own, true);
             run_steps(n_own, false);
         }
-        for (; next_sync < n_steps; ++next_sync) step_sync(next_sync);
+        for (; next_sync < n_steps; ++next_sync) step_sync();
         __builtin_amdgcn_s_waitcnt(0xC07F);
         __builtin_amdgcn_s_barrier();  // the partial states go where the rings were
     }

@@ -135,8 +135,8 @@ hipError_t launch_proj_mfma(const Problem& pb, const bf16_t* X, const bf16_t* Wq
 // X and Wq given: the kernel projects its queries itself (q is not read).
 hipError_t launch_attn_pipe(const Problem& pb, const h16_t* q, const h16_t* k, const h16_t* vt,
                             bf16_t* out, int waves, hipStream_t s, const bf16_t* X, const bf16_t* Wq);
-// The same for launches that leave much of the chip idle with the workgroups above: `strands` (2, or 4 for d_k = 64) sets of
-// wavefronts share the keys of 256 / strands rows.
+// The same for launches that leave much of the chip idle with the workgroups above: `strands` sets of wavefronts share the
+// keys of a workgroup's rows: 2 (d_k = 128, 128 rows), 3 (d_k = 64, 128 rows) or 4 (d_k = 64, 64 rows).
 hipError_t launch_attn_strands(const Problem& pb, const h16_t* q, const h16_t* k, const h16_t* vt, bf16_t* out, int strands,
                                hipStream_t s);
 // One of attn_pipe.hip, attn_strands.hip and attn_split.hip, by the size of the launch; asked_waves: 4 or 8 when the
