@@ -34,10 +34,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16, published
 # the same counter reads for a plain 1 GiB device copy: x2.00 and x1.00; see profiles/).  They hold for
 # the sources of these kernels with the hash below; with other sources the bench line carries null.
 TRAFFIC_SOURCES = ("proj_mfma.hip", "attn_pipe.hip", "attn_walk.h", "attn_common.h", "mfma_common.h", "common.h")
-TRAFFIC_SOURCES_SHA256 = "007151e3fc0b78480c8603f89c3a9c07c786cf8c37f76d0c4e8bdc122f9afed7"
+TRAFFIC_SOURCES_SHA256 = "34354e3a6552f2cb3c5ff0dc7615b13d49e90588978758464771fc61a6c60b47"
 TRAFFIC_BYTES = {
-    "long": {"projection": int((2 * 589944 + 196640) * 1024), "attention": int((2 * 137374 + 65792) * 1024)},
-    "causal": {"projection": int((2 * 38104 + 36896) * 1024), "attention": int((2 * 18772 + 12480) * 1024)},
+    "long": {"projection": int((2 * 589945 + 196640) * 1024), "attention": int((2 * 142379 + 65792) * 1024)},
+    "causal": {"projection": int((2 * 38104 + 36896) * 1024), "attention": int((2 * 18725 + 12480) * 1024)},
 }
 
 
