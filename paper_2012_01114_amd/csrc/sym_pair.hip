@@ -22,7 +22,7 @@
 // The 8 keep weights down to 2^-22 of the own one at all bits of half precision and to 2^-33 off zero: the others
 // of vectors from N(0, 1) lie around 2^-12 of it at d_k = 64 and 2^-16 at 128.  A model in 64 bits of the roundings
 // between z and out (n 200 .. 16384, z of rms 0.3 .. 1.4) has errors of 1.0 to 1.4 times those of a maximum per tile
-// with sums of unrounded weights where either is above 1e-6 (out rounds by 1.7e-3); 6 to 380 times without the 8 at
+// with sums of unrounded weights where either is above 1e-6 (out rounds by 1.7e-3); 5 to 380 times without the 8 at
 // rms 1.2 to 1.4 and n 8192 and more.
 // The exponentials of the second use are stored to LDS in half precision, [row of A][row of B], and
 // read back as operands by the transposing read.  Row sums are MFMAs with ones: float sums of the weights
@@ -32,7 +32,7 @@
 // 512 at d_k = 64, us (pairs, merge): 30.9, 10.3 with a workgroup per pair of tiles, scores staged in fp32,
 // maxima and a state per use, 22.2, 7.3 so; 32 heads of 2048 159 -> 93 together, 8 heads of 2048 at d_k = 128
 // 97 -> 62.  Of that the barriers that leave memory alone gave 4, addresses recomputed per tile (no spills) 4.
-// One vector in 50 four times as long as the others, so that most tiles raise a reference: 8 heads of 2048,
+// One vector in 50 four times as long as the others, so that many tiles raise a reference: 8 heads of 2048,
 // whole calls, 43 -> 48 us.
 //
 // The paper's selection rule (Sec. 4.2: circulant diagonals 0 .. floor(P/2) of the P x P matrix of
@@ -182,12 +182,12 @@ __device__ __forceinline__ unsigned max_f16(unsigned a, unsigned b)
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b)));
 }
-// Scores above a row's reference by more raise it; their weights are at most 2^15.5, and one of two weights (not negative)
-// that are such says so here.
+// A score further above its row's reference raises it: no weight is above 2^15.5 then, and half precision holds them all.
 constexpr float RAISE = 15.5f;
 constexpr float BELOW = 8.f;
 // A row's reference by the score at hand.  From 2^26 on scores are 8 and more apart, and a step of 8 could become one of 16.
 __device__ __forceinline__ float reference(float score) { return score < 0x1p26f ? score - BELOW : score; }
+// Whether one of two weights (not negative) is 2^15 or more: only then scores are compared with RAISE.
 __device__ __forceinline__ bool near_the_end(unsigned m) { return (m & 0xFFFFu) >= 0x7800u || m >= 0x78000000u; }
 
 template <int DK>
